@@ -11,6 +11,7 @@
 #include "kernels_small.h"
 #include "kernels_pipe.h"
 #include "kernels_tiled.h"
+#include <algorithm>
 
 TascConfig g_tasc_config = {/*small_path*/ 2, /*small_grid*/ 0, /*layer_wgs*/ 0, /*layer_stride*/ 0, /*tiled_path*/ 1, /*xcd_local*/ 1,
                              /*layer_workers*/ 0, /*small_kernel*/ 1, /*pipe_share*/ 1, /*chains*/ 0, /*step_graph*/ 1};
@@ -168,21 +169,44 @@ bool tiled_path_fits(const tasc_model_desc& c) {
 
 
 // tile shapes: 128 x 128 on 4 waves, and 256 x 256 on 8 waves for row counts where the GEMMs are MFMA-bound.
-// Both reduce every output element over k in the same order, so the choice may depend on the row count.
+// All reduce every output element over k in the same order, so the choice may depend on the row count.
 #define TILE_SMALL 128, 128, 2, 2
 #define TILE_LARGE 256, 256, 2, 4
-#define TILE_NARROW 64, 128, 1, 4      // few rows and a narrow output: twice the workgroups of the small tile
 #define TILE_MID 256, 192, 4, 2        // 192 rows per tile where that leaves fewer padded rows than 256 (576 = 3 x 192)
+#define TILE_NARROW 64, 128, 1, 4      // few rows and a narrow output: twice the workgroups of the small tile
+// Launches of more large tiles than compute units take the streaming kernel (kernels_gemm.h), one workgroup per compute unit:
+// it hides a tile's start, first fetch and stores under its neighbours in the stream.  With one tile per workgroup there is no
+// neighbour, and the two-steps-ahead register staging of the other kernel fills faster (us, in the forwards; one per workgroup |
+// streaming: gate/up 576 x 17920 x 1536 37.9 | 42.3, down in slices 1280 x 2048 x 11008 59.1 | 59.4; more tiles than units:
+// gate/up 16384 x 22016 x 2048 1327 | 1248, 1280 x 22016 x 2048 114 | 111, q/k/v 16384 x 2560 x 2048 240 | 206).
+// Stages of 64 of k, two in LDS, against stages of 32, four in LDS (random operands, us): gate/up 16384 x 22016 x 2048
+// 1245 / 1310, down 16384 x 2048 x 11008 635 / 681 -- half the barriers; but the LM head 1280 x 49152 x 2048 262 / 235, whose
+// longer epilogue leaves a following fetch less time.
+#define GEMM_LARGE 256, 256, 2, 4, 64, 2
+#define GEMM_LARGE_LM 256, 256, 2, 4, 32, 4
+#define GEMM_MID 256, 192, 4, 2, 64, 2
 constexpr int kLargeTileRows = 384;
+
+template <int EPI>
+constexpr int kLdsLarge = EPI == TEPI_LMHEAD ? gemm_lds_bytes(GEMM_LARGE_LM) : gemm_lds_bytes(GEMM_LARGE);
+template <int EPI>
+constexpr auto k_gemm_large() {
+    if constexpr (EPI == TEPI_LMHEAD) return &k_gemm<EPI, GEMM_LARGE_LM>;
+    else return &k_gemm<EPI, GEMM_LARGE>;
+}
 
 template <int EPI>
 tasc_status tiled_attrs() {
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_SMALL>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  TG_LDS_BYTES(128, 128)));
+    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_large<EPI>()), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLarge<EPI>));
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_LARGE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  TG_LDS_BYTES(256, 256)));
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  TG_LDS_BYTES(256, 192)));
+    if constexpr (EPI != TEPI_ROPE)
+        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm<EPI, GEMM_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     gemm_lds_bytes(GEMM_MID)));
     if constexpr (EPI != TEPI_LMHEAD)
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_NARROW>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      TG_LDS_BYTES(64, 128)));
@@ -192,7 +216,7 @@ tasc_status tiled_attrs() {
 // launches out = epilogue(A W^T) with the tile shape that suits M; `slices` > 1 only for TEPI_PARTIAL
 template <int EPI>
 void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf, BF16* outb, const LmEpi& lm, int slices,
-                 hipStream_t st, const RopeEpi& rp = RopeEpi{}) {
+                 hipStream_t st, int cus, const RopeEpi& rp = RopeEpi{}) {
     // large tiles need enough of them to fill the chip: narrow outputs stay on the small tile (the k order, and so
     // every row's result, is the same for both shapes)
     const long large_wgs = (long)((M + 255) / 256) * ((N + 255) / 256) * slices;
@@ -202,12 +226,26 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
         // 192-row tiles where they cover the rows with less padding and no more tiles (the tile shape never changes a
         // row's result)
         const int mt256 = (M + 255) / 256, mt192 = (M + 191) / 192;
-        if (mt192 <= mt256 && mt192 * 192 < mt256 * 256) {
-            dim3 g((unsigned)(mt192 * ((N + 255) / 256)), (unsigned)slices);
+        const int nt = (N + 255) / 256;
+        const bool mid = mt192 <= mt256 && mt192 * 192 < mt256 * 256;
+        const int tiles = (mid ? mt192 : mt256) * nt * slices;
+        if (tiles > cus && !(EPI == TEPI_ROPE && (mid || 128 % rp.gm.hd != 0))) {   // (that rotation needs whole heads in a wave's 128 features)
+            if constexpr (EPI != TEPI_ROPE) {
+                if (mid) {
+                    k_gemm<EPI, GEMM_MID><<<dim3((unsigned)cus), dim3(512), gemm_lds_bytes(GEMM_MID), st>>>(A, (const BF16*)Wm, M, N, K, slices, outf,
+                                                                                                           outb, lm, rp);
+                    return;
+                }
+            }
+            k_gemm_large<EPI>()<<<dim3((unsigned)cus), dim3(512), kLdsLarge<EPI>, st>>>(A, (const BF16*)Wm, M, N, K, slices, outf, outb, lm, rp);
+            return;
+        }
+        if (mid) {
+            dim3 g((unsigned)(mt192 * nt), (unsigned)slices);
             k_gemm_tiled<EPI, TILE_MID><<<g, dim3(512), TG_LDS_BYTES(256, 192), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
             return;
         }
-        dim3 g((unsigned)(mt256 * ((N + 255) / 256)), (unsigned)slices);
+        dim3 g((unsigned)(mt256 * nt), (unsigned)slices);
         k_gemm_tiled<EPI, TILE_LARGE><<<g, dim3(512), TG_LDS_BYTES(256, 256), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
     } else {
         const long small_wgs = (long)((M + 127) / 128) * ((N + 127) / 128) * slices;
@@ -224,9 +262,16 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
     }
 }
 
-tasc_status tiled_ready() {
+// one-off set-up of the tiled kernels; *cus = the device's compute units
+tasc_status tiled_ready(int* cus) {
     std::lock_guard<std::mutex> lock(g_dev_mu);
     DevState& ds = dev_state();
+    if (ds.cu_count == 0) {
+        int dev = 0;
+        TASC_HIP(hipGetDevice(&dev));
+        TASC_HIP(hipDeviceGetAttribute(&ds.cu_count, hipDeviceAttributeMultiprocessorCount, dev));
+    }
+    *cus = ds.cu_count;
     if (ds.tiled_ready) return TASC_OK;
     tasc_status rc;
     if ((rc = tiled_attrs<TEPI_STORE>()) != TASC_OK) return rc;
@@ -251,8 +296,9 @@ int tiled_auto_chains(const tasc_model_desc& c, int batch, int nq) {
 tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, bool decode, hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
+    int cus = 0;
     {
-        const tasc_status rc = tiled_ready();
+        const tasc_status rc = tiled_ready(&cus);
         if (rc != TASC_OK) return rc;
     }
     const int M_all = s->batch * nq;
@@ -320,11 +366,11 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
         auto gemm_sliced = [&](const BF16* A, const void* Wm, int N, int K, float* out, bool resid, const float* norm_g) {
             const int ks = slices(N, K);
             if (ks == 1) {
-                if (resid) launch_gemm<TEPI_RESID>(A, Wm, M, N, K, out, nullptr, none, 1, st);
-                else launch_gemm<TEPI_STORE>(A, Wm, M, N, K, out, nullptr, none, 1, st);
+                if (resid) launch_gemm<TEPI_RESID>(A, Wm, M, N, K, out, nullptr, none, 1, st, cus);
+                else launch_gemm<TEPI_STORE>(A, Wm, M, N, K, out, nullptr, none, 1, st, cus);
                 return false;
             }
-            launch_gemm<TEPI_PARTIAL>(A, Wm, M, N, K, part, nullptr, none, ks, st);
+            launch_gemm<TEPI_PARTIAL>(A, Wm, M, N, K, part, nullptr, none, ks, st, cus);
             const size_t mn = (size_t)M * N;
             if (resid && norm_g && N == D && D <= RRN_MAX_D) {
                 bool fused = true;
@@ -357,9 +403,9 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
                 // one slice: rotation and cache append ride in the projection's epilogue
                 PROF(TASC_KC_GEMM_QKV);
                 if (ks_qkv == 1)
-                    launch_gemm<TEPI_ROPE>(h, w.wqkv, M, nqkv, D, nullptr, q, none, 1, st,
+                    launch_gemm<TEPI_ROPE>(h, w.wqkv, M, nqkv, D, nullptr, q, none, 1, st, cus,
                                            RopeEpi{m->rope_cos, m->rope_sin, n_rows, pos0, block_tab, kv_layer, gm, c.max_pos});
-                else launch_gemm<TEPI_PARTIAL>(h, w.wqkv, M, nqkv, D, part, nullptr, none, ks_qkv, st);
+                else launch_gemm<TEPI_PARTIAL>(h, w.wqkv, M, nqkv, D, part, nullptr, none, ks_qkv, st, cus);
             }
             if (ks_qkv > 1) {
                 // the k-slices of a split projection are added inside the rotation kernel (same order as the reduction kernel)
@@ -401,7 +447,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
             }
             {
                 PROF(TASC_KC_GEMM_GU);
-                launch_gemm<TEPI_SWIGLU>(h, w.wgu, M, 2 * F, D, nullptr, act, none, 1, st);
+                launch_gemm<TEPI_SWIGLU>(h, w.wgu, M, 2 * F, D, nullptr, act, none, 1, st, cus);
             }
             {
                 // the next layer's first RMSNorm rides on this reduction
@@ -439,15 +485,16 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
             PROF(TASC_KC_NORM);
             k_rmsnorm<BF16><<<dim3(n_sel), dim3(64), 0, st>>>(d.x, m->gf, d.sel_rows, D, c.rms_eps, (BF16*)d.h);
         }
-        LmEpi lm{BiasCsr{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base}, d.sel_tok, d.bias_ptr, d.part_val, d.part_idx,
+        LmEpi lm{BiasCsr{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base}, d.bias_ptr, d.bias_first, d.bias_base, d.part_val, d.part_idx,
                  logits_dbg, s->n_strips};
         {
             PROF(TASC_KC_LMHEAD);
             if (m->bias_rowptr) {
                 const int n = n_sel * (s->n_strips + 1);
-                k_bias_ptr<<<dim3((n + 255) / 256), dim3(256), 0, st>>>(lm.bias, d.sel_tok, n_sel, s->n_strips, d.bias_ptr);
+                k_bias_ptr<<<dim3((n + 255) / 256), dim3(256), 0, st>>>(lm.bias, d.sel_tok, n_sel, s->n_strips, d.bias_ptr,
+                                                                        d.bias_first, d.bias_base);
             }
-            launch_gemm<TEPI_LMHEAD>((const BF16*)d.h, m->lm_head, n_sel, c.vocab, D, nullptr, nullptr, lm, 1, st);
+            launch_gemm<TEPI_LMHEAD>((const BF16*)d.h, m->lm_head, n_sel, c.vocab, D, nullptr, nullptr, lm, 1, st, cus);
         }
         {
             PROF(TASC_KC_ACCEPT);
@@ -729,7 +776,8 @@ extern "C" tasc_status tasc_calibration_gemm(int32_t M, int32_t N, int32_t K, in
                  "calibration_gemm: 1 .. %d k-slices, more than one only with the partial-sum epilogue", TG_MAX_SLICES);
     TASC_REQUIRE(iters >= 1 && iters <= 10000, "calibration_gemm: 1 .. 10000 launches");
     hipStream_t st = (hipStream_t)stream;
-    tasc_status rc = tiled_ready();
+    int cus = 0;
+    tasc_status rc = tiled_ready(&cus);
     if (rc != TASC_OK) return rc;
     const size_t a_bytes = (size_t)M * K * 2, w_bytes = (size_t)N * K * 2, o_bytes = (size_t)M * N * 4 * slices;
     struct Tmp { void* p[3] = {nullptr, nullptr, nullptr}; ~Tmp() { for (void* q : p) if (q) (void)hipFree(q); } } t;
@@ -742,10 +790,10 @@ extern "C" tasc_status tasc_calibration_gemm(int32_t M, int32_t N, int32_t K, in
     LmEpi none{};
     auto launch = [&]() {
         const BF16* A = (const BF16*)t.p[0];
-        if (epilogue == TEPI_STORE) launch_gemm<TEPI_STORE>(A, t.p[1], M, N, K, (float*)t.p[2], nullptr, none, 1, st);
-        else if (epilogue == TEPI_RESID) launch_gemm<TEPI_RESID>(A, t.p[1], M, N, K, (float*)t.p[2], nullptr, none, 1, st);
-        else if (epilogue == TEPI_SWIGLU) launch_gemm<TEPI_SWIGLU>(A, t.p[1], M, N, K, nullptr, (BF16*)t.p[2], none, 1, st);
-        else launch_gemm<TEPI_PARTIAL>(A, t.p[1], M, N, K, (float*)t.p[2], nullptr, none, slices, st);
+        if (epilogue == TEPI_STORE) launch_gemm<TEPI_STORE>(A, t.p[1], M, N, K, (float*)t.p[2], nullptr, none, 1, st, cus);
+        else if (epilogue == TEPI_RESID) launch_gemm<TEPI_RESID>(A, t.p[1], M, N, K, (float*)t.p[2], nullptr, none, 1, st, cus);
+        else if (epilogue == TEPI_SWIGLU) launch_gemm<TEPI_SWIGLU>(A, t.p[1], M, N, K, nullptr, (BF16*)t.p[2], none, 1, st, cus);
+        else launch_gemm<TEPI_PARTIAL>(A, t.p[1], M, N, K, (float*)t.p[2], nullptr, none, slices, st, cus);
     };
     struct Ev { hipEvent_t e[2] = {nullptr, nullptr}; ~Ev() { for (hipEvent_t q : e) if (q) (void)hipEventDestroy(q); } } ev;
     TASC_HIP(hipEventCreate(&ev.e[0]));

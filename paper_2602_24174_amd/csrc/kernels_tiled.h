@@ -10,49 +10,10 @@
 // how many rows the launch holds.  Workgroup ids are remapped so that the workgroups sharing a weight
 // tile run on the same XCD and find it in that XCD's L2.
 #pragma once
-#include "kernels_small.h"
+#include "kernels_gemm.h"
 
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-#ifndef IGLP
-#define IGLP 0
-#endif
-
-#define TG_BK 64
 #define TG_LD (TG_BK + 8)                                     // padded LDS row (elements)
 #define TG_LDS_BYTES(BN, BM) (2 * ((BN) + (BM)) * TG_LD * 2)   // 73728 for 128 x 128, 147456 for 256 x 256
-#define TG_MAX_SLICES 8                                       // most k-slices of a narrow GEMM
-
-// TEPI_PARTIAL: the grid's y extent is the number of slices of k (a workgroup's slice comes from the tile order
-// below); the slice's sums go to outf[slice][M][N] and k_splitk_reduce adds the slices in order (plain store or
-// residual add).  Used where N is too narrow for the tile count to fill the chip; the number of slices depends on
-// N and K only.
-// TEPI_ROPE: the fused q/k/v projection of a layer whose output is not sliced: the epilogue rotates the q and k heads (RoPE
-// at the row's position), writes q to outb and the new k / v rows straight into the row's cache page.
-enum { TEPI_STORE = 0, TEPI_RESID = 1, TEPI_SWIGLU = 2, TEPI_LMHEAD = 3, TEPI_PARTIAL = 4, TEPI_ROPE = 5 };
-
-struct RopeEpi {          // TEPI_ROPE only: what k_rope_kv takes
-    const float* cosT;        // [max_pos][hd / 2]
-    const float* sinT;
-    const int32_t* n_rows;    // [B] active rows of the sequence
-    const int32_t* pos0;      // [B] position of the sequence's first row
-    const int32_t* block_tab; // [B][max_blocks]
-    BF16* kv_layer;           // the layer's pages
-    KvGeom gm;
-    int32_t max_pos;
-};
-
-struct LmEpi {            // TEPI_LMHEAD only
-    BiasCsr bias;
-    const int32_t* sel_tok;   // input token of every row (bias row)
-    const int32_t* bias_ptr;  // [M][n_strips + 1] cursor table
-    float* part_val;          // [M][n_strips]
-    int32_t* part_idx;
-    float* logits;            // nullable [M][V]
-    int32_t n_strips;
-};
-
-// rows of the accumulator a lane holds: element i of a 32x32 tile is output feature 8 (i / 4) + 4 (lane / 32) + i % 4
-__device__ inline int tile_row(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 
 // BN x BM = output features x rows of the workgroup tile; WN x WM waves, each computing a
 // (BN / WN) x (BM / WM) block as TI x TJ MFMA tiles of 32 x 32.
@@ -136,9 +97,8 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1,
             lm_cur[j] = 0;
             lm_end[j] = 0;
             if (m < M && lm.bias.rowptr && strip < lm.n_strips) {
-                const int u = lm.sel_tok[m];
-                lm_base[j] = lm.bias.base[u];
-                const int64_t r0 = lm.bias.rowptr[u];
+                lm_base[j] = lm.row_base[m];
+                const int64_t r0 = lm.row_first[m];
                 lm_cur[j] = r0 + lm.bias_ptr[(size_t)m * (lm.n_strips + 1) + strip];
                 lm_end[j] = r0 + lm.bias_ptr[(size_t)m * (lm.n_strips + 1) + strip + 1];
             }
@@ -547,8 +507,9 @@ __global__ __launch_bounds__(256) void k_rmsnorm_row(const float* __restrict__ x
     }
 }
 
-// cursor table of the LM-head bias (see LmEpi): one thread per (row, strip boundary)
-__global__ void k_bias_ptr(BiasCsr bias, const int32_t* __restrict__ sel_tok, int n_sel, int n_strips, int32_t* __restrict__ out) {
+// cursor table of the LM-head bias and the rows' list starts and bases (see LmEpi): one thread per (row, strip boundary)
+__global__ void k_bias_ptr(BiasCsr bias, const int32_t* __restrict__ sel_tok, int n_sel, int n_strips, int32_t* __restrict__ out,
+                           int64_t* __restrict__ row_first, float* __restrict__ row_base) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     const int per_row = n_strips + 1;
     if (idx >= n_sel * per_row) return;
@@ -556,6 +517,10 @@ __global__ void k_bias_ptr(BiasCsr bias, const int32_t* __restrict__ sel_tok, in
     const int u = sel_tok[r];
     const int64_t r0 = bias.rowptr[u];
     int64_t lo = r0, hi = bias.rowptr[u + 1];
+    if (st == 0) {
+        row_first[r] = r0;
+        row_base[r] = bias.base[u];
+    }
     const int c_first = st * TASC_LM_STRIP;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;

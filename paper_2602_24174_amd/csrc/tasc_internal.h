@@ -187,7 +187,9 @@ struct TascSessDev {
     float* att_part;     // attention split partials
     char* small_ws;      // the small-batch kernel's per-phase / per-layer activation buffers (tasc_small_ws_bytes)
     int32_t* drafts;     // [B, TASC_MAX_K] used by tasc_generate
-    int32_t* bias_ptr;   // [M_max, n_strips + 1] LM-head bias cursors of the small-batch kernel
+    int32_t* bias_ptr;   // [M_max, n_strips + 1] LM-head bias cursors
+    int64_t* bias_first; // [M_max] first entry of an LM-head row's bias list (tiled kernels)
+    float* bias_base;    // [M_max] its bias of unseen successors
 };
 
 // one verify step of the tiled kernels, recorded once and replayed: its launches only name buffers of the session and

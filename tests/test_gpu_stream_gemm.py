@@ -1,0 +1,69 @@
+"""Launches of more large GEMM tiles than the device has compute units (the streaming kernel): rotation epilogue at every head
+size, gate/up and LM head at 192- and 256-row tiles, one to three stages of k, ragged feature and row edges, an odd vocabulary
+(logit rows at any 4-byte address), bias lists that are empty, short, and longer than the ones a lane fetches ahead."""
+import numpy as np
+import pytest
+
+import workload as W
+from oracle import model as OM
+
+pytestmark = pytest.mark.gpu
+
+
+def _bias(vocab, rng):
+    """Sparse rows: none, up to three scattered entries, or (every seventh token) a run of 150 neighbouring columns."""
+    rows = []
+    for u in range(vocab):
+        if u % 7 == 0:
+            first = int(rng.integers(0, vocab - 150))
+            rows.append(np.arange(first, first + 150))
+        else:
+            rows.append(np.unique(rng.integers(0, vocab, u % 4)))
+    col = np.concatenate(rows).astype(np.int32)
+    ptr = np.cumsum([0] + [len(r) for r in rows]).astype(np.int64)
+    return {"rowptr": ptr, "col": col, "val": rng.normal(0, 2, col.size).astype(np.float32),
+            "base": rng.normal(-3, 0.5, vocab).astype(np.float32)}
+
+
+@pytest.mark.parametrize("heads,d_model", [((120, 4, 32), 64), ((60, 2, 64), 128), ((28, 2, 128), 192)])
+def test_streaming_gemm(heads, d_model):
+    import torch
+    import paper_2602_24174_amd as T
+    H, Hkv, hd = heads
+    B, max_rows, V = 288, 16, 22_101
+    cfg = W.get_config("cfg1").scaled(dtype="bf16", n_layers=1, d_model=d_model, n_heads=H, n_kv_heads=Hkv, head_dim=hd, d_ffn=11_072,
+                                      vocab=V, batch=B)
+    rng = np.random.default_rng(5)
+    weights = W.make_model(cfg)
+    weights["bias"] = _bias(V, rng)
+    lens = [int(n) for n in rng.integers(3, 30, B)]
+    prompts = [rng.integers(0, V, n).astype(np.int32) for n in lens]
+    max_len = 30 + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, weights, max_len)
+    sess = T.tasc_session_create(model, B, max_len, max_rows)
+    # prompt chunks: 288 x 16 = 4608 rows (18 row tiles x 16 column tiles of q/k/v, x 87 of gate/up); one token asked for, so
+    # the sequences are finished and every verify step below sees the same state
+    T.tasc_session_prefill(model, sess, np.concatenate(prompts), np.cumsum([0] + lens).astype(np.int64), 1)
+    got = {}
+    drafts = rng.integers(0, V, (B, 2)).astype(np.int32)
+    for k in (0, 1, 2):          # 288 rows (small tiles), 576 rows (192-row tiles: 3 x 87), 864 rows (256-row tiles: 4 x 87)
+        print(f"heads {heads} k {k}", flush=True)
+        z = torch.full((B, k + 1, V), -7.0, dtype=torch.float32, device="cuda")
+        em = torch.zeros((B, k + 1), dtype=torch.int32, device="cuda")
+        d = torch.from_numpy(np.ascontiguousarray(drafts[:, :k])).cuda() if k else None
+        T.tasc_verify_step(model, sess, d, k, None, em, z)
+        torch.cuda.synchronize()
+        got[k] = z.cpu().numpy()
+    # a row's result does not depend on the tile shape or on the kernel: the same bits from all three launches
+    assert (got[1][:, 0] == got[0][:, 0]).all() and (got[2][:, 0] == got[0][:, 0]).all()
+    assert (got[2][:, 1] == got[1][:, 1]).all()
+    om = OM.OracleModel(cfg, weights)
+    for b in (0, 100, B - 1):
+        c = om.new_cache(max_len)
+        om.forward(prompts[b].tolist(), c, last_only=True)
+        c.length = lens[b]
+        first = int(T.tasc_session_get_tokens(sess, b)[-1])
+        z = om.forward([first] + drafts[b].tolist(), c)
+        worst = float(np.abs(got[2][b].astype(np.float64) - z).max())
+        print(f"heads {heads} sequence {b}: max |logit - oracle| = {worst:.3e}", flush=True)
+        assert worst <= 5e-2     # bf16 matrix operands, one layer: the bound of the other bf16 parity tests
