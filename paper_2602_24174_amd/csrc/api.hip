@@ -33,32 +33,48 @@ __global__ void k_check_prompts(const int32_t* __restrict__ prompts, int64_t n, 
     if (i < n && (prompts[i] < 0 || prompts[i] >= vocab)) atomicOr(flag, 1ull);
 }
 
-// prompt chunk c of C positions: rows, positions, and which rows feed the LM head
-__global__ void k_prepare_prefill(int B, int C, int chunk, int max_len, const int32_t* __restrict__ tokens,
-                                  const int32_t* __restrict__ n_prompt, int32_t* row_tok, int32_t* n_rows, int32_t* pos0,
-                                  int32_t* sel_rows, int32_t* sel_tok) {
+// Prompt chunk [base, base + C): rows, positions, and which rows feed the LM head.  Packed (stride 0): the sequences' rows lie one
+// behind the other, none for a sequence whose prompt ended before; otherwise sequence b has the `stride` rows from b * stride on,
+// padded with token 0.
+__global__ __launch_bounds__(256) void k_prepare_prefill(int C, int base, int stride, int max_len, const int32_t* __restrict__ tokens,
+                                                         const int32_t* __restrict__ n_prompt, int32_t* row_tok, int32_t* row_seq, int32_t* row0,
+                                                         int32_t* n_rows, int32_t* pos0, int32_t* sel_rows, int32_t* sel_tok) {
     const int b = blockIdx.x;
-    const int P = n_prompt[b], base = chunk * C;
+    const int P = n_prompt[b];
     const int nr = max(0, min(C, P - base));
-    for (int i = threadIdx.x; i < C; i += blockDim.x) row_tok[b * C + i] = i < nr ? tokens[(size_t)b * max_len + base + i] : 0;
+    __shared__ int s_sum[4];
+    int first = b * stride;
+    if (stride == 0) {
+        int mine = 0;
+        for (int q = threadIdx.x; q < b; q += 256) mine += max(0, min(C, n_prompt[q] - base));
+        for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+        if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = mine;
+        __syncthreads();
+        first = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+    }
+    for (int i = threadIdx.x; i < max(stride, nr); i += 256) {
+        row_tok[first + i] = i < nr ? tokens[(size_t)b * max_len + base + i] : 0;
+        row_seq[first + i] = b;
+    }
     if (threadIdx.x == 0) {
+        row0[b] = first;
         n_rows[b] = nr;
         pos0[b] = base;
         const bool last = P - 1 >= base && P - 1 < base + C;
-        sel_rows[b] = last ? b * C + (P - 1 - base) : -1;
+        sel_rows[b] = last ? first + (P - 1 - base) : -1;
         sel_tok[b] = last ? tokens[(size_t)b * max_len + P - 1] : 0;
     }
 }
 
 // after a prompt chunk: the cache now covers the chunk; a sequence whose prompt ended in it commits
 // the argmax of its last position as generated token #1
-__global__ void k_commit_prefill(int B, int C, int chunk, int max_len, int max_new, const int32_t* __restrict__ n_prompt,
+__global__ void k_commit_prefill(int B, int end, int max_len, int max_new, const int32_t* __restrict__ n_prompt,
                                  const int32_t* __restrict__ sel_rows, const int32_t* __restrict__ amax, int have_lm,
                                  int32_t* tokens, int32_t* n_tok, int32_t* cached, int32_t* n_emit, u64* counters) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= B) return;
     const int P = n_prompt[b];
-    cached[b] = min(P, (chunk + 1) * C);
+    cached[b] = min(P, end);
     if (have_lm && sel_rows[b] >= 0) {
         tokens[(size_t)b * max_len + P] = amax[b];
         n_tok[b] = P + 1;
@@ -69,8 +85,8 @@ __global__ void k_commit_prefill(int B, int C, int chunk, int max_len, int max_n
 
 __global__ void k_prepare_verify(int B, int k, int max_len, int vocab, const int32_t* __restrict__ tokens,
                                  const int32_t* __restrict__ n_tok, const int32_t* __restrict__ cached,
-                                 const int32_t* __restrict__ drafts, int32_t* row_tok, int32_t* n_rows, int32_t* pos0,
-                                 int32_t* sel_rows, int32_t* sel_tok) {
+                                 const int32_t* __restrict__ drafts, int32_t* row_tok, int32_t* row_seq, int32_t* row0, int32_t* n_rows,
+                                 int32_t* pos0, int32_t* sel_rows, int32_t* sel_tok) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     const int nq = k + 1;
     if (idx >= B * nq) return;
@@ -79,12 +95,14 @@ __global__ void k_prepare_verify(int B, int k, int max_len, int vocab, const int
     if (i == 0) {
         t = tokens[(size_t)b * max_len + n_tok[b] - 1];
         n_rows[b] = nq;
+        row0[b] = idx;
         pos0[b] = cached[b];
     } else {
         t = drafts[b * k + i - 1];
         t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);   // a draft outside the vocabulary can only be rejected
     }
     row_tok[idx] = t;
+    row_seq[idx] = b;
     sel_rows[idx] = idx;
     sel_tok[idx] = t;
 }
@@ -298,9 +316,20 @@ struct WsLayout {
     size_t off[32];
     size_t total;
 };
+// Rows of a prompt chunk.  A session with prompt chunks of more than 16 rows (and so the tiled kernels for them) gets buffers
+// for at least kPromptRows, where its prompts can be that many: 8192 rows give the projections several rounds of large tiles,
+// which a few sequences with max_rows rows each do not (1.5B shape, 16 prompts of 1024 to 2048 tokens: 32 chunks of 16 x 64 rows
+// ran the gate/up projection at 0.71 PFLOP/s).  About 100 to 150 KB a row.
+constexpr int64_t kPromptRows = 8192;
+int64_t prompt_rows(const tasc_model_desc& c, int B, int max_len, int max_rows) {
+    const int64_t rows = (int64_t)B * max_rows;
+    if (max_rows <= 16 || !tasc_tiled_fits(c)) return rows;
+    return std::max(rows, std::min(kPromptRows, (int64_t)B * max_len));
+}
+
 // carves the workspace; order must match bind_workspace
 WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows) {
-    const size_t M = (size_t)B * max_rows, es = elt_size(c.dtype);
+    const size_t ML = (size_t)B * max_rows, M = (size_t)prompt_rows(c, B, max_len, max_rows), es = elt_size(c.dtype);
     const size_t HD = (size_t)c.n_heads * c.head_dim, KD = (size_t)c.n_kv_heads * c.head_dim;
     const size_t n_strips = ((size_t)c.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP;
     const size_t max_blocks = ((size_t)max_len + TASC_KV_BLOCK - 1) / TASC_KV_BLOCK;
@@ -308,17 +337,21 @@ WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows) {
         (size_t)B * max_len * 4,  // tokens
         (size_t)B * 4, (size_t)B * 4, (size_t)B * 4, (size_t)B * 4,  // n_tok n_prompt cached n_emit
         (size_t)B * max_blocks * 4,                                  // block_tab
-        M * 4, (size_t)B * 4, (size_t)B * 4, M * 4, M * 4,           // row_tok n_rows pos0 sel_rows sel_tok
+        M * 4, (size_t)B * 4, (size_t)B * 4,                         // row_tok n_rows pos0
+        M * 4, (size_t)B * 4, ((size_t)B + 1) * 8,                   // row_seq row0 off
+        ML * 4, ML * 4,                                              // sel_rows sel_tok
         TASC_N_COUNTERS * 8,                                         // counters (+ barrier flags)
         M * c.d_model * 4,                                           // x
         M * std::max<size_t>(c.d_model, 1) * es,                     // h
         M * (HD + 2 * KD) * 4,                                       // qkv
         M * HD * es, M * HD * es,                                    // q att
         M * (size_t)c.d_ffn * es,                                    // act
-        M * n_strips * 4, M * n_strips * 4, M * 4,                   // part_val part_idx amax
-        8 * M * std::max<size_t>(HD + 2 * KD, c.d_model) * 4,        // att_part: k-slice partial sums of the narrow GEMMs
+        ML * n_strips * 4, ML * n_strips * 4, ML * 4,                // part_val part_idx amax
+        // att_part: k-slice partial sums of the narrow GEMMs (8 of a verify step, 4 of a larger prompt chunk), or up to 4 partial
+        // results of the attention with their maxima and denominators
+        std::max(8 * ML * std::max<size_t>(HD + 2 * KD, c.d_model), 4 * M * (std::max<size_t>(HD + 2 * KD, c.d_model) + 2 * (size_t)c.n_heads)) * 4,
         (size_t)B * TASC_MAX_K * 4,                                  // drafts
-        M * (n_strips + 1) * 4, M * 8, M * 4,                        // bias_ptr bias_first bias_base
+        ML * (n_strips + 1) * 4, ML * 8, ML * 4,                     // bias_ptr bias_first bias_base
         tasc_small_ws_bytes(c),                                      // write-once activation buffers of the small-batch kernel
     };
     WsLayout L;
@@ -365,6 +398,7 @@ extern "C" tasc_status tasc_session_create(const tasc_model* m, int32_t batch, i
     s->batch = batch;
     s->max_len = max_len;
     s->max_rows = max_rows;
+    s->row_cap = (int32_t)prompt_rows(m->desc, batch, max_len, max_rows);
     s->max_blocks = (max_len + TASC_KV_BLOCK - 1) / TASC_KV_BLOCK;
     s->n_strips = (m->desc.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP;
     s->max_new = 0;
@@ -391,6 +425,9 @@ extern "C" tasc_status tasc_session_create(const tasc_model* m, int32_t batch, i
     d.row_tok = (int32_t*)(w + L.off[i++]);
     d.n_rows = (int32_t*)(w + L.off[i++]);
     d.pos0 = (int32_t*)(w + L.off[i++]);
+    d.row_seq = (int32_t*)(w + L.off[i++]);
+    d.row0 = (int32_t*)(w + L.off[i++]);
+    d.off = (int64_t*)(w + L.off[i++]);
     d.sel_rows = (int32_t*)(w + L.off[i++]);
     d.sel_tok = (int32_t*)(w + L.off[i++]);
     d.counters = (u64*)(w + L.off[i++]);
@@ -493,11 +530,9 @@ extern "C" tasc_status tasc_session_prefill(const tasc_model* m, tasc_session* s
         TASC_HIP(hipMemcpyAsync(p, prompts, total * 4, hipMemcpyHostToDevice, st));
         d_prompts = (const int32_t*)p;
     }
-    int64_t* d_off;
-    TASC_HIP(hipMalloc((void**)&d_off, (B + 1) * 8)); tmp.p.push_back(d_off);
-    TASC_HIP(hipMemcpyAsync(d_off, prompt_offsets, (B + 1) * 8, hipMemcpyHostToDevice, st));
     TascSessDev& d = s->d;
-    k_reset<<<dim3(B), dim3(256), 0, st>>>(B, s->max_len, d_prompts, d_off, d.tokens, d.n_tok, d.n_prompt, d.cached, d.n_emit,
+    TASC_HIP(hipMemcpyAsync(d.off, prompt_offsets, (B + 1) * 8, hipMemcpyHostToDevice, st));
+    k_reset<<<dim3(B), dim3(256), 0, st>>>(B, s->max_len, d_prompts, d.off, d.tokens, d.n_tok, d.n_prompt, d.cached, d.n_emit,
                                            d.counters);
     TASC_LAUNCH_CHECK();
     s->bar_epoch = 0;  // k_reset cleared the barrier flags and counters (the time-out flag among them) with the other counters
@@ -511,22 +546,45 @@ extern "C" tasc_status tasc_session_prefill(const tasc_model* m, tasc_session* s
     TASC_HIP(hipMemsetAsync(&d.counters[31], 0, 8, st));
     s->max_new = max_new;
 
-    const int n_chunks = (int)((longest + C - 1) / C);
-    for (int c = 0; c < n_chunks; ++c) {
+    // Chunks of positions [base, base + step).  The persistent kernels take batch x max_rows rows, padded; the others take the
+    // rows there are, one sequence behind the other, and the tiled ones as many positions at a time as row_cap holds, in chunks
+    // of about equal row counts.
+    const bool tiled = tasc_forward_is_tiled(m, s, C), padded = !tiled && tasc_forward_is_small(m, s, C);
+    auto rows_of = [&](int64_t base, int64_t step) {
+        int64_t n = 0;
+        for (int b = 0; b < B; ++b) n += std::clamp<int64_t>(prompt_offsets[b + 1] - prompt_offsets[b] - base, 0, step);
+        return n;
+    };
+    for (int64_t base = 0; base < longest;) {
+        int64_t step = std::min<int64_t>(C, longest - base), rows = (int64_t)B * C;
+        if (tiled) {
+            const int64_t left = rows_of(base, longest), parts = (left + s->row_cap - 1) / s->row_cap, want = (left + parts - 1) / parts;
+            int64_t lo = 1, hi = longest - base;                  // the fewest positions that make `want` rows ...
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) / 2;
+                if (rows_of(base, mid) >= want) hi = mid; else lo = mid + 1;
+            }
+            step = lo;
+            if (step > 1 && rows_of(base, step) > s->row_cap) --step;   // ... or one less where they do not fit
+        }
+        if (!padded) rows = rows_of(base, step);
         bool any_last = false;
         for (int b = 0; b < B && !any_last; ++b) {
             const int64_t P = prompt_offsets[b + 1] - prompt_offsets[b];
-            any_last = P - 1 >= (int64_t)c * C && P - 1 < (int64_t)(c + 1) * C;
+            any_last = P - 1 >= base && P - 1 < base + step;
         }
-        k_prepare_prefill<<<dim3(B), dim3(64), 0, st>>>(B, C, c, s->max_len, d.tokens, d.n_prompt, d.row_tok, d.n_rows, d.pos0,
-                                                        d.sel_rows, d.sel_tok);
+        k_prepare_prefill<<<dim3(B), dim3(256), 0, st>>>((int)step, (int)base, padded ? C : 0, s->max_len, d.tokens, d.n_prompt, d.row_tok,
+                                                         d.row_seq, d.row0, d.n_rows, d.pos0, d.sel_rows, d.sel_tok);
         TASC_LAUNCH_CHECK();
-        tasc_status rc = tasc_forward_rows(m, s, C, any_last ? B : 0, nullptr, nullptr, st);
+        // (a tail of a few positions stays with the tiled kernels: the persistent ones want the device to themselves)
+        const int nq = padded ? C : (tiled ? std::max((int)step, 17) : (int)step);
+        tasc_status rc = tasc_forward_rows(m, s, nq, (int)rows, any_last ? B : 0, nullptr, nullptr, st);
         if (rc != TASC_OK) return rc;
-        k_commit_prefill<<<dim3((B + 63) / 64), dim3(64), 0, st>>>(B, C, c, s->max_len, max_new, d.n_prompt, d.sel_rows, d.amax,
+        k_commit_prefill<<<dim3((B + 63) / 64), dim3(64), 0, st>>>(B, (int)(base + step), s->max_len, max_new, d.n_prompt, d.sel_rows, d.amax,
                                                                    any_last ? 1 : 0, d.tokens, d.n_tok, d.cached, d.n_emit,
                                                                    d.counters);
         TASC_LAUNCH_CHECK();
+        base += step;
     }
     TASC_HIP(hipStreamSynchronize(st));   // the temporaries above are freed on return
     s->prefilled = 1;
@@ -540,10 +598,11 @@ tasc_status verify_step_enqueue(const tasc_model* m, tasc_session* s, const int3
     const int B = s->batch, nq = k + 1;
     TascSessDev& d = s->d;
     k_prepare_verify<<<dim3((B * nq + 255) / 256), dim3(256), 0, st>>>(B, k, s->max_len, m->desc.vocab, d.tokens, d.n_tok, d.cached,
-                                                                       drafts, d.row_tok, d.n_rows, d.pos0, d.sel_rows, d.sel_tok);
+                                                                       drafts, d.row_tok, d.row_seq, d.row0, d.n_rows, d.pos0, d.sel_rows,
+                                                                       d.sel_tok);
     TASC_LAUNCH_CHECK();
     TascVerifyTail tail{k, drafts, accept_len, emitted, trace_step, false};
-    tasc_status rc = tasc_forward_rows(m, s, nq, B * nq, logits_dbg, &tail, st);
+    tasc_status rc = tasc_forward_rows(m, s, nq, B * nq, B * nq, logits_dbg, &tail, st);
     if (rc != TASC_OK) return rc;
     if (!tail.done) {
         TascProfScope ps(TASC_KC_ACCEPT, st);

@@ -1,4 +1,4 @@
-// One target forward over M = batch * nq rows against the paged KV cache, ending (optionally) in the
+// One target forward over M rows, at most nq of a sequence, against the paged KV cache, ending (optionally) in the
 // LM head with fused bias and argmax.  Used by the prompt forward (nq = chunk length) and by the
 // verify step (nq = k + 1; paper, subsection "Speculative Decoding": the drafted tokens are verified
 // in parallel via a single forward pass).
@@ -84,13 +84,12 @@ namespace {
 #define PROF(cls) TascProfScope _ps(cls, st)
 
 template <typename T>
-tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, hipStream_t st) {
+tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M, int n_sel, float* logits_dbg, hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
-    const int M = s->batch * nq;
     const int D = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
     const int nqkv = (H + 2 * Hkv) * hd, nqo = H * hd;
-    KvGeom gm{H, Hkv, hd, nq, s->max_blocks, s->page_elems};
+    KvGeom gm{H, Hkv, hd, s->max_blocks, s->page_elems, d.row_seq, d.row0, 0};
     const float scale = 1.0f / sqrtf((float)hd);
     {
         PROF(TASC_KC_PREPARE);
@@ -162,11 +161,12 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int n_
 }
 
 // the LDS-tiled MFMA kernels serve bf16 forwards of any row count with these shapes
-bool tiled_path_fits(const tasc_model_desc& c) {
+}  // namespace
+bool tasc_tiled_fits(const tasc_model_desc& c) {
     return c.dtype == TASC_BF16 && c.d_model % 64 == 0 && (c.n_heads * c.head_dim) % 64 == 0 && c.d_ffn % 64 == 0 &&
            (c.head_dim == 32 || c.head_dim == 64 || c.head_dim == 128);
 }
-
+namespace {
 
 // tile shapes: 128 x 128 on 4 waves, and 256 x 256 on 8 waves for row counts where the GEMMs are MFMA-bound.
 // All reduce every output element over k in the same order, so the choice may depend on the row count.
@@ -293,7 +293,7 @@ int tiled_auto_chains(const tasc_model_desc& c, int batch, int nq) {
     return 1;
 }
 
-tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, bool decode, hipStream_t st) {
+tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_all, int n_sel, float* logits_dbg, bool decode, hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
     int cus = 0;
@@ -301,10 +301,8 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
         const tasc_status rc = tiled_ready(&cus);
         if (rc != TASC_OK) return rc;
     }
-    const int M_all = s->batch * nq;
     const int D = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
     const int nqkv = (H + 2 * Hkv) * hd, nqo = H * hd;
-    KvGeom gm{H, Hkv, hd, nq, s->max_blocks, s->page_elems};
     LmEpi none{};
     // Narrow outputs (few column tiles) are computed in k-slices.  The slice count fixes the order in which a row's
     // products are added, so it must be the same for every DECODE forward of a session (a greedy step and a verify step
@@ -313,7 +311,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
     // stands for the verify steps the session is sized for.  A prompt forward is the same computation in the
     // speculative and in the greedy run whatever its slice count, so it takes the count that suits its own rows (its
     // chunks of batch x max_rows rows fill the chip without slices, and every slice is a pass over rows x N partial sums).
-    const int rows_ref = decode ? s->batch * 5 : s->batch * nq;
+    const int rows_ref = decode ? s->batch * 5 : M_all;
     auto slices = [&](int N, int K) {
         const int n_nt = (N + 127) / 128, nk = K / TG_BK;
         if (n_nt >= 32) return 1;
@@ -335,10 +333,15 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
         if (rows_ref > 256 && rows_ref < kLargeTileRows && ks > 4) ks = 4;
         ks = ks < nk / 4 ? ks : nk / 4;                       // slices of at least 4 k-steps
         ks = ks < TG_MAX_SLICES ? ks : TG_MAX_SLICES;
+        if (M_all > s->batch * s->max_rows && ks > 4) ks = 4;  // the scratch holds 8 slices of a verify step's rows, 4 of row_cap
         return ks < 1 ? 1 : ks;
     };
-    int att_chunks = 512 / (s->batch * Hkv);          // two workgroups per compute unit in one round,
-    att_chunks = att_chunks < 1 ? 1 : (att_chunks > 4 ? 4 : att_chunks);   // but no more than 4 partial results to merge
+    // Key chunks of the attention: two workgroups per compute unit in one round, but no more than 4 partial results to merge.
+    // For decode forwards a session constant (it fixes the order in which a row's keys are added); a prompt forward counts
+    // its row passes too, so that its long chunks need no merge.
+    const int att_passes = decode ? 1 : (nq * (H / Hkv) + 63) / 64;
+    int att_chunks = 512 / (s->batch * Hkv * att_passes);
+    att_chunks = att_chunks < 1 ? 1 : (att_chunks > 4 ? 4 : att_chunks);
     {
         PROF(TASC_KC_PREPARE);
         k_embed<BF16><<<dim3(M_all), dim3(64), 0, st>>>((const BF16*)m->embed, d.row_tok, D, d.x);
@@ -350,17 +353,18 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
     // sequences side by side ("chains", each on a stream of its own with its own share of every buffer) without
     // changing a bit of any row.
     auto run_layers = [&](int b0, int nb, hipStream_t st) -> tasc_status {
-        const int M = nb * nq;
+        const int M = nb == s->batch ? M_all : nb * nq;          // (ranges of sequences only where all have nq rows)
         const size_t r0 = (size_t)b0 * nq;
+        const KvGeom gm{H, Hkv, hd, s->max_blocks, s->page_elems, d.row_seq + r0, d.row0, (int32_t)r0};
         float* const x = d.x + r0 * D;
         BF16* const h = (BF16*)d.h + r0 * D;
         BF16* const q = (BF16*)d.q + r0 * nqo;
         BF16* const att = (BF16*)d.att + r0 * nqo;
         BF16* const act = (BF16*)d.act + r0 * F;
         float* const part = d.att_part + r0 * 8 * (size_t)(nqkv > D ? nqkv : D);   // the scratch is sized per row
-        const int32_t* const n_rows = d.n_rows + b0;
-        const int32_t* const pos0 = d.pos0 + b0;
-        const int32_t* const block_tab = d.block_tab + (size_t)b0 * s->max_blocks;
+        const int32_t* const n_rows = d.n_rows;
+        const int32_t* const pos0 = d.pos0;
+        const int32_t* const block_tab = d.block_tab;
         // out (+)= A W^T through k-slices and the ordered reduction.  With `norm_g` the RMSNorm of the updated rows (gain
         // norm_g, into h) is fused into the reduction; returns false if the caller still has to run it (no slices).
         auto gemm_sliced = [&](const BF16* A, const void* Wm, int N, int K, float* out, bool resid, const float* norm_g) {
@@ -415,7 +419,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
             }
             {
                 PROF(TASC_KC_ATTN);
-                AttnArgs aa{q, att, kv_layer, n_rows, pos0, block_tab, nb, nq, H, Hkv,
+                AttnArgs aa{q, att, kv_layer, n_rows, pos0, block_tab, d.row0, b0, (int32_t)r0, M, nq, H, Hkv,
                             s->max_blocks, s->page_elems, 1.0f / sqrtf((float)hd)};
                 if (hd == 32 || s->max_blocks > TA_MAX_BLOCKS) {
                     if (hd == 64) k_attn_tiled<2><<<attn_grid, dim3(SMALL_THREADS), 0, st>>>(aa);
@@ -462,7 +466,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int n_se
     // chains: few rows leave the layer kernels short of workgroups and bound by their own start-up and dependent
     // memory round trips; ranges of sequences that run side by side fill the compute units.  Each reads the weights
     // again (from the caches when the chains keep pace), so the count stays small.
-    const int chains = tasc_forward_chains(m, s, nq);
+    const int chains = M_all == s->batch * nq ? tasc_forward_chains(m, s, nq) : 1;
     if (chains <= 1) {
         const tasc_status rc = run_layers(0, s->batch, st);
         if (rc != TASC_OK) return rc;
@@ -819,20 +823,24 @@ int tasc_forward_chains(const tasc_model* m, const tasc_session* s, int32_t nq) 
     return chains;
 }
 
-bool tasc_forward_is_tiled(const tasc_model* m, const tasc_session* s, int32_t nq) {
+bool tasc_forward_is_small(const tasc_model* m, const tasc_session* s, int32_t nq) {
     const int decode_rows = s->max_rows < SMALL_ROWS ? s->max_rows : SMALL_ROWS;
-    if (g_tasc_config.small_path != 0 && nq <= SMALL_ROWS && small_path_fits(m, s->batch, decode_rows, s->max_blocks)) return false;
-    return g_tasc_config.tiled_path != 0 && tiled_path_fits(m->desc);
+    return g_tasc_config.small_path != 0 && nq <= SMALL_ROWS && small_path_fits(m, s->batch, decode_rows, s->max_blocks);
 }
 
-tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, int32_t n_sel, float* logits_dbg,
+bool tasc_forward_is_tiled(const tasc_model* m, const tasc_session* s, int32_t nq) {
+    if (tasc_forward_is_small(m, s, nq)) return false;
+    return g_tasc_config.tiled_path != 0 && tasc_tiled_fits(m->desc);
+}
+
+tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, int32_t n_rows, int32_t n_sel, float* logits_dbg,
                               TascVerifyTail* tail, hipStream_t st) {
     if (tail) tail->done = false;
     // The kernel family of a decode step (nq <= 16 rows per sequence) is a property of the session, not of the
     // call's row count, so that a greedy step and a speculative step of one session use the same kernels and
     // reduce every row in the same order.  Prompt chunks of more than 16 rows always take the tiled kernels.
     const int decode_rows = s->max_rows < SMALL_ROWS ? s->max_rows : SMALL_ROWS;
-    if (g_tasc_config.small_path != 0 && nq <= SMALL_ROWS && small_path_fits(m, s->batch, decode_rows, s->max_blocks)) {
+    if (tasc_forward_is_small(m, s, nq)) {
         if (g_tasc_config.small_kernel != 0) {
             int cus = 0;
             {
@@ -851,7 +859,7 @@ tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, 
         }
         return forward_small(m, s, nq, n_sel, logits_dbg, tail, st);
     }
-    if (g_tasc_config.tiled_path != 0 && tiled_path_fits(m->desc)) return forward_tiled(m, s, nq, n_sel, logits_dbg, tail != nullptr, st);
-    if (m->desc.dtype == TASC_F32) return forward_generic<float>(m, s, nq, n_sel, logits_dbg, st);
-    return forward_generic<BF16>(m, s, nq, n_sel, logits_dbg, st);
+    if (g_tasc_config.tiled_path != 0 && tasc_tiled_fits(m->desc)) return forward_tiled(m, s, nq, n_rows, n_sel, logits_dbg, tail != nullptr, st);
+    if (m->desc.dtype == TASC_F32) return forward_generic<float>(m, s, nq, n_rows, n_sel, logits_dbg, st);
+    return forward_generic<BF16>(m, s, nq, n_rows, n_sel, logits_dbg, st);
 }

@@ -438,7 +438,7 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
                 const int m = mwave + 32 * j + lr, mc = min(m, M - 1);
-                const int b = mc / gm.nq, ir = mc % gm.nq, pos = rp.pos0[b] + ir;
+                const int b = gm.seq(mc), ir = gm.index(mc, b), pos = rp.pos0[b] + ir;
                 const bool active = m < M && ir < rp.n_rows[b];
                 const int tpos = pos < rp.max_pos ? pos : rp.max_pos - 1, slot = pos % TASC_KV_BLOCK;
                 BF16* const page = rp.kv_layer + (active ? (size_t)rp.block_tab[(size_t)b * gm.max_blocks + pos / TASC_KV_BLOCK] * gm.page_elems : 0);

@@ -139,9 +139,16 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const T* __restrict__ A, c
 }
 
 // ---------------------------------------------------------------- RoPE + KV append
+// Rows of a forward: sequence b has the n_rows[b] rows row0[b] .. row0[b] + n_rows[b] - 1, row_seq[r] = the sequence of row r.
+// Rows that belong to no sequence (the persistent kernels' prompt chunks) have i >= n_rows[b].
 struct KvGeom {
-    int32_t H, Hkv, hd, nq, max_blocks;
-    size_t page_elems;   // elements of one page: K [Hkv][16][hd] then V^T [Hkv][hd][16]
+    int32_t H, Hkv, hd, max_blocks;
+    size_t page_elems;        // elements of one page: K [Hkv][16][hd] then V^T [Hkv][hd][16]
+    const int32_t* row_seq;   // of the launch's first row on
+    const int32_t* row0;      // [B], counted over the whole forward
+    int32_t first;            // the launch's first row in that count
+    __device__ int seq(int r) const { return row_seq[r]; }
+    __device__ int index(int r, int b) const { return r + first - row0[b]; }
 };
 
 // Row r = (sequence b, i) sits at position pos0[b] + i.  q is rotated into `q_out`; k is rotated and
@@ -152,7 +159,7 @@ __global__ void k_rope_kv(const float* __restrict__ qkv, const float* __restrict
                           int max_pos, const int32_t* __restrict__ n_rows, const int32_t* __restrict__ pos0,
                           const int32_t* __restrict__ block_tab, KvGeom gm, T* __restrict__ q_out, T* __restrict__ kv_layer,
                           int n_slices = 1, size_t slice_stride = 0) {
-    const int r = blockIdx.x, b = r / gm.nq, i = r % gm.nq;
+    const int r = blockIdx.x, b = gm.seq(r), i = gm.index(r, b);
     const bool active = i < n_rows[b];
     const int pos = pos0[b] + i;
     const int tpos = pos < max_pos ? pos : max_pos - 1;
@@ -196,24 +203,20 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T* __restrict__ q, c
                                                       const int32_t* __restrict__ n_rows, const int32_t* __restrict__ pos0,
                                                       const int32_t* __restrict__ block_tab, KvGeom gm, float scale,
                                                       T* __restrict__ att) {
-    extern __shared__ float s_q[];   // [nq][hd]
+    extern __shared__ float s_q[];   // [most rows of a sequence][hd]
     const int b = blockIdx.x, j = blockIdx.y, g = (j * gm.Hkv) / gm.H;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int hd = gm.hd, nr = n_rows[b], p0 = pos0[b];
-    const size_t qstride = (size_t)gm.H * hd;
-    for (int idx = threadIdx.x; idx < gm.nq * hd; idx += blockDim.x) {
+    const size_t qstride = (size_t)gm.H * hd, row0 = gm.row0[b];
+    for (int idx = threadIdx.x; idx < nr * hd; idx += blockDim.x) {
         const int i = idx / hd, e = idx % hd;
-        s_q[idx] = to_f(q[(size_t)(b * gm.nq + i) * qstride + j * hd + e]);
+        s_q[idx] = to_f(q[(row0 + i) * qstride + j * hd + e]);
     }
     __syncthreads();
     const int32_t* bt = block_tab + (size_t)b * gm.max_blocks;
     const size_t v_off = (size_t)gm.Hkv * TASC_KV_BLOCK * hd;
-    for (int i = wave; i < gm.nq; i += 4) {
-        T* out = att + (size_t)(b * gm.nq + i) * qstride + j * hd;
-        if (i >= nr) {
-            for (int e = lane; e < hd; e += 64) out[e] = from_f<T>(0.f);
-            continue;
-        }
+    for (int i = wave; i < nr; i += 4) {
+        T* out = att + (row0 + i) * qstride + j * hd;
         const float* qi = s_q + i * hd;
         const int L = p0 + i + 1;
         float m = -INFINITY, l = 0.f, acc[4] = {0, 0, 0, 0};

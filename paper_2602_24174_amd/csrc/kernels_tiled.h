@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1,
     __shared__ int32_t s_rpage[EPI == TEPI_ROPE ? BM : 1];     // its page
     if (EPI == TEPI_ROPE && tid < BM) {
         const int m = min(m0 + tid, M - 1);
-        const int b = m / rp.gm.nq, ir = m % rp.gm.nq;
+        const int b = rp.gm.seq(m), ir = rp.gm.index(m, b);
         const int pos = rp.pos0[b] + ir;
         const bool active = ir < rp.n_rows[b];
         s_rpos[tid] = pos < rp.max_pos ? pos : rp.max_pos - 1;
@@ -534,13 +534,15 @@ __global__ void k_bias_ptr(BiasCsr bias, const int32_t* __restrict__ sel_tok, in
 // attention phase of the small-batch kernel (S^T = K Q^T, O^T = V^T P^T, key tiles of 32 at absolute
 // positions dealt to the 8 waves, fixed merge tree), with plain kernel arguments.
 struct AttnArgs {
-    const BF16* q;            // [B * nq, H * hd]
-    BF16* att;                // [B * nq, H * hd]
+    const BF16* q;            // [rows, H * hd]
+    BF16* att;                // [rows, H * hd]
     const BF16* kv_layer;
     const int32_t* n_rows;
     const int32_t* pos0;
     const int32_t* block_tab;
-    int32_t B, nq, H, Hkv, max_blocks;
+    const int32_t* row0;      // [B] first row of the sequence, counted over the whole forward
+    int32_t b0, first, rows;  // first sequence and first row (in that count) of the launch, and its rows
+    int32_t nq, H, Hkv, max_blocks;   // nq = most rows of a sequence
     size_t page_elems;
     float scale;
 };
@@ -557,9 +559,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_attn_tiled(AttnArgs a) {
     const size_t v_off = (size_t)a.Hkv * TASC_KV_BLOCK * hd;
     const int m = lane & 15, qd = lane >> 4;
     float* slot_ml = s_buf + 4 * TILED_ATT_SLOT;
-    const int b = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
+    const int b = a.b0 + blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
     const int r0 = blockIdx.y * rows_pass;
-    const int nr = a.n_rows[b], p0 = a.pos0[b];
+    const int nr = a.n_rows[b], p0 = a.pos0[b], row_b = a.row0[b] - a.first;
+    if (r0 >= nr * Gq) return;               // a shorter sequence: no rows in this pass
     const int32_t* bt = a.block_tab + (size_t)b * a.max_blocks;
     // keys this pass can see: up to the position of its last query row
     const int i_last = min(nr - 1, (min(r0 + rows_pass, R) - 1) / Gq);
@@ -573,7 +576,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_attn_tiled(AttnArgs a) {
         const int i = r / Gq, jq = r % Gq;
         const bool ok = r < R && i < nr;
         qi[rt] = ok ? p0 + i : -1;
-        const BF16* qp = a.q + (size_t)(b * a.nq + (ok ? i : 0)) * a.H * hd + (size_t)(g * Gq + (ok ? jq : 0)) * hd;
+        const BF16* qp = a.q + (size_t)(row_b + (ok ? i : 0)) * a.H * hd + (size_t)(g * Gq + (ok ? jq : 0)) * hd;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             bf16x8 v = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * qd);
@@ -727,10 +730,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_attn_tiled(AttnArgs a) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const int r = r0 + 16 * rt + m;
-            if (r < R) {
+            if (r < nr * Gq) {
                 const int i = r / Gq, jq = r % Gq;
                 const float inv = lsum[rt] > 0.f ? 1.0f / lsum[rt] : 0.f;
-                BF16* op = a.att + (size_t)(b * a.nq + i) * a.H * hd + (size_t)(g * Gq + jq) * hd;
+                BF16* op = a.att + (size_t)(row_b + i) * a.H * hd + (size_t)(g * Gq + jq) * hd;
 #pragma unroll
                 for (int dt = 0; dt < ndt; ++dt)
                     *reinterpret_cast<u32x2*>(op + 16 * dt + 4 * qd) =
@@ -752,8 +755,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_attn_tiled(AttnArgs a) {
 // denominators go to part_o / part_ml for k_attn_merge, which adds the chunks in the order c = 0, 1, ...
 struct AttnStagedArgs {
     AttnArgs a;
-    float* part_o;            // [C][B * nq][H * hd]
-    float* part_ml;           // [C][B * nq][H][2]
+    float* part_o;            // [C][rows][H * hd]
+    float* part_ml;           // [C][rows][H][2]
     int32_t C;
 };
 #define TA_KPAD 8             // bf16 elements of padding per key row / value row in LDS
@@ -774,9 +777,10 @@ __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(4
     const int m = lane & 15, qd = lane >> 4;
     const int rt = wave & 3, par = wave >> 2;
     const int Gq = a.H / a.Hkv, R = a.nq * Gq;
-    const int b = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
+    const int b = a.b0 + blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
     const int r0 = blockIdx.y * 64, c = blockIdx.z, C = aa.C;
-    const int nr = a.n_rows[b], p0 = a.pos0[b];
+    const int nr = a.n_rows[b], p0 = a.pos0[b], row_b = a.row0[b] - a.first;
+    if (r0 >= nr * Gq) return;                                       // a shorter sequence: no rows in this pass
     const int32_t* bt = a.block_tab + (size_t)b * a.max_blocks;
     const size_t v_off = (size_t)a.Hkv * TASC_KV_BLOCK * hd;
     const int i_last = min(nr - 1, (min(r0 + 64, R) - 1) / Gq);
@@ -796,7 +800,7 @@ __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(4
     const bool tile_rows = r0 + 16 * rt < R;                         // the wave has rows at all
     bf16x8 qf[NKS];
     {
-        const BF16* qp = a.q + (size_t)(b * a.nq + (row_ok ? qi_row : 0)) * a.H * hd + (size_t)(g * Gq + (row_ok ? jq : 0)) * hd;
+        const BF16* qp = a.q + (size_t)(row_b + (row_ok ? qi_row : 0)) * a.H * hd + (size_t)(g * Gq + (row_ok ? jq : 0)) * hd;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             bf16x8 v = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * qd);
@@ -921,8 +925,8 @@ __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(4
             const f32x4 o2 = *reinterpret_cast<const f32x4*>(so + (size_t)m * hd + 16 * dt + 4 * qd);
             o[dt] = o[dt] * c1 + o2 * c2;
         }
-        if (r < R && qi_row < a.nq) {
-            const size_t row = (size_t)(b * a.nq + qi_row), head = (size_t)(g * Gq + jq);
+        if (row_ok) {
+            const size_t row = (size_t)(row_b + qi_row), head = (size_t)(g * Gq + jq);
             if (C == 1) {
                 const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
                 BF16* op = a.att + (row * a.H + head) * hd;
@@ -930,7 +934,7 @@ __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(4
                 for (int dt = 0; dt < ndt; ++dt)
                     *reinterpret_cast<u32x2*>(op + 16 * dt + 4 * qd) = pack_bf16x4(o[dt][0] * inv, o[dt][1] * inv, o[dt][2] * inv, o[dt][3] * inv);
             } else {
-                const size_t rows_all = (size_t)a.B * a.nq;
+                const size_t rows_all = (size_t)a.rows;
                 float* po = aa.part_o + (((size_t)c * rows_all + row) * a.H + head) * hd;
 #pragma unroll
                 for (int dt = 0; dt < ndt; ++dt) *reinterpret_cast<f32x4*>(po + 16 * dt + 4 * qd) = o[dt];

@@ -157,6 +157,8 @@ struct tasc_model {
 #define TASC_DRAFT_MAX_LEN 4096   // longest sequence the draft kernel can hold in LDS
 #define TASC_LM_STRIP 128         // vocabulary columns per partial-argmax strip
 
+// M_lm = batch x max_rows: rows of a verify step, and at least the rows a prompt chunk feeds to the LM head.
+// M_max >= M_lm: rows of a prompt chunk of the tiled kernels (tasc_session::row_cap).
 struct TascSessDev {
     // per-sequence state (device)
     int32_t* tokens;     // [B, max_len] committed tokens: prompt then generated (last one = pending)
@@ -169,8 +171,11 @@ struct TascSessDev {
     int32_t* row_tok;    // [M_max] input token of every row (clamped into the vocabulary)
     int32_t* n_rows;     // [B] active rows of the sequence in this forward
     int32_t* pos0;       // [B] position of the sequence's first row
-    int32_t* sel_rows;   // [M_max] rows fed to the LM head (negative: none, row 0 is used and ignored)
-    int32_t* sel_tok;    // [M_max] input token of every LM-head row (its bias row)
+    int32_t* row_seq;    // [M_max] sequence of every row
+    int32_t* row0;       // [B] the sequence's first row
+    int64_t* off;        // [B + 1] prompt offsets of the running prefill
+    int32_t* sel_rows;   // [M_lm] rows fed to the LM head (negative: none, row 0 is used and ignored)
+    int32_t* sel_tok;    // [M_lm] input token of every LM-head row (its bias row)
     // counters: [0] sequences that reached max_new, [1] min n_emit scratch, [2] steps, [3] accepted,
     // [4] proposed, [8..8+TASC_MAX_K] accept-length histogram
     u64* counters;
@@ -181,15 +186,15 @@ struct TascSessDev {
     void* q;             // [M_max, H hd] rotated queries, model dtype
     void* att;           // [M_max, H hd]
     void* act;           // [M_max, F]
-    float* part_val;     // [M_max, n_strips]
-    int32_t* part_idx;   // [M_max, n_strips]
-    int32_t* amax;       // [M_max] argmax token of every LM-head row
+    float* part_val;     // [M_lm, n_strips]
+    int32_t* part_idx;   // [M_lm, n_strips]
+    int32_t* amax;       // [M_lm] argmax token of every LM-head row
     float* att_part;     // attention split partials
     char* small_ws;      // the small-batch kernel's per-phase / per-layer activation buffers (tasc_small_ws_bytes)
     int32_t* drafts;     // [B, TASC_MAX_K] used by tasc_generate
-    int32_t* bias_ptr;   // [M_max, n_strips + 1] LM-head bias cursors
-    int64_t* bias_first; // [M_max] first entry of an LM-head row's bias list (tiled kernels)
-    float* bias_base;    // [M_max] its bias of unseen successors
+    int32_t* bias_ptr;   // [M_lm, n_strips + 1] LM-head bias cursors
+    int64_t* bias_first; // [M_lm] first entry of an LM-head row's bias list (tiled kernels)
+    float* bias_base;    // [M_lm] its bias of unseen successors
 };
 
 // one verify step of the tiled kernels, recorded once and replayed: its launches only name buffers of the session and
@@ -206,6 +211,7 @@ struct TascStepGraph {
 struct tasc_session {
     const tasc_model* model;
     int32_t batch, max_len, max_rows, max_blocks, n_strips;
+    int32_t row_cap;          // rows the activation buffers hold
     int32_t max_new;
     int32_t prefilled;
     void* kv_pool;
@@ -293,10 +299,15 @@ extern TascConfig g_tasc_config;
 tasc_status tasc_pipe_arm(tasc_session* s, hipStream_t st);
 // true if a forward of nq rows per sequence of this session takes the tiled kernels (and no fused persistent one)
 bool tasc_forward_is_tiled(const tasc_model* m, const tasc_session* s, int32_t nq);
+// true if it takes a fused persistent kernel (whose rows are batch x nq, sequence by sequence)
+bool tasc_forward_is_small(const tasc_model* m, const tasc_session* s, int32_t nq);
 // the chain count forward_tiled would use
 int tasc_forward_chains(const tasc_model* m, const tasc_session* s, int32_t nq);
-tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, int32_t n_sel,
+// a forward of n_rows rows, at most nq of one sequence (a verify step and the persistent kernels: batch x nq)
+tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, int32_t n_rows, int32_t n_sel,
                               float* logits_dbg, TascVerifyTail* tail, hipStream_t st);
+// true if the model has the shapes the tiled kernels serve
+bool tasc_tiled_fits(const tasc_model_desc& c);
 
 // profile.hip: optional event timing per kernel class
 bool tasc_prof_on(int cls);

@@ -1,0 +1,59 @@
+"""Prompt chunks without padding rows: prompts of very different lengths (one token to many chunks) lie one behind the other in
+a forward, on the type-generic kernels and on every head size of the tiled ones; more rows than one chunk holds; then a verify
+step over the cache they filled, against the oracle."""
+import numpy as np
+import pytest
+
+import workload as W
+from oracle import model as OM
+
+pytestmark = pytest.mark.gpu
+
+BF16 = dict(dtype="bf16", d_model=128, d_ffn=192)
+CASES = {
+    # fp32, chunks of 24 positions: the last one holds a single position of a single sequence
+    "f32": (dict(n_heads=4, n_kv_heads=2, head_dim=32), [73, 1, 24, 25, 3], 24, 1e-3),
+    # one chunk (5 to 37 rows of head_dim 32: the unstaged attention), tail sequences of one token
+    "hd32": (dict(BF16, n_heads=6, n_kv_heads=2, head_dim=32, d_model=192), [37, 1, 5, 30], 32, 5e-2),
+    "hd64": (dict(BF16, n_heads=4, n_kv_heads=2, head_dim=64), [300, 1, 2, 77, 150, 16], 40, 5e-2),
+    "hd128": (dict(BF16, n_heads=4, n_kv_heads=1, head_dim=128), [260, 64, 65, 1], 17, 5e-2),
+    # 21,000 rows: three chunks of about 7,000 whose sequences end in different ones
+    "many": (dict(BF16, n_heads=2, n_kv_heads=1, head_dim=64), [640 - (b * 53) % 600 for b in range(64)], 20, 5e-2),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_packed_prompts(name):
+    import torch
+    import paper_2602_24174_amd as T
+    shape, lens, max_rows, tol = CASES[name]
+    k, B = 3, len(lens)
+    cfg = W.get_config("cfg1").scaled(n_layers=2, vocab=700, batch=B, n_docs=800, **shape)
+    weights = W.make_model(cfg, W.make_corpus(cfg))
+    rng = np.random.default_rng(3)
+    prompts = [rng.integers(0, cfg.vocab, n).astype(np.int32) for n in lens]
+    max_len = max(lens) + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, weights, max_len)
+    sess = T.tasc_session_create(model, B, max_len, max_rows)
+    drafts = rng.integers(0, cfg.vocab, (B, k)).astype(np.int32)
+    z = torch.zeros((B, k + 1, cfg.vocab), dtype=torch.float32, device="cuda")
+    for again in range(2):       # the second prefill finds the first one's rows in every buffer
+        print(f"{name} prefill {again}", flush=True)
+        T.tasc_session_prefill(model, sess, np.concatenate(prompts), np.cumsum([0] + lens).astype(np.int64), 1)
+        T.tasc_verify_step(model, sess, torch.from_numpy(drafts).cuda(), k, None, None, z)
+        torch.cuda.synchronize()
+        if again == 0:
+            first = z.cpu().numpy()
+    assert (z.cpu().numpy() == first).all()
+    om = OM.OracleModel(cfg, weights)
+    for b in sorted({0, 1, B // 2, B - 1}):
+        c = om.new_cache(max_len)
+        zp = om.forward(prompts[b].tolist(), c, last_only=True)[0]
+        c.length = lens[b]
+        tok = T.tasc_session_get_tokens(sess, b)
+        assert tok[:-1].tolist() == prompts[b].tolist()
+        assert zp[int(tok[-1])] >= zp.max() - 2 * tol, "the committed token is not the target's argmax"
+        want = om.forward([int(tok[-1])] + drafts[b].tolist(), c)
+        worst = float(np.abs(first[b].astype(np.float64) - want).max())
+        print(f"{name} sequence {b} ({lens[b]} tokens): max |logit - oracle| = {worst:.3e}", flush=True)
+        assert worst <= tol
