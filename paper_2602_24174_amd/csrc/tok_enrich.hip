@@ -1,9 +1,10 @@
 // Counting core of the paper's tokenizer enrichment ("Enriching the Tokenizer": merge reward
 // f_merge(t^n) = freq(t^n) (n - 1) and the loop of the algorithm "Tokenizer Enrichment"), without the
 // prefix-collision filter, which needs token strings: every step counts the n-grams (2 <= n <= n_max) of the corpus
-// as currently tokenised with the ordinary table builder (p_min = 1), picks the n-gram with the largest reward
+// as currently tokenised with the table builder's counting stage, picks the n-gram with the largest reward
 // (ties: shorter, then smallest token tuple), gives it the next free token id and re-tokenises the corpus on the
 // device (left to right, without overlap, inside each output).
+#include <algorithm>
 #include <vector>
 
 #include "tasc_internal.h"
@@ -42,17 +43,41 @@ __device__ inline void block_best(MergeCand& mine, int bits, MergeCand* out) {
     if (threadIdx.x == 0) *out = s_c[0];
 }
 
-// best candidate of every workgroup over the full table of one order
-__global__ __launch_bounds__(kThreads) void k_best_in_table(const TascSlot* __restrict__ slots, u64 cap, int n, int bits, MergeCand* block_out) {
+// The largest count of a counting table ({position + 1 : 32, count : 32} slots), then the best n-gram among the slots that
+// have it: only those look their tokens up in the corpus (one slot in two holds a count of 1 or 2).
+__global__ __launch_bounds__(kThreads) void k_max_count(const u64* __restrict__ slots, u64 cap, u32* max_count) {
+    u32 best = 0;
+    for (u64 i = ((u64)blockIdx.x * kThreads + threadIdx.x) * 2; i < cap; i += (u64)gridDim.x * kThreads * 2) {
+        const ulonglong2 s = *reinterpret_cast<const ulonglong2*>(slots + i);          // cap is a power of two
+        best = max(best, max((u32)s.x, (u32)s.y));
+    }
+    for (int o = 32; o > 0; o >>= 1) best = max(best, (u32)__shfl_xor((int)best, o));
+    __shared__ u32 s_b[kThreads / 64];
+    if ((threadIdx.x & 63) == 0) s_b[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) best = max(best, s_b[w]);
+        if (best > __hip_atomic_load(max_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(max_count, best);
+    }
+}
+__global__ __launch_bounds__(kThreads) void k_best_in_table(const u64* __restrict__ slots, u64 cap, const int32_t* __restrict__ tok,
+                                                            const u32* __restrict__ max_count, int n, int bits, MergeCand* block_out) {
     MergeCand best{0, 0, 0, 0, 0};
-    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < cap; i += (u64)gridDim.x * kThreads) {
-        const TascSlot s = slots[i];
-        if (s.a) {
-            MergeCand c{(u64)s.a * (u64)(n - 1), s.lo, s.hi, (u32)n, s.a};
-            if (cand_before(c, best, bits)) best = c;
-        }
+    const u32 want = *max_count;
+    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; want && i < cap; i += (u64)gridDim.x * kThreads) {
+        const u64 s = slots[i];
+        if ((u32)s != want) continue;
+        MergeCand c{(u64)want * (u64)(n - 1), 0, 0, (u32)n, want};
+        for (int j = 0; j < n; ++j) tasc_key_put(c.lo, c.hi, j, bits, (u32)tok[(s >> 32) - 1 + j]);
+        if (cand_before(c, best, bits)) best = c;
     }
     block_best(best, bits, block_out + blockIdx.x);
+}
+// flag = 1 if a token lies outside [0, vocab)
+__global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __restrict__ tok, u64 T, int vocab, u32* flag) {
+    bool bad = false;
+    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < T; i += (u64)gridDim.x * kThreads) bad = bad || tok[i] < 0 || tok[i] >= vocab;
+    if (bad) atomicOr(flag, 1u);
 }
 __global__ __launch_bounds__(kThreads) void k_best_final(const MergeCand* __restrict__ cands, int count, int bits, MergeCand* out) {
     MergeCand best{0, 0, 0, 0, 0};
@@ -232,28 +257,45 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     TOK_TRY(bufs.get(&pos, T0 + 1)); TOK_TRY(bufs.get(&bsum, scan_blocks));
     TOK_TRY(bufs.get(&d_off, (size_t)n_docs + 1)); TOK_TRY(bufs.get(&d_off2, (size_t)n_docs + 1));
     TOK_TRY(bufs.get(&cands, (size_t)cand_blocks * (TASC_MAX_ORDER + 1))); TOK_TRY(bufs.get(&best, 1));
+    auto windows_of = [&](const std::vector<int64_t>& o, int n) {
+        u64 w = 0;
+        for (int64_t d = 0; d < n_docs; ++d) w += (u64)std::max<int64_t>(0, o[d + 1] - o[d] - n + 1);
+        return w;
+    };
     if (T0) TASC_HIP(hipMemcpyAsync(cur, tokens, T0 * sizeof(int32_t), where == TASC_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
     std::vector<int64_t> offs(doc_offsets, doc_offsets + n_docs + 1);
     TASC_HIP(hipMemcpyAsync(d_off, offs.data(), (size_t)(n_docs + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
 
-    // the builder's buffers are kept across the merges (the corpus only shrinks, so they are allocated once)
-    struct CacheOwner {
-        TascBuildCache c{};
-        ~CacheOwner() { tasc_build_cache_free(&c); }
-    } build_cache;
+    // the counting table is kept across the merges (the corpus only shrinks)
+    u64 *slots, *counters;                                   // counters: [0], [1] the counting stage's; [2] token flag; [8 + n] largest count of order n
+    unsigned char* rem;
+    TOK_TRY(bufs.get(&slots, budget > 0 ? tasc_count_cap(windows_of(offs, 2)) : 1)); TOK_TRY(bufs.get(&counters, 8 + TASC_MAX_ORDER + 1));
+    TOK_TRY(bufs.get(&rem, T0));
     u64 T = T0;
     corpus_len[0] = (int64_t)T;
     int done = 0;
     for (; done < budget; ++done) {
         if (T == 0) break;
-        tasc_ngram* ng = nullptr;
-        TOK_TRY(tasc_ngram_build_cached(cur, offs.data(), n_docs, vocab_all, n_max, 1, TASC_MEM_DEVICE, stream, &build_cache.c, true, &ng));
-        struct Guard { tasc_ngram* p; ~Guard() { tasc_ngram_destroy(p); } } guard{ng};
+        TASC_HIP(hipMemsetAsync(counters, 0, (8 + TASC_MAX_ORDER + 1) * sizeof(u64), st));
+        if (done == 0) {
+            k_check_tokens<<<dim3(1024), dim3(kThreads), 0, st>>>(cur, T, vocab_all, (u32*)&counters[2]);
+            TASC_LAUNCH_CHECK();
+            u64 bad = 0;
+            TASC_HIP(hipMemcpyAsync(&bad, &counters[2], sizeof bad, hipMemcpyDeviceToHost, st));
+            TASC_HIP(hipStreamSynchronize(st));
+            TASC_REQUIRE(bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
+        }
+        TOK_TRY(tasc_mark_tails(d_off, n_docs, n_max, T, rem, st));
         int n_cand = 0;
         for (int n = 2; n <= n_max; ++n) {
-            const TascSlot* slots = ng->slots[n][1];
-            if (!slots) continue;
-            k_best_in_table<<<dim3(cand_blocks), dim3(kThreads), 0, st>>>(slots, ng->view.ord[n].full_mask + 1, n, bits, cands + n_cand);
+            const u64 windows = windows_of(offs, n);
+            if (windows == 0) continue;
+            const u64 cap = tasc_count_cap(windows);
+            TOK_TRY(tasc_count_order(cur, rem, T, n, bits, slots, cap, counters, st));
+            u32* const top = (u32*)&counters[8 + n];
+            k_max_count<<<dim3(cand_blocks), dim3(kThreads), 0, st>>>(slots, cap, top);
+            TASC_LAUNCH_CHECK();
+            k_best_in_table<<<dim3(cand_blocks), dim3(kThreads), 0, st>>>(slots, cap, cur, top, n, bits, cands + n_cand);
             TASC_LAUNCH_CHECK();
             n_cand += cand_blocks;
         }
