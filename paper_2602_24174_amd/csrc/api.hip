@@ -613,14 +613,14 @@ tasc_status verify_step_enqueue(const tasc_model* m, tasc_session* s, const int3
     return TASC_OK;
 }
 
-// A verify step of the tiled kernels is a few hundred launches whose arguments never change from step to step (row
+// A verify step outside the persistent kernels is a few dozen to a few hundred launches whose arguments never change from step to step (row
 // counts, positions and tokens live in device memory), so the second step with the same arguments is recorded into a
 // graph, on a stream of the session's own, and every later one is a single graph launch on the caller's stream.
 tasc_status verify_step_impl(const tasc_model* m, tasc_session* s, const int32_t* drafts, int32_t k, int32_t* accept_len,
                              int32_t* emitted, float* logits_dbg, int32_t* trace_step, hipStream_t st) {
     TascProfScope whole(TASC_KC_VERIFY, st);
     bool graphable = g_tasc_config.step_graph != 0 && s->chain_ready && !logits_dbg && !trace_step && !tasc_prof_any() &&
-                     tasc_forward_is_tiled(m, s, k + 1);
+                     !tasc_forward_is_small(m, s, k + 1);
     if (graphable) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {

@@ -115,7 +115,7 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
         }
         {
             PROF(TASC_KC_ATTN);
-            k_attn_generic<T><<<dim3(s->batch, H), dim3(256), (size_t)nq * hd * sizeof(float), st>>>(
+            k_attn_generic<T><<<dim3(s->batch, H), dim3(ATTN_GENERIC_THREADS), (size_t)nq * hd * sizeof(float), st>>>(
                 (const T*)d.q, kv_layer, d.n_rows, d.pos0, d.block_tab, gm, scale, (T*)d.att);
         }
         {
@@ -147,7 +147,7 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
         BiasCsr bias{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base};
         {
             PROF(TASC_KC_LMHEAD);
-            k_lmhead_generic<T><<<dim3(s->n_strips), dim3(256), 0, st>>>((const T*)d.h, (const T*)m->lm_head, d.sel_tok, n_sel,
+            k_lmhead_generic<T><<<dim3(s->n_strips), dim3(64 * LM_GENERIC_WAVES), 0, st>>>((const T*)d.h, (const T*)m->lm_head, d.sel_tok, n_sel,
                                                                       c.vocab, D, bias, d.part_val, d.part_idx, s->n_strips,
                                                                       logits_dbg);
         }

@@ -197,9 +197,12 @@ __global__ void k_rope_kv(const float* __restrict__ qkv, const float* __restrict
 
 // ---------------------------------------------------------------- generic attention over the paged cache
 // One workgroup per (sequence, query head); a wave per query row.  Keys are visited in tiles of 64 at
-// absolute positions 0, 64, ...; running max / sum (online softmax) in fp32.
+// absolute positions 0, 64, ...; running max / sum (online softmax) in fp32.  A lane holds one dimension of the output and
+// reads the 16 tokens of a value page in one go (they are contiguous), all pages of the tile ahead of the first product: with a
+// load per key, one sequence of 100 tokens took 46 us, nearly all of it waiting.
+#define ATTN_GENERIC_THREADS 512
 template <typename T>
-__global__ __launch_bounds__(256) void k_attn_generic(const T* __restrict__ q, const T* __restrict__ kv_layer,
+__global__ __launch_bounds__(ATTN_GENERIC_THREADS) void k_attn_generic(const T* __restrict__ q, const T* __restrict__ kv_layer,
                                                       const int32_t* __restrict__ n_rows, const int32_t* __restrict__ pos0,
                                                       const int32_t* __restrict__ block_tab, KvGeom gm, float scale,
                                                       T* __restrict__ att) {
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T* __restrict__ q, c
     __syncthreads();
     const int32_t* bt = block_tab + (size_t)b * gm.max_blocks;
     const size_t v_off = (size_t)gm.Hkv * TASC_KV_BLOCK * hd;
-    for (int i = wave; i < nr; i += 4) {
+    for (int i = wave; i < nr; i += ATTN_GENERIC_THREADS / 64) {
         T* out = att + (row0 + i) * qstride + j * hd;
         const float* qi = s_q + i * hd;
         const int L = p0 + i + 1;
@@ -227,6 +230,7 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T* __restrict__ q, c
                 const T* kp = kv_layer + (size_t)bt[key / TASC_KV_BLOCK] * gm.page_elems +
                               (size_t)(g * TASC_KV_BLOCK + key % TASC_KV_BLOCK) * hd;
                 float dot = 0.f;
+#pragma unroll 4
                 for (int e = 0; e < hd; e += 8) {
                     float kvv[8];
                     load8(kp + e, kvv);
@@ -242,15 +246,27 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T* __restrict__ q, c
             m = m_new;
             const int nk = min(64, L - t0);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] *= corr;
-            for (int kk = 0; kk < nk; ++kk) {
-                const float pk = __shfl(p, kk);
-                const int kpos = t0 + kk;
-                const T* vt = kv_layer + (size_t)bt[kpos / TASC_KV_BLOCK] * gm.page_elems + v_off;
+            for (int c = 0; c < 4; ++c) {
+                acc[c] *= corr;
+                const int e = lane + 64 * c;
+                if (64 * c >= hd) break;
+                // (pages past the row's position are not read, slots past it do not count)
+                float v[4][TASC_KV_BLOCK];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int e = lane + 64 * c;
-                    if (e < hd) acc[c] = fmaf(pk, to_f(vt[(size_t)(g * hd + e) * TASC_KV_BLOCK + kpos % TASC_KV_BLOCK]), acc[c]);
+                for (int pg = 0; pg < 4; ++pg) {
+                    const int kpos = min(t0 + TASC_KV_BLOCK * pg, L - 1);
+                    const T* vt = kv_layer + (size_t)bt[kpos / TASC_KV_BLOCK] * gm.page_elems + v_off + (size_t)(g * hd + min(e, hd - 1)) * TASC_KV_BLOCK;
+                    load8(vt, v[pg]);
+                    load8(vt + 8, v[pg] + 8);
+                }
+#pragma unroll
+                for (int pg = 0; pg < 4; ++pg) {
+                    if (TASC_KV_BLOCK * pg >= nk) break;
+#pragma unroll
+                    for (int q = 0; q < TASC_KV_BLOCK; ++q) {
+                        const float vq = TASC_KV_BLOCK * pg + q < nk ? v[pg][q] : 0.f;
+                        acc[c] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), TASC_KV_BLOCK * pg + q)), vq, acc[c]);
+                    }
                 }
             }
         }
@@ -271,19 +287,23 @@ struct BiasCsr {
 };
 
 // h: [n_rows, d] normalised hidden rows; row r was fed token tok[r] (bias row).  A workgroup covers a
-// strip of TASC_LM_STRIP vocabulary columns, 32 per wave, and leaves, per row, the best (value, index)
-// of its strip; index ties go to the lowest column.  logits (nullable) receives every logit.
+// strip of TASC_LM_STRIP vocabulary columns, 8 per wave, and leaves, per row, the best (value, index)
+// of its strip; index ties go to the lowest column.  logits (nullable) receives every logit.  Four columns
+// at a time: the 32 sums over the wave are independent chains (one column at a time and 32 columns a wave, a vocabulary of
+// 512 took 50 us, all of it the chains' latency).
+#define LM_GENERIC_WAVES 16
 template <typename T>
-__global__ __launch_bounds__(256) void k_lmhead_generic(const T* __restrict__ h, const T* __restrict__ W,
+__global__ __launch_bounds__(64 * LM_GENERIC_WAVES) void k_lmhead_generic(const T* __restrict__ h, const T* __restrict__ W,
                                                         const int32_t* __restrict__ tok, int n_rows, int V, int d,
                                                         BiasCsr bias, float* __restrict__ part_val,
                                                         int32_t* __restrict__ part_idx, int n_strips,
                                                         float* __restrict__ logits) {
-    __shared__ float s_v[4][8];
-    __shared__ int32_t s_i[4][8];
+    constexpr int CW = TASC_LM_STRIP / LM_GENERIC_WAVES, CB = 4;      // columns of a wave, and at a time
+    __shared__ float s_v[LM_GENERIC_WAVES][8];
+    __shared__ int32_t s_i[LM_GENERIC_WAVES][8];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int strip = blockIdx.x;
-    const int c0 = strip * TASC_LM_STRIP + wave * 32;
+    const int c0 = strip * TASC_LM_STRIP + wave * CW;
     for (int r0 = 0; r0 < n_rows; r0 += 8) {
         const int row = r0 + lane;
         const bool own = lane < 8 && row < n_rows;
@@ -303,36 +323,50 @@ __global__ __launch_bounds__(256) void k_lmhead_generic(const T* __restrict__ h,
             bp = lo;
             base = bias.base[u];
         }
-        for (int c = c0; c < c0 + 32 && c < V; ++c) {
-            const T* w = W + (size_t)c * d;
-            float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int cb = c0; cb < c0 + CW && cb < V; cb += CB) {
+            float acc[CB][8];
+#pragma unroll
+            for (int u = 0; u < CB; ++u)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) acc[u][r] = 0.f;
             for (int k = lane * 8; k < d; k += 512) {
-                float wv[8];
-                load8(w + k, wv);
+                float wv[CB][8];
+#pragma unroll
+                for (int u = 0; u < CB; ++u) load8(W + (size_t)min(cb + u, V - 1) * d + k, wv[u]);
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
                     if (r0 + r < n_rows) {
                         float av[8];
                         load8(h + (size_t)(r0 + r) * d + k, av);
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) acc[r] = fmaf(av[e], wv[e], acc[r]);
+                        for (int u = 0; u < CB; ++u)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) acc[u][r] = fmaf(av[e], wv[u][e], acc[u][r]);
                     }
                 }
             }
-            float mine = 0.f;
+            float mine[CB];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                float v = wave_sum(acc[r]);
-                if (lane == r) mine = v;
-            }
-            if (own) {
-                float z = mine;
-                if (bias.rowptr) {
-                    if (bp < be && bias.col[bp] == c) z += bias.val[bp++];
-                    else z += base;
+            for (int u = 0; u < CB; ++u) mine[u] = 0.f;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int u = 0; u < CB; ++u) {
+                    const float v = wave_sum(acc[u][r]);
+                    if (lane == r) mine[u] = v;
                 }
-                if (logits) logits[(size_t)row * V + c] = z;
-                if (z > best) { best = z; best_i = c; }
+#pragma unroll
+            for (int u = 0; u < CB; ++u) {
+                const int c = cb + u;
+                if (own && c < V) {
+                    float z = mine[u];
+                    if (bias.rowptr) {
+                        if (bp < be && bias.col[bp] == c) z += bias.val[bp++];
+                        else z += base;
+                    }
+                    if (logits) logits[(size_t)row * V + c] = z;
+                    if (z > best) { best = z; best_i = c; }
+                }
             }
         }
         if (lane < 8) { s_v[wave][lane] = best; s_i[wave][lane] = best_i; }
@@ -340,7 +374,7 @@ __global__ __launch_bounds__(256) void k_lmhead_generic(const T* __restrict__ h,
         if (wave == 0 && own) {
             float bv = s_v[0][lane];
             int32_t bi = s_i[0][lane];
-            for (int w = 1; w < 4; ++w)
+            for (int w = 1; w < LM_GENERIC_WAVES; ++w)
                 if (s_v[w][lane] > bv) { bv = s_v[w][lane]; bi = s_i[w][lane]; }
             part_val[(size_t)row * n_strips + strip] = bv;
             part_idx[(size_t)row * n_strips + strip] = bi;

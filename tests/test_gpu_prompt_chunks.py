@@ -13,6 +13,9 @@ BF16 = dict(dtype="bf16", d_model=128, d_ffn=192)
 CASES = {
     # fp32, chunks of 24 positions: the last one holds a single position of a single sequence
     "f32": (dict(n_heads=4, n_kv_heads=2, head_dim=32), [73, 1, 24, 25, 3], 24, 1e-3),
+    # head sizes and a vocabulary that only the type-generic kernels take: several dimensions per lane, odd columns
+    "f32_hd200": (dict(n_heads=2, n_kv_heads=1, head_dim=200, d_model=136, vocab=701), [70, 1, 130, 65], 24, 1e-3),
+    "bf16_hd96": (dict(BF16, n_heads=2, n_kv_heads=2, head_dim=96, vocab=1003), [40, 17, 3], 24, 5e-2),
     # one chunk (5 to 37 rows of head_dim 32: the unstaged attention), tail sequences of one token
     "hd32": (dict(BF16, n_heads=6, n_kv_heads=2, head_dim=32, d_model=192), [37, 1, 5, 30], 32, 5e-2),
     "hd64": (dict(BF16, n_heads=4, n_kv_heads=2, head_dim=64), [300, 1, 2, 77, 150, 16], 40, 5e-2),
@@ -28,7 +31,7 @@ def test_packed_prompts(name):
     import paper_2602_24174_amd as T
     shape, lens, max_rows, tol = CASES[name]
     k, B = 3, len(lens)
-    cfg = W.get_config("cfg1").scaled(n_layers=2, vocab=700, batch=B, n_docs=800, **shape)
+    cfg = W.get_config("cfg1").scaled(**dict(dict(n_layers=2, vocab=700, batch=B, n_docs=800), **shape))
     weights = W.make_model(cfg, W.make_corpus(cfg))
     rng = np.random.default_rng(3)
     prompts = [rng.integers(0, cfg.vocab, n).astype(np.int32) for n in lens]
