@@ -34,27 +34,56 @@ __device__ inline bool probe(const TascSlot* __restrict__ tab, u64 mask, u64 lo,
     return false;
 }
 
-// One WAVE per sequence: every exchange between lanes is a ballot, a shuffle or an LDS access of the same wave, so
-// the k sequential proposals cross no workgroup barrier.  Per proposal:
-//   * corpus source: lanes 0 .. n_max-2 request the first slot of one order each, and the answers are only looked at
-//     after the context phase, so the round trip runs under it;
-//   * context source: the match length of every position with the running suffix is UPDATED from the previous
-//     proposal's (a position matches m + 1 tokens iff the token before it is the one just appended and its predecessor
-//     matched m): one compare pass over the sequence compacts the matching positions into a list (ballot + prefix
-//     count), everything after that touches list entries only.  The positions of the longest match feed their
-//     successors into a hash table in LDS (token -> multiplicity; entries carry a generation number, so the table
-//     is never cleared), whose distinct entries are the candidates;
-//   * the candidates' corpus counts are requested at EVERY order before the corpus context is known (a second round
+// One WAVE per sequence: every exchange between lanes is a ballot, a lane read or an LDS access of the same wave, so
+// the k sequential proposals cross no workgroup barrier.  What bounds it is that chain of dependent steps and not memory
+// (64 sequences of 64 to 2,300 tokens, k = 8: 56 us, 92 before; its tokens and slots are 0.7 MB).  Per proposal, in cycles of
+// that workload:
+//   * the running suffix comes from LDS into registers, all tokens of it at once, and keys are shifted together from it
+//     without a loop over LDS;
+//   * corpus source (1,400 with the keys): lanes 0 .. n_max-2 request the first slot of one order each, and the answers are
+//     only looked at after the context phase, so the round trip runs under it;
+//   * context source (5,100): one pass over the sequence, 4 tokens per lane and read, lists the positions that follow an
+//     occurrence of the last token (29 on average), then only those are compared with the rest of the suffix.  Carrying every
+//     position's match length from proposal to proposal instead cost three more passes over LDS.  The successors of the longest
+//     matches (900) are counted with a ballot per distinct one while the list fits the wave's lanes, else in a hash table in LDS
+//     (token -> multiplicity; entries carry a generation number, so the table is never cleared); the distinct ones are the
+//     candidates;
+//   * the candidates' corpus counts (1,000) are requested at EVERY order before the corpus context is known (a second round
 //     trip that would otherwise wait for the first), and the ones of the matching order are used;
-//   * the argmax over (score, smallest token) is a wave reduction.
+//   * the argmax over (score, smallest token) is a reduction over neighbouring lanes (DPP, no LDS round trips); with the two
+//     answers 3,000.
 constexpr int kHashSlots = 2 * TASC_DRAFT_MAX_LEN;        // more than any sequence has successors
+static_assert(TASC_DRAFT_MAX_LEN <= 4096 && TASC_DRAFT_MAX_LEN % 4 == 0 && TASC_MAX_ORDER <= 16, "list entries, token reads");
 
+// wave reductions: after the six steps lane 63 has the result, which a lane read hands to all
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u32 dpp_max_step(u32 v) {
+    const u32 w = (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false);
+    return w > v ? w : v;
+}
+__device__ __forceinline__ u32 wave_max_u32(u32 v) {
+    v = dpp_max_step<0x111, 0xf>(v);          // row_shr:1, 2, 4, 8: within 16 lanes
+    v = dpp_max_step<0x112, 0xf>(v);
+    v = dpp_max_step<0x114, 0xf>(v);
+    v = dpp_max_step<0x118, 0xf>(v);
+    v = dpp_max_step<0x142, 0xa>(v);          // row_bcast:15, 31: across them
+    v = dpp_max_step<0x143, 0xc>(v);
+    return (u32)__builtin_amdgcn_readlane((int)v, 63);
+}
 __device__ __forceinline__ u64 wave_max_u64(u64 v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        const u64 w = __shfl_xor(v, o);
-        v = w > v ? w : v;
-    }
-    return v;
+    const u32 hi = wave_max_u32((u32)(v >> 32));
+    return ((u64)hi << 32) | wave_max_u32((u32)(v >> 32) == hi ? (u32)v : 0u);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add_step(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ int wave_add(int v) {
+    v = dpp_add_step<0x111, 0xf>(v);
+    v = dpp_add_step<0x112, 0xf>(v);
+    v = dpp_add_step<0x114, 0xf>(v);
+    v = dpp_add_step<0x118, 0xf>(v);
+    v = dpp_add_step<0x142, 0xa>(v);
+    v = dpp_add_step<0x143, 0xc>(v);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 __device__ __forceinline__ TascSlot slot_load(const TascSlot* p) {
     const uint4 a = reinterpret_cast<const uint4*>(p)[0], b = reinterpret_cast<const uint4*>(p)[1];
@@ -74,13 +103,22 @@ __device__ __forceinline__ bool probe_finish(const TascSlot* __restrict__ tab, u
     return false;
 }
 
+// The key of the m tokens t[m - 1], .., t[0], the oldest as element 0 (the layout of tasc_key_put): shifted together from the
+// newest one down, so every shift is by `bits`.
+__device__ __forceinline__ void key_of(const u32* t, int m, int bits, u64& lo, u64& hi) {
+    lo = hi = 0;
+#pragma unroll
+    for (int i = 0; i < TASC_MAX_ORDER; ++i) {
+        const u64 h = (hi << bits) | (lo >> (64 - bits)), l = (lo << bits) | t[i];
+        if (i < m) { hi = h; lo = l; }
+    }
+}
+
 __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
-    __shared__ int32_t s_tok[TASC_DRAFT_MAX_LEN];
-    __shared__ uint8_t s_ml[TASC_DRAFT_MAX_LEN];          // match length of every position with the suffix (0 outside the list)
-    __shared__ uint16_t s_pos[2][TASC_DRAFT_MAX_LEN];     // positions with a match length >= 1, ping-pong
-    __shared__ u64 s_tab[kHashSlots];                     // {generation : 16, multiplicity : 16, token : 32}
+    __shared__ __attribute__((aligned(16))) int32_t s_tok[TASC_DRAFT_MAX_LEN];
+    __shared__ uint16_t s_pos[TASC_DRAFT_MAX_LEN];        // positions of the last token before the end; of lists beyond 64: {match length - 1 : 4, position : 12}
+    __shared__ __attribute__((aligned(16))) u64 s_tab[kHashSlots];   // {generation : 16, multiplicity : 16, token : 32}
     __shared__ uint16_t s_dl[TASC_DRAFT_MAX_LEN];         // slots of the distinct successors of the current generation
-    __shared__ int32_t s_suf[TASC_MAX_ORDER];             // s_suf[i] = i-th token from the end of the running context
     __shared__ int32_t s_d[TASC_MAX_K];                   // the proposals so far
     __shared__ int s_nd;
     __shared__ TascSlot s_hit[TASC_MAX_ORDER + 1];
@@ -90,29 +128,31 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
     const int N = a.n_tok[b];
     const int Nctx = a.ctx_gen ? N : min(N, a.n_prompt[b]);   // tokens the context statistics cover
     const int32_t* seq = a.tokens + (size_t)b * a.max_len;
-    for (int i0 = 0; i0 < N; i0 += 256) {                  // four loads in flight per lane
-        int32_t v[4];
+    for (int i0 = 0; i0 < N; i0 += 1024) {                 // sixteen loads in flight per lane
+        int32_t v[16];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = seq[min(i0 + 64 * u + lane, N - 1)];
+        for (int u = 0; u < 16; ++u) v[u] = seq[min(i0 + 64 * u + lane, N - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 16; ++u)
             if (i0 + 64 * u + lane < N) s_tok[i0 + 64 * u + lane] = v[u];
     }
-    for (int i = lane; i < kHashSlots; i += 64) s_tab[i] = 0;     // generation 0 = never used
+    u32 tab_mask = 127;                                    // slots of the hash table: at least twice the successors there can be
+    while (tab_mask + 1 < 2 * (u32)Nctx) tab_mask = 2 * tab_mask + 1;
+    for (u32 i = 2 * lane; i <= tab_mask; i += 128) *reinterpret_cast<ulonglong2*>(&s_tab[i]) = make_ulonglong2(0, 0);   // generation 0 = never used
     const u64 q = (u64)a.q16, qb = (u64)(65536 - a.q16);
     const int n_max = a.ng.n_max, bits = a.ng.bits;
     u32 gen = 0;
-    int cur = 0, n_list = 0;                               // which half of s_pos is current, and its length
-    int x_prev = 0, nsuf_prev = -1;
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
 
     for (int j = 0; j < a.k; ++j) {
         const int wlen = N + j;
-        const int nsuf = min(n_max - 1, wlen);
-        if (lane < nsuf) s_suf[lane] = lane < j ? s_d[j - 1 - lane] : s_tok[N - 1 - (lane - j)];
-        __builtin_amdgcn_s_waitcnt(0);
-        __builtin_amdgcn_wave_barrier();
+        const int nsuf = min(n_max - 1, wlen);             // at least 1
+        u32 run[TASC_MAX_ORDER + 1];                       // a candidate, then the suffix
+        u32* const suf = run + 1;                          // suf[i] = i-th token from the end of the running context
+        run[0] = suf[TASC_MAX_ORDER - 1] = 0;
+#pragma unroll
+        for (int i = 0; i < TASC_MAX_ORDER - 1; ++i) suf[i] = (u32)(i < j ? s_d[j - 1 - i] : s_tok[max(N - 1 - (i - j), 0)]);
 
         // ---- corpus source: the first slot of every order is requested now and examined after the context phase
         const int my_n = n_max - lane;                     // lane l probes the contexts of n - 1 = n_max - 1 - l tokens
@@ -120,120 +160,137 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
         u64 c_lo = 0, c_hi = 0, c_idx = 0;
         TascSlot c_slot = {0, 0, 0, 0, 0, 0};
         if (c_probe) {
-            for (int i = 0; i < my_n - 1; ++i) tasc_key_put(c_lo, c_hi, i, bits, (u32)s_suf[my_n - 2 - i]);
+            key_of(suf, my_n - 1, bits, c_lo, c_hi);
             c_idx = tasc_hash_key(c_lo, c_hi, my_n - 1) & a.ng.ord[my_n].ctx_mask;
             c_slot = slot_load(a.ng.ord[my_n].ctx + c_idx);
         }
 
         // ---- context source
         int n_ctx = 0, T_ctx = 0, n_dist = 0;
+        bool in_regs = false;                              // the candidates are (cand_x, cand_c) of the lanes below n_dist, else in the table
+        int cand_x = 0, cand_c = 0;
         if (qb > 0) {
-            int lmax = 0;
-            const int nxt = cur ^ 1;
-            int n_new = 0;
-            if (j == 0 || nsuf_prev < n_max - 1) {
-                // from scratch (the first proposal; or a context still shorter than n_max - 1: a handful of tokens)
-                for (int p0 = 0; p0 < Nctx; p0 += 64) {
-                    const int p = p0 + lane;
-                    int ml = 0;
-                    if (p < Nctx)
-                        while (ml < nsuf && p - 1 - ml >= 0 && s_tok[p - 1 - ml] == s_suf[ml]) ++ml;
-                    if (p < Nctx) s_ml[p] = (uint8_t)ml;
-                    const u64 hit = __ballot(ml > 0);
-                    if (ml > 0) s_pos[nxt][n_new + __popcll(hit & lt_mask)] = (uint16_t)p;
-                    n_new += __popcll(hit);
-                    lmax = max(lmax, ml);
-                }
-            } else {
-                // the positions that follow an occurrence of the token just appended: one compare pass, compacted
-                uint8_t* s_val = reinterpret_cast<uint8_t*>(s_dl);        // their new match lengths, parked until all old ones are read
-                for (int p0 = 1; p0 < Nctx; p0 += 256) {          // 256 positions per round: all their LDS reads in flight together
-                    bool hit1[4];
-                    int mlp[4];
+            int n_list = 0, my_ml = 0;
+            // the places of the last token, 4 tokens per lane and read ...
+            for (int p0 = 0; p0 < Nctx - 1; p0 += 256) {
+                const int t0 = p0 + 4 * lane;
+                const int4 t = *reinterpret_cast<const int4*>(&s_tok[min(t0, TASC_DRAFT_MAX_LEN - 4)]);
+                const u32 tv[4] = {(u32)t.x, (u32)t.y, (u32)t.z, (u32)t.w};
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int p = min(p0 + 64 * u + lane, Nctx - 1);
-                        hit1[u] = p0 + 64 * u + lane < Nctx && s_tok[p - 1] == x_prev;
-                        mlp[u] = (int)s_ml[p - 1];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int p = p0 + 64 * u + lane;
-                        const u64 hit = __ballot(hit1[u]);
-                        if (hit1[u]) {
-                            const int ml = min(mlp[u] + 1, nsuf);
-                            const int at = n_new + __popcll(hit & lt_mask);
-                            s_pos[nxt][at] = (uint16_t)p;
-                            s_val[at] = (uint8_t)ml;
-                            lmax = max(lmax, ml);
-                        }
-                        n_new += __popcll(hit);
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    const bool hit = t0 + u + 1 < Nctx && tv[u] == suf[0];
+                    const u64 m = __ballot(hit);
+                    if (m == 0) continue;
+                    if (hit) s_pos[n_list + __popcll(m & lt_mask)] = (uint16_t)(t0 + u);
+                    n_list += __popcll(m);
                 }
-                __builtin_amdgcn_s_waitcnt(0);
-                __builtin_amdgcn_wave_barrier();
-                for (int e = lane; e < n_list; e += 64) s_ml[s_pos[cur][e]] = 0;          // the old matches go ...
-                __builtin_amdgcn_s_waitcnt(0);
-                __builtin_amdgcn_wave_barrier();
-                for (int e = lane; e < n_new; e += 64) s_ml[s_pos[nxt][e]] = s_val[e];    // ... the new ones come
             }
-            cur = nxt;
-            n_list = n_new;
-            for (int o = 32; o > 0; o >>= 1) lmax = max(lmax, __shfl_xor(lmax, o));
             __builtin_amdgcn_s_waitcnt(0);
             __builtin_amdgcn_wave_barrier();
+            // ... and how much of the suffix before it matches there
+            int e_ml = 0, e_x = 0;                         // the lane's (last) list entry: match length and successor
+            for (int e0 = 0; e0 < n_list; e0 += 64) {
+                const int at = s_pos[min(e0 + lane, n_list - 1)];
+                int before[TASC_MAX_ORDER - 2];
+#pragma unroll
+                for (int i = 1; i < TASC_MAX_ORDER - 1; ++i) before[i - 1] = s_tok[max(at - i, 0)];
+                e_x = s_tok[at + 1];
+                int ml = 1;
+                bool on = true;
+#pragma unroll
+                for (int i = 1; i < TASC_MAX_ORDER - 1; ++i) {
+                    on = on && i < nsuf && at - i >= 0 && (u32)before[i - 1] == suf[i];
+                    ml += on ? 1 : 0;
+                }
+                e_ml = e0 + lane < n_list ? ml : 0;
+                my_ml = max(my_ml, e_ml);
+                if (n_list > 64 && e_ml) s_pos[e0 + lane] = (uint16_t)(((ml - 1) << 12) | at);
+            }
+            int lmax = 0;
+            if (n_list > 0) {
+                lmax = 1;
+                for (int v = nsuf; v > 1; --v)
+                    if (__ballot(my_ml >= v)) { lmax = v; break; }
+            }
+            __builtin_amdgcn_s_waitcnt(0);
+            __builtin_amdgcn_wave_barrier();
+            in_regs = n_list <= 64;
             // back off from the longest matching context until one has a kept successor
             for (int n = lmax + 1; n >= 2 && !n_ctx; --n) {
-                ++gen;
-                if (lane == 0) s_nd = 0;
-                __builtin_amdgcn_s_waitcnt(0);
-                __builtin_amdgcn_wave_barrier();
-                for (int e0 = 0; e0 < n_list; e0 += 64) {
-                    const int e = e0 + lane;
-                    const int p = e < n_list ? s_pos[cur][e] : 0;
-                    const bool in = e < n_list && p >= 1 && s_ml[p] >= n - 1;
-                    const u32 key = in ? (u32)s_tok[p] : 0u;
-                    const u64 act = __ballot(in);
-                    if (!act) continue;
-                    // a run of one token (every lane the same successor) is added in one go by the first lane
-                    const int first = __ffsll((unsigned long long)act) - 1;
-                    const u32 k0 = (u32)__shfl((int)key, first);
-                    const bool uniform = __ballot(in && key == k0) == act;
-                    const bool me = uniform ? lane == first : in;
-                    const u64 add = uniform ? (u64)__popcll(act) : 1ull;
-                    if (me) {
-                        u32 slot = (u32)(tasc_mix64(key) & (kHashSlots - 1));
-                        for (;;) {
-                            const u64 w = s_tab[slot];
-                            if ((u32)(w >> 48) != gen) {
-                                // empty for this generation: claim it
-                                const u64 neu = ((u64)gen << 48) | (add << 32) | key;
-                                if (atomicCAS(reinterpret_cast<unsigned long long*>(&s_tab[slot]), w, neu) == w) {
-                                    s_dl[atomicAdd(&s_nd, 1)] = (uint16_t)slot;
+                int t = 0;
+                if (in_regs) {
+                    n_dist = 0;
+                    u64 todo = __ballot(e_ml >= n - 1);
+                    while (todo) {                         // one round per distinct successor
+                        const int key = __builtin_amdgcn_readlane(e_x, __ffsll((unsigned long long)todo) - 1);
+                        const u64 same = __ballot(e_x == key) & todo;
+                        const int cnt = __popcll(same);
+                        if (lane == n_dist) { cand_x = key; cand_c = cnt; }
+                        ++n_dist;
+                        if (cnt >= a.p_min_ctx) t += cnt;
+                        todo &= ~same;
+                    }
+                } else {
+                    ++gen;
+                    if (lane == 0) s_nd = 0;
+                    __builtin_amdgcn_s_waitcnt(0);
+                    __builtin_amdgcn_wave_barrier();
+                    for (int e0 = 0; e0 < n_list; e0 += 64) {
+                        const int e = e0 + lane;
+                        const int w = e < n_list ? s_pos[e] : 0;
+                        const bool in = e < n_list && (w >> 12) + 1 >= n - 1;
+                        const u32 key = in ? (u32)s_tok[(w & 0xFFF) + 1] : 0u;
+                        const u64 act = __ballot(in);
+                        if (!act) continue;
+                        // a run of one token (every lane the same successor) is added in one go by the first lane
+                        const int first = __ffsll((unsigned long long)act) - 1;
+                        const u32 k0 = (u32)__builtin_amdgcn_readlane((int)key, first);
+                        const bool uniform = __ballot(in && key == k0) == act;
+                        const u64 add = uniform ? (u64)__popcll(act) : 1ull;
+                        if (uniform ? lane == first : in) {
+                            u32 slot = (u32)tasc_mix64(key) & tab_mask;
+                            for (;;) {
+                                const u64 w64 = s_tab[slot];
+                                if ((u32)(w64 >> 48) != gen) {
+                                    // empty for this generation: claim it
+                                    const u64 neu = ((u64)gen << 48) | (add << 32) | key;
+                                    if (atomicCAS(reinterpret_cast<unsigned long long*>(&s_tab[slot]), w64, neu) == w64) {
+                                        s_dl[atomicAdd(&s_nd, 1)] = (uint16_t)slot;
+                                        break;
+                                    }
+                                    continue;              // somebody else took it: look at it again
+                                }
+                                if ((u32)w64 == key) {
+                                    atomicAdd(reinterpret_cast<unsigned long long*>(&s_tab[slot]), add << 32);
                                     break;
                                 }
-                                continue;                  // somebody else took it: look at it again
+                                slot = (slot + 1) & tab_mask;
                             }
-                            if ((u32)w == key) {
-                                atomicAdd(reinterpret_cast<unsigned long long*>(&s_tab[slot]), add << 32);
-                                break;
-                            }
-                            slot = (slot + 1) & (kHashSlots - 1);
                         }
                     }
+                    __builtin_amdgcn_s_waitcnt(0);
+                    __builtin_amdgcn_wave_barrier();
+                    n_dist = s_nd;
+                    for (int e = lane; e < n_dist; e += 64) {
+                        const int c = (int)((s_tab[s_dl[e]] >> 32) & 0xFFFFu);
+                        if (c >= a.p_min_ctx) t += c;
+                    }
+                    t = wave_add(t);
                 }
-                __builtin_amdgcn_s_waitcnt(0);
-                __builtin_amdgcn_wave_barrier();
-                n_dist = s_nd;
-                int t = 0;
-                for (int e = lane; e < n_dist; e += 64) {
-                    const int c = (int)((s_tab[s_dl[e]] >> 32) & 0xFFFFu);
-                    if (c >= a.p_min_ctx) t += c;
-                }
-                for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
                 if (t > 0) { n_ctx = n; T_ctx = t; }
             }
         }
+        // candidate e, from wherever the candidates are
+        auto candidate = [&](int e, int& x, int& c) {
+            if (in_regs) {
+                x = __shfl(cand_x, e & 63);
+                c = __shfl(cand_c, e & 63);
+            } else {
+                const u64 w = s_tab[s_dl[min(e, n_dist - 1)]];
+                x = (int)(u32)w;
+                c = (int)((w >> 32) & 0xFFFFu);
+            }
+        };
 
         // ---- the candidates' corpus counts, requested at every order a corpus context could match (pair = candidate x order)
         const int n_ord = n_max - 1;
@@ -241,18 +298,18 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
         u64 f_lo = 0, f_hi = 0, f_idx = 0;
         TascSlot f_slot = {0, 0, 0, 0, 0, 0};
         int f_n = 0, f_x = 0, f_c = 0;
-        if (spec && lane < n_dist * n_ord) {
-            const u64 w = s_tab[s_dl[lane / n_ord]];
-            f_x = (int)(u32)w;
-            f_c = (int)((w >> 32) & 0xFFFFu);
-            f_n = n_max - lane % n_ord;
-            if (f_c >= a.p_min_ctx && f_n - 1 <= nsuf && a.ng.ord[f_n].full != nullptr) {
-                for (int i = 0; i < f_n - 1; ++i) tasc_key_put(f_lo, f_hi, i, bits, (u32)s_suf[f_n - 2 - i]);
-                tasc_key_put(f_lo, f_hi, f_n - 1, bits, (u32)f_x);
-                f_idx = tasc_hash_key(f_lo, f_hi, f_n) & a.ng.ord[f_n].full_mask;
-                f_slot = slot_load(a.ng.ord[f_n].full + f_idx);
-            } else {
-                f_n = 0;
+        if (spec) {
+            candidate(lane / n_ord, f_x, f_c);
+            if (lane < n_dist * n_ord) {
+                f_n = n_max - lane % n_ord;
+                if (f_c >= a.p_min_ctx && f_n - 1 <= nsuf && a.ng.ord[f_n].full != nullptr) {
+                    run[0] = (u32)f_x;
+                    key_of(run, f_n, bits, f_lo, f_hi);
+                    f_idx = tasc_hash_key(f_lo, f_hi, f_n) & a.ng.ord[f_n].full_mask;
+                    f_slot = slot_load(a.ng.ord[f_n].full + f_idx);
+                } else {
+                    f_n = 0;
+                }
             }
         }
 
@@ -294,13 +351,11 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
                 }
             } else {
                 u64 lo0 = 0, hi0 = 0;
-                if (n_corp)
-                    for (int i = 0; i < n_corp - 1; ++i) tasc_key_put(lo0, hi0, i, bits, (u32)s_suf[n_corp - 2 - i]);
-                for (int e = lane; e < n_dist; e += 64) {
-                    const u64 w = s_tab[s_dl[e]];
-                    const int c = (int)((w >> 32) & 0xFFFFu);
-                    if (c < a.p_min_ctx) continue;
-                    const int xe = (int)(u32)w;
+                if (n_corp) key_of(suf, n_corp - 1, bits, lo0, hi0);
+                for (int e0 = 0; e0 < n_dist; e0 += 64) {
+                    int xe, c;
+                    candidate(e0 + lane, xe, c);
+                    if (e0 + lane >= n_dist || c < a.p_min_ctx) continue;
                     u64 sc;
                     if (n_corp) {
                         u64 lo = lo0, hi = hi0;
@@ -322,16 +377,13 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
                 if (sc > my_score || (sc == my_score && xe < my_x)) { my_score = sc; my_x = xe; }
             }
             const u64 best = wave_max_u64(my_x != 0x7FFFFFFF ? my_score : 0);
-            int cand = (my_x != 0x7FFFFFFF && my_score == best) ? my_x : 0x7FFFFFFF;
-            for (int o = 32; o > 0; o >>= 1) cand = min(cand, __shfl_xor(cand, o));
-            x = cand;
+            const int cand = (my_x != 0x7FFFFFFF && my_score == best) ? my_x : 0x7FFFFFFF;
+            x = (int)(0x7FFFFFFFu - wave_max_u32(0x7FFFFFFFu - (u32)cand));          // the smallest
         }
         if (lane == 0) {
             s_d[j] = x;
             a.drafts[(size_t)b * a.k + j] = x;
         }
-        x_prev = x;
-        nsuf_prev = nsuf;
         __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_wave_barrier();
     }
