@@ -200,16 +200,17 @@ tasc_status tiled_attrs() {
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_SMALL>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  TG_LDS_BYTES(128, 128)));
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_large<EPI>()), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLarge<EPI>));
-    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_LARGE>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TG_LDS_BYTES(256, 256)));
-    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TG_LDS_BYTES(256, 192)));
     if constexpr (EPI != TEPI_ROPE)
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm<EPI, GEMM_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      gemm_lds_bytes(GEMM_MID)));
-    if constexpr (EPI != TEPI_LMHEAD)
+    if constexpr (EPI != TEPI_LMHEAD) {
+        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_LARGE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     TG_LDS_BYTES(256, 256)));
+        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     TG_LDS_BYTES(256, 192)));
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_NARROW>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      TG_LDS_BYTES(64, 128)));
+    }
     return TASC_OK;
 }
 
@@ -220,16 +221,23 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
     // large tiles need enough of them to fill the chip: narrow outputs stay on the small tile (the k order, and so
     // every row's result, is the same for both shapes)
     const long large_wgs = (long)((M + 255) / 256) * ((N + 255) / 256) * slices;
-    // ... and a very wide output (the LM head) takes them from 129 rows on: one row tile then reads every weight tile
-    // once, and the activations are re-read per 256 instead of per 128 output features
-    if ((M >= kLargeTileRows && large_wgs >= 128) || (M > 128 && large_wgs >= 512)) {
+    const long small_wgs = (long)((M + 127) / 128) * ((N + 127) / 128) * slices;
+    // ... a very wide output takes them from 129 rows on: one row tile then reads every weight tile once, and the activations
+    // are re-read per 256 instead of per 128 output features.  The LM head takes the streaming kernel as soon as the small tiles
+    // are more than one per compute unit: it stores logits as whole row segments and hides the weights' latency (us of a whole
+    // verify step of one layer, with logits, small | streaming: 160 x 49152 x 896 156 | 115, 224 x 49152 x 2048 224 | 181,
+    // 301 x 16384 x 896 133 | 116, 64 x 49152 x 896 123 | 109; one per compute unit: 224 x 16384 x 896 106 | 125,
+    // 128 x 32768 x 2048 131 | 146).  Up to 32 rows its tiles are mostly padding (25 x 49152 x 896 106 | 108, 25 x 151936 x 896
+    // 165 | 169).
+    const bool large = EPI == TEPI_LMHEAD ? M > 32 && small_wgs > cus : (M >= kLargeTileRows && large_wgs >= 128) || (M > 128 && large_wgs >= 512);
+    if (large) {
         // 192-row tiles where they cover the rows with less padding and no more tiles (the tile shape never changes a
         // row's result)
         const int mt256 = (M + 255) / 256, mt192 = (M + 191) / 192;
         const int nt = (N + 255) / 256;
         const bool mid = mt192 <= mt256 && mt192 * 192 < mt256 * 256;
         const int tiles = (mid ? mt192 : mt256) * nt * slices;
-        if (tiles > cus && !(EPI == TEPI_ROPE && (mid || 128 % rp.gm.hd != 0))) {   // (that rotation needs whole heads in a wave's 128 features)
+        if (EPI == TEPI_LMHEAD || (tiles > cus && !(EPI == TEPI_ROPE && (mid || 128 % rp.gm.hd != 0)))) {   // (that rotation needs whole heads in a wave's 128 features)
             if constexpr (EPI != TEPI_ROPE) {
                 if (mid) {
                     k_gemm<EPI, GEMM_MID><<<dim3((unsigned)cus), dim3(512), gemm_lds_bytes(GEMM_MID), st>>>(A, (const BF16*)Wm, M, N, K, slices, outf,
@@ -240,15 +248,16 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
             k_gemm_large<EPI>()<<<dim3((unsigned)cus), dim3(512), kLdsLarge<EPI>, st>>>(A, (const BF16*)Wm, M, N, K, slices, outf, outb, lm, rp);
             return;
         }
-        if (mid) {
-            dim3 g((unsigned)(mt192 * nt), (unsigned)slices);
-            k_gemm_tiled<EPI, TILE_MID><<<g, dim3(512), TG_LDS_BYTES(256, 192), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
-            return;
+        if constexpr (EPI != TEPI_LMHEAD) {
+            if (mid) {
+                dim3 g((unsigned)(mt192 * nt), (unsigned)slices);
+                k_gemm_tiled<EPI, TILE_MID><<<g, dim3(512), TG_LDS_BYTES(256, 192), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
+                return;
+            }
+            dim3 g((unsigned)(mt256 * nt), (unsigned)slices);
+            k_gemm_tiled<EPI, TILE_LARGE><<<g, dim3(512), TG_LDS_BYTES(256, 256), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
         }
-        dim3 g((unsigned)(mt256 * nt), (unsigned)slices);
-        k_gemm_tiled<EPI, TILE_LARGE><<<g, dim3(512), TG_LDS_BYTES(256, 256), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
     } else {
-        const long small_wgs = (long)((M + 127) / 128) * ((N + 127) / 128) * slices;
         if constexpr (EPI != TEPI_LMHEAD) {
             // (the rotation epilogue needs whole heads inside a tile)
             if (small_wgs <= 128 && !(EPI == TEPI_ROPE && rp.gm.hd > 64)) {     // half of the compute units idle: halve the tile's width (a workgroup each, still)

@@ -67,3 +67,43 @@ def test_streaming_gemm(heads, d_model):
         worst = float(np.abs(got[2][b].astype(np.float64) - z).max())
         print(f"heads {heads} sequence {b}: max |logit - oracle| = {worst:.3e}", flush=True)
         assert worst <= 5e-2     # bf16 matrix operands, one layer: the bound of the other bf16 parity tests
+
+
+@pytest.mark.parametrize("B,V,ks", [(33, 22_101, (0, 2, 3, 5)), (14, 33_000, (1, 2, 9, 15))])
+def test_lm_head_tile_edges(B, V, ks):
+    """The LM head on both sides of its line (more 128 x 128 tiles than compute units, more than 32 rows): 33 and 99 rows on
+    small tiles, 132 and 198 on the streaming kernel with fewer tiles than workgroups; 28 rows small, 42, 140 and 224 streaming."""
+    import torch
+    import paper_2602_24174_amd as T
+    max_rows = max(ks) + 1
+    cfg = W.get_config("cfg1").scaled(dtype="bf16", n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=192, vocab=V, batch=B)
+    rng = np.random.default_rng(V)
+    weights = W.make_model(cfg)
+    weights["bias"] = _bias(V, rng)
+    prompts = [rng.integers(0, V, 3 + b % 5).astype(np.int32) for b in range(B)]
+    lens = [len(p) for p in prompts]
+    max_len = 8 + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, weights, max_len)
+    sess = T.tasc_session_create(model, B, max_len, max_rows)
+    T.tasc_session_prefill(model, sess, np.concatenate(prompts), np.cumsum([0] + lens).astype(np.int64), 1)
+    drafts = rng.integers(0, V, (B, max(ks))).astype(np.int32)
+    got = {}
+    for k in ks:
+        print(f"batch {B} vocab {V} k {k}", flush=True)
+        z = torch.full((B, k + 1, V), -7.0, dtype=torch.float32, device="cuda")
+        d = torch.from_numpy(np.ascontiguousarray(drafts[:, :k])).cuda() if k else None
+        T.tasc_verify_step(model, sess, d, k, None, None, z)
+        torch.cuda.synchronize()
+        got[k] = z.cpu().numpy()
+        assert (got[k] != -7.0).all()
+    for k in ks[1:]:             # the same bits whatever the tile shape
+        n = ks[0] + 1
+        assert (got[k][:, :n] == got[ks[0]][:, :n]).all()
+    om = OM.OracleModel(cfg, weights)
+    for b in (0, B - 1):
+        c = om.new_cache(max_len)
+        om.forward(prompts[b].tolist(), c, last_only=True)
+        c.length = lens[b]
+        first = int(T.tasc_session_get_tokens(sess, b)[-1])
+        z = om.forward([first] + drafts[b].tolist(), c)
+        assert float(np.abs(got[ks[-1]][b].astype(np.float64) - z).max()) <= 5e-2    # one bf16 layer: the bound of the other parity tests
