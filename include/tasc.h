@@ -68,8 +68,9 @@ const char* tasc_last_error(void);
  *   n_max        in [2, TASC_MAX_ORDER];  p_min >= 1.
  * An element (c, x) of M_n is kept iff count(c, x) >= p_min; per kept context c the table holds
  * T(c) = sum of kept counts and its most frequent kept successor (smallest id among equals).
- * Synchronous: allocates device memory, runs on `stream` and waits for it.  *out is owned by the
- * library until tasc_ngram_destroy.
+ * Synchronous: allocates device memory, runs on `stream` and waits for it.  While it runs it holds, in one allocation,
+ * a counting table, a byte (and the token, from host memory) per corpus token and, for all orders together, 8 bytes per
+ * window / p_min (orders are taken in groups where that exceeds 8 GiB).  *out is owned by the library until tasc_ngram_destroy.
  */
 tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs,
                              int32_t vocab, int32_t n_max, int32_t p_min, tasc_mem where,
@@ -200,7 +201,9 @@ void tasc_model_destroy(tasc_model* m);
 /* ------------------------------------------------------------------------------------------
  * Session: `batch` sequences decoded in lock-step.
  *   max_len   most tokens (prompt + generated + drafts in flight) a sequence may hold
- *   max_rows  most rows per sequence in one forward: >= k + 1, also the prefill chunk length
+ *   max_rows  most rows per sequence in one verify step: >= k + 1; also the length of a prompt chunk, except that bf16
+ *             sessions on the tiled kernels with max_rows > 16 take prompt chunks of up to 8192 rows in all, of
+ *             whatever sequences still have prompt left (their workspace holds that many rows)
  * KV cache: pages of 16 positions, [page][K|V][kv_head][...], one pool per layer, all inside the
  * caller's kv_pool; a block table maps (sequence, position / 16) to a page.  Positions whose
  * drafts were rejected stay allocated and are overwritten by the next step ("rollback" only
@@ -337,10 +340,10 @@ tasc_status tasc_session_get_tokens(const tasc_session* s, int32_t b, int32_t* t
  *                        A row's kernels and summation order do not depend on it, so neither does any result; with few
  *                        rows per sequence range the layer kernels of one range leave compute units idle that another
  *                        range's kernels fill.  The caller's stream waits for every range before the LM head.
- *   TASC_CFG_STEP_GRAPH  1 (default): a verify step of the tiled kernels (forwards of more than 16 rows) is recorded
+ *   TASC_CFG_STEP_GRAPH  1 (default): a verify step outside the persistent small-batch kernels is recorded
  *                        into a HIP graph the second time it is called with the same k and the same draft / result
- *                        pointers, and replayed as one graph launch from then on (a step is a few hundred launches
- *                        with step-invariant arguments); 0: every kernel is launched on its own.  Same kernels, same
+ *                        pointers, and replayed as one graph launch from then on (a step is dozens to hundreds of
+ *                        launches with step-invariant arguments); 0: every kernel is launched on its own.  Same kernels, same
  *                        results.  Steps that ask for logits or a trace, run under the per-class timers, or are
  *                        called on a stream that is itself being captured are always launched one by one.
  */
@@ -398,7 +401,7 @@ tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem where, int3
  *   n_merges            HOST: merges performed (<= budget).
  * Limits: n_max in [2, TASC_MAX_ORDER], n_max * ceil(log2(vocab + budget)) <= 128, corpus < 2^32 - 1
  * tokens.  Synchronous (one host round trip per merge); allocates about 20 bytes of device scratch per
- * corpus token plus the tables of one tasc_ngram_build.  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
+ * corpus token plus one counting table (8-byte slots, at least twice the corpus' tokens).  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
  * ---------------------------------------------------------------------------------------- */
 tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs, int32_t vocab,
                             int32_t n_max, int32_t budget, tasc_mem where, void* stream, int32_t* merges,

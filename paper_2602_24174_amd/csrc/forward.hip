@@ -351,11 +351,24 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
     const int att_passes = decode ? 1 : (nq * (H / Hkv) + 63) / 64;
     int att_chunks = 512 / (s->batch * Hkv * att_passes);
     att_chunks = att_chunks < 1 ? 1 : (att_chunks > 4 ? 4 : att_chunks);
+    const BiasCursors bc{BiasCsr{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base}, d.sel_tok,
+                         m->bias_rowptr ? n_sel * (s->n_strips + 1) : 0, s->n_strips, d.bias_ptr, d.bias_first, d.bias_base};
+    const unsigned bias_wgs = (unsigned)((bc.n + 255) / 256);
     {
         PROF(TASC_KC_PREPARE);
-        k_embed<BF16><<<dim3(M_all), dim3(64), 0, st>>>((const BF16*)m->embed, d.row_tok, D, d.x);
+        if (D <= RRN_MAX_D) {
+            k_embed_norm<<<dim3(M_all + bias_wgs), dim3(256), 0, st>>>((const BF16*)m->embed, d.row_tok, m->layers[0].g1, M_all, D, c.rms_eps,
+                                                                      d.x, (BF16*)d.h, bc);
+        } else {
+            k_embed<BF16><<<dim3(M_all), dim3(64), 0, st>>>((const BF16*)m->embed, d.row_tok, D, d.x);
+            if (bias_wgs) k_bias_ptr<<<dim3(bias_wgs), dim3(256), 0, st>>>(bc);
+        }
     }
     TASC_LAUNCH_CHECK();
+    // A verify step's LM-head rows are its rows, so the last layer's reduction can normalise them as well.  (Of a decode forward
+    // only, and whether it does depends on the slices alone: a row's bits are the same in steps of any row count.)
+    const bool all_rows = decode && n_sel == M_all;
+    bool final_normed = false;
 
     // The layers of sequences [b0, b0 + nb) on stream `st`: every kernel below computes a row from that row's own data
     // (and its sequence's cache), in an order fixed by the session, so the layers may run for several ranges of
@@ -402,7 +415,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         };
         const int rows_pass = 32;
         const dim3 attn_grid(nb * Hkv, (nq * (H / Hkv) + rows_pass - 1) / rows_pass);
-        bool h_ready = false;                 // h already holds the layer's normalised input
+        bool h_ready = D <= RRN_MAX_D;        // h already holds the layer's normalised input
         for (int l = 0; l < c.n_layers; ++l) {
             const TascLayerW& w = m->layers[l];
             BF16* kv_layer = (BF16*)s->kv_pool + (size_t)l * s->kv_layer_stride;
@@ -465,10 +478,11 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
             {
                 // the next layer's first RMSNorm rides on this reduction
                 PROF(TASC_KC_GEMM_D);
-                h_ready = gemm_sliced(act, w.wd, D, F, x, true, l + 1 < c.n_layers ? m->layers[l + 1].g1 : nullptr);
+                h_ready = gemm_sliced(act, w.wd, D, F, x, true, l + 1 < c.n_layers ? m->layers[l + 1].g1 : all_rows ? m->gf : nullptr);
             }
             TASC_LAUNCH_CHECK();
         }
+        final_normed = h_ready;
         return TASC_OK;
     };
 
@@ -494,19 +508,13 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         }
     }
     if (n_sel > 0) {
-        {
+        if (!final_normed) {
             PROF(TASC_KC_NORM);
             k_rmsnorm<BF16><<<dim3(n_sel), dim3(64), 0, st>>>(d.x, m->gf, d.sel_rows, D, c.rms_eps, (BF16*)d.h);
         }
-        LmEpi lm{BiasCsr{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base}, d.bias_ptr, d.bias_first, d.bias_base, d.part_val, d.part_idx,
-                 logits_dbg, s->n_strips};
+        LmEpi lm{bc.bias, d.bias_ptr, d.bias_first, d.bias_base, d.part_val, d.part_idx, logits_dbg, s->n_strips};
         {
             PROF(TASC_KC_LMHEAD);
-            if (m->bias_rowptr) {
-                const int n = n_sel * (s->n_strips + 1);
-                k_bias_ptr<<<dim3((n + 255) / 256), dim3(256), 0, st>>>(lm.bias, d.sel_tok, n_sel, s->n_strips, d.bias_ptr,
-                                                                        d.bias_first, d.bias_base);
-            }
             launch_gemm<TEPI_LMHEAD>((const BF16*)d.h, m->lm_head, n_sel, c.vocab, D, nullptr, nullptr, lm, 1, st, cus);
         }
         {

@@ -383,16 +383,27 @@ __global__ __launch_bounds__(64 * LM_GENERIC_WAVES) void k_lmhead_generic(const 
     }
 }
 
-// amax[r] = argmax over the strips of row r (lowest index among equal values).  One wave per row.
+// amax[r] = argmax over the strips of row r (lowest index among equal values).  One wave per row, the loads of 512 strips in
+// flight at a time: a chain of round trips otherwise (576 rows of 1187 strips: 6.2 us, 11.9 with one pair of loads at a time).
 __global__ __launch_bounds__(64) void k_argmax_reduce(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
                                                       int n_strips, int32_t* __restrict__ amax) {
     const int r = blockIdx.x, lane = threadIdx.x;
+    const float* pv = part_val + (size_t)r * n_strips;
+    const int32_t* pi = part_idx + (size_t)r * n_strips;
     float bv = -INFINITY;
     int32_t bi = 0x7FFFFFFF;
-    for (int s = lane; s < n_strips; s += 64) {
-        const float v = part_val[(size_t)r * n_strips + s];
-        const int32_t i = part_idx[(size_t)r * n_strips + s];
-        if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
+    for (int s0 = lane; s0 < n_strips; s0 += 512) {
+        float v[8];
+        int32_t i[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {                     // (past the end the last strip again: it changes nothing)
+            const int s = min(s0 + 64 * u, n_strips - 1);
+            v[u] = pv[s];
+            i[u] = pi[s];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (v[u] > bv || (v[u] == bv && i[u] < bi)) { bv = v[u]; bi = i[u]; }
     }
     for (int o = 32; o > 0; o >>= 1) {
         const float v = __shfl_xor(bv, o);

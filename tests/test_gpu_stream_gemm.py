@@ -69,14 +69,17 @@ def test_streaming_gemm(heads, d_model):
         assert worst <= 5e-2     # bf16 matrix operands, one layer: the bound of the other bf16 parity tests
 
 
-@pytest.mark.parametrize("B,V,ks", [(33, 22_101, (0, 2, 3, 5)), (14, 33_000, (1, 2, 9, 15))])
-def test_lm_head_tile_edges(B, V, ks):
+@pytest.mark.parametrize("B,V,ks,d_model", [(33, 22_101, (0, 2, 3, 5), 128), (14, 33_000, (1, 2, 9, 15), 128), (14, 3001, (1, 15), 2048),
+                                            (14, 3001, (1, 15), 2112)])
+def test_lm_head_tile_edges(B, V, ks, d_model):
     """The LM head on both sides of its line (more 128 x 128 tiles than compute units, more than 32 rows): 33 and 99 rows on
-    small tiles, 132 and 198 on the streaming kernel with fewer tiles than workgroups; 28 rows small, 42, 140 and 224 streaming."""
+    small tiles, 132 and 198 on the streaming kernel with fewer tiles than workgroups; 28 rows small, 42, 140 and 224
+    streaming.  Embedding, first norm and bias cursors in one launch, also without a spare thread per row, and (2112) apart."""
     import torch
     import paper_2602_24174_amd as T
     max_rows = max(ks) + 1
-    cfg = W.get_config("cfg1").scaled(dtype="bf16", n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=192, vocab=V, batch=B)
+    cfg = W.get_config("cfg1").scaled(dtype="bf16", n_layers=1, d_model=d_model, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=192, vocab=V,
+                                      batch=B)
     rng = np.random.default_rng(V)
     weights = W.make_model(cfg)
     weights["bias"] = _bias(V, rng)
