@@ -339,7 +339,8 @@ tasc_status tasc_session_get_tokens(const tasc_session* s, int32_t b, int32_t* t
  *                        layers, each range on a stream of its own beside the caller's (0 = the library's rule, 1..4).
  *                        A row's kernels and summation order do not depend on it, so neither does any result; with few
  *                        rows per sequence range the layer kernels of one range leave compute units idle that another
- *                        range's kernels fill.  The caller's stream waits for every range before the LM head.
+ *                        range's kernels fill.  The caller's stream waits for every range before the LM head.  Prompt chunks of more
+ *                        than batch x max_rows rows, and of sequences with different row counts, run as one range.
  *   TASC_CFG_STEP_GRAPH  1 (default): a verify step outside the persistent small-batch kernels is recorded
  *                        into a HIP graph the second time it is called with the same k and the same draft / result
  *                        pointers, and replayed as one graph launch from then on (a step is dozens to hundreds of

@@ -383,7 +383,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         BF16* const q = (BF16*)d.q + r0 * nqo;
         BF16* const att = (BF16*)d.att + r0 * nqo;
         BF16* const act = (BF16*)d.act + r0 * F;
-        float* const part = d.att_part + r0 * 8 * (size_t)(nqkv > D ? nqkv : D);   // the scratch is sized per row
+        float* const part = d.att_part + r0 * 8 * (size_t)(nqkv > D ? nqkv : D);   // (r0 > 0 only among the batch x max_rows rows the scratch has 8 slices for)
         const int32_t* const n_rows = d.n_rows;
         const int32_t* const pos0 = d.pos0;
         const int32_t* const block_tab = d.block_tab;
@@ -489,7 +489,9 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
     // chains: few rows leave the layer kernels short of workgroups and bound by their own start-up and dependent
     // memory round trips; ranges of sequences that run side by side fill the compute units.  Each reads the weights
     // again (from the caches when the chains keep pace), so the count stays small.
-    const int chains = M_all == s->batch * nq ? tasc_forward_chains(m, s, nq) : 1;
+    // (Not for prompt chunks of more than batch x max_rows rows: a chain's share of the partial sums below is 8 slices of its
+    // rows, and beyond those rows the scratch holds 4.)
+    const int chains = M_all == s->batch * nq && nq <= s->max_rows ? tasc_forward_chains(m, s, nq) : 1;
     if (chains <= 1) {
         const tasc_status rc = run_layers(0, s->batch, st);
         if (rc != TASC_OK) return rc;

@@ -60,3 +60,33 @@ def test_packed_prompts(name):
         worst = float(np.abs(first[b].astype(np.float64) - want).max())
         print(f"{name} sequence {b} ({lens[b]} tokens): max |logit - oracle| = {worst:.3e}", flush=True)
         assert worst <= tol
+
+
+@pytest.mark.parametrize("chains", [2, 4])
+def test_chains_of_equal_prompts(chains):
+    """Prompts of one length make chunks in which every sequence has as many rows as the next, the only ones the forward could cut
+    into chains; these hold more rows (32 x 250) than a chain's share of the partial sums.  The same bits as one chain, then and
+    in the verify step over the cache, which does run as chains."""
+    import torch
+    import paper_2602_24174_amd as T
+    B, P, k, max_rows = 32, 250, 3, 20
+    cfg = W.get_config("cfg1").scaled(**dict(BF16, n_layers=2, vocab=700, batch=B, n_docs=800, n_heads=4, n_kv_heads=2, head_dim=64, d_ffn=3072))
+    rng = np.random.default_rng(9)
+    prompts = rng.integers(0, cfg.vocab, B * P).astype(np.int32)
+    max_len = P + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, W.make_model(cfg, W.make_corpus(cfg)), max_len)
+    sess = T.tasc_session_create(model, B, max_len, max_rows)
+    drafts = torch.from_numpy(rng.integers(0, cfg.vocab, (B, k)).astype(np.int32)).cuda()
+    z = torch.zeros((B, k + 1, cfg.vocab), dtype=torch.float32, device="cuda")
+    got = []
+    try:
+        for c in (1, chains):
+            print(f"chains {c}", flush=True)
+            T.tasc_config_set(T.TASC_CFG_CHAINS, c)
+            T.tasc_session_prefill(model, sess, prompts, np.arange(B + 1, dtype=np.int64) * P, 1)
+            T.tasc_verify_step(model, sess, drafts, k, None, None, z)
+            torch.cuda.synchronize()
+            got.append((z.cpu().numpy(), [T.tasc_session_get_tokens(sess, b).tolist() for b in range(B)]))
+    finally:
+        T.tasc_config_set(T.TASC_CFG_CHAINS, 0)
+    assert (got[0][0] == got[1][0]).all() and got[0][1] == got[1][1]
