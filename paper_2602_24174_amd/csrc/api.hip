@@ -13,7 +13,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---------------------------------------------------------------- per-forward row metadata
 __global__ void k_reset(int B, int max_len, const int32_t* __restrict__ prompts, const int64_t* __restrict__ off,
-                        int32_t* tokens, int32_t* n_tok, int32_t* n_prompt, int32_t* cached, int32_t* n_emit, u64* counters) {
+                        int32_t* tokens, int32_t* n_tok, int32_t* n_prompt, int32_t* cached, int32_t* n_emit, int max_new, u64* counters) {
     const int b = blockIdx.x;
     const int64_t o = off[b];
     const int P = (int)(off[b + 1] - o);
@@ -25,7 +25,7 @@ __global__ void k_reset(int B, int max_len, const int32_t* __restrict__ prompts,
         n_emit[b] = 0;
     }
     if (b == 0)
-        for (int i = threadIdx.x; i < TASC_N_COUNTERS; i += blockDim.x) counters[i] = 0;
+        for (int i = threadIdx.x; i < TASC_N_COUNTERS; i += blockDim.x) counters[i] = i == TASC_CTR_MAX_NEW ? (u64)max_new : 0;
 }
 
 __global__ void k_check_prompts(const int32_t* __restrict__ prompts, int64_t n, int vocab, u64* flag) {
@@ -109,13 +109,14 @@ __global__ void k_prepare_verify(int B, int k, int max_len, int vocab, const int
 
 // Greedy acceptance (one thread per sequence): longest prefix of the drafts equal to the target's
 // argmax, plus the bonus token; rollback = the cached length only grows by the accepted rows.
-__global__ void k_accept(int B, int k, int max_len, int max_new, const int32_t* __restrict__ drafts,
+__global__ void k_accept(int B, int k, int max_len, const int32_t* __restrict__ drafts,
                          const int32_t* __restrict__ amax, int32_t* tokens, int32_t* n_tok, int32_t* cached, int32_t* n_emit,
                          u64* counters, int32_t* accept_len, int32_t* emitted, int32_t* trace_step) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= B) return;
     const int nq = k + 1;
     const int N = n_tok[b];
+    const int max_new = (int)counters[TASC_CTR_MAX_NEW];
     const bool frozen = n_emit[b] >= max_new;
     int m = 0;
     if (!frozen) {
@@ -533,7 +534,7 @@ extern "C" tasc_status tasc_session_prefill(const tasc_model* m, tasc_session* s
     TascSessDev& d = s->d;
     TASC_HIP(hipMemcpyAsync(d.off, prompt_offsets, (B + 1) * 8, hipMemcpyHostToDevice, st));
     k_reset<<<dim3(B), dim3(256), 0, st>>>(B, s->max_len, d_prompts, d.off, d.tokens, d.n_tok, d.n_prompt, d.cached, d.n_emit,
-                                           d.counters);
+                                           max_new, d.counters);
     TASC_LAUNCH_CHECK();
     s->bar_epoch = 0;  // k_reset cleared the barrier flags and counters (the time-out flag among them) with the other counters
     s->barb_base = 0;
@@ -606,7 +607,7 @@ tasc_status verify_step_enqueue(const tasc_model* m, tasc_session* s, const int3
     if (rc != TASC_OK) return rc;
     if (!tail.done) {
         TascProfScope ps(TASC_KC_ACCEPT, st);
-        k_accept<<<dim3((B + 63) / 64), dim3(64), 0, st>>>(B, k, s->max_len, s->max_new, drafts, d.amax, d.tokens, d.n_tok,
+        k_accept<<<dim3((B + 63) / 64), dim3(64), 0, st>>>(B, k, s->max_len, drafts, d.amax, d.tokens, d.n_tok,
                                                            d.cached, d.n_emit, d.counters, accept_len, emitted, trace_step);
     }
     TASC_LAUNCH_CHECK();
@@ -717,7 +718,12 @@ extern "C" tasc_status tasc_generate(const tasc_model* m, const tasc_ngram* ng, 
         TASC_LAUNCH_CHECK();
         TASC_HIP(hipMemcpyAsync(s->host_counters, d.counters, 32 * 8, hipMemcpyDeviceToHost, st));
         TASC_HIP(hipStreamSynchronize(st));
+        if ((int64_t)s->host_counters[1] <= min_emit && s->host_counters[TASC_CTR_BAR_ERR] == 0) {
+            tasc_set_error("generate: %lld steps emitted nothing for a sequence of %lld tokens", (long long)run, (long long)min_emit);
+            return TASC_ESTATE;
+        }
         min_emit = (int64_t)s->host_counters[1];
+        if (s->host_counters[TASC_CTR_BAR_ERR] != 0) break;   // (reported below: no later step of this session emits anything)
     }
     k_gather_out<<<dim3(B), dim3(256), 0, st>>>(B, s->max_len, max_new, d.tokens, d.n_prompt, out_tokens);
     TASC_LAUNCH_CHECK();

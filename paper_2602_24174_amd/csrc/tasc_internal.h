@@ -226,6 +226,7 @@ struct tasc_session {
 // counters[] slots used beyond the statistics
 #define TASC_CTR_FLAGS 32     // 64 32-bit arrival flags of the layer-group barrier (slots 32..63)
 #define TASC_N_COUNTERS 64
+#define TASC_CTR_MAX_NEW 5    // tokens to generate per sequence (set by the prefill; in memory because recorded steps outlive a prefill)
 #define TASC_CTR_BAR_ERR 25   // grid-barrier time-out flag (low 32 bits)
 #define TASC_CTR_BARB 26      // whole-grid barrier arrival counter
 #define TASC_CTR_XCD_STEPS 28 // steps of the persistent kernel whose layer group used XCD-local barriers
