@@ -631,15 +631,16 @@ tasc_status verify_step_impl(const tasc_model* m, tasc_session* s, const int32_t
     }
     if (!graphable) return verify_step_enqueue(m, s, drafts, k, accept_len, emitted, logits_dbg, trace_step, st);
     const int chains = tasc_forward_chains(m, s, k + 1);
+    const bool tiled = tasc_forward_is_tiled(m, s, k + 1);
     TascStepGraph* g = nullptr;
     for (TascStepGraph& e : s->step_graphs)
-        if (e.k == k && e.chains == chains && e.drafts == drafts && e.accept_len == accept_len && e.emitted == emitted) g = &e;
+        if (e.k == k && e.chains == chains && e.tiled == tiled && e.drafts == drafts && e.accept_len == accept_len && e.emitted == emitted) g = &e;
     if (!g) {
         if (s->step_graphs.size() >= 8) {     // a caller that keeps changing its buffers: forget the oldest
             if (s->step_graphs.front().exec) (void)hipGraphExecDestroy(s->step_graphs.front().exec);
             s->step_graphs.erase(s->step_graphs.begin());
         }
-        s->step_graphs.push_back(TascStepGraph{k, chains, drafts, accept_len, emitted, 0, nullptr});
+        s->step_graphs.push_back(TascStepGraph{k, chains, tiled, drafts, accept_len, emitted, 0, nullptr});
         g = &s->step_graphs.back();
     }
     if (!g->exec && g->seen >= 1) {

@@ -190,10 +190,11 @@ struct TascSessDev {
     float* bias_base;    // [M_lm] its bias of unseen successors
 };
 
-// one verify step of the tiled kernels, recorded once and replayed: its launches only name buffers of the session and
-// the caller's draft / result pointers, which make the key
+// one verify step outside the persistent kernels, recorded once and replayed: its launches only name buffers of the session and
+// the caller's draft / result pointers, which make the key together with what chooses the launches
 struct TascStepGraph {
     int32_t k, chains;
+    bool tiled;               // the kernels it was recorded from: tiled, else type-generic
     const int32_t* drafts;
     int32_t* accept_len;
     int32_t* emitted;
