@@ -221,7 +221,8 @@ void tasc_session_destroy(tasc_session* s);
 /*
  * Resets the session and runs the prompt forward: fills the KV cache for all prompt positions and
  * commits, as generated token #1, the argmax at the last prompt position (the "pending" token,
- * whose own KV is not cached yet).
+ * whose own KV is not cached yet).  A prompt's keys, values and first token do not depend on the other prompts of the call, bit
+ * for bit: the order of every sum follows the model and the session's batch, max_len and max_rows.
  *   prompts         int32, concatenated, host or device per `where`
  *   prompt_offsets  HOST int64[batch + 1]; every prompt has 1..max_len tokens
  *   max_new         tokens to generate per sequence (>= 1); a sequence that has them is frozen

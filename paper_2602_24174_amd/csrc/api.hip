@@ -328,6 +328,13 @@ int64_t prompt_rows(const tasc_model_desc& c, int B, int max_len, int max_rows) 
     return std::max(rows, std::min(kPromptRows, (int64_t)B * max_len));
 }
 
+// Rows a prompt chunk is taken to have wherever that decides in which order a row's sums are added: prompts of half of max_len,
+// as many as a chunk holds.  It must not follow the prompts of a call, or a prompt's keys, values and first token would depend on
+// the lengths of its neighbours.
+int32_t prompt_ref_rows(int B, int max_len, int max_rows, int row_cap) {
+    return (int32_t)std::min<int64_t>(row_cap, std::max((int64_t)B * max_rows, (int64_t)B * max_len / 2));
+}
+
 // carves the workspace; order must match bind_workspace
 WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows) {
     const size_t ML = (size_t)B * max_rows, M = (size_t)prompt_rows(c, B, max_len, max_rows), es = elt_size(c.dtype);
@@ -400,6 +407,7 @@ extern "C" tasc_status tasc_session_create(const tasc_model* m, int32_t batch, i
     s->max_len = max_len;
     s->max_rows = max_rows;
     s->row_cap = (int32_t)prompt_rows(m->desc, batch, max_len, max_rows);
+    s->prompt_ref = prompt_ref_rows(batch, max_len, max_rows, s->row_cap);
     s->max_blocks = (max_len + TASC_KV_BLOCK - 1) / TASC_KV_BLOCK;
     s->n_strips = (m->desc.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP;
     s->max_new = 0;

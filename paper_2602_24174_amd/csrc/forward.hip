@@ -3,9 +3,10 @@
 // verify step (nq = k + 1; paper, subsection "Speculative Decoding": the drafted tokens are verified
 // in parallel via a single forward pass).
 //
-// Which kernels run depends on the model and the session only (dtype, row count of the call), never on
-// data, so plain greedy decoding (k = 0) and speculative decoding of the same session shapes reduce
-// every row in the same order.
+// The order in which a row is reduced depends on the model and the session only, never on data or on the
+// other rows of the call (whose number chooses tile shapes, which do not change it), so plain greedy decoding
+// (k = 0) and speculative decoding of one session agree bit for bit, and a prompt's cache and first token do not
+// depend on the prompts beside it.
 #include "tasc_internal.h"
 #include "kernels_generic.h"
 #include "kernels_small.h"
@@ -318,9 +319,10 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
     // of one session differ in their row count, and speculative decoding must reproduce greedy decoding bit for bit): it
     // depends on N, K and the session's batch only, never on the rows of the call; rows_ref = 5 rows per sequence
     // stands for the verify steps the session is sized for.  A prompt forward is the same computation in the
-    // speculative and in the greedy run whatever its slice count, so it takes the count that suits its own rows (its
-    // chunks of batch x max_rows rows fill the chip without slices, and every slice is a pass over rows x N partial sums).
-    const int rows_ref = decode ? s->batch * 5 : M_all;
+    // speculative and in the greedy run whatever its slice count, so it takes the count that suits the many rows of its
+    // chunks (they fill the chip without slices, and every slice is a pass over rows x N partial sums) -- but not the rows this
+    // call happens to have, which are the other prompts' as well: prompt_ref, a session constant.
+    const int rows_ref = decode ? s->batch * 5 : s->prompt_ref;
     auto slices = [&](int N, int K) {
         const int n_nt = (N + 127) / 128, nk = K / TG_BK;
         if (n_nt >= 32) return 1;
@@ -342,13 +344,13 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         if (rows_ref > 256 && rows_ref < kLargeTileRows && ks > 4) ks = 4;
         ks = ks < nk / 4 ? ks : nk / 4;                       // slices of at least 4 k-steps
         ks = ks < TG_MAX_SLICES ? ks : TG_MAX_SLICES;
-        if (M_all > s->batch * s->max_rows && ks > 4) ks = 4;  // the scratch holds 8 slices of a verify step's rows, 4 of row_cap
+        if (!decode && s->row_cap > s->batch * s->max_rows && ks > 4) ks = 4;   // the scratch holds 8 slices of batch x max_rows rows, 4 of row_cap
         return ks < 1 ? 1 : ks;
     };
     // Key chunks of the attention: two workgroups per compute unit in one round, but no more than 4 partial results to merge.
-    // For decode forwards a session constant (it fixes the order in which a row's keys are added); a prompt forward counts
-    // its row passes too, so that its long chunks need no merge.
-    const int att_passes = decode ? 1 : (nq * (H / Hkv) + 63) / 64;
+    // A session constant, since it fixes the order in which a row's keys are added; the one for prompts counts the row passes of
+    // prompt_ref rows too, so that long chunks need no merge.
+    const int att_passes = decode ? 1 : (s->prompt_ref / s->batch * (H / Hkv) + 63) / 64;
     int att_chunks = 512 / (s->batch * Hkv * att_passes);
     att_chunks = att_chunks < 1 ? 1 : (att_chunks > 4 ? 4 : att_chunks);
     const BiasCursors bc{BiasCsr{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base}, d.sel_tok,

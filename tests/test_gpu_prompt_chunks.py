@@ -90,3 +90,37 @@ def test_chains_of_equal_prompts(chains):
     finally:
         T.tasc_config_set(T.TASC_CFG_CHAINS, 0)
     assert (got[0][0] == got[1][0]).all() and got[0][1] == got[1][1]
+
+
+@pytest.mark.parametrize("heads", [(4, 2, 64), (4, 1, 128), (6, 2, 32)])
+def test_prompt_does_not_depend_on_its_neighbours(heads):
+    """One prompt among short, long and ragged others, so that a chunk holds from 250 to several thousand rows, split over one or
+    more chunks: its cached keys and values, its first token and the logits of the next step are the same bits."""
+    import torch
+    import paper_2602_24174_amd as T
+    H, Hkv, hd = heads
+    B, k, max_rows, longest = 16, 3, 20, 900
+    cfg = W.get_config("cfg1").scaled(**dict(BF16, n_layers=2, d_model=192, d_ffn=3072, vocab=700, batch=B, n_docs=800, n_heads=H,
+                                             n_kv_heads=Hkv, head_dim=hd))
+    rng = np.random.default_rng(13)
+    mine = rng.integers(0, cfg.vocab, 230).astype(np.int32)
+    max_len = longest + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, W.make_model(cfg, W.make_corpus(cfg)), max_len)
+    sess = T.tasc_session_create(model, B, max_len, max_rows)
+    drafts = torch.from_numpy(rng.integers(0, cfg.vocab, (B, k)).astype(np.int32)).cuda()
+    z = torch.zeros((B, k + 1, cfg.vocab), dtype=torch.float32, device="cuda")
+    blocks = (max_len + 15) // 16
+    got = []
+    for others in ([1] * 15, [230] * 15, [longest] * 15, [longest - 55 * i for i in range(15)]):
+        print(f"heads {heads} others {others}", flush=True)
+        lens = others[:5] + [len(mine)] + others[5:]
+        prompts = [mine if b == 5 else rng.integers(0, cfg.vocab, n).astype(np.int32) for b, n in enumerate(lens)]
+        T.tasc_session_prefill(model, sess, np.concatenate(prompts), np.cumsum([0] + lens).astype(np.int64), 1)
+        pool = sess._kv_pool.view(torch.int16).view(cfg.n_layers, blocks, B, -1)     # block j of sequence b: page j B + b
+        kv = pool[:, :len(mine) // 16, 5].clone()                                    # those the prompt fills
+        assert bool((kv != 0).any())
+        T.tasc_verify_step(model, sess, drafts, k, None, None, z)
+        torch.cuda.synchronize()
+        got.append((kv, z[5].clone(), T.tasc_session_get_tokens(sess, 5).tolist()))
+    for kv, logits, tokens in got[1:]:
+        assert torch.equal(kv, got[0][0]) and torch.equal(logits, got[0][1]) and tokens == got[0][2]
