@@ -203,7 +203,7 @@ void tasc_model_destroy(tasc_model* m);
  *   max_len   most tokens (prompt + generated + drafts in flight) a sequence may hold
  *   max_rows  most rows per sequence in one verify step: >= k + 1; also the length of a prompt chunk, except that bf16
  *             sessions on the tiled kernels with max_rows > 16 take prompt chunks of up to 8192 rows in all, of
- *             whatever sequences still have prompt left (their workspace holds that many rows)
+ *             whatever sequences still have prompt left (tasc_session_workspace_bytes counts that many rows)
  * KV cache: pages of 16 positions, [page][K|V][kv_head][...], one pool per layer, all inside the
  * caller's kv_pool; a block table maps (sequence, position / 16) to a page.  Positions whose
  * drafts were rejected stay allocated and are overwritten by the next step ("rollback" only
@@ -211,8 +211,10 @@ void tasc_model_destroy(tasc_model* m);
  * ---------------------------------------------------------------------------------------- */
 size_t tasc_session_kv_bytes(const tasc_model* m, int32_t batch, int32_t max_len);
 size_t tasc_session_workspace_bytes(const tasc_model* m, int32_t batch, int32_t max_len, int32_t max_rows);
-/* kv_pool and workspace: DEVICE memory, 256-byte aligned, at least the sizes above; owned by the
- * caller and must outlive the session.  Synchronous (initialises the block table). */
+/* kv_pool and workspace: DEVICE memory, 256-byte aligned, of the sizes above; owned by the
+ * caller and must outlive the session.  A smaller workspace makes the prompt chunks shorter, down to batch x max_rows
+ * rows (100 to 150 KB a row); below that TASC_ENOMEM, with the least size in tasc_last_error.  Synchronous (initialises
+ * the block table). */
 tasc_status tasc_session_create(const tasc_model* m, int32_t batch, int32_t max_len, int32_t max_rows,
                                 void* kv_pool, size_t kv_bytes, void* workspace, size_t ws_bytes,
                                 tasc_session** out);
@@ -222,7 +224,7 @@ void tasc_session_destroy(tasc_session* s);
  * Resets the session and runs the prompt forward: fills the KV cache for all prompt positions and
  * commits, as generated token #1, the argmax at the last prompt position (the "pending" token,
  * whose own KV is not cached yet).  A prompt's keys, values and first token do not depend on the other prompts of the call, bit
- * for bit: the order of every sum follows the model and the session's batch, max_len and max_rows.
+ * for bit: the order of every sum follows the model and the session's batch, max_len, max_rows and workspace size.
  *   prompts         int32, concatenated, host or device per `where`
  *   prompt_offsets  HOST int64[batch + 1]; every prompt has 1..max_len tokens
  *   max_new         tokens to generate per sequence (>= 1); a sequence that has them is frozen

@@ -336,8 +336,8 @@ int32_t prompt_ref_rows(int B, int max_len, int max_rows, int row_cap) {
 }
 
 // carves the workspace; order must match bind_workspace
-WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows) {
-    const size_t ML = (size_t)B * max_rows, M = (size_t)prompt_rows(c, B, max_len, max_rows), es = elt_size(c.dtype);
+WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows, int64_t chunk_rows) {
+    const size_t ML = (size_t)B * max_rows, M = (size_t)chunk_rows, es = elt_size(c.dtype);
     const size_t HD = (size_t)c.n_heads * c.head_dim, KD = (size_t)c.n_kv_heads * c.head_dim;
     const size_t n_strips = ((size_t)c.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP;
     const size_t max_blocks = ((size_t)max_len + TASC_KV_BLOCK - 1) / TASC_KV_BLOCK;
@@ -384,7 +384,7 @@ extern "C" size_t tasc_session_kv_bytes(const tasc_model* m, int32_t batch, int3
 
 extern "C" size_t tasc_session_workspace_bytes(const tasc_model* m, int32_t batch, int32_t max_len, int32_t max_rows) {
     if (!m || batch < 1 || max_len < 1 || max_rows < 1) return 0;
-    return ws_layout(m->desc, batch, max_len, max_rows).total;
+    return ws_layout(m->desc, batch, max_len, max_rows, prompt_rows(m->desc, batch, max_len, max_rows)).total;
 }
 
 extern "C" tasc_status tasc_session_create(const tasc_model* m, int32_t batch, int32_t max_len, int32_t max_rows, void* kv_pool,
@@ -396,7 +396,13 @@ extern "C" tasc_status tasc_session_create(const tasc_model* m, int32_t batch, i
     TASC_REQUIRE(((uintptr_t)kv_pool & 255) == 0 && ((uintptr_t)workspace & 255) == 0, "session_create: buffers must be 256-byte "
                  "aligned");
     const size_t need_kv = tasc_session_kv_bytes(m, batch, max_len);
-    const WsLayout L = ws_layout(m->desc, batch, max_len, max_rows);
+    // a workspace that does not hold prompt_rows gets as many as it does, batch x max_rows at least
+    int64_t lo = (int64_t)batch * max_rows, hi = prompt_rows(m->desc, batch, max_len, max_rows);
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo + 1) / 2;
+        if (ws_layout(m->desc, batch, max_len, max_rows, mid).total <= ws_bytes) lo = mid; else hi = mid - 1;
+    }
+    const WsLayout L = ws_layout(m->desc, batch, max_len, max_rows, lo);
     if (kv_bytes < need_kv || ws_bytes < L.total) {
         tasc_set_error("session_create: kv pool %zu of %zu bytes, workspace %zu of %zu bytes", kv_bytes, need_kv, ws_bytes, L.total);
         return TASC_ENOMEM;
@@ -406,7 +412,7 @@ extern "C" tasc_status tasc_session_create(const tasc_model* m, int32_t batch, i
     s->batch = batch;
     s->max_len = max_len;
     s->max_rows = max_rows;
-    s->row_cap = (int32_t)prompt_rows(m->desc, batch, max_len, max_rows);
+    s->row_cap = (int32_t)lo;
     s->prompt_ref = prompt_ref_rows(batch, max_len, max_rows, s->row_cap);
     s->max_blocks = (max_len + TASC_KV_BLOCK - 1) / TASC_KV_BLOCK;
     s->n_strips = (m->desc.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP;

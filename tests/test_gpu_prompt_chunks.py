@@ -124,3 +124,54 @@ def test_prompt_does_not_depend_on_its_neighbours(heads):
         got.append((kv, z[5].clone(), T.tasc_session_get_tokens(sess, 5).tolist()))
     for kv, logits, tokens in got[1:]:
         assert torch.equal(kv, got[0][0]) and torch.equal(logits, got[0][1]) and tokens == got[0][2]
+
+
+def test_smaller_workspaces():
+    """A session in less memory than tasc_session_workspace_bytes asks for takes shorter prompt chunks, down to batch x max_rows
+    rows; below that it is refused.  Logits of every size against the oracle, and nothing past the workspace is written."""
+    import ctypes as C
+    import re
+    import torch
+    import paper_2602_24174_amd as T
+    from paper_2602_24174_amd.binding import Session
+    shape, lens, _, tol = CASES["hd64"]
+    B, max_rows, k = len(lens), 20, 3
+    cfg = W.get_config("cfg1").scaled(**dict(dict(n_layers=2, vocab=700, batch=B, n_docs=800), **shape))
+    weights = W.make_model(cfg, W.make_corpus(cfg))
+    rng = np.random.default_rng(3)
+    prompts = [rng.integers(0, cfg.vocab, n).astype(np.int32) for n in lens]
+    drafts = rng.integers(0, cfg.vocab, (B, k)).astype(np.int32)
+    max_len = max(lens) + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, weights, max_len)
+    kvb, full = T.tasc_session_kv_bytes(model, B, max_len), T.tasc_session_workspace_bytes(model, B, max_len, max_rows)
+    kv = torch.empty(kvb, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(full + 4096, dtype=torch.uint8, device="cuda")
+
+    def create(nbytes):
+        out = C.c_void_p()
+        rc = T.lib().tasc_session_create(model.handle, B, max_len, max_rows, kv.data_ptr(), kvb, ws.data_ptr(), nbytes, C.byref(out))
+        return rc, Session(out.value, model, B, max_len, max_rows, kv, ws) if rc == 0 else None
+
+    rc, _ = create(16)
+    assert rc == -2
+    least = int(re.search(rb"workspace 16 of (\d+) bytes", T.lib().tasc_last_error()).group(1))
+    assert least < full // 2 and create(least - 1)[0] == -2
+    om = OM.OracleModel(cfg, weights)
+    for nbytes in (least, least + (full - least) // 3, full - 1, full):
+        print(f"workspace {nbytes} of {full}", flush=True)
+        ws.fill_(0x5A)
+        rc, sess = create(nbytes)
+        assert rc == 0
+        T.tasc_session_prefill(model, sess, np.concatenate(prompts), np.cumsum([0] + lens).astype(np.int64), 1)
+        z = torch.zeros((B, k + 1, cfg.vocab), dtype=torch.float32, device="cuda")
+        T.tasc_verify_step(model, sess, torch.from_numpy(drafts).cuda(), k, None, None, z)
+        torch.cuda.synchronize()
+        assert bool((ws[nbytes:] == 0x5A).all())
+        for b in (0, 3, B - 1):
+            c = om.new_cache(max_len)
+            om.forward(prompts[b].tolist(), c, last_only=True)
+            c.length = lens[b]
+            first = int(T.tasc_session_get_tokens(sess, b)[-1])
+            want = om.forward([first] + drafts[b].tolist(), c)
+            assert float(np.abs(z[b].cpu().numpy().astype(np.float64) - want).max()) <= tol
+        sess.close()
