@@ -215,8 +215,8 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
         m->allocs.push_back(*p);
         return TASC_OK;
     };
-    auto dev_copy = [&](const void* src, size_t bytes, void** p) -> tasc_status {
-        tasc_status rc = dev_alloc(bytes, p);
+    auto dev_copy = [&](const void* src, size_t bytes, void** p, size_t pad = 0) -> tasc_status {
+        tasc_status rc = dev_alloc(bytes + pad, p);
         if (rc != TASC_OK) return rc;
         if (bytes) TASC_HIP(hipMemcpy(*p, src, bytes, hipMemcpyDefault));
         return TASC_OK;
@@ -295,8 +295,9 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
         TASC_REQUIRE(nnz >= 0 && (nnz == 0 || (w->bias_col && w->bias_val)), "model_create: bias table has %lld entries but no "
                      "column/value arrays", (long long)nnz);
         if ((rc = dev_copy(w->bias_rowptr, (size_t)(c.vocab + 1) * 8, (void**)&m->bias_rowptr)) != TASC_OK) return rc;
-        if ((rc = dev_copy(w->bias_col, (size_t)nnz * 4, (void**)&m->bias_col)) != TASC_OK) return rc;
-        if ((rc = dev_copy(w->bias_val, (size_t)nnz * 4, (void**)&m->bias_val)) != TASC_OK) return rc;
+        // (padded: the LM head reads 4 entries at a time from any one on, and from the end of an empty list)
+        if ((rc = dev_copy(w->bias_col, (size_t)nnz * 4, (void**)&m->bias_col, 16)) != TASC_OK) return rc;
+        if ((rc = dev_copy(w->bias_val, (size_t)nnz * 4, (void**)&m->bias_val, 16)) != TASC_OK) return rc;
         if ((rc = dev_copy(w->bias_base, (size_t)c.vocab * 4, (void**)&m->bias_base)) != TASC_OK) return rc;
     }
     TASC_HIP(hipDeviceSynchronize());

@@ -228,8 +228,11 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
     // are more than one per compute unit: it stores logits as whole row segments and hides the weights' latency (us of a whole
     // verify step of one layer, with logits, small | streaming: 160 x 49152 x 896 156 | 115, 224 x 49152 x 2048 224 | 181,
     // 301 x 16384 x 896 133 | 116, 64 x 49152 x 896 123 | 109; one per compute unit: 224 x 16384 x 896 106 | 125,
-    // 128 x 32768 x 2048 131 | 146).  Up to 32 rows its tiles are mostly padding (25 x 49152 x 896 106 | 108, 25 x 151936 x 896
-    // 165 | 169).
+    // 128 x 32768 x 2048 131 | 146; us of the launch alone without logits, as in the decode loop, with the bias of a corpus of 32 M
+    // tokens: 40 x 49152 x 896 59 | 36, 128 x 49152 x 2048 102 | 89, 64 x 151936 x 896 127 | 123, of 80 M: 64 x 151936 x 1536
+    // 188 | 175, of 0.5 M: 40 x 49152 x 896 46 | 31, 64 x 151936 x 1536 152 | 142; it loses where one row tile is half padding
+    // and the lists are long: 96 x 151936 x 1536 180 | 200 at 32 M, 156 | 147 at 0.5 M).  Up to 32 rows its tiles are mostly
+    // padding (25 x 49152 x 896 106 | 108, 25 x 151936 x 896 165 | 169).
     const bool large = EPI == TEPI_LMHEAD ? M > 32 && small_wgs > cus : (M >= kLargeTileRows && large_wgs >= 128) || (M > 128 && large_wgs >= 512);
     if (large) {
         // 192-row tiles where they cover the rows with less padding and no more tiles (the tile shape never changes a

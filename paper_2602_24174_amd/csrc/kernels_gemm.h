@@ -58,6 +58,9 @@ struct LmEpi {            // TEPI_LMHEAD only
 __device__ inline int tile_row(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));    // four floats at any 4-byte address
+typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int gemm_lds_bytes(int BN, int BM, int WN, int WM, int SK, int ST) { return ST * (BN + BM) * SK * 2 + WN * WM * 4096; }
 
@@ -299,61 +302,123 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                 lm_p0[j] = lm_p1[j] = 0;
                 if (lm.bias.rowptr) {
                     lm_p0[j] = f[0];
-                    lm_p1[j] = nwave < N ? f[64 * LM_R] : lm_p0[j];
+                    lm_p1[j] = nwave < N && mwave + 32 * j + lr < M ? f[64 * LM_R] : lm_p0[j];
                     lm_first[j] = (int64_t)(uint32_t)f[128 * LM_R] | ((int64_t)f[192 * LM_R] << 32);
                     lm_base[j] = __int_as_float(f[256 * LM_R]);
                 }
             }
-            // The seen successors of a row get their own bias instead of `base`.  The first four of a strip are fetched now, two
-            // by each of the row's lanes (most strips of a row hold none or one); a list that goes on is read again per tile.
+            // the lane number once more, so that what follows from it is computed where it is used and not kept in registers
+            auto lane_again = [&]() __attribute__((always_inline)) {
+                int l_ = el;
+                asm volatile("" : "+v"(l_));
+                return l_;
+            };
+            // The seen successors of a row get their own bias instead of `base`: the wave scatters the differences into a patch in
+            // its LDS and every lane adds the elements of its registers.  With a corpus of 32 to 160 M tokens the rows of frequent
+            // tokens hold most of a strip's features (119 of 128 and more in a fifth of the (row, strip) pairs at 160 M), the others
+            // few or none, so rows are taken in groups of eight and a group goes one of two ways.  Latency bounds both: a
+            // list's lines come from memory, once per step.  LM head without logits (us; four entries a row fetched ahead and longer
+            // lists read again for each tile of 32 features | this): 1280 x 151936 x 2048 at 160 M tokens 1340 | 880, 576 x 151936 x
+            // 1536 at 80 M 540 | 425, 224 x 151936 x 896 at 32 M 181 | 141; where hardly any list is long, at 0.5 M, 780 | 750,
+            // 310 | 310, 114 | 108.  All lists the first way, in rounds of 32 entries: 960, 452, 147; the second way from five
+            // entries on instead of 17: 46 instead of 31 for 40 x 49152 x 896 at 0.5 M.
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
-                int e_n[2];
-                float e_v[2];
+                constexpr int GR = 8;
+                float* const patch = reinterpret_cast<float*>(stg);
+                const int len = lm_p1[j] - lm_p0[j];
+                const int64_t start = lm_first[j] + lm_p0[j];
+                constexpr int FEW = 16;
+                const uint32_t long_rows = (uint32_t)__ballot(len > FEW);
+                // At most FEW in every row of the group: fetched by the row's lanes, four by each in a round, and patched in
+                // [32 rows][32 features]; tiles without any are left alone.
+                const int few = ((long_rows >> (lr & ~(GR - 1))) & 0xFF) != 0 ? 0 : len;
+#pragma unroll 1
+                for (int p = 0; __ballot(p < few) != 0; p += 8) {
+                    const int l_ = lane_again(), r_ = l_ & 31, h_ = l_ >> 5;
+                    const int64_t at = start + (p + 4 * h_ < few ? p + 4 * h_ : 0);      // (4 entries from any one on, or from the end of an empty list, are there: padded)
+                    const u32x4_u e_c = *reinterpret_cast<const u32x4_u*>(lm.bias.col + at);
+                    const f32x4_u e_v = *reinterpret_cast<const f32x4_u*>(lm.bias.val + at);
+                    uint32_t e_n[4];
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int p = lm_p0[j] + 2 * lh + q;
-                    e_n[q] = -1;
-                    e_v[q] = 0.f;
-                    if (p < lm_p1[j]) {
-                        e_n[q] = lm.bias.col[lm_first[j] + p] - nwave;
-                        e_v[q] = lm.bias.val[lm_first[j] + p] - lm_base[j];
-                    }
-                }
-                // The wave scatters the differences to `base` into a [32 rows][32 features] patch and every lane adds the
-                // elements of its registers; tiles without a seen successor (most) are left alone.
-                const bool more = lm_p1[j] - lm_p0[j] > 4;
+                    for (int q = 0; q < 4; ++q) e_n[q] = p + 4 * h_ + q < few ? e_c[q] - (uint32_t)nwave : ~0u;
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    if (__ballot((e_n[0] >> 5) == i || (e_n[1] >> 5) == i || more) == 0) continue;
-                    float* patch = reinterpret_cast<float*>(stg);
-                    __builtin_amdgcn_wave_barrier();
+                    for (int i = 0; i < TI; ++i) {
+                        if (__ballot((e_n[0] >> 5) == i || (e_n[1] >> 5) == i || (e_n[2] >> 5) == i || (e_n[3] >> 5) == i) == 0) continue;
+                        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(stg + q * 1024 + el * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        if ((e_n[q] >> 5) == i) patch[lr * 32 + (((e_n[q] & 31) + 4 * (lr & 7)) & 31)] = e_v[q];
-                    for (int p = lm_p0[j] + 4 + 4 * lh; more && p < lm_p1[j]; p += 8) {
-                        int nl[4];
-                        float bv[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {             // all loads in flight before the first use
-                            const int64_t at = lm_first[j] + min(p + q, lm_p1[j] - 1);
-                            nl[q] = lm.bias.col[at] - (nwave + 32 * i);
-                            bv[q] = lm.bias.val[at];
-                        }
+                        for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(stg + q * 1024 + l_ * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
+                        __builtin_amdgcn_wave_barrier();
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            if (p + q < lm_p1[j] && nl[q] >= 0 && nl[q] < 32) patch[lr * 32 + ((nl[q] + 4 * (lr & 7)) & 31)] = bv[q] - lm_base[j];
-                    }
-                    __builtin_amdgcn_wave_barrier();
+                            if ((e_n[q] >> 5) == i) patch[r_ * 32 + (((e_n[q] & 31) + 4 * (r_ & 7)) & 31)] = e_v[q] - lm_base[j];
+                        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 t = *reinterpret_cast<const float4*>(patch + lr * 32 + ((8 * q + 4 * lh + 4 * (lr & 7)) & 31));
-                        acc[i][j][4 * q] += t.x; acc[i][j][4 * q + 1] += t.y; acc[i][j][4 * q + 2] += t.z; acc[i][j][4 * q + 3] += t.w;
+                        for (int q = 0; q < 4; ++q) {
+                            const float4 t = *reinterpret_cast<const float4*>(patch + r_ * 32 + ((8 * q + 4 * h_ + 4 * (r_ & 7)) & 31));
+                            acc[i][j][4 * q] += t.x; acc[i][j][4 * q + 1] += t.y; acc[i][j][4 * q + 2] += t.z; acc[i][j][4 * q + 3] += t.w;
+                        }
+                        __builtin_amdgcn_wave_barrier();
                     }
-                    __builtin_amdgcn_wave_barrier();
+                }
+                // More: the whole wave on one row after the other, two entries a lane, patched in [8 rows][SN features]; the next
+                // group's entries are requested before this group's patch is added.
+                uint32_t todo = 0;
+#pragma unroll
+                for (int g = 0; g < 32 / GR; ++g) todo |= ((long_rows >> (GR * g)) & 0xFF) != 0 ? 1u << g : 0;
+                if (todo != 0) {
+                    static_assert(TASC_LM_STRIP <= 128, "a row's part of a strip in one load per lane");
+                    static_assert(GR * SN * 4 <= 4096, "the patch fits the wave's LDS");
+                    const int l_ = lane_again();
+                    u32x2_u c[GR];
+                    f32x2_u v[GR];
+                    auto fetch = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int r = 0; r < GR; ++r) {            // (2 entries from any one on, or from the end of an empty list, are there: padded)
+                            const int64_t at = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)start, g * GR + r) |
+                                               ((int64_t)__builtin_amdgcn_readlane((int)(start >> 32), g * GR + r) << 32);
+                            const uint32_t off = 2 * l_ < __builtin_amdgcn_readlane(len, g * GR + r) ? 8 * l_ : 0;
+                            c[r] = *reinterpret_cast<const u32x2_u*>(reinterpret_cast<const char*>(lm.bias.col + at) + off);
+                            v[r] = *reinterpret_cast<const f32x2_u*>(reinterpret_cast<const char*>(lm.bias.val + at) + off);
+                        }
+                    };
+                    fetch(__builtin_ctz(todo));
+#pragma unroll 1
+                    while (todo != 0) {
+                        const int g = __builtin_ctz(todo);
+                        todo &= todo - 1;
+                        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                        for (int q = 0; q < GR * SN * 4 / 1024; ++q) *reinterpret_cast<float4*>(stg + q * 1024 + l_ * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
+                        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                        for (int r = 0; r < GR; ++r) {
+                            const int n = __builtin_amdgcn_readlane(len, g * GR + r);
+                            const float base = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lm_base[j]), g * GR + r));
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                const uint32_t f = c[r][u] - (uint32_t)nwave;
+                                if (2 * l_ + u < n && f < (uint32_t)SN) patch[r * SN + (f ^ ((r & 3) << 3))] = v[r][u] - base;
+                            }
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        if (todo != 0) fetch(__builtin_ctz(todo));
+                        if ((l_ & 31) / GR == g) {
+                            const int a_ = lane_again(), r_ = a_ & (GR - 1);
+                            const float* row = patch + r_ * SN;
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const float* at = row + ((8 * q + 4 * (a_ >> 5)) ^ ((r_ & 3) << 3));
+#pragma unroll
+                                for (int i = 0; i < TI; ++i) {
+                                    const float4 t = *reinterpret_cast<const float4*>(at + 32 * i);
+                                    acc[i][j][4 * q] += t.x; acc[i][j][4 * q + 1] += t.y; acc[i][j][4 * q + 2] += t.z; acc[i][j][4 * q + 3] += t.w;
+                                }
+                                __builtin_amdgcn_sched_barrier(0);            // (few registers of the patch at a time)
+                            }
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                    }
                 }
                 float best = -INFINITY;
                 int32_t best_i = 0x7FFFFFFF;
@@ -540,5 +605,8 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                 }
         }
         __builtin_amdgcn_wave_barrier();
+        // (the LM head's epilogue has other use for the registers of the next stage's first fragments, and they are read again here:
+        // 40 bytes of spills otherwise, 874 instead of 860 us for 1280 x 151936 x 2048)
+        if constexpr (EPI == TEPI_LMHEAD) read_frags(0, stage % ST, 0);
     }
 }

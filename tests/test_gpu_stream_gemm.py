@@ -110,3 +110,63 @@ def test_lm_head_tile_edges(B, V, ks, d_model):
         first = int(T.tasc_session_get_tokens(sess, b)[-1])
         z = om.forward([first] + drafts[b].tolist(), c)
         assert float(np.abs(got[ks[-1]][b].astype(np.float64) - z).max()) <= 5e-2    # one bf16 layer: the bound of the other parity tests
+
+
+LENGTHS = (0, 1, 4, 5, 8, 9, 16, 17, 63, 64, 65, 104)
+
+
+def _bias_by_strip(vocab, rng, strips):
+    """Rows that hold up to 104 successors in each of the given strips of 128 columns, and none elsewhere: lists that end on
+    both sides of the ones the streaming LM head takes four entries a lane, and two; the last strip ends the whole table."""
+    rows = []
+    for u in range(vocab):
+        n = rng.permutation(LENGTHS)[:len(strips)]
+        if u % 3 == 0:
+            n = np.minimum(n, 9)             # rows, and by chance groups of rows, without a long list
+        rows.append(np.concatenate([128 * s + np.sort(rng.permutation(min(128, vocab - 128 * s))[:m]) for s, m in zip(strips, n)]))
+    rows[-1] = np.arange(128 * strips[-1], vocab)
+    col = np.concatenate(rows).astype(np.int32)
+    ptr = np.cumsum([0] + [len(r) for r in rows]).astype(np.int64)
+    return {"rowptr": ptr, "col": col, "val": rng.normal(0, 2, col.size).astype(np.float32),
+            "base": rng.normal(-3, 0.5, vocab).astype(np.float32)}
+
+
+@pytest.mark.parametrize("B,V", [(24, 16_488), (30, 33_000)])
+def test_lm_head_bias_lists(B, V):
+    """Bias lists of every length class, mixed within a block of 32 rows: 24 or 30 rows on small tiles, then the same rows in steps
+    of more rows on the streaming kernel's 192- and 256-row tiles, bit for bit, and against the oracle."""
+    import torch
+    import paper_2602_24174_amd as T
+    ks, max_rows, d_model = (0, 3, 8, 15), 16, 128
+    cfg = W.get_config("cfg1").scaled(dtype="bf16", n_layers=1, d_model=d_model, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=192, vocab=V,
+                                      batch=B)
+    rng = np.random.default_rng(V)
+    weights = W.make_model(cfg)
+    weights["bias"] = _bias_by_strip(V, rng, (0, 1, 6, 77, V // 128))
+    prompts = [rng.integers(0, V, 3 + b % 5).astype(np.int32) for b in range(B)]
+    lens = [len(p) for p in prompts]
+    max_len = 8 + 1 + 2 * max_rows
+    model = T.tasc_model_create(cfg, weights, max_len)
+    sess = T.tasc_session_create(model, B, max_len, max_rows)
+    T.tasc_session_prefill(model, sess, np.concatenate(prompts), np.cumsum([0] + lens).astype(np.int64), 1)
+    drafts = rng.integers(0, V, (B, max(ks))).astype(np.int32)
+    drafts[::4, 2] = V - 1                   # the row whose list ends the table
+    got = {}
+    for k in ks:
+        print(f"batch {B} vocab {V} k {k}", flush=True)
+        z = torch.full((B, k + 1, V), -7.0, dtype=torch.float32, device="cuda")
+        em = torch.zeros((B, k + 1), dtype=torch.int32, device="cuda")
+        d = torch.from_numpy(np.ascontiguousarray(drafts[:, :k])).cuda() if k else None
+        T.tasc_verify_step(model, sess, d, k, None, em, z)
+        torch.cuda.synchronize()
+        got[k] = z.cpu().numpy()
+    for a, b in zip(ks, ks[1:]):             # the same bits whatever the kernel and the tile shape
+        assert (got[b][:, :a + 1] == got[a]).all()
+    om = OM.OracleModel(cfg, weights)
+    for b in (0, 4, B - 1):
+        c = om.new_cache(max_len)
+        om.forward(prompts[b].tolist(), c, last_only=True)
+        c.length = lens[b]
+        first = int(T.tasc_session_get_tokens(sess, b)[-1])
+        z = om.forward([first] + drafts[b].tolist(), c)
+        assert float(np.abs(got[ks[-1]][b].astype(np.float64) - z).max()) <= 5e-2    # one bf16 layer: the bound of the other parity tests
