@@ -347,7 +347,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         if (rows_ref > 256 && rows_ref < kLargeTileRows && ks > 4) ks = 4;
         ks = ks < nk / 4 ? ks : nk / 4;                       // slices of at least 4 k-steps
         ks = ks < TG_MAX_SLICES ? ks : TG_MAX_SLICES;
-        if (!decode && s->row_cap > s->batch * s->max_rows && ks > 4) ks = 4;   // the scratch holds 8 slices of batch x max_rows rows, 4 of row_cap
+        if (!decode && ks > s->prompt_slices) ks = s->prompt_slices;
         return ks < 1 ? 1 : ks;
     };
     // Key chunks of the attention: two workgroups per compute unit in one round, but no more than 4 partial results to merge.
@@ -495,7 +495,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
     // memory round trips; ranges of sequences that run side by side fill the compute units.  Each reads the weights
     // again (from the caches when the chains keep pace), so the count stays small.
     // (Not for prompt chunks of more than batch x max_rows rows: a chain's share of the partial sums below is 8 slices of its
-    // rows, and beyond those rows the scratch holds 4.)
+    // rows, and beyond batch x max_rows the scratch may hold 4.)
     const int chains = M_all == s->batch * nq && nq <= s->max_rows ? tasc_forward_chains(m, s, nq) : 1;
     if (chains <= 1) {
         const tasc_status rc = run_layers(0, s->batch, st);

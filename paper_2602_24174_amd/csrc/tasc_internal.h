@@ -206,6 +206,7 @@ struct tasc_session {
     const tasc_model* model;
     int32_t batch, max_len, max_rows, max_blocks, n_strips;
     int32_t row_cap;          // rows the activation buffers hold
+    int32_t prompt_slices;    // most k-slices of a prompt chunk (the scratch holds them for row_cap rows)
     int32_t prompt_ref;       // rows of a prompt chunk as the split reductions are sized for (at least batch)
     int32_t max_new;
     int32_t prefilled;
