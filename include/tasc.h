@@ -70,7 +70,7 @@ const char* tasc_last_error(void);
  * T(c) = sum of kept counts and its most frequent kept successor (smallest id among equals).
  * Synchronous: allocates device memory, runs on `stream` and waits for it.  While it runs it holds, in one allocation,
  * a counting table, a byte (and the token, from host memory) per corpus token and, for all orders together, 8 bytes per
- * window / p_min (orders are taken in groups where that exceeds 8 GiB).  *out is owned by the library until tasc_ngram_destroy.
+ * window / p_min (orders are taken in groups where that exceeds TASC_CFG_BUILD_LIST_KIB).  *out is owned by the library until tasc_ngram_destroy.
  */
 tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs,
                              int32_t vocab, int32_t n_max, int32_t p_min, tasc_mem where,
@@ -350,11 +350,14 @@ tasc_status tasc_session_get_tokens(const tasc_session* s, int32_t b, int32_t* t
  *                        launches with step-invariant arguments); 0: every kernel is launched on its own.  Same kernels, same
  *                        results.  Steps that ask for logits or a trace, run under the per-class timers, or are
  *                        called on a stream that is itself being captured are always launched one by one.
+ *   TASC_CFG_BUILD_LIST_KIB
+ *                        KiB of kept-n-gram lists a table build holds at a time (default 8 GiB; one order's list is always
+ *                        held): less memory for one host round trip more per group of orders.  Tables do not depend on it.
  */
 enum {
     TASC_CFG_SMALL_PATH = 0, TASC_CFG_SMALL_GRID = 1, TASC_CFG_SMALL_LAYER_WGS = 2, TASC_CFG_SMALL_LAYER_STRIDE = 3,
     TASC_CFG_TILED_PATH = 4, TASC_CFG_SMALL_XCD_LOCAL = 5, TASC_CFG_SMALL_LAYER_WORKERS = 6, TASC_CFG_SMALL_KERNEL = 7,
-    TASC_CFG_PIPE_SHARE = 8, TASC_CFG_CHAINS = 9, TASC_CFG_STEP_GRAPH = 10
+    TASC_CFG_PIPE_SHARE = 8, TASC_CFG_CHAINS = 9, TASC_CFG_STEP_GRAPH = 10, TASC_CFG_BUILD_LIST_KIB = 11
 };
 tasc_status tasc_config_set(int32_t key, int32_t value);
 

@@ -407,6 +407,7 @@ TASC_CFG_SMALL_KERNEL = 7
 TASC_CFG_PIPE_SHARE = 8
 TASC_CFG_CHAINS = 9
 TASC_CFG_STEP_GRAPH = 10
+TASC_CFG_BUILD_LIST_KIB = 11
 
 
 def tasc_config_set(key: int, value: int):

@@ -15,7 +15,7 @@
 #include <algorithm>
 
 TascConfig g_tasc_config = {/*small_path*/ 2, /*small_grid*/ 0, /*layer_wgs*/ 0, /*layer_stride*/ 0, /*tiled_path*/ 1, /*xcd_local*/ 1,
-                             /*layer_workers*/ 0, /*small_kernel*/ 1, /*pipe_share*/ 1, /*chains*/ 0, /*step_graph*/ 1};
+                             /*layer_workers*/ 0, /*small_kernel*/ 1, /*pipe_share*/ 1, /*chains*/ 0, /*step_graph*/ 1, /*build_list_kib*/ 8 << 20};
 // One-time set-up (kernel attributes, the compute-unit count) is kept per device and done under a lock, so that calls
 // from several host threads, or sessions on different devices of one process, each find their own device prepared.
 #include <mutex>
@@ -67,6 +67,9 @@ extern "C" tasc_status tasc_config_set(int32_t key, int32_t value) {
     } else if (key == TASC_CFG_CHAINS) {
         TASC_REQUIRE(value >= 0 && value <= TASC_MAX_CHAINS, "config_set: chains %d outside [0, %d]", value, TASC_MAX_CHAINS);
         g_tasc_config.chains = value;
+    } else if (key == TASC_CFG_BUILD_LIST_KIB) {
+        TASC_REQUIRE(value >= 0, "config_set: build list size %d KiB", value);
+        g_tasc_config.build_list_kib = value;
     } else if (key == TASC_CFG_PIPE_SHARE) {
         TASC_REQUIRE(value >= 1 && value <= 3, "config_set: pipeline share %d outside [1, 3]", value);
         g_tasc_config.pipe_share = value;

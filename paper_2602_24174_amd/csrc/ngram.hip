@@ -372,8 +372,6 @@ u64 pow2_at_least(u64 v) {
     return c;
 }
 
-constexpr size_t kListBytes = (size_t)8 << 30;
-
 // a workgroup counts several chunks, so that it clears its LDS table once
 unsigned count_grid(u64 T) { return (unsigned)std::min<u64>((T + kChunk - 1) / kChunk, 4096); }
 
@@ -451,7 +449,7 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
     // One block for everything that is only needed here: counters ([n][0] distinct, [n][1] kept, [n][2] contexts of order n;
     // [0][3] unigram best, [0][4] bad-token flag), document ends, counting table, kept n-grams of every order (their counts add
     // up to the windows, so there are at most windows / p_min), a host corpus.  The orders go through in groups whose lists
-    // take no more than kListBytes (one group but for corpora of a billion tokens), each with one look at its counts.
+    // take no more than TASC_CFG_BUILD_LIST_KIB (one group but for corpora of a billion tokens), each with one look at its counts.
     size_t used = 0;
     auto carve = [&](size_t bytes) { const size_t at = used; used += (bytes + 255) / 256 * 256; return at; };
     const size_t at_counters = carve((TASC_MAX_ORDER + 1) * 8 * sizeof(u64));
@@ -460,11 +458,12 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
     const u64 slots_cap = any ? count_cap(windows[2]) : 0;     // windows[n] falls with n
     const size_t at_rem = carve(any ? T : 0), at_off = carve(any ? (size_t)(n_docs + 1) * sizeof(int64_t) : 0);
     const size_t at_slots = carve(slots_cap * sizeof(u64));
+    const size_t list_bytes = (size_t)g_tasc_config.build_list_kib << 10;
     size_t at_list[TASC_MAX_ORDER + 1] = {0}, lists = 0, longest = 0;
     int group_end[TASC_MAX_ORDER + 2] = {0};                   // [n] = one past the last order of the group that n begins
     for (int n = 2, first = 2; n <= n_max; ++n) {
         const size_t bytes = (windows[n] / (u64)p_min * sizeof(u64) + 255) / 256 * 256;
-        if (n > first && lists + bytes > kListBytes) {
+        if (n > first && lists + bytes > list_bytes) {
             first = n;
             lists = 0;
         }

@@ -287,7 +287,8 @@ struct TascConfig {
     int small_kernel;         // 1: the spatial-pipeline kernel where the model fits it, 0: the barrier kernel always
     int pipe_share;           // tiles a workgroup of the pipeline kernel takes per layer at least (1..3): fewer, fatter workgroups
     int chains;               // ranges of sequences whose layers run side by side on streams of their own (0 = the library's rule)
-    int step_graph;           // 1: verify steps of the tiled kernels are recorded into a graph and replayed, 0: launched one by one
+    int step_graph;           // 1: verify steps outside the persistent kernels are recorded into a graph and replayed, 0: launched one by one
+    int build_list_kib;       // KiB of kept-n-gram lists a table build fills before it builds their tables
 };
 extern TascConfig g_tasc_config;
 
