@@ -244,7 +244,7 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
         const int nt = (N + 255) / 256;
         const bool mid = mt192 <= mt256 && mt192 * 192 < mt256 * 256;
         const int tiles = (mid ? mt192 : mt256) * nt * slices;
-        if (EPI == TEPI_LMHEAD || (tiles > cus && !(EPI == TEPI_ROPE && (mid || 128 % rp.gm.hd != 0)))) {   // (that rotation needs whole heads in a wave's 128 features)
+        if (EPI == TEPI_LMHEAD || (tiles > cus && !(EPI == TEPI_ROPE && mid))) {   // (that rotation needs whole heads in a wave's features: 128, not 64)
             if constexpr (EPI != TEPI_ROPE) {
                 if (mid) {
                     k_gemm<EPI, GEMM_MID><<<dim3((unsigned)cus), dim3(512), gemm_lds_bytes(GEMM_MID), st>>>(A, (const BF16*)Wm, M, N, K, slices, outf,
