@@ -184,6 +184,15 @@ __global__ void k_repack_frag(const uint16_t* __restrict__ W, int N, int K, int 
     *reinterpret_cast<uint4*>(out + chunk * 8) = v;
 }
 
+// out (blocks of 16 gate rows, each followed by the 16 up rows of the same features) <- the two matrices one behind the other;
+// `blk` = 16-byte chunks of 16 rows, `n` = those of a matrix
+__global__ void k_interleave_gu(const uint4* __restrict__ gate_up, int64_t blk, int64_t n, uint4* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 2 * n) return;
+    const int64_t b = i / blk;
+    out[i] = gate_up[(b & 1) * n + (b >> 1) * blk + i % blk];
+}
+
 extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc_weight_ptrs* w, tasc_model** out) {
     TASC_REQUIRE(desc && w && out, "model_create: null argument");
     const tasc_model_desc& c = *desc;
@@ -242,6 +251,10 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
     if ((rc = dev_copy(w->gf, D * 4, (void**)&m->gf)) != TASC_OK) return rc;
     m->d_layers = nullptr;
     m->layers.resize(c.n_layers);
+    // Gate and up pass through device memory in whole matrices and are interleaved there.  (hipMemcpy2D straight into place left every
+    // layer's matrices zero, and reported success, in models created after a first one had run under rocprofv3.)
+    struct Staging { void* p = nullptr; ~Staging() { if (p) (void)hipFree(p); } } gate_up;
+    TASC_HIP(hipMalloc(&gate_up.p, 2 * F * D * es));
     for (int l = 0; l < c.n_layers; ++l) {
         TASC_REQUIRE(w->wq[l] && w->wk[l] && w->wv[l] && w->wo[l] && w->wg[l] && w->wu[l] && w->wd[l] && w->g1[l] && w->g2[l],
                      "model_create: null weight pointer in layer %d", l);
@@ -256,9 +269,11 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
         L.wo = p;
         // gate / up interleaved in blocks of 16 rows
         if ((rc = dev_alloc(2 * F * D * es, &p)) != TASC_OK) return rc;
-        const size_t blk = 16 * D * es;
-        TASC_HIP(hipMemcpy2D(p, 2 * blk, w->wg[l], blk, blk, F / 16, hipMemcpyDefault));
-        TASC_HIP(hipMemcpy2D((char*)p + blk, 2 * blk, w->wu[l], blk, blk, F / 16, hipMemcpyDefault));
+        TASC_HIP(hipMemcpy(gate_up.p, w->wg[l], F * D * es, hipMemcpyDefault));
+        TASC_HIP(hipMemcpy((char*)gate_up.p + F * D * es, w->wu[l], F * D * es, hipMemcpyDefault));
+        const int64_t chunks = (int64_t)(F * D * es / 16);        // d_model is a multiple of 8, so rows are whole chunks
+        k_interleave_gu<<<dim3((unsigned)((2 * chunks + 255) / 256)), dim3(256), 0, 0>>>((const uint4*)gate_up.p, (int64_t)(16 * D * es / 16), chunks, (uint4*)p);
+        TASC_LAUNCH_CHECK();
         L.wgu = p;
         if ((rc = dev_copy(w->wd[l], D * F * es, &p)) != TASC_OK) return rc;
         L.wd = p;
