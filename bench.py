@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0        # MI355X published HBM3E bandwidth
 # HBM bytes of one verify step from rocprofv3 hardware counters (FETCH_SIZE, WRITE_SIZE, each scaled by what the same counter
 # reads for a plain copy kernel of known size); bench.py cannot collect counters itself, so the figure of the committed
 # counter runs is carried here, for the workload they were taken on only
-MEASURED_TRAFFIC = {"cfg5": 29473969869}
+MEASURED_TRAFFIC = {"cfg5": 31170418716}
 MEASURED_TRAFFIC_SOURCE = "profiles/cfg5_verify_step_hbm_traffic.txt (bytes per verify step: every kernel of the step)"
 MFMA_PEAK_TFLOPS = 2500.0    # MI355X published dense bf16 matrix rate
 FP32_PEAK_TFLOPS = 157.3     # fp32 vector rate (the fp32 configuration runs on the type-generic kernels)

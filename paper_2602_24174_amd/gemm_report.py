@@ -7,6 +7,10 @@
 2. The verify-step shapes of the three larger workloads (rows = batch x (k + 1)), each with the epilogue and k-slices the
    forward uses, and the time of torch.matmul (the vendor's GEMM library: plain bf16 output, no epilogue) for the same
    operand shapes -- the attainable rate at these shapes, not part of the product path.
+3. The same four products at the rows of a full prompt chunk of the largest workload.
+
+Launches of more 256 x 256 (or 256 x 192) tiles than compute units run the streaming kernel k_gemm, the others k_gemm_tiled.  The
+calibration operands are constant, which spares the matrix cores power: products of real data run at a lower clock.
 """
 import argparse
 import os
@@ -53,10 +57,10 @@ def main():
               f"   -> {slope:.1f} us per 1024 of k ({ideal:.1f} at the MFMA peak: {ideal / slope:.0%}), {fixed:.1f} us per launch whatever k")
         rows.append((name, slope, fixed))
 
-    print("verify-step projections (rows = batch x (k + 1)); TFLOP/s and the share of the 2.5 PFLOP/s peak in brackets")
-    for cname in ("cfg5", "cfg4", "cfg3"):
+    print("verify-step projections (rows = batch x (k + 1)), then a prompt chunk; TFLOP/s and the share of the 2.5 PFLOP/s peak in brackets")
+    for cname, M in (("cfg5", 0), ("cfg4", 0), ("cfg3", 0), ("cfg5", 8192)):
         c = W.get_config(cname)
-        M = c.batch * (c.k + 1)
+        M = M or c.batch * (c.k + 1)
         nqkv, nqo = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim, c.n_heads * c.head_dim
         shapes = [("qkv", nqkv, c.d_model), ("output", c.d_model, nqo), ("gate/up + SwiGLU", 2 * c.d_ffn, c.d_model), ("down", c.d_model, c.d_ffn)]
         for name, N, K in shapes:

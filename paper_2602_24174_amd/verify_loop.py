@@ -7,7 +7,8 @@ between the steps, nothing but the hot path's own kernels after the set-up.
     rocprofv3 --pmc TCC_HIT_sum TCC_MISS_sum -- python -m paper_2602_24174_amd.verify_loop --config cfg5
 
 Set-up (untimed): synthetic corpus (--docs outputs: the tables only shape the drafts, so a small corpus does for
-kernel profiles of the verify step), tables, model, session, prompt prefill.  Then --steps times tasc_draft +
+kernel profiles of the layers; the bias lists of the LM head grow with it, so profiles of that take --docs 0), tables,
+model, session, prompt prefill.  Then --steps times tasc_draft +
 tasc_verify_step at the configuration's batch and draft length, one synchronisation at the end, and the mean wall time
 of a step.  In a trace the verify-step launches are told from the prefill's by their grid size.
 """
