@@ -614,8 +614,8 @@ extern "C" tasc_status tasc_session_prefill(const tasc_model* m, tasc_session* s
         k_prepare_prefill<<<dim3(B), dim3(256), 0, st>>>((int)step, (int)base, padded ? C : 0, s->max_len, d.tokens, d.n_prompt, d.row_tok,
                                                          d.row_seq, d.row0, d.n_rows, d.pos0, d.sel_rows, d.sel_tok);
         TASC_LAUNCH_CHECK();
-        // (a tail of a few positions stays with the tiled kernels: the persistent ones want the device to themselves)
-        const int nq = padded ? C : (tiled ? std::max((int)step, 17) : (int)step);
+        // (a tail of a few positions stays with the kernels of the chunks before it: the persistent ones want the device to themselves)
+        const int nq = padded ? C : (tiled || C > 16 ? std::max((int)step, 17) : (int)step);
         tasc_status rc = tasc_forward_rows(m, s, nq, (int)rows, any_last ? B : 0, nullptr, nullptr, st);
         if (rc != TASC_OK) return rc;
         k_commit_prefill<<<dim3((B + 63) / 64), dim3(64), 0, st>>>(B, (int)(base + step), s->max_len, max_new, d.n_prompt, d.sel_rows, d.amax,

@@ -175,3 +175,28 @@ def test_smaller_workspaces():
             want = om.forward([first] + drafts[b].tolist(), c)
             assert float(np.abs(z[b].cpu().numpy().astype(np.float64) - want).max()) <= tol
         sess.close()
+
+
+def test_tail_of_a_prompt_stays_with_its_kernels():
+    """One sequence of a model that the persistent kernels serve and the tiled ones do not, in prompt chunks of more than 16 rows: the
+    few rows that the last chunk has left run on the kernels of the chunks before, so the cache and the first token are, bit for bit,
+    those of a session that may not use the persistent kernels at all."""
+    import torch
+    import paper_2602_24174_amd as T
+    cfg = W.get_config("cfg1").scaled(dtype="bf16", n_layers=2, d_model=96, n_heads=3, n_kv_heads=3, head_dim=32, d_ffn=160, vocab=700,
+                                      batch=1, n_docs=800)
+    rng = np.random.default_rng(17)
+    model = T.tasc_model_create(cfg, W.make_model(cfg, W.make_corpus(cfg)), 208)
+    try:
+        for n in (5, 17, 70, 73):
+            prompt, got = rng.integers(0, cfg.vocab, n).astype(np.int32), []
+            for small in (2, 0):
+                print(f"prompt of {n}, small path {small}", flush=True)
+                T.tasc_config_set(T.TASC_CFG_SMALL_PATH, small)
+                sess = T.tasc_session_create(model, 1, 208, 64)
+                T.tasc_session_prefill(model, sess, prompt, np.array([0, n], dtype=np.int64), 1)
+                torch.cuda.synchronize()
+                got.append((sess._kv_pool.clone(), T.tasc_session_get_tokens(sess, 0).tolist()))
+            assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1], f"prompt of {n}"
+    finally:
+        T.tasc_config_set(T.TASC_CFG_SMALL_PATH, 2)
