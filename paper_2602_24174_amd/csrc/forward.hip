@@ -865,7 +865,8 @@ tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, 
     if (tail) tail->done = false;
     // The kernel family of a decode step (nq <= 16 rows per sequence) is a property of the session, not of the
     // call's row count, so that a greedy step and a speculative step of one session use the same kernels and
-    // reduce every row in the same order.  Prompt chunks of more than 16 rows always take the tiled kernels.
+    // reduce every row in the same order.  Prompt chunks of sessions with max_rows > 16 never
+    // take the persistent kernels, however few rows the last one has (the prefill asks for 17 a sequence at least).
     const int decode_rows = s->max_rows < SMALL_ROWS ? s->max_rows : SMALL_ROWS;
     if (tasc_forward_is_small(m, s, nq)) {
         if (g_tasc_config.small_kernel != 0) {
