@@ -69,8 +69,10 @@ const char* tasc_last_error(void);
  * An element (c, x) of M_n is kept iff count(c, x) >= p_min; per kept context c the table holds
  * T(c) = sum of kept counts and its most frequent kept successor (smallest id among equals).
  * Synchronous: allocates device memory, runs on `stream` and waits for it.  While it runs it holds, in one allocation,
- * a counting table, a byte (and the token, from host memory) per corpus token and, for all orders together, 8 bytes per
- * window / p_min (orders are taken in groups where that exceeds TASC_CFG_BUILD_LIST_KIB).  *out is owned by the library until tasc_ngram_destroy.
+ * 13 to 22 bytes (and the token, from host memory) per corpus token and, for all orders together, 20 bytes per window / p_min
+ * (orders are taken in groups where that exceeds TASC_CFG_BUILD_LIST_KIB).  One such allocation of up to 2 GiB per device
+ * stays with the library for the next build or enrichment while the process holds a model or a table; it is also given
+ * back when an allocation of the library finds no memory.  *out is owned by the library until tasc_ngram_destroy.
  */
 tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs,
                              int32_t vocab, int32_t n_max, int32_t p_min, tasc_mem where,

@@ -211,6 +211,7 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
     TASC_REQUIRE(!has_bias || (w->bias_rowptr && w->bias_base), "model_create: incomplete bias table");
 
     tasc_model* m = new tasc_model();
+    tasc_handles_add(1);
     m->desc = c;
     m->embed = m->lm_head = nullptr;
     m->gf = m->rope_cos = m->rope_sin = nullptr;
@@ -220,7 +221,8 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
     const size_t D = c.d_model, HD = (size_t)c.n_heads * c.head_dim, KD = (size_t)c.n_kv_heads * c.head_dim, F = c.d_ffn;
 
     auto dev_alloc = [&](size_t bytes, void** p) -> tasc_status {
-        TASC_HIP(hipMalloc(p, std::max<size_t>(bytes, 16)));
+        const tasc_status rc = tasc_device_malloc(p, std::max<size_t>(bytes, 16));
+        if (rc != TASC_OK) return rc;
         m->allocs.push_back(*p);
         return TASC_OK;
     };
@@ -325,6 +327,7 @@ extern "C" void tasc_model_destroy(tasc_model* m) {
     if (!m) return;
     for (void* p : m->allocs) (void)hipFree(p);
     delete m;
+    tasc_handles_add(-1);
 }
 
 // ================================================================ session

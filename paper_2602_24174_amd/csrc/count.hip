@@ -1,0 +1,566 @@
+// Exact n-gram counts of a corpus: the counting stage of the table build and of the tokenizer enrichment.
+//
+// A counting table of tens of millions of random slots in memory is bound by the rate of its atomics (9 to 12 G windows/s on
+// this card, whatever is done to keep more of them in flight), so no count is ever kept in memory.  Two kernels per order:
+//   * k_partition: a workgroup takes a chunk of consecutive corpus positions, merges equal windows of the chunk in an LDS table and
+//     writes what is left, ordered by partition, as records into the chunk's own region, with the partitions' offsets beside
+//     it: no exchange between workgroups, nothing to reserve, and the regions are as large as the corpus whatever its n-grams are;
+//   * k_tables: one partition, all chunks: a workgroup gathers the partition's records into a hash table in its LDS and
+//     reads the finished counts off it.
+// Partitions are ranges of the key's 64-bit hash.  With the upper half `hi` of the 128-bit key given, the hash is a bijection of the
+// lower half, so (hash, hi) is the key itself: records and LDS slots hold 8 bytes for keys of up to 64 bits and 16 beyond, the
+// comparison is exact, and nothing looks at the corpus again.
+#include "tasc_internal.h"
+#include <algorithm>
+
+namespace {
+
+// The hash: a bijection of lo for every hi, of few multiplications (each of 64 bits is four instructions of a quarter of the rate).
+constexpr u64 kMulHi = 0x9E3779B97F4A7C15ull, kMulA = 0xBF58476D1CE4E5B9ull, kMulB = 0x94D049BB133111EBull;
+constexpr u64 kUnmulA = 0x96DE1B173F119089ull, kUnmulB = 0x319642B2D24D8EC3ull;          // their inverses modulo 2^64
+__device__ __forceinline__ u64 count_hash(u64 lo, u64 hi, bool wide) {
+    u64 x = wide ? lo + hi * kMulHi : lo;
+    x ^= x >> 32;
+    x *= kMulA;
+    x ^= x >> 29;
+    return x * kMulB;
+}
+__device__ __forceinline__ u64 key_lo_of(u64 hash, u64 hi) {
+    u64 x = hash * kUnmulB;
+    x ^= (x >> 29) ^ (x >> 58);
+    x *= kUnmulA;
+    x ^= x >> 32;
+    return x - hi * kMulHi;
+}
+static_assert(kMulA * kUnmulA == 1 && kMulB * kUnmulB == 1, "inverses");
+
+// A record is {low 56 bits of the hash : 56, count - 1 : 8}, followed by the key's upper half where keys have more than 64 bits;
+// larger counts of a chunk take several.  The upper 8 bits of the hash follow from the partition: at least TASC_COUNT_MIN_PARTS =
+// 256 ranges of the hash's upper 32 bits, so a range is no longer than 2^24.
+__device__ inline u32 part_of(u64 hash, u32 parts) { return __umulhi((u32)(hash >> 32), parts); }
+__device__ inline u64 hash_of(u64 rec, u32 part, u32 parts) {
+    const u32 first = (u32)((((u64)part << 32) + parts - 1) / parts);         // smallest upper half of the partition
+    const u32 low24 = (u32)(rec >> 40);
+    const u32 top = (first >> 24) + (low24 < (first & 0xFFFFFFu) ? 1u : 0u);
+    return ((u64)top << 56) | (rec >> 8);
+}
+
+// exclusive scan over the workgroup; s_wave holds a word per wave and may be used again after the next barrier
+template <int TH>
+__device__ __forceinline__ u32 block_scan(u32 v, u32* s_wave, u32& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    u32 at = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const u32 w = __shfl_up(at, o);
+        if (lane >= o) at += w;
+    }
+    if (lane == 63) s_wave[wave] = at;
+    __syncthreads();
+    u32 before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < TH / 64; ++w) {
+        const u32 n = s_wave[w];
+        before += w < wave ? n : 0;
+        total += n;
+    }
+    return before + at - v;
+}
+
+// LDS (dynamic): tokens [C + 8], slots [2 C] of {position in the chunk + 1 : 16, count : 16}, partition counters [parts], wave sums, the
+// windows' slots [C].  A few rotations of the tokens make a hash that is good enough for the chunk's table; the key and its hash are
+// computed once per window that is left.
+template <int N, int C, int TH>
+__device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, u64 T, int bits, u32 parts,
+                                                u64* __restrict__ rec, uint16_t* __restrict__ offs) {
+    constexpr int W = C / TH;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    u32* s_slot = reinterpret_cast<u32*>(lds);
+    u32* s_tok = s_slot + 2 * C;
+    u32* s_hist = s_tok + C + 8;
+    u32* s_wave = s_hist + parts;
+    uint16_t* s_claim = reinterpret_cast<uint16_t*>(s_wave + TH / 64);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const u64 base = (u64)blockIdx.x * C;
+    const int n_here = (int)min((u64)(C + N - 1), T - base), n_win = (int)min((u64)C, T - base);
+    for (int i = tid; i < n_here; i += TH) s_tok[i] = (u32)tok[base + i];
+    // a window stays inside its document if none of its tokens but the last ends one: 64 windows of a wave from their ends' ballots
+    u32 inside = 0;                                        // bit w: window w TH + tid
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const int i = w * TH + tid;
+        const u64 here = __ballot(i < n_win && last[base + i]), then = __ballot(lane < N && base + i + 64 < T && last[base + i + 64]);
+        const u64 ends = lane == 0 ? here : (here >> lane) | (then << (64 - lane));
+        inside |= (i < n_win && (ends & ((1u << (N - 1)) - 1)) == 0) ? 1u << w : 0;      // (the corpus' last token ends a document)
+    }
+    for (int i = tid; i < 2 * C / 4; i += TH) reinterpret_cast<uint4*>(s_slot)[i] = make_uint4(0, 0, 0, 0);
+    for (u32 i = tid; i < parts; i += TH) s_hist[i] = 0;
+    __syncthreads();
+
+    // ---- equal windows merged: a lane probes once per turn and takes its next window as soon as it is done with one
+    u32 mine = 0;                                          // bit w: the window claimed a slot, s_claim[w TH + tid]
+    {
+        u32 t[N], idx = 0;
+        int i = 0;
+        bool busy = false;
+        for (;;) {
+            if (!busy && inside != 0) {
+                i = (__ffs((int)inside) - 1) * TH + tid;
+                inside &= inside - 1;
+#pragma unroll
+                for (int j = 0; j < N; ++j) t[j] = s_tok[i + j];
+                u32 h = t[0];
+#pragma unroll
+                for (int j = 1; j < N; ++j) h ^= (t[j] << (13 * j % 32)) | (t[j] >> (32 - 13 * j % 32));      // (never by 0 or 32)
+                idx = (h * 0x9E3779B1u) >> (31 - __builtin_ctz(C));
+                busy = true;
+            }
+            if (__ballot(busy) == 0) break;
+            if (busy) {
+                // (the exchange at once: a look first would be one more round trip)
+                const u32 sl = atomicCAS(&s_slot[idx], 0u, ((u32)(i + 1) << 16) | 1u);
+                if (sl == 0) {
+                    s_claim[i] = (uint16_t)idx;
+                    mine |= 1u << (i / TH);
+                    busy = false;
+                } else {
+                    const int p = (int)(sl >> 16) - 1;
+                    bool eq = true;
+#pragma unroll
+                    for (int j = 0; j < N; ++j) eq = eq & (s_tok[p + j] == t[j]);
+                    if (eq) atomicAdd(&s_slot[idx], 1u);
+                    busy = !eq;
+                    idx = (idx + 1) & (2 * C - 1);         // (twice as many slots as windows: one is free)
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- the windows that are left, and how many records of a partition come before each
+    const bool wide = N * bits > 64;
+    u64 hash[W], hi[W];
+    u32 cnt[W], rank[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        cnt[w] = 0;
+        if (!((mine >> w) & 1)) continue;
+        const u32 sl = s_slot[s_claim[w * TH + tid]];
+        const u32* at = s_tok + w * TH + tid;
+        cnt[w] = sl & 0xFFFFu;
+        u64 lo = 0;
+        hi[w] = 0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) tasc_key_put(lo, hi[w], j, bits, at[j]);
+        hash[w] = count_hash(lo, hi[w], wide);
+        rank[w] = atomicAdd(&s_hist[part_of(hash[w], parts)], (cnt[w] + 255) / 256);
+    }
+    __syncthreads();
+    // exclusive scan of the partitions' record counts, a run of consecutive partitions per thread
+    const u32 per = ((parts + TH - 1) / TH) | 1, p0 = min(tid * per, parts), p1 = min(p0 + per, parts);     // (odd: no bank conflicts)
+    u32 sum = 0, total;
+    for (u32 p = p0; p < p1; ++p) sum += s_hist[p];
+    u32 at = block_scan<TH>(sum, s_wave, total);
+    for (u32 p = p0; p < p1; ++p) {
+        const u32 n = s_hist[p];
+        s_hist[p] = at;
+        at += n;
+    }
+    __syncthreads();
+    for (u32 p = tid; p <= parts; p += TH) offs[p] = (uint16_t)(p < parts ? s_hist[p] : total);
+    // ---- records in order: put together in the slots' memory, stored as whole lines
+    const u32 step = wide ? C / 2 : C;                     // records that fit there
+    u64* s_rec = reinterpret_cast<u64*>(s_slot);
+    for (u32 first = 0; first < total; first += step) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if (!cnt[w]) continue;
+            u32 to = s_hist[part_of(hash[w], parts)] + rank[w] - first;
+            for (u32 n = cnt[w]; n > 0; ++to) {
+                const u32 c = min(n, 256u);
+                n -= c;
+                if (to >= step) continue;
+                const u64 r = (hash[w] << 8) | (c - 1);
+                if (wide) reinterpret_cast<ulonglong2*>(s_rec)[to] = make_ulonglong2(r, hi[w]);
+                else s_rec[to] = r;
+            }
+        }
+        __syncthreads();
+        const u32 here = min(total - first, step), units = wide ? here : (here + 1) / 2;     // of 16 bytes
+        ulonglong2* dst = reinterpret_cast<ulonglong2*>(rec) + (wide ? base + first : (base + first) / 2);
+        for (u32 u = tid; u < units; u += TH) dst[u] = reinterpret_cast<const ulonglong2*>(s_rec)[u];
+        __syncthreads();
+    }
+}
+
+struct PartitionArgs {
+    const int32_t* tok;
+    const u64* d_T;            // nullable: the corpus' length, where the host does not know it (T is then no less)
+    const uint8_t* last;       // 1: the document's last token
+    u64 T;
+    int32_t bits, n0;          // n0 + blockIdx.y = order of the launch's block
+    u32 parts, row;            // row = parts + 1, rounded up: a chunk's offsets
+    size_t order_recs;         // 8-byte words of an order's records
+    u64* rec;                  // [orders][chunks C] of 8 bytes, or 16 for keys of more than 64 bits
+    uint16_t* offs;            // [orders][chunks][row]
+};
+template <int C, int TH>
+__global__ __launch_bounds__(TH) void k_partition(PartitionArgs a) {
+    if (a.d_T) a.T = *a.d_T;
+    if ((u64)blockIdx.x * C >= a.T) return;
+    const int n = a.n0 + blockIdx.y;
+    u64* const rec = a.rec + blockIdx.y * a.order_recs;
+    uint16_t* const offs = a.offs + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * a.row;
+    switch (n) {
+        case 2: partition_chunk<2, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        case 3: partition_chunk<3, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        case 4: partition_chunk<4, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        case 5: partition_chunk<5, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        case 6: partition_chunk<6, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        case 7: partition_chunk<7, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        default: partition_chunk<8, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+    }
+}
+
+// [chunks][row] -> [row][chunks], both padded to whole tiles of 64: with the offsets as they are written, every lane of k_tables would
+// read lines of its own for two offsets
+__global__ __launch_bounds__(256) void k_turn(const uint16_t* __restrict__ in, u32 row, u32 col, u32 chunks, uint16_t* __restrict__ out) {
+    __shared__ uint16_t s[64][66];
+    const u32 p0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    for (int q = threadIdx.x; q < 64 * 32; q += 256) {
+        const u32 c = c0 + q / 32;
+        const u32 v = c < chunks ? *reinterpret_cast<const u32*>(in + (size_t)c * row + p0 + 2 * (q % 32)) : 0;
+        s[q / 32][2 * (q % 32)] = (uint16_t)v;
+        s[q / 32][2 * (q % 32) + 1] = (uint16_t)(v >> 16);
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 64 * 32; q += 256) {
+        const int p = q / 32, c = 2 * (q % 32);
+        *reinterpret_cast<u32*>(out + (size_t)(p0 + p) * col + c0 + c) = (u32)s[c][p] | ((u32)s[c + 1][p] << 16);
+    }
+}
+
+constexpr int kTabThreads = 768;
+constexpr int kSlotsNarrow = 5376, kSlotsWide = 3072;      // 60 KB of tables: two workgroups per compute unit
+constexpr int kPrimeNarrow = 5351, kPrimeWide = 3067;      // (primes: any step visits all of them)
+constexpr int kStageNarrow = 1536, kStageWide = 768;       // records on their way into the table: 12 KB
+constexpr int kRuns = 4;                                   // chunks of a thread at a time
+constexpr u64 kLow57 = (1ull << 57) - 1;
+constexpr int kMaxProbe = 128;                             // a longer probe sequence means a table that is as good as full
+
+struct TablesArgs {
+    const u64* rec;
+    const uint16_t* offs;
+    size_t order_recs, order_offs;     // from one order to the next
+    u32 chunk_step, part_step;         // offs[chunk * chunk_step + partition * part_step]
+    u32 chunks, chunk, parts;
+    const u64* d_T;            // nullable, as above (chunks is then an upper bound)
+    int32_t n, bits;
+    u32 p_min, rounds;         // rounds: ranges that a partition is cut into from the start
+    u64* counters;             // [0] distinct n-grams, [1] kept n-grams, [TASC_COUNT_FAILED] set where a partition could not be cut fine enough
+    TascKept kept;
+    TascGram* best;            // [orders][parts] the partition's n-gram with the largest count, smallest tuple among equals
+};
+
+template <bool WIDE>
+constexpr int table_bytes() { return WIDE ? kSlotsWide * 20 : kSlotsNarrow * 12; }
+template <bool WIDE>
+constexpr int tables_lds() { return table_bytes<WIDE>() + (WIDE ? kStageWide * 16 : kStageNarrow * 8); }
+
+// BEST: no list, but the most frequent n-gram of the workgroup's partition
+template <bool WIDE, bool BEST>
+__device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, TascGram* best_out) {
+    constexpr int SLOTS = WIDE ? kSlotsWide : kSlotsNarrow, PRIME = WIDE ? kPrimeWide : kPrimeNarrow, PER = SLOTS / kTabThreads;
+    constexpr int STAGE = WIDE ? kStageWide : kStageNarrow, RW = WIDE ? 2 : 1;
+    static_assert(SLOTS % kTabThreads == 0 && STAGE % kTabThreads == 0 && table_bytes<WIDE>() % 16 == 0, "slots and records per thread; clearing");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    u64* s_key = reinterpret_cast<u64*>(lds);                                  // {low 56 bits of the hash, 1, upper 7 bits of hi}; 0 = free
+    u64* s_hi = s_key + SLOTS;                                                 // WIDE only: {1 : 7, low 57 bits of hi}; 0 = nobody's yet
+    u32* s_cnt = reinterpret_cast<u32*>(s_key + RW * SLOTS);
+    u64* s_rec = reinterpret_cast<u64*>(lds + table_bytes<WIDE>());            // first where they are, then the records
+    __shared__ u32 s_full, s_wave[2][kTabThreads / 64];
+    __shared__ u64 s_at;
+    const int tid = threadIdx.x, lane = tid & 63;
+    auto hi_of = [&](u64 key, int i) { return WIDE ? ((key & 0x7F) << 57) | (s_hi[i] & kLow57) : 0ull; };
+    TascGram best{0, 0, 0, 0};
+    u32 distinct = 0;                                      // (a thread's are fewer than the corpus' positions)
+    const u32 runs = a.chunks > 2 * kTabThreads ? kRuns : a.chunks > kTabThreads ? 2 : 1;
+    const uint16_t* const offs = a.offs + (size_t)part * a.part_step;
+
+    u32 den = a.rounds, num = 0;                           // the range of the partition that is being counted: num / den
+    while (num < den) {
+        for (int i = tid; i < table_bytes<WIDE>() / 16; i += kTabThreads) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
+        if (tid == 0) s_full = 0;
+        for (u32 c0 = 0; c0 < a.chunks; c0 += runs * kTabThreads) {
+            // the thread's runs and their place among the records of these chunks
+            u32 at[kRuns], len[kRuns], sum = 0, total;
+#pragma unroll
+            for (int u = 0; u < kRuns; ++u) {
+                const u32 c = c0 + tid * runs + u;
+                at[u] = len[u] = 0;
+                if (u < (int)runs && c < a.chunks) {
+                    at[u] = offs[(size_t)c * a.chunk_step];
+                    len[u] = offs[(size_t)c * a.chunk_step + a.part_step] - at[u];
+                }
+                sum += len[u];
+            }
+            const u32 before = block_scan<kTabThreads>(sum, s_wave[(c0 / (runs * kTabThreads)) & 1], total);
+            for (u32 first = 0; first < total; first += STAGE) {
+                u32 to = before;
+#pragma unroll
+                for (int u = 0; u < kRuns; ++u)
+                    for (u32 j = 0; j < len[u]; ++j, ++to)
+                        if (to - first < (u32)STAGE) reinterpret_cast<u32*>(s_rec + RW * (to - first))[0] = (c0 + tid * runs + u) * a.chunk + at[u] + j;
+                __syncthreads();
+                const u32 here = min(total - first, (u32)STAGE);
+                {
+                    u64 r[STAGE / kTabThreads][RW];
+#pragma unroll
+                    for (int k = 0; k < STAGE / kTabThreads; ++k) {
+                        const u32 e = k * kTabThreads + tid;
+                        if (e < here) {
+                            const u32 src = reinterpret_cast<const u32*>(s_rec + RW * e)[0];
+                            if constexpr (WIDE) {
+                                const ulonglong2 v = reinterpret_cast<const ulonglong2*>(a.rec)[src];
+                                r[k][0] = v.x;
+                                r[k][1] = v.y;
+                            } else {
+                                r[k][0] = a.rec[src];
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < STAGE / kTabThreads; ++k) {
+                        const u32 e = k * kTabThreads + tid;
+                        if (e < here) {
+                            if constexpr (WIDE) reinterpret_cast<ulonglong2*>(s_rec)[e] = make_ulonglong2(r[k][0], r[k][1]);
+                            else s_rec[e] = r[k][0];
+                        }
+                    }
+                }
+                // every thread inserts the records that it fetched; a lane probes once per turn
+                u32 e = tid, idx = 0, step = 0, c = 0;
+                int probes = 0;
+                u64 key = 0, hv = 0;
+                bool busy = false;
+                for (;;) {
+                    if (!busy && e < here) {
+                        const u64 r = s_rec[RW * e];
+                        const u64 hi = WIDE ? s_rec[RW * e + RW - 1] : 0;
+                        e += kTabThreads;
+                        busy = true;
+                        if (den > 1) {                     // where in the partition: the lower half of the product that chose it
+                            const u32 upper = (u32)(hash_of(r, part, a.parts) >> 32);
+                            busy = (u32)(((u64)(upper * a.parts) * den) >> 32) == num;
+                        }
+                        key = (r & ~0xFFull) | 0x80 | (hi >> 57);
+                        hv = (hi & kLow57) | ~kLow57;
+                        c = (u32)(r & 0xFF) + 1;
+                        idx = __umulhi((u32)(r >> 8), (u32)PRIME);
+                        step = ((u32)(r >> 20) & 1023) + 1;
+                        probes = 0;
+                    }
+                    if (__ballot(busy || e < here) == 0) break;
+                    if (!busy) continue;
+                    // Nobody waits for anybody: a slot whose hash is there without its hi takes the hi of whoever comes first, and the
+                    // one that claimed it goes on where that was another's.
+                    const u64 k = atomicCAS(&s_key[idx], 0ull, key);
+                    bool mine = k == 0 || k == key;
+                    if (WIDE && mine) {
+                        const u64 v = atomicCAS(&s_hi[idx], 0ull, hv);
+                        mine = v == 0 || v == hv;
+                    }
+                    if (mine) atomicAdd(&s_cnt[idx], c);
+                    busy = !mine;
+                    idx += step;
+                    idx -= idx >= (u32)PRIME ? PRIME : 0;
+                    if (busy && ++probes == kMaxProbe) {
+                        s_full = 1;
+                        busy = false;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+        if (s_full) {                                      // more n-grams than slots: the range in two halves
+            __syncthreads();
+            if (den >= 1u << 24) {                         // (n-grams whose hashes agree in all bits that cut partitions: not a corpus)
+                if (tid == 0) {
+                    atomicOr(&a.counters[TASC_COUNT_FAILED], 1ull);
+                    if (BEST) *best_out = TascGram{0, 0, 0, 0};
+                }
+                return;
+            }
+            den *= 2;
+            num *= 2;
+            continue;
+        }
+        u32 keep = 0, most = 0;
+#pragma unroll
+        for (int s = 0; s < PER; ++s) {
+            const int i = s * kTabThreads + tid;
+            if (s_key[i] == 0) continue;
+            ++distinct;
+            if (s_cnt[i] >= a.p_min) ++keep;
+            most = max(most, s_cnt[i]);
+        }
+        if (BEST) {
+            // only what has the largest count is taken apart
+            for (int o = 32; o > 0; o >>= 1) most = max(most, (u32)__shfl_xor((int)most, o));
+            if (lane == 0) s_wave[0][tid >> 6] = most;
+            __syncthreads();
+            for (int w = 0; w < kTabThreads / 64; ++w) most = max(most, s_wave[0][w]);
+            for (int i = tid; i < SLOTS && most >= best.count; i += kTabThreads) {
+                const u64 key = s_key[i];
+                if (key == 0 || s_cnt[i] != most) continue;
+                const u64 hi = hi_of(key, i);
+                const TascGram g{key_lo_of(hash_of(key, part, a.parts), hi), hi, most, (u32)a.n};
+                if (tasc_gram_before(g, best, a.bits)) best = g;
+            }
+        }
+        if (!BEST) {
+            // the kept n-grams behind those of other workgroups: one addition per workgroup and range
+            u32 all;
+            const u32 before = block_scan<kTabThreads>(keep, s_wave[0], all);
+            if (tid == 0) s_at = all ? atomicAdd(&a.counters[1], (u64)all) : 0;
+            __syncthreads();
+            u64 to = s_at + before;
+            if (keep) {
+#pragma unroll
+                for (int s = 0; s < PER; ++s) {
+                    const int i = s * kTabThreads + tid;
+                    const u64 key = s_key[i];
+                    const u32 c = s_cnt[i];
+                    if (key == 0 || c < a.p_min) continue;
+                    const u64 hi = hi_of(key, i);
+                    a.kept.lo[to] = key_lo_of(hash_of(key, part, a.parts), hi);
+                    a.kept.hi[to] = hi;
+                    a.kept.count[to] = c;
+                    ++to;
+                }
+            }
+        }
+        ++num;
+        __syncthreads();
+    }
+    if (BEST) {
+        TascGram* s_best = reinterpret_cast<TascGram*>(lds);
+        static_assert(kTabThreads <= 1024 && kTabThreads * sizeof(TascGram) <= table_bytes<false>(), "a candidate per thread in the tables' LDS");
+        s_best[tid] = best;
+        __syncthreads();
+        for (int w = 512; w > 0; w >>= 1) {
+            if (tid < w && tid + w < kTabThreads && tasc_gram_before(s_best[tid + w], s_best[tid], a.bits)) s_best[tid] = s_best[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) *best_out = s_best[0];
+    } else {
+        u32 n = distinct;
+        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+        if (lane == 0) s_wave[0][tid >> 6] = n;
+        __syncthreads();
+        if (tid == 0) {
+            u64 all = 0;
+            for (int w = 0; w < kTabThreads / 64; ++w) all += s_wave[0][w];
+            if (all) atomicAdd(&a.counters[0], all);
+        }
+    }
+}
+
+// The partition of a workgroup: the dispatcher deals ids to the 8 XCDs in turn, and each XCD takes one contiguous range of the
+// partitions, so that the records of neighbouring partitions, which share cache lines, are read into one L2.
+__device__ inline u32 my_part(u32 parts) {
+    const u32 xcd = blockIdx.x % 8;
+    return xcd * (parts / 8) + min(xcd, parts % 8) + blockIdx.x / 8;
+}
+template <bool WIDE>
+__global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_tables(TablesArgs a) { partition_table<WIDE, false>(a, my_part(a.parts), nullptr); }
+
+// every order n + blockIdx.y
+__global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_tables_best(TablesArgs a) {
+    const u32 y = blockIdx.y;
+    a.n += (int32_t)y;
+    a.rec += y * a.order_recs;
+    a.offs += y * a.order_offs;
+    a.best += (size_t)y * gridDim.x + blockIdx.x;
+    if (a.d_T) a.chunks = (u32)((*a.d_T + a.chunk - 1) / a.chunk);
+    if (a.n * a.bits > 64) partition_table<true, true>(a, my_part(a.parts), a.best);
+    else partition_table<false, true>(a, my_part(a.parts), a.best);
+}
+
+constexpr int kChunkLarge = 8192, kThreadsLarge = 1024, kChunkSmall = 2048, kThreadsSmall = 512;
+size_t partition_lds(u32 chunk, u32 parts) { return (size_t)(2 * chunk + chunk + 8 + parts + 16) * 4 + 2 * (size_t)chunk; }
+u32 up64(u32 v) { return (v + 63) / 64 * 64; }
+
+}  // namespace
+
+// Chunks of 8192 positions merge more windows (of 32 M tokens 0.55 / 0.84 of the 2- / 5-grams are left, 0.65 / 0.89 with 2048)
+// and leave longer runs of a partition, but they need 2 M tokens to fill the chip.  A partition is as many windows as there
+// are LDS slots: about half of a corpus' windows are distinct (0.21 to 0.51 of the 2- to 5-grams of 24 M tokens), and where
+// nearly all are, it is cut in two.  Offsets are turned round where there are many chunks.
+TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide) {
+    TascCountPlan p;
+    p.chunk = T >= (u64)256 * kChunkLarge ? kChunkLarge : kChunkSmall;
+    p.chunks = (u32)((T + p.chunk - 1) / p.chunk);
+    const u64 per = wide ? kSlotsWide : kSlotsNarrow;
+    p.parts = (u32)std::clamp<u64>((windows + per - 1) / per, TASC_COUNT_MIN_PARTS, TASC_COUNT_MAX_PARTS);
+    p.rounds = (u32)std::max<u64>(1, windows / p.parts / per);
+    p.rec_bytes = (size_t)p.chunks * p.chunk * (wide ? 16 : 8);
+    p.offs_bytes = (size_t)up64(p.chunks) * up64(p.parts + 1) * sizeof(uint16_t) * (p.chunk == kChunkLarge ? 2 : 1);
+    return p;
+}
+
+tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, const uint8_t* d_last, u64 T, const u64* d_T, int32_t n0,
+                                 int32_t n_orders, int32_t bits, const TascCountBufs& b, hipStream_t st) {
+    const u32 row = up64(p.parts + 1);
+    PartitionArgs a{d_tok, d_T, d_last, T, bits, n0, p.parts, row, p.rec_bytes / sizeof(u64), b.rec, b.offs};
+    const size_t lds = partition_lds(p.chunk, p.parts);
+    auto launch = [&](auto kernel, int threads) -> tasc_status {
+        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)partition_lds(p.chunk, TASC_COUNT_MAX_PARTS)));
+        kernel<<<dim3(p.chunks, (unsigned)n_orders), dim3(threads), lds, st>>>(a);
+        TASC_LAUNCH_CHECK();
+        return TASC_OK;
+    };
+    if (p.chunk != kChunkLarge) return launch(&k_partition<kChunkSmall, kThreadsSmall>, kThreadsSmall);
+    const tasc_status rc = launch(&k_partition<kChunkLarge, kThreadsLarge>, kThreadsLarge);
+    if (rc != TASC_OK) return rc;
+    const u32 col = up64(p.chunks);
+    const size_t one = (size_t)col * row;
+    for (int y = 0; y < n_orders; ++y) {
+        k_turn<<<dim3(row / 64, col / 64), dim3(256), 0, st>>>(b.offs + (size_t)y * p.chunks * row, row, col, p.chunks, b.offs + n_orders * one + y * one);
+        TASC_LAUNCH_CHECK();
+    }
+    return TASC_OK;
+}
+
+static TablesArgs tables_args(const TascCountPlan& p, const u64* d_T, int32_t n, int32_t n_orders, int32_t bits, u32 p_min, const TascCountBufs& b,
+                              u64* d_counters, const TascKept& kept, TascGram* d_best) {
+    const u32 row = up64(p.parts + 1), col = up64(p.chunks);
+    const bool turned = p.chunk == kChunkLarge;
+    return TablesArgs{b.rec, turned ? b.offs + (size_t)n_orders * col * row : b.offs, p.rec_bytes / sizeof(u64),
+                      turned ? (size_t)col * row : (size_t)p.chunks * row, turned ? 1 : row, turned ? col : 1,
+                      p.chunks, p.chunk, p.parts, d_T, n, bits, p_min, p.rounds, d_counters, kept, d_best};
+}
+
+tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u32 p_min, const TascCountBufs& b, u64* d_counters,
+                              const TascKept& kept, hipStream_t st) {
+    const TablesArgs a = tables_args(p, nullptr, n, 1, bits, p_min, b, d_counters, kept, nullptr);
+    auto launch = [&](auto kernel, int lds) -> tasc_status {
+        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        kernel<<<dim3(p.parts), dim3(kTabThreads), lds, st>>>(a);
+        TASC_LAUNCH_CHECK();
+        return TASC_OK;
+    };
+    return n * bits > 64 ? launch(&k_tables<true>, tables_lds<true>()) : launch(&k_tables<false>, tables_lds<false>());
+}
+
+tasc_status tasc_count_best(const TascCountPlan& p, const u64* d_T, int32_t n0, int32_t n_orders, int32_t bits, const TascCountBufs& b,
+                            u64* d_counters, TascGram* d_best, hipStream_t st) {
+    const TablesArgs a = tables_args(p, d_T, n0, n_orders, bits, 1, b, d_counters, TascKept{}, d_best);
+    constexpr int lds = std::max(tables_lds<false>(), tables_lds<true>());
+    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tables_best), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    k_tables_best<<<dim3(p.parts, (unsigned)n_orders), dim3(kTabThreads), lds, st>>>(a);
+    TASC_LAUNCH_CHECK();
+    return TASC_OK;
+}

@@ -39,6 +39,24 @@ void tasc_set_error(const char* fmt, ...);
         }                                                                            \
     } while (0)
 
+// ---------------------------------------------------------------- scratch of synchronous calls (scratch.hip)
+// A block of device memory, one that an earlier call left behind or a new one.  keep() leaves it to a later call, of any thread and
+// stream: only when nothing on the device uses it any more.  A block that is not kept is freed with the object.
+struct TascScratch {
+    char* p = nullptr;
+    size_t bytes = 0;
+    tasc_status get(size_t need);
+    void keep();
+    TascScratch() = default;
+    TascScratch(const TascScratch&) = delete;
+    TascScratch& operator=(const TascScratch&) = delete;
+    ~TascScratch();
+};
+// hipMalloc that gives kept scratch back where memory runs out
+tasc_status tasc_device_malloc(void** p, size_t bytes);
+// models and tables that exist: kept scratch is freed with the last of them
+void tasc_handles_add(int n);
+
 // ---------------------------------------------------------------- n-gram tables
 // One 32-byte slot of a finished (read-only) table.  The key is the packed token string
 // (token j at bit j*bits of the 128-bit integer hi:lo).  Context tables: a = T (sum of kept
@@ -70,13 +88,43 @@ struct tasc_ngram {
     TascSlot* tables[TASC_MAX_ORDER + 1];   // the blocks slots[][] lie in, by the first order of each
 };
 
-// The counting stage of a table build, for callers that work on the counting table itself (ngram.hip; all on `st`):
-// slots of the table for `windows` windows; rem[i] = tokens left in the document from position i on (saturated at 255);
-// the n-gram counts of order n, slots {position of one occurrence + 1 : 32, count : 32}, 0 = empty
-u64 tasc_count_cap(u64 windows);
-tasc_status tasc_mark_tails(const int64_t* d_off, int64_t n_docs, int32_t n_max, u64 T, uint8_t* d_rem, hipStream_t st);
-tasc_status tasc_count_order(const int32_t* d_tok, const uint8_t* d_rem, u64 T, int32_t n, int32_t bits, u64* d_slots, u64 cap, u64* d_counters,
-                             hipStream_t st);
+// ---------------------------------------------------------------- exact n-gram counts (count.hip)
+#define TASC_COUNT_MIN_PARTS 256
+#define TASC_COUNT_MAX_PARTS 11264  // their counters fit a workgroup's LDS beside a chunk
+#define TASC_COUNT_FAILED 5         // of an order's counters: a partition that could not be cut fine enough
+
+struct TascCountPlan {
+    u32 chunk, chunks;        // corpus positions of a workgroup, and how many such chunks
+    u32 parts, rounds;        // hash ranges, and how many a range is cut into once more
+    size_t rec_bytes, offs_bytes;   // buffers of one order
+};
+struct TascCountBufs {        // of every order of a call, one behind the other
+    u64* rec;
+    uint16_t* offs;
+};
+struct TascKept {             // n-grams with their packed keys and counts
+    u64* lo;
+    u64* hi;
+    u32* count;
+};
+struct TascGram {             // one n-gram; count 0 = none
+    u64 lo, hi;
+    u32 count, n;
+};
+// wide: keys of more than 64 bits (a call of several orders takes the plan of its longest)
+TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide);
+// Records of the orders n0 .. n0 + n_orders - 1.  last[i] = 1 where position i ends a document, as the corpus' last one does;
+// d_T (nullable): the corpus' length in device memory, no more than T.
+tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, const uint8_t* d_last, u64 T, const u64* d_T, int32_t n0,
+                                 int32_t n_orders, int32_t bits, const TascCountBufs& b, hipStream_t st);
+// Finished counts of one order: d_counters[0] += distinct n-grams, [1] += those of at least p_min, which go to `kept`
+tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u32 p_min, const TascCountBufs& b, u64* d_counters,
+                              const TascKept& kept, hipStream_t st);
+// The most frequent n-gram of every partition (smallest tuple among equals): d_best[n_orders][parts]
+tasc_status tasc_count_best(const TascCountPlan& p, const u64* d_T, int32_t n0, int32_t n_orders, int32_t bits, const TascCountBufs& b,
+                            u64* d_counters, TascGram* d_best, hipStream_t st);
+// last[0..T) as above (ngram.hip)
+tasc_status tasc_mark_ends(const int64_t* d_off, int64_t n_docs, u64 T, uint8_t* d_last, hipStream_t st);
 
 __host__ __device__ inline u64 tasc_mix64(u64 x) {
     x ^= x >> 30; x *= 0xBF58476D1CE4E5B9ull;
@@ -107,6 +155,19 @@ __host__ __device__ inline u32 tasc_key_get(u64 lo, u64 hi, int j, int bits) {
         v = hi >> (sh - 64);
     }
     return (u32)(v & ((1ull << bits) - 1));
+}
+
+// a before b among candidates for a merge: larger count x (n - 1), then shorter, then the smaller token tuple
+__device__ inline bool tasc_gram_before(const TascGram& a, const TascGram& b, int bits) {
+    const u64 ra = (u64)a.count * (a.n - 1), rb = (u64)b.count * (b.n - 1);
+    if (a.count == 0 || b.count == 0) return a.count != 0 && b.count == 0;
+    if (ra != rb) return ra > rb;
+    if (a.n != b.n) return a.n < b.n;
+    for (u32 j = 0; j < a.n; ++j) {
+        const u32 ta = tasc_key_get(a.lo, a.hi, (int)j, bits), tb = tasc_key_get(b.lo, b.hi, (int)j, bits);
+        if (ta != tb) return ta < tb;
+    }
+    return false;
 }
 
 // ---------------------------------------------------------------- model

@@ -4,221 +4,274 @@
 // as currently tokenised with the table builder's counting stage, picks the n-gram with the largest reward
 // (ties: shorter, then smallest token tuple), gives it the next free token id and re-tokenises the corpus on the
 // device (left to right, without overlap, inside each output).
+//
+// What bounds a merge on a small corpus is its launches and whoever waits for them, so the steps of a merge follow each other
+// without the host: what one finds out (the n-gram, the new length, that nothing is left to merge) the next ones read from
+// device memory, and the host looks at it once per kBatch merges.  1.0 M tokens, eight merges, orders 2 to 4: 1.1 ms (4.4
+// with counting tables in memory, some 35 launches a merge and two looks from the host).
 #include <algorithm>
+#include <string.h>
 #include <vector>
 
 #include "tasc_internal.h"
 
 namespace {
 constexpr int kThreads = 256;
-constexpr int kScanItems = 16;                       // elements per thread of a scan block
-constexpr int kScanBlock = kThreads * kScanItems;    // 4096
+constexpr int kItems = 4;                            // positions of a thread
+constexpr int kBlock = kThreads * kItems;            // 1024
+constexpr int kBatch = 16;
 
-struct MergeCand {
-    u64 reward;      // freq * (n - 1); 0 = none
-    u64 lo, hi;      // packed token tuple
-    u32 n, freq;
+struct Merge {           // one line of the result, as the caller's arrays have it
+    int32_t row[1 + TASC_MAX_ORDER];
+    u32 freq;
+};
+struct State {
+    u32 merges, done;    // merges so far; 1: nothing left to merge, or a failure: every later step does nothing
+    u32 bad, failed;     // a token outside the vocabulary; the counting stage gave up
+    u32 n, overlaps;     // the running merge: its n-gram, and whether two occurrences of it can overlap
+    int32_t t[TASC_MAX_ORDER], new_id;
 };
 
-// a before b: larger reward, then shorter n-gram, then lexicographically smaller tuple
-__device__ inline bool cand_before(const MergeCand& a, const MergeCand& b, int bits) {
-    if (a.reward != b.reward) return a.reward > b.reward;
-    if (a.reward == 0) return false;
-    if (a.n != b.n) return a.n < b.n;
-    for (u32 j = 0; j < a.n; ++j) {
-        const u32 ta = tasc_key_get(a.lo, a.hi, (int)j, bits), tb = tasc_key_get(b.lo, b.hi, (int)j, bits);
-        if (ta != tb) return ta < tb;
-    }
-    return false;
-}
-
-__device__ inline void block_best(MergeCand& mine, int bits, MergeCand* out) {
-    __shared__ MergeCand s_c[kThreads];
-    s_c[threadIdx.x] = mine;
-    __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w && cand_before(s_c[threadIdx.x + w], s_c[threadIdx.x], bits)) s_c[threadIdx.x] = s_c[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = s_c[0];
-}
-
-// The largest count of a counting table ({position + 1 : 32, count : 32} slots), then the best n-gram among the slots that
-// have it: only those look their tokens up in the corpus (one slot in two holds a count of 1 or 2).
-__global__ __launch_bounds__(kThreads) void k_max_count(const u64* __restrict__ slots, u64 cap, u32* max_count) {
-    u32 best = 0;
-    for (u64 i = ((u64)blockIdx.x * kThreads + threadIdx.x) * 2; i < cap; i += (u64)gridDim.x * kThreads * 2) {
-        const ulonglong2 s = *reinterpret_cast<const ulonglong2*>(slots + i);          // cap is a power of two
-        best = max(best, max((u32)s.x, (u32)s.y));
-    }
-    for (int o = 32; o > 0; o >>= 1) best = max(best, (u32)__shfl_xor((int)best, o));
-    __shared__ u32 s_b[kThreads / 64];
-    if ((threadIdx.x & 63) == 0) s_b[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) best = max(best, s_b[w]);
-        if (best > __hip_atomic_load(max_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(max_count, best);
-    }
-}
-__global__ __launch_bounds__(kThreads) void k_best_in_table(const u64* __restrict__ slots, u64 cap, const int32_t* __restrict__ tok,
-                                                            const u32* __restrict__ max_count, int n, int bits, MergeCand* block_out) {
-    MergeCand best{0, 0, 0, 0, 0};
-    const u32 want = *max_count;
-    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; want && i < cap; i += (u64)gridDim.x * kThreads) {
-        const u64 s = slots[i];
-        if ((u32)s != want) continue;
-        MergeCand c{(u64)want * (u64)(n - 1), 0, 0, (u32)n, want};
-        for (int j = 0; j < n; ++j) tasc_key_put(c.lo, c.hi, j, bits, (u32)tok[(s >> 32) - 1 + j]);
-        if (cand_before(c, best, bits)) best = c;
-    }
-    block_best(best, bits, block_out + blockIdx.x);
-}
-// flag = 1 if a token lies outside [0, vocab)
-__global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __restrict__ tok, u64 T, int vocab, u32* flag) {
+// st->bad = 1 if a token lies outside [0, vocab)
+__global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __restrict__ tok, u64 T, int vocab, State* st) {
     bool bad = false;
     for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < T; i += (u64)gridDim.x * kThreads) bad = bad || tok[i] < 0 || tok[i] >= vocab;
-    if (bad) atomicOr(flag, 1u);
-}
-__global__ __launch_bounds__(kThreads) void k_best_final(const MergeCand* __restrict__ cands, int count, int bits, MergeCand* out) {
-    MergeCand best{0, 0, 0, 0, 0};
-    for (int i = threadIdx.x; i < count; i += kThreads)
-        if (cand_before(cands[i], best, bits)) best = cands[i];
-    block_best(best, bits, out);
+    if (bad) st->bad = 1;
 }
 
-__global__ void k_doc_starts(const int64_t* __restrict__ off, int64_t n_docs, unsigned char* start) {
-    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d < n_docs && off[d] < off[d + 1]) start[off[d]] = 1;
-}
-
-struct Gram { int32_t t[TASC_MAX_ORDER]; };
-
-// mark[i] = 1 iff the n-gram starts at i and lies inside one output (no output starts in (i, i + n - 1])
-__global__ void k_mark(const int32_t* __restrict__ tok, const unsigned char* __restrict__ start, u64 T, Gram g, int n, unsigned char* mark) {
-    const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T) return;
-    bool ok = i + (u64)n <= T;
-    if (ok) {
-        for (int j = 0; j < n; ++j) ok = ok && tok[i + j] == g.t[j] && (j == 0 || !start[i + j]);
+// the best of the partitions' candidates becomes merge number st->merges
+constexpr int kPickThreads = 1024;
+__global__ __launch_bounds__(kPickThreads) void k_pick(const TascGram* __restrict__ cands, u32 count, int bits, int vocab, const u64* __restrict__ counters,
+                                                   State* st, Merge* merges) {
+    if (st->done) return;
+    TascGram best{0, 0, 0, 0};
+    for (u32 i = threadIdx.x; i < count; i += kPickThreads)
+        if (tasc_gram_before(cands[i], best, bits)) best = cands[i];
+    __shared__ TascGram s_c[kPickThreads];
+    s_c[threadIdx.x] = best;
+    __syncthreads();
+    for (int w = kPickThreads / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w && tasc_gram_before(s_c[threadIdx.x + w], s_c[threadIdx.x], bits)) s_c[threadIdx.x] = s_c[threadIdx.x + w];
+        __syncthreads();
     }
-    mark[i] = ok ? 1 : 0;
+    if (threadIdx.x != 0) return;
+    best = s_c[0];
+    const bool failed = counters[TASC_COUNT_FAILED] != 0;
+    if (failed || best.count == 0) {
+        st->failed = failed;
+        st->done = 1;
+        return;
+    }
+    const u32 m = st->merges;
+    Merge out;
+    out.freq = best.count;
+    out.row[0] = (int32_t)best.n;
+    for (int j = 0; j < TASC_MAX_ORDER; ++j) {
+        const bool in = j < (int)best.n;
+        st->t[j] = in ? (int32_t)tasc_key_get(best.lo, best.hi, j, bits) : 0;
+        out.row[1 + j] = in ? st->t[j] : -1;
+    }
+    merges[m] = out;
+    bool overlaps = false;
+    for (u32 s = 1; s < best.n; ++s) {                       // shifted by s, the n-gram agrees with itself
+        bool same = true;
+        for (u32 j = 0; j + s < best.n; ++j) same = same && out.row[1 + j] == out.row[1 + j + s];
+        overlaps = overlaps || same;
+    }
+    st->n = best.n;
+    st->overlaps = overlaps;
+    st->new_id = vocab + (int32_t)m;
+    st->merges = m + 1;
 }
 
-// Left-to-right choice among overlapping matches.  A match with no match in the n - 1 positions before it ("head")
-// is always taken; from it, one thread walks the run of matches that overlap each other, taking the first match at
-// or after the end of the last taken one, and stops when that one is a head itself (its own thread takes it) or lies
-// beyond the reach of an overlap.  The walk ends at the latest at the end of the corpus.
-__global__ void k_select(const unsigned char* __restrict__ mark, u64 T, int n, unsigned char* sel) {
-    const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T || !mark[i]) return;
+struct Gram {            // the running merge, in registers
+    u32 n, overlaps, merges;
+    int32_t t[TASC_MAX_ORDER], new_id;
+};
+__device__ __forceinline__ Gram running(const State* __restrict__ st) {
+    Gram g{st->n, st->overlaps, st->merges, {}, st->new_id};
+#pragma unroll
+    for (int j = 0; j < TASC_MAX_ORDER; ++j) g.t[j] = st->t[j];
+    return g;
+}
+// the n-gram starts at i and lies inside one output; tok[0] is position i's token
+__device__ __forceinline__ bool matches(const int32_t* tok, const uint8_t* __restrict__ last, u64 T, u64 i, const Gram& g) {
+    if (tok[0] != g.t[0] || i + g.n > T || last[i]) return false;
+    bool ok = true;
+#pragma unroll
+    for (int j = 1; j < TASC_MAX_ORDER; ++j)
+        if (j < (int)g.n) ok = ok && tok[j] == g.t[j] && (j + 1 == (int)g.n || !last[i + j]);
+    return ok;
+}
+
+// Left-to-right choice among occurrences that can overlap (the others are all taken, and found where they are needed): sel[i] =
+// number of the merge.  An occurrence with none in the n - 1 positions before it ("head") is always taken; from it, one thread
+// walks the run of occurrences that overlap each other, taking the first at or after the end of the last taken one, and stops when
+// that one is a head itself (its own thread takes it) or lies beyond the reach of an overlap.  The walk ends at the latest at
+// the end of the corpus.
+constexpr unsigned kSelectBlocks = 1024;
+__global__ __launch_bounds__(kThreads) void k_select(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, const u64* __restrict__ len,
+                                                     const State* __restrict__ st, u32* sel) {
+    if (st->done || !st->overlaps) return;
+    const u64 T = *len;
+    const Gram g = running(st);
+    const int n = (int)g.n;
     auto is_head = [&](u64 p) {
         for (int j = 1; j < n; ++j)
-            if (p >= (u64)j && mark[p - j]) return false;
+            if (p >= (u64)j && matches(tok + (p - j), last, T, p - j, g)) return false;
         return true;
     };
-    if (!is_head(i)) return;
-    u64 cur = i;
-    for (;;) {
-        sel[cur] = 1;
-        u64 next = T;
-        for (u64 p = cur + n; p < cur + 2 * (u64)n - 1 && p < T; ++p)
-            if (mark[p]) { next = p; break; }
-        if (next >= T || is_head(next)) break;
-        cur = next;
-    }
-}
-
-// keep[i] = 0 for the positions a taken match swallows (all but its first); val[i] = token after the merge
-__global__ void k_keep(const int32_t* __restrict__ tok, const unsigned char* __restrict__ sel, u64 T, int n, int32_t new_id, unsigned char* keep,
-                       int32_t* val) {
-    const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T) return;
-    bool inside = false;
-    for (int j = 1; j < n; ++j) inside = inside || (i >= (u64)j && sel[i - j]);
-    keep[i] = inside ? 0 : 1;
-    val[i] = sel[i] ? new_id : tok[i];
-}
-
-// exclusive scan of keep[] into pos[0..T] in three steps: per-block sums, scan of the sums (one workgroup), apply
-__global__ __launch_bounds__(kThreads) void k_scan_sums(const unsigned char* __restrict__ keep, u64 T, u32* bsum) {
-    const u64 base = (u64)blockIdx.x * kScanBlock;
-    u32 c = 0;
-    for (int j = 0; j < kScanItems; ++j) {
-        const u64 i = base + (u64)j * kThreads + threadIdx.x;
-        if (i < T) c += keep[i];
-    }
-    __shared__ u32 s[kThreads];
-    s[threadIdx.x] = c;
-    __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) bsum[blockIdx.x] = s[0];
-}
-__global__ __launch_bounds__(kThreads) void k_scan_offsets(u32* bsum, u32 n_blocks) {   // in place: exclusive scan, one workgroup
-    __shared__ u32 s[kThreads];
-    __shared__ u32 carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (u32 b0 = 0; b0 < n_blocks; b0 += kThreads) {
-        const u32 i = b0 + threadIdx.x;
-        const u32 v = i < n_blocks ? bsum[i] : 0;
-        s[threadIdx.x] = v;
-        __syncthreads();
-        for (int w = 1; w < kThreads; w <<= 1) {             // inclusive scan of the chunk
-            const u32 add = (int)threadIdx.x >= w ? s[threadIdx.x - w] : 0;
-            __syncthreads();
-            s[threadIdx.x] += add;
-            __syncthreads();
-        }
-        if (i < n_blocks) bsum[i] = carry + s[threadIdx.x] - v;
-        __syncthreads();
-        if (threadIdx.x == 0) carry += s[kThreads - 1];
-        __syncthreads();
-    }
-}
-// thread t of a block owns the kScanItems consecutive elements base + t * kScanItems ..
-__global__ __launch_bounds__(kThreads) void k_scan_apply(const unsigned char* __restrict__ keep, const int32_t* __restrict__ val, u64 T,
-                                                         const u32* __restrict__ boff, u32* pos, int32_t* out) {
-    const u64 base = (u64)blockIdx.x * kScanBlock + (u64)threadIdx.x * kScanItems;
-    u32 c = 0;
-    for (int j = 0; j < kScanItems; ++j)
-        if (base + j < T) c += keep[base + j];
-    __shared__ u32 s[kThreads];
-    s[threadIdx.x] = c;
-    __syncthreads();
-    for (int w = 1; w < kThreads; w <<= 1) {
-        const u32 add = (int)threadIdx.x >= w ? s[threadIdx.x - w] : 0;
-        __syncthreads();
-        s[threadIdx.x] += add;
-        __syncthreads();
-    }
-    u32 p = boff[blockIdx.x] + s[threadIdx.x] - c;
-    for (int j = 0; j < kScanItems; ++j) {
-        const u64 i = base + j;
-        if (i < T) {
-            pos[i] = p;
-            if (keep[i]) { out[p] = val[i]; ++p; }
+    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < T; i += (u64)gridDim.x * kThreads) {
+        if (!matches(tok + i, last, T, i, g) || !is_head(i)) continue;
+        u64 cur = i;
+        for (;;) {
+            sel[cur] = st->merges;
+            u64 next = T;
+            for (u64 p = cur + n; p < cur + 2 * (u64)n - 1 && p < T; ++p)
+                if (matches(tok + p, last, T, p, g)) { next = p; break; }
+            if (next >= T || is_head(next)) break;
+            cur = next;
         }
     }
-    if (base <= T && T < base + kScanItems) pos[T] = p;         // the thread whose range holds position T (all its kept ones counted)
-}
-__global__ void k_new_offsets(const int64_t* __restrict__ off, int64_t n_docs, const u32* __restrict__ pos, int64_t* off_out) {
-    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d <= n_docs) off_out[d] = (int64_t)pos[off[d]];
 }
 
-struct Bufs {
-    std::vector<void*> p;
-    ~Bufs() { for (void* q : p) (void)hipFree(q); }
-    template <class T> tasc_status get(T** out, size_t count) {
-        void* q = nullptr;
-        TASC_HIP(hipMalloc(&q, (count ? count : 1) * sizeof(T)));
-        p.push_back(q);
-        *out = (T*)q;
-        return TASC_OK;
+// What a block of kBlock positions does with the merge: its tokens, 8 more on either side, come to LDS, and from them (or from the
+// choice made above) where occurrences start.  keep: of the kItems positions of a thread, those that no taken
+// occurrence swallows; starts: those where one begins.
+struct BlockTokens {
+    int32_t tok[kBlock + 16];
+    __attribute__((aligned(16))) uint8_t start[kBlock + 16];
+};
+__device__ inline void block_keep(BlockTokens& s, const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, const u32* __restrict__ sel,
+                                  u64 T, const Gram& g, u32& keep, u32& starts) {
+    const int64_t base = (int64_t)blockIdx.x * kBlock - 8;
+    for (int q = threadIdx.x; q < kBlock + 16; q += kThreads) s.tok[q] = base + q >= 0 && base + q < (int64_t)T ? tok[base + q] : -1;
+    __syncthreads();
+    for (int q = threadIdx.x; q < kBlock + 8; q += kThreads) {
+        const int64_t p = base + q;
+        s.start[q] = p >= 0 && p < (int64_t)T && (g.overlaps ? sel[p] == g.merges : matches(s.tok + q, last, T, (u64)p, g)) ? 1 : 0;
     }
+    __syncthreads();
+    u32 f = 0;                                               // bit 8 + e: an occurrence starts at the thread's position e
+    const uint8_t* at = s.start + kItems * threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 8 + kItems; ++q) f |= (u32)(at[q] & 1) << q;
+    u32 gone = 0;
+    for (u32 j = 1; j < g.n; ++j) gone |= f << j;
+    const int64_t left = (int64_t)T - (base + 8) - kItems * (int64_t)threadIdx.x;
+    const u32 mine = left >= kItems ? (1u << kItems) - 1 : left > 0 ? (1u << left) - 1 : 0;
+    starts = (f >> 8) & mine;
+    keep = ~(gone >> 8) & mine;
+}
+
+__device__ inline u32 block_scan(u32 v, u32* s_wave, u32* total) {      // exclusive
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    u32 at = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const u32 u = __shfl_up(at, o);
+        if (lane >= o) at += u;
+    }
+    if (lane == 63) s_wave[wave] = at;
+    __syncthreads();
+    u32 before = 0, all = 0;
+    for (int w = 0; w < kThreads / 64; ++w) {
+        if (w < wave) before += s_wave[w];
+        all += s_wave[w];
+    }
+    __syncthreads();
+    *total = all;
+    return before + at - v;
+}
+
+// records that stay in the blocks before this one, from the blocks' sums, or their scan where there are many
+constexpr u32 kScanFrom = 4096;
+__device__ __forceinline__ u32 blocks_before(const u32* __restrict__ bsum, u32* s_wave) {
+    if (gridDim.x > kScanFrom) return bsum[blockIdx.x];
+    u32 n = 0, all;
+#pragma unroll 4
+    for (u32 b = threadIdx.x; b < blockIdx.x; b += kThreads) n += bsum[b];
+    block_scan(n, s_wave, &all);
+    return all;
+}
+__global__ __launch_bounds__(kThreads) void k_scan(u32* bsum, u32 n) {      // in place, exclusive, one workgroup
+    __shared__ u32 s_wave[kThreads / 64];
+    u32 carry = 0;
+    for (u32 b0 = 0; b0 < n; b0 += kThreads * 4) {
+        u32 v[4], own = 0, all;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const u32 b = b0 + threadIdx.x * 4 + u;
+            v[u] = b < n ? bsum[b] : 0;
+            own += v[u];
+        }
+        u32 at = carry + block_scan(own, s_wave, &all);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const u32 b = b0 + threadIdx.x * 4 + u;
+            if (b < n) bsum[b] = at;
+            at += v[u];
+        }
+        carry += all;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_sums(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, const u32* __restrict__ sel,
+                                                   const u64* __restrict__ len, const State* __restrict__ st, u32* bsum) {
+    __shared__ BlockTokens s;
+    __shared__ u32 s_wave[kThreads / 64];
+    if (st->done) return;
+    u32 keep, starts, sum;
+    block_keep(s, tok, last, sel, len[0], running(st), keep, starts);
+    block_scan(__popc(keep), s_wave, &sum);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
+}
+// len[0] = the corpus' length before the merge, len[1] after it
+__global__ __launch_bounds__(kThreads) void k_apply(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, const u32* __restrict__ sel,
+                                                    u64* len, const State* __restrict__ st, const u32* __restrict__ bsum,
+                                                    int32_t* __restrict__ out, uint8_t* __restrict__ last_out) {
+    __shared__ BlockTokens s;
+    __shared__ u32 s_wave[kThreads / 64];
+    if (st->done) return;
+    const Gram g = running(st);
+    u32 keep, starts, sum;
+    block_keep(s, tok, last, sel, len[0], g, keep, starts);
+    const u32 base = blocks_before(bsum, s_wave);
+    u32 to = base + block_scan(__popc(keep), s_wave, &sum);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) len[1] = base + sum;
+    const u64 first = (u64)blockIdx.x * kBlock + kItems * threadIdx.x;
+    for (u32 k = keep; k != 0; k &= k - 1, ++to) {
+        const int e = __ffs((int)k) - 1;
+        const bool merged = (starts >> e) & 1;
+        out[to] = merged ? g.new_id : s.tok[8 + kItems * threadIdx.x + e];
+        last_out[to] = last[first + e + (merged ? g.n - 1 : 0)];
+    }
+}
+
+// where the outputs end, in order
+__device__ __forceinline__ u32 ends_here(const uint8_t* __restrict__ last, u64 T) {
+    const u64 first = (u64)blockIdx.x * kBlock + kItems * threadIdx.x;
+    u32 f = 0;
+#pragma unroll
+    for (int e = 0; e < kItems; ++e) f |= first + e < T && last[first + e] ? 1u << e : 0;
+    return f;
+}
+__global__ __launch_bounds__(kThreads) void k_end_sums(const uint8_t* __restrict__ last, u64 T, u32* bsum) {
+    __shared__ u32 s_wave[kThreads / 64];
+    u32 sum;
+    block_scan(__popc(ends_here(last, T)), s_wave, &sum);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
+}
+__global__ __launch_bounds__(kThreads) void k_ends(const uint8_t* __restrict__ last, u64 T, const u32* __restrict__ bsum, u32* ends) {
+    __shared__ u32 s_wave[kThreads / 64];
+    u32 sum;
+    const u32 here = ends_here(last, T);
+    u32 to = blocks_before(bsum, s_wave) + block_scan(__popc(here), s_wave, &sum);
+    for (u32 k = here; k != 0; k &= k - 1) ends[to++] = blockIdx.x * kBlock + kItems * threadIdx.x + __ffs((int)k);
+}
+
+struct Arena : TascScratch {
+    size_t used = 0;
+    size_t carve(size_t bytes) { const size_t at = used; used += (bytes + 255) / 256 * 256; return at; }
 };
 }  // namespace
 
@@ -244,112 +297,98 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     TASC_REQUIRE(T0 == 0 || (tokens && out_tokens), "tok_enrich: null tokens");
     hipStream_t st = (hipStream_t)stream;
 
-    Bufs bufs;
-    int32_t *cur, *nxt, *val;
-    unsigned char *start, *mark, *sel, *keep;
-    u32 *pos, *bsum;
-    int64_t *d_off, *d_off2;
-    MergeCand *cands, *best;
-    const u32 scan_blocks = (u32)((T0 + kScanBlock) / kScanBlock);          // covers positions 0..T
-    const int cand_blocks = 512;
-    TOK_TRY(bufs.get(&cur, T0)); TOK_TRY(bufs.get(&nxt, T0)); TOK_TRY(bufs.get(&val, T0));
-    TOK_TRY(bufs.get(&start, T0 + TASC_MAX_ORDER)); TOK_TRY(bufs.get(&mark, T0)); TOK_TRY(bufs.get(&sel, T0)); TOK_TRY(bufs.get(&keep, T0));
-    TOK_TRY(bufs.get(&pos, T0 + 1)); TOK_TRY(bufs.get(&bsum, scan_blocks));
-    TOK_TRY(bufs.get(&d_off, (size_t)n_docs + 1)); TOK_TRY(bufs.get(&d_off2, (size_t)n_docs + 1));
-    TOK_TRY(bufs.get(&cands, (size_t)cand_blocks * (TASC_MAX_ORDER + 1))); TOK_TRY(bufs.get(&best, 1));
-    auto windows_of = [&](const std::vector<int64_t>& o, int n) {
-        u64 w = 0;
-        for (int64_t d = 0; d < n_docs; ++d) w += (u64)std::max<int64_t>(0, o[d + 1] - o[d] - n + 1);
-        return w;
-    };
-    if (T0) TASC_HIP(hipMemcpyAsync(cur, tokens, T0 * sizeof(int32_t), where == TASC_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
-    std::vector<int64_t> offs(doc_offsets, doc_offsets + n_docs + 1);
-    TASC_HIP(hipMemcpyAsync(d_off, offs.data(), (size_t)(n_docs + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+    // Nothing of the device is looked at before the first kBatch merges are on their way, a token outside the vocabulary included.
+    u64 windows = 0;                                         // of order 2, the most of any
+    for (int64_t d = 0; d < n_docs; ++d) windows += (u64)std::max<int64_t>(0, doc_offsets[d + 1] - doc_offsets[d] - 1);
+    const int orders = n_max - 1;
+    const TascCountPlan plan = tasc_count_plan(T0, windows, n_max * bits > 64);
+    const bool run = budget > 0 && T0 > 0;
+    Arena ar;
+    const size_t at_state = ar.carve(sizeof(State)), at_counters = ar.carve(8 * sizeof(u64)), at_len = ar.carve(((size_t)budget + 1) * sizeof(u64));
+    const size_t at_sel = ar.carve(T0 * sizeof(u32)), zeroed = ar.used;
+    const size_t at_tok[2] = {ar.carve(T0 * sizeof(int32_t)), ar.carve(T0 * sizeof(int32_t))}, at_last[2] = {ar.carve(T0), ar.carve(T0)};
+    const size_t at_off = ar.carve(((size_t)n_docs + 1) * sizeof(int64_t)), at_ends = ar.carve((size_t)n_docs * sizeof(u32));
+    const size_t at_bsum = ar.carve((T0 + kBlock - 1) / kBlock * sizeof(u32)), at_merges = ar.carve((size_t)budget * sizeof(Merge));
+    const size_t at_best = ar.carve(run ? (size_t)orders * plan.parts * sizeof(TascGram) : 0);
+    const size_t at_rec = ar.carve(run ? orders * plan.rec_bytes : 0), at_roff = ar.carve(run ? orders * plan.offs_bytes : 0);
+    TOK_TRY(ar.get(ar.used));
+    State* const state = (State*)(ar.p + at_state);
+    u64 *const counters = (u64*)(ar.p + at_counters), *const len = (u64*)(ar.p + at_len);
+    int32_t* const tok[2] = {(int32_t*)(ar.p + at_tok[0]), (int32_t*)(ar.p + at_tok[1])};
+    uint8_t *const last[2] = {(uint8_t*)(ar.p + at_last[0]), (uint8_t*)(ar.p + at_last[1])};
+    int64_t* const d_off = (int64_t*)(ar.p + at_off);
+    u32 *const bsum = (u32*)(ar.p + at_bsum), *const sel = (u32*)(ar.p + at_sel), *const ends = (u32*)(ar.p + at_ends);
+    Merge* const d_merges = (Merge*)(ar.p + at_merges);
+    TascGram* const best = (TascGram*)(ar.p + at_best);
+    const TascCountBufs bufs{(u64*)(ar.p + at_rec), (uint16_t*)(ar.p + at_roff)};
 
-    // the counting table is kept across the merges (the corpus only shrinks)
-    u64 *slots, *counters;                                   // counters: [0], [1] the counting stage's; [2] token flag; [8 + n] largest count of order n
-    unsigned char* rem;
-    TOK_TRY(bufs.get(&slots, budget > 0 ? tasc_count_cap(windows_of(offs, 2)) : 1)); TOK_TRY(bufs.get(&counters, 8 + TASC_MAX_ORDER + 1));
-    TOK_TRY(bufs.get(&rem, T0));
-    u64 T = T0;
-    corpus_len[0] = (int64_t)T;
-    int done = 0;
-    for (; done < budget; ++done) {
-        if (T == 0) break;
-        TASC_HIP(hipMemsetAsync(counters, 0, (8 + TASC_MAX_ORDER + 1) * sizeof(u64), st));
-        if (done == 0) {
-            k_check_tokens<<<dim3(1024), dim3(kThreads), 0, st>>>(cur, T, vocab_all, (u32*)&counters[2]);
-            TASC_LAUNCH_CHECK();
-            u64 bad = 0;
-            TASC_HIP(hipMemcpyAsync(&bad, &counters[2], sizeof bad, hipMemcpyDeviceToHost, st));
-            TASC_HIP(hipStreamSynchronize(st));
-            TASC_REQUIRE(bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
-        }
-        TOK_TRY(tasc_mark_tails(d_off, n_docs, n_max, T, rem, st));
-        int n_cand = 0;
-        for (int n = 2; n <= n_max; ++n) {
-            const u64 windows = windows_of(offs, n);
-            if (windows == 0) continue;
-            const u64 cap = tasc_count_cap(windows);
-            TOK_TRY(tasc_count_order(cur, rem, T, n, bits, slots, cap, counters, st));
-            u32* const top = (u32*)&counters[8 + n];
-            k_max_count<<<dim3(cand_blocks), dim3(kThreads), 0, st>>>(slots, cap, top);
-            TASC_LAUNCH_CHECK();
-            k_best_in_table<<<dim3(cand_blocks), dim3(kThreads), 0, st>>>(slots, cap, cur, top, n, bits, cands + n_cand);
-            TASC_LAUNCH_CHECK();
-            n_cand += cand_blocks;
-        }
-        if (n_cand == 0) break;                                  // no n-gram left in the corpus
-        k_best_final<<<dim3(1), dim3(kThreads), 0, st>>>(cands, n_cand, bits, best);
-        TASC_LAUNCH_CHECK();
-        MergeCand h;
-        TASC_HIP(hipMemcpyAsync(&h, best, sizeof h, hipMemcpyDeviceToHost, st));
-        TASC_HIP(hipStreamSynchronize(st));
-        if (h.reward == 0) break;
-        Gram g{};
-        const int n = (int)h.n;
-        int32_t* row = merges + (size_t)done * (1 + TASC_MAX_ORDER);
-        row[0] = n;
-        for (int j = 0; j < TASC_MAX_ORDER; ++j) {
-            g.t[j] = j < n ? (int32_t)tasc_key_get(h.lo, h.hi, j, bits) : 0;
-            row[1 + j] = j < n ? g.t[j] : -1;
-        }
-        merge_freq[done] = (int64_t)h.freq;
-        const int32_t new_id = vocab + done;
-
-        // re-tokenise
-        const unsigned gridT = (unsigned)((T + kThreads - 1) / kThreads);
-        TASC_HIP(hipMemsetAsync(start, 0, T + TASC_MAX_ORDER, st));
-        TASC_HIP(hipMemsetAsync(sel, 0, T, st));
-        if (n_docs) {
-            k_doc_starts<<<dim3((unsigned)((n_docs + kThreads - 1) / kThreads)), dim3(kThreads), 0, st>>>(d_off, n_docs, start);
-            TASC_LAUNCH_CHECK();
-        }
-        k_mark<<<dim3(gridT), dim3(kThreads), 0, st>>>(cur, start, T, g, n, mark);
-        TASC_LAUNCH_CHECK();
-        k_select<<<dim3(gridT), dim3(kThreads), 0, st>>>(mark, T, n, sel);
-        TASC_LAUNCH_CHECK();
-        k_keep<<<dim3(gridT), dim3(kThreads), 0, st>>>(cur, sel, T, n, new_id, keep, val);
-        TASC_LAUNCH_CHECK();
-        const u32 nb = (u32)((T + kScanBlock) / kScanBlock);      // blocks covering positions 0..T
-        k_scan_sums<<<dim3(nb), dim3(kThreads), 0, st>>>(keep, T, bsum);
-        TASC_LAUNCH_CHECK();
-        k_scan_offsets<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, nb);
-        TASC_LAUNCH_CHECK();
-        k_scan_apply<<<dim3(nb), dim3(kThreads), 0, st>>>(keep, val, T, bsum, pos, nxt);
-        TASC_LAUNCH_CHECK();
-        k_new_offsets<<<dim3((unsigned)((n_docs + 1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st>>>(d_off, n_docs, pos, d_off2);
-        TASC_LAUNCH_CHECK();
-        TASC_HIP(hipMemcpyAsync(offs.data(), d_off2, (size_t)(n_docs + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        TASC_HIP(hipStreamSynchronize(st));
-        std::swap(cur, nxt);
-        std::swap(d_off, d_off2);
-        T = (u64)offs[n_docs];
-        corpus_len[done + 1] = (int64_t)T;
+    TASC_HIP(hipMemsetAsync(ar.p, 0, zeroed, st));
+    TASC_HIP(hipMemcpyAsync(len, &T0, sizeof T0, hipMemcpyHostToDevice, st));
+    if (T0) {
+        TASC_HIP(hipMemcpyAsync(tok[0], tokens, T0 * sizeof(int32_t), where == TASC_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
+        TASC_HIP(hipMemcpyAsync(d_off, doc_offsets, (size_t)(n_docs + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+        TOK_TRY(tasc_mark_ends(d_off, n_docs, T0, last[0], st));
     }
-    *n_merges = done;
-    if (T) TASC_HIP(hipMemcpyAsync(out_tokens, cur, T * sizeof(int32_t), where == TASC_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, st));
+    if (run) {
+        k_check_tokens<<<dim3(1024), dim3(kThreads), 0, st>>>(tok[0], T0, vocab_all, state);
+        TASC_LAUNCH_CHECK();
+    }
+    State h;
+    memset(&h, 0, sizeof h);
+    std::vector<u64> lens((size_t)budget + 1, 0);
+    lens[0] = T0;
+    u64 T = T0;                                              // the corpus is no longer than this
+    for (int done = 0; run && done < budget && !h.done; ) {
+        const int end = std::min(budget, done + kBatch), begin = done;
+        TascCountPlan p = plan;                              // (the records' strides are those of the whole corpus)
+        p.chunks = (u32)((T + p.chunk - 1) / p.chunk);
+        const dim3 grid1((unsigned)std::min<u64>((T + kThreads - 1) / kThreads, kSelectBlocks)), grid2((unsigned)((T + kBlock - 1) / kBlock));
+        for (; done < end; ++done) {
+            int32_t* const cur = tok[done & 1];
+            const uint8_t* const cur_last = last[done & 1];
+            TOK_TRY(tasc_count_partition(p, cur, cur_last, T, len + done, 2, orders, bits, bufs, st));
+            TOK_TRY(tasc_count_best(p, len + done, 2, orders, bits, bufs, counters, best, st));
+            k_pick<<<dim3(1), dim3(kPickThreads), 0, st>>>(best, (u32)orders * p.parts, bits, vocab, counters, state, d_merges);
+            k_select<<<grid1, dim3(kThreads), 0, st>>>(cur, cur_last, len + done, state, sel);
+            k_sums<<<grid2, dim3(kThreads), 0, st>>>(cur, cur_last, sel, len + done, state, bsum);
+            if (grid2.x > kScanFrom) k_scan<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, grid2.x);
+            k_apply<<<grid2, dim3(kThreads), 0, st>>>(cur, cur_last, sel, len + done, state, bsum, tok[(done + 1) & 1], last[(done + 1) & 1]);
+            TASC_LAUNCH_CHECK();
+        }
+        TASC_HIP(hipMemcpyAsync(&h, state, sizeof h, hipMemcpyDeviceToHost, st));
+        TASC_HIP(hipMemcpyAsync(&lens[begin + 1], len + begin + 1, (size_t)(end - begin) * sizeof(u64), hipMemcpyDeviceToHost, st));
+        TASC_HIP(hipStreamSynchronize(st));
+        TASC_REQUIRE(h.bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
+        if (h.failed) {
+            tasc_set_error("tok_enrich: too many n-grams of one hash");
+            return TASC_ESTATE;
+        }
+        T = lens[h.merges];
+    }
+    const int n_done = (int)h.merges;
+    T = lens[n_done];
+    std::vector<Merge> rows(n_done);
+    std::vector<u32> h_ends(n_docs);
+    if (n_done) TASC_HIP(hipMemcpyAsync(rows.data(), d_merges, rows.size() * sizeof(Merge), hipMemcpyDeviceToHost, st));
+    if (T) {
+        const dim3 grid2((unsigned)((T + kBlock - 1) / kBlock));
+        k_end_sums<<<grid2, dim3(kThreads), 0, st>>>(last[n_done & 1], T, bsum);
+        if (grid2.x > kScanFrom) k_scan<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, grid2.x);
+        k_ends<<<grid2, dim3(kThreads), 0, st>>>(last[n_done & 1], T, bsum, ends);
+        TASC_LAUNCH_CHECK();
+        TASC_HIP(hipMemcpyAsync(h_ends.data(), ends, h_ends.size() * sizeof(u32), hipMemcpyDeviceToHost, st));
+        TASC_HIP(hipMemcpyAsync(out_tokens, tok[n_done & 1], T * sizeof(int32_t), where == TASC_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, st));
+    }
     TASC_HIP(hipStreamSynchronize(st));
-    for (int64_t d = 0; d <= n_docs; ++d) out_offsets[d] = offs[d];
+    ar.keep();
+    *n_merges = n_done;
+    for (int i = 0; i < n_done; ++i) {
+        memcpy(merges + (size_t)i * (1 + TASC_MAX_ORDER), rows[i].row, sizeof rows[i].row);
+        merge_freq[i] = (int64_t)rows[i].freq;
+    }
+    for (int i = 0; i <= n_done; ++i) corpus_len[i] = (int64_t)lens[i];
+    out_offsets[0] = 0;
+    for (int64_t d = 0, e = 0; d < n_docs; ++d)              // (an output that had tokens keeps at least one)
+        out_offsets[d + 1] = doc_offsets[d] < doc_offsets[d + 1] ? (int64_t)h_ends[e++] : out_offsets[d];
     return TASC_OK;
 }
