@@ -83,70 +83,6 @@ __global__ void k_commit_prefill(int B, int end, int max_len, int max_new, const
     }
 }
 
-__global__ void k_prepare_verify(int B, int k, int max_len, int vocab, const int32_t* __restrict__ tokens,
-                                 const int32_t* __restrict__ n_tok, const int32_t* __restrict__ cached,
-                                 const int32_t* __restrict__ drafts, int32_t* row_tok, int32_t* row_seq, int32_t* row0, int32_t* n_rows,
-                                 int32_t* pos0, int32_t* sel_rows, int32_t* sel_tok) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nq = k + 1;
-    if (idx >= B * nq) return;
-    const int b = idx / nq, i = idx % nq;
-    int t;
-    if (i == 0) {
-        t = tokens[(size_t)b * max_len + n_tok[b] - 1];
-        n_rows[b] = nq;
-        row0[b] = idx;
-        pos0[b] = cached[b];
-    } else {
-        t = drafts[b * k + i - 1];
-        t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);   // a draft outside the vocabulary can only be rejected
-    }
-    row_tok[idx] = t;
-    row_seq[idx] = b;
-    sel_rows[idx] = idx;
-    sel_tok[idx] = t;
-}
-
-// Greedy acceptance (one thread per sequence): longest prefix of the drafts equal to the target's
-// argmax, plus the bonus token; rollback = the cached length only grows by the accepted rows.
-__global__ void k_accept(int B, int k, int max_len, const int32_t* __restrict__ drafts,
-                         const int32_t* __restrict__ amax, int32_t* tokens, int32_t* n_tok, int32_t* cached, int32_t* n_emit,
-                         u64* counters, int32_t* accept_len, int32_t* emitted, int32_t* trace_step) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const int nq = k + 1;
-    const int N = n_tok[b];
-    const int max_new = (int)counters[TASC_CTR_MAX_NEW];
-    const bool frozen = n_emit[b] >= max_new;
-    int m = 0;
-    if (!frozen) {
-        while (m < k && drafts[b * k + m] == amax[b * nq + m]) ++m;
-        int32_t* seq = tokens + (size_t)b * max_len;
-        for (int i = 0; i < m; ++i) seq[N + i] = drafts[b * k + i];
-        seq[N + m] = amax[b * nq + m];
-        n_tok[b] = N + m + 1;
-        cached[b] += m + 1;
-        const int e = n_emit[b] + m + 1;
-        n_emit[b] = e;
-        if (e >= max_new) atomicAdd(&counters[0], 1ull);
-        atomicAdd(&counters[3], (u64)m);
-        atomicAdd(&counters[4], (u64)k);
-        atomicAdd(&counters[8 + m], 1ull);
-    }
-    if (accept_len) accept_len[b] = m;
-    if (emitted)
-        for (int i = 0; i < nq; ++i)
-            emitted[b * nq + i] = frozen ? -1 : (i < m ? drafts[b * k + i] : (i == m ? amax[b * nq + m] : -1));
-    if (trace_step) {
-        int32_t* t = trace_step + (size_t)b * (2 * k + 3);
-        t[0] = N;
-        for (int i = 0; i < k; ++i) t[1 + i] = drafts[b * k + i];
-        for (int i = 0; i < nq; ++i) t[1 + k + i] = amax[b * nq + i];
-        t[2 * k + 2] = frozen ? -1 : m;
-    }
-    if (b == 0) atomicAdd(&counters[2], 1ull);
-}
-
 // counters[1] = the fewest tokens any sequence has generated (valid after the kernel; reset before)
 __global__ void k_min_emit(int B, const int32_t* __restrict__ n_emit, u64* counters) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
@@ -633,25 +569,12 @@ extern "C" tasc_status tasc_session_prefill(const tasc_model* m, tasc_session* s
 }
 
 namespace {
-// the launches of one verify step on `st`
+// the launches of one verify step on `st`: rows, forward, acceptance
 tasc_status verify_step_enqueue(const tasc_model* m, tasc_session* s, const int32_t* drafts, int32_t k, int32_t* accept_len,
                                 int32_t* emitted, float* logits_dbg, int32_t* trace_step, hipStream_t st) {
     const int B = s->batch, nq = k + 1;
-    TascSessDev& d = s->d;
-    k_prepare_verify<<<dim3((B * nq + 255) / 256), dim3(256), 0, st>>>(B, k, s->max_len, m->desc.vocab, d.tokens, d.n_tok, d.cached,
-                                                                       drafts, d.row_tok, d.row_seq, d.row0, d.n_rows, d.pos0, d.sel_rows,
-                                                                       d.sel_tok);
-    TASC_LAUNCH_CHECK();
-    TascVerifyTail tail{k, drafts, accept_len, emitted, trace_step, false};
-    tasc_status rc = tasc_forward_rows(m, s, nq, B * nq, B * nq, logits_dbg, &tail, st);
-    if (rc != TASC_OK) return rc;
-    if (!tail.done) {
-        TascProfScope ps(TASC_KC_ACCEPT, st);
-        k_accept<<<dim3((B + 63) / 64), dim3(64), 0, st>>>(B, k, s->max_len, drafts, d.amax, d.tokens, d.n_tok,
-                                                           d.cached, d.n_emit, d.counters, accept_len, emitted, trace_step);
-    }
-    TASC_LAUNCH_CHECK();
-    return TASC_OK;
+    const TascVerifyTail tail{k, drafts, accept_len, emitted, trace_step};
+    return tasc_forward_rows(m, s, nq, B * nq, B * nq, logits_dbg, &tail, st);
 }
 
 // A verify step outside the persistent kernels is a few dozen to a few hundred launches whose arguments never change from step to step (row

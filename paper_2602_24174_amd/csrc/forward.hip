@@ -87,10 +87,39 @@ namespace {
 
 #define PROF(cls) TascProfScope _ps(cls, st)
 
+StepRows step_rows(const tasc_model* m, const tasc_session* s, const TascVerifyTail* tail) {
+    const TascSessDev& d = s->d;
+    if (!tail) return StepRows{};
+    return StepRows{d.tokens, d.n_tok, d.cached, tail->drafts, s->max_len, tail->k, m->desc.vocab, d.row_tok, d.row_seq, d.row0, d.n_rows, d.pos0,
+                    d.sel_rows, d.sel_tok};
+}
+tasc_status prepare_verify(const tasc_model* m, const tasc_session* s, const TascVerifyTail* tail, hipStream_t st) {
+    if (!tail) return TASC_OK;
+    const int rows = s->batch * (tail->k + 1);
+    k_prepare_verify<<<dim3((rows + 255) / 256), dim3(256), 0, st>>>(step_rows(m, s, tail), rows);
+    TASC_LAUNCH_CHECK();
+    return TASC_OK;
+}
+// the LM head's partial maxima -> argmax of the selected rows (a prompt forward), or the acceptance of a verify step
+tasc_status finish_rows(const tasc_session* s, int n_sel, int n_parts, const float* part_val, const int32_t* part_idx, const TascVerifyTail* tail,
+                        hipStream_t st) {
+    const TascSessDev& d = s->d;
+    PROF(TASC_KC_ACCEPT);
+    if (tail)
+        k_argmax_accept<<<dim3(s->batch), dim3(ACCEPT_THREADS(tail->k + 1)), 0, st>>>(
+            AcceptArgs{part_val, part_idx, n_parts, tail->k, s->max_len, tail->drafts, d.tokens, d.n_tok, d.cached, d.n_emit, d.counters,
+                       tail->accept_len, tail->emitted, tail->trace_step});
+    else k_argmax_reduce<<<dim3(n_sel), dim3(64), 0, st>>>(part_val, part_idx, n_parts, d.amax);
+    TASC_LAUNCH_CHECK();
+    return TASC_OK;
+}
+
 template <typename T>
-tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M, int n_sel, float* logits_dbg, hipStream_t st) {
+tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M, int n_sel, float* logits_dbg, const TascVerifyTail* tail, hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
+    tasc_status rc = prepare_verify(m, s, tail, st);
+    if (rc != TASC_OK) return rc;
     const int D = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
     const int nqkv = (H + 2 * Hkv) * hd, nqo = H * hd;
     KvGeom gm{H, Hkv, hd, s->max_blocks, s->page_elems, d.row_seq, d.row0, 0};
@@ -155,11 +184,8 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
                                                                       c.vocab, D, bias, d.part_val, d.part_idx, s->n_strips,
                                                                       logits_dbg);
         }
-        {
-            PROF(TASC_KC_ACCEPT);
-            k_argmax_reduce<<<dim3(n_sel), dim3(64), 0, st>>>(d.part_val, d.part_idx, s->n_strips, d.amax);
-        }
         TASC_LAUNCH_CHECK();
+        return finish_rows(s, n_sel, s->n_strips, d.part_val, d.part_idx, tail, st);
     }
     return TASC_OK;
 }
@@ -309,7 +335,8 @@ int tiled_auto_chains(const tasc_model_desc& c, int batch, int nq) {
     return 1;
 }
 
-tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_all, int n_sel, float* logits_dbg, bool decode, hipStream_t st) {
+tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_all, int n_sel, float* logits_dbg, const TascVerifyTail* tail, hipStream_t st) {
+    const bool decode = tail != nullptr;
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
     int cus = 0;
@@ -366,8 +393,10 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         PROF(TASC_KC_PREPARE);
         if (D <= RRN_MAX_D) {
             k_embed_norm<<<dim3(M_all + bias_wgs), dim3(256), 0, st>>>((const BF16*)m->embed, d.row_tok, m->layers[0].g1, M_all, D, c.rms_eps,
-                                                                      d.x, (BF16*)d.h, bc);
+                                                                      d.x, (BF16*)d.h, bc, step_rows(m, s, tail));
         } else {
+            const tasc_status rc = prepare_verify(m, s, tail, st);
+            if (rc != TASC_OK) return rc;
             k_embed<BF16><<<dim3(M_all), dim3(64), 0, st>>>((const BF16*)m->embed, d.row_tok, D, d.x);
             if (bias_wgs) k_bias_ptr<<<dim3(bias_wgs), dim3(256), 0, st>>>(bc);
         }
@@ -527,11 +556,8 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
             PROF(TASC_KC_LMHEAD);
             launch_gemm<TEPI_LMHEAD>((const BF16*)d.h, m->lm_head, n_sel, c.vocab, D, nullptr, nullptr, lm, 1, st, cus);
         }
-        {
-            PROF(TASC_KC_ACCEPT);
-            k_argmax_reduce<<<dim3(n_sel), dim3(64), 0, st>>>(d.part_val, d.part_idx, s->n_strips, d.amax);
-        }
         TASC_LAUNCH_CHECK();
+        return finish_rows(s, n_sel, s->n_strips, d.part_val, d.part_idx, tail, st);
     }
     return TASC_OK;
 }
@@ -545,10 +571,12 @@ bool small_path_fits(const tasc_model* m, int batch, int nq, int max_blocks) {
 }
 
 
-tasc_status forward_small(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, TascVerifyTail* tail,
+tasc_status forward_small(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, const TascVerifyTail* tail,
                           hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
+    tasc_status prc = prepare_verify(m, s, tail, st);
+    if (prc != TASC_OK) return prc;
     DevState& ds = dev_state();
     if (std::lock_guard<std::mutex> lock(g_dev_mu); !ds.small_ready) {
         int dev = 0, cus = 0;
@@ -643,7 +671,6 @@ tasc_status forward_small(const tasc_model* m, tasc_session* s, int nq, int n_se
         }
     }
     TASC_LAUNCH_CHECK();
-    if (tail) tail->done = n_sel > 0;
     return TASC_OK;
 }
 
@@ -700,10 +727,12 @@ tasc_status pipe_attr() {
     return TASC_OK;
 }
 
-tasc_status forward_pipe(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, TascVerifyTail* tail, int grid,
+tasc_status forward_pipe(const tasc_model* m, tasc_session* s, int nq, int n_sel, float* logits_dbg, const TascVerifyTail* tail, int grid,
                          hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
+    tasc_status prc = prepare_verify(m, s, tail, st);
+    if (prc != TASC_OK) return prc;
     if (std::lock_guard<std::mutex> lock(g_dev_mu); !dev_state().pipe_ready) {
         tasc_status rc;
         if ((rc = pipe_attr<1, 3>()) != TASC_OK || (rc = pipe_attr<2, 3>()) != TASC_OK || (rc = pipe_attr<4, 3>()) != TASC_OK ||
@@ -781,7 +810,6 @@ tasc_status forward_pipe(const tasc_model* m, tasc_session* s, int nq, int n_sel
     }
     TASC_LAUNCH_CHECK();
     s->ll_copy = 1 - s->ll_copy;
-    if (tail) tail->done = n_sel > 0;
     return TASC_OK;
 }
 
@@ -861,8 +889,7 @@ bool tasc_forward_is_tiled(const tasc_model* m, const tasc_session* s, int32_t n
 }
 
 tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, int32_t n_rows, int32_t n_sel, float* logits_dbg,
-                              TascVerifyTail* tail, hipStream_t st) {
-    if (tail) tail->done = false;
+                              const TascVerifyTail* tail, hipStream_t st) {
     // The kernel family of a decode step (nq <= 16 rows per sequence) is a property of the session, not of the
     // call's row count, so that a greedy step and a speculative step of one session use the same kernels and
     // reduce every row in the same order.  Prompt chunks of sessions with max_rows > 16 never
@@ -887,7 +914,7 @@ tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, 
         }
         return forward_small(m, s, nq, n_sel, logits_dbg, tail, st);
     }
-    if (g_tasc_config.tiled_path != 0 && tasc_tiled_fits(m->desc)) return forward_tiled(m, s, nq, n_rows, n_sel, logits_dbg, tail != nullptr, st);
-    if (m->desc.dtype == TASC_F32) return forward_generic<float>(m, s, nq, n_rows, n_sel, logits_dbg, st);
-    return forward_generic<BF16>(m, s, nq, n_rows, n_sel, logits_dbg, st);
+    if (g_tasc_config.tiled_path != 0 && tasc_tiled_fits(m->desc)) return forward_tiled(m, s, nq, n_rows, n_sel, logits_dbg, tail, st);
+    if (m->desc.dtype == TASC_F32) return forward_generic<float>(m, s, nq, n_rows, n_sel, logits_dbg, tail, st);
+    return forward_generic<BF16>(m, s, nq, n_rows, n_sel, logits_dbg, tail, st);
 }

@@ -40,6 +40,39 @@ __device__ inline float wave_max(float v) {
     return v;
 }
 
+// ---------------------------------------------------------------- rows of a verify step
+// Row idx = (sequence idx / (k + 1), i = idx % (k + 1)): the pending token (i = 0) or draft i - 1.
+struct StepRows {
+    const int32_t* tokens;    // [B, max_len]; null: not a verify step, the rows have been made already
+    const int32_t* n_tok;
+    const int32_t* cached;
+    const int32_t* drafts;    // [B, k]
+    int32_t max_len, k, vocab;
+    int32_t *row_tok, *row_seq, *row0, *n_rows, *pos0, *sel_rows, *sel_tok;
+};
+__device__ __forceinline__ int step_token(const StepRows& a, int idx) {
+    const int nq = a.k + 1, b = idx / nq, i = idx % nq;
+    if (i == 0) return a.tokens[(size_t)b * a.max_len + a.n_tok[b] - 1];
+    const int t = a.drafts[b * a.k + i - 1];
+    return t < 0 ? 0 : (t >= a.vocab ? a.vocab - 1 : t);     // a draft outside the vocabulary can only be rejected
+}
+__device__ __forceinline__ void step_row(const StepRows& a, int idx, int t) {
+    const int nq = a.k + 1, b = idx / nq;
+    if (idx % nq == 0) {
+        a.n_rows[b] = nq;
+        a.row0[b] = idx;
+        a.pos0[b] = a.cached[b];
+    }
+    a.row_tok[idx] = t;
+    a.row_seq[idx] = b;
+    a.sel_rows[idx] = idx;
+    a.sel_tok[idx] = t;
+}
+__global__ void k_prepare_verify(StepRows a, int rows) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < rows) step_row(a, idx, step_token(a, idx));
+}
+
 // ---------------------------------------------------------------- embedding gather
 template <typename T>
 __global__ void k_embed(const T* __restrict__ E, const int32_t* __restrict__ row_tok, int d, float* __restrict__ x) {
@@ -383,13 +416,9 @@ __global__ __launch_bounds__(64 * LM_GENERIC_WAVES) void k_lmhead_generic(const 
     }
 }
 
-// amax[r] = argmax over the strips of row r (lowest index among equal values).  One wave per row, the loads of 512 strips in
-// flight at a time: a chain of round trips otherwise (576 rows of 1187 strips: 6.2 us, 11.9 with one pair of loads at a time).
-__global__ __launch_bounds__(64) void k_argmax_reduce(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
-                                                      int n_strips, int32_t* __restrict__ amax) {
-    const int r = blockIdx.x, lane = threadIdx.x;
-    const float* pv = part_val + (size_t)r * n_strips;
-    const int32_t* pi = part_idx + (size_t)r * n_strips;
+// Argmax over the strips of a row (lowest index among equal values) by one wave, the loads of 512 strips in flight at a time: a
+// chain of round trips otherwise (576 rows of 1187 strips: 6.2 us, 11.9 with one pair of loads at a time).
+__device__ __forceinline__ int32_t strips_argmax(const float* __restrict__ pv, const int32_t* __restrict__ pi, int n_strips, int lane) {
     float bv = -INFINITY;
     int32_t bi = 0x7FFFFFFF;
     for (int s0 = lane; s0 < n_strips; s0 += 512) {
@@ -410,5 +439,69 @@ __global__ __launch_bounds__(64) void k_argmax_reduce(const float* __restrict__ 
         const int32_t i = __shfl_xor(bi, o);
         if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
     }
-    if (lane == 0) amax[r] = bi == 0x7FFFFFFF ? 0 : bi;   // all-NaN row: still a valid token id
+    return bi == 0x7FFFFFFF ? 0 : bi;                     // all-NaN row: still a valid token id
+}
+// amax[r] = argmax of row r: the prompt forward's selected rows
+__global__ __launch_bounds__(64) void k_argmax_reduce(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
+                                                      int n_strips, int32_t* __restrict__ amax) {
+    const size_t r = blockIdx.x;
+    const int32_t t = strips_argmax(part_val + r * n_strips, part_idx + r * n_strips, n_strips, threadIdx.x);
+    if (threadIdx.x == 0) amax[r] = t;
+}
+
+// The end of a verify step, one workgroup per sequence: a wave per row finds its argmax, then the first wave accepts greedily:
+// the longest prefix of the drafts equal to the target's argmax, plus the bonus token; rollback = the cached length only grows by
+// the accepted rows.  Latency bounds it (two or three dependent loads); as two launches with the acceptance in one thread
+// per sequence they took 4.7 + 4.6 us.
+struct AcceptArgs {
+    const float* part_val;    // [B (k + 1), n_strips]
+    const int32_t* part_idx;
+    int32_t n_strips, k, max_len;
+    const int32_t* drafts;    // [B, k]
+    int32_t *tokens, *n_tok, *cached, *n_emit;
+    u64* counters;
+    int32_t* accept_len;      // nullable [B]
+    int32_t* emitted;         // nullable [B, k + 1]
+    int32_t* trace_step;      // nullable [B, 2 k + 3]
+};
+#define ACCEPT_THREADS(nq) (64 * (nq))       // at most 16 rows a sequence
+static_assert(TASC_MAX_K + 1 <= 16, "a wave per row");
+__global__ __launch_bounds__(1024) void k_argmax_accept(AcceptArgs a) {
+    __shared__ int32_t s_am[16];
+    const int b = blockIdx.x, nq = a.k + 1, k = a.k, lane = threadIdx.x & 63, i = threadIdx.x >> 6;
+    const int N = a.n_tok[b], emit = a.n_emit[b], cached = a.cached[b], max_new = (int)a.counters[TASC_CTR_MAX_NEW];
+    const int draft = lane < k ? a.drafts[b * k + lane] : 0;
+    const size_t r = (size_t)b * nq + i;
+    const int32_t t = strips_argmax(a.part_val + r * a.n_strips, a.part_idx + r * a.n_strips, a.n_strips, lane);
+    if (lane == 0) s_am[i] = t;
+    __syncthreads();
+    if (i != 0) return;
+    const int32_t am = lane < nq ? s_am[lane] : 0;
+    const bool frozen = emit >= max_new;
+    const u64 differ = __ballot(lane >= k || draft != am);
+    const int m = frozen ? 0 : __ffsll((unsigned long long)differ) - 1;
+    const int32_t own = lane < m ? draft : am;             // the token that lane <= m emits
+    if (!frozen && lane <= m) a.tokens[(size_t)b * a.max_len + N + lane] = own;
+    if (a.emitted && lane < nq) a.emitted[b * nq + lane] = frozen || lane > m ? -1 : own;
+    if (a.trace_step) {
+        int32_t* tr = a.trace_step + (size_t)b * (2 * k + 3);
+        if (lane < k) tr[1 + lane] = draft;
+        if (lane < nq) tr[1 + k + lane] = am;
+        if (lane == 0) {
+            tr[0] = N;
+            tr[2 * k + 2] = frozen ? -1 : m;
+        }
+    }
+    if (lane != 0) return;
+    if (a.accept_len) a.accept_len[b] = m;
+    if (!frozen) {
+        a.n_tok[b] = N + m + 1;
+        a.cached[b] = cached + m + 1;
+        a.n_emit[b] = emit + m + 1;
+        if (emit + m + 1 >= max_new) atomicAdd(&a.counters[0], 1ull);
+        atomicAdd(&a.counters[3], (u64)m);
+        atomicAdd(&a.counters[4], (u64)k);
+        atomicAdd(&a.counters[8 + m], 1ull);
+    }
+    if (b == 0) atomicAdd(&a.counters[2], 1ull);
 }

@@ -516,11 +516,11 @@ struct BiasCursors {
     int64_t* row_first;
     float* row_base;
 };
-__device__ __forceinline__ void bias_cursor(const BiasCursors& a, int idx) {
+__device__ __forceinline__ void bias_cursor(const BiasCursors& a, const StepRows& step, int idx) {
     const int per_row = a.n_strips + 1;
     if (idx >= a.n) return;
     const int r = idx / per_row, st = idx % per_row;
-    const int u = a.sel_tok[r];
+    const int u = step.tokens ? step_token(step, r) : a.sel_tok[r];
     const int64_t r0 = a.bias.rowptr[u];
     int64_t lo = r0, hi = a.bias.rowptr[u + 1];
     if (st == 0) {
@@ -534,22 +534,26 @@ __device__ __forceinline__ void bias_cursor(const BiasCursors& a, int idx) {
     }
     a.out[idx] = (int32_t)(lo - r0);
 }
-__global__ __launch_bounds__(256) void k_bias_ptr(BiasCursors a) { bias_cursor(a, blockIdx.x * 256 + threadIdx.x); }
+__global__ __launch_bounds__(256) void k_bias_ptr(BiasCursors a) { bias_cursor(a, StepRows{}, blockIdx.x * 256 + threadIdx.x); }
 
 // First launch of a forward: one workgroup per row copies the token's embedding into x and normalises it for the first layer (the
-// sums of k_rmsnorm_row), the workgroups after them fill the bias cursors of the LM head, which need nothing but the tokens.
+// sums of k_rmsnorm_row), the workgroups after them fill the bias cursors of the LM head, which need nothing but the tokens.  In a
+// verify step they look the tokens up themselves, and the rows' workgroups write down whose they are (a launch of its own: 4.5 us).
 // Latency bounds all three parts (two dependent loads, a sum, a binary search): 576 rows x 1536 with 1188 boundaries a row 10.3 us
 // side by side, 4.9 + 5.0 + 8.9 one after the other, with the lists of a corpus of 0.5 M tokens.  Longer lists make the searches deeper and their
 // lines come from memory: 29 us there with 80 M tokens, 54 us for 1280 rows with 160 M.
 // d <= RRN_MAX_D, d % 4 == 0.
-__global__ __launch_bounds__(256) void k_embed_norm(const BF16* __restrict__ E, const int32_t* __restrict__ row_tok, const float* __restrict__ g,
-                                                    int rows, int d, float eps, float* __restrict__ x, BF16* __restrict__ h, BiasCursors bc) {
+__global__ __launch_bounds__(256) void k_embed_norm(const BF16* __restrict__ E, const int32_t* row_tok, const float* __restrict__ g,
+                                                    int rows, int d, float eps, float* __restrict__ x, BF16* __restrict__ h, BiasCursors bc,
+                                                    StepRows step) {
     const int r = blockIdx.x, t = threadIdx.x;
     if (r >= rows) {
-        bias_cursor(bc, (r - rows) * 256 + t);
+        bias_cursor(bc, step, (r - rows) * 256 + t);
         return;
     }
-    const BF16* e = E + (size_t)row_tok[r] * d;
+    const int tok = step.tokens ? step_token(step, r) : row_tok[r];
+    if (step.tokens && t == 0) step_row(step, r, tok);
+    const BF16* e = E + (size_t)tok * d;
     f32x4 v[2], gg[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {

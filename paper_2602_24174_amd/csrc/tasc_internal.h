@@ -296,14 +296,13 @@ struct tasc_session {
 #define TASC_CTR_XCD_STEPS 28 // steps of the persistent kernel whose layer group used XCD-local barriers
 #define TASC_CTR_XCC 27       // XCDs the layer group of the running step found itself on (low 32 bits)
 
-// the tail of a verify step, fused into the forward when the small-batch kernel runs it
+// what makes a forward a verify step: its rows are the sequences' pending tokens and the drafts, and it ends with the acceptance
 struct TascVerifyTail {
     int32_t k;
     const int32_t* drafts;
     int32_t* accept_len;
     int32_t* emitted;
     int32_t* trace_step;
-    bool done;                // out: the forward already performed the accept
 };
 
 // library-wide options (tasc_config_set)
@@ -362,9 +361,10 @@ bool tasc_forward_is_tiled(const tasc_model* m, const tasc_session* s, int32_t n
 bool tasc_forward_is_small(const tasc_model* m, const tasc_session* s, int32_t nq);
 // the chain count forward_tiled would use
 int tasc_forward_chains(const tasc_model* m, const tasc_session* s, int32_t nq);
-// a forward of n_rows rows, at most nq of one sequence (a verify step and the persistent kernels: batch x nq)
+// A forward of n_rows rows, at most nq of one sequence (a verify step and the persistent kernels: batch x nq).  With `tail` it makes
+// its rows itself (k + 1 = nq of every sequence, all of them through the LM head) and accepts; otherwise they are there.
 tasc_status tasc_forward_rows(const tasc_model* m, tasc_session* s, int32_t nq, int32_t n_rows, int32_t n_sel,
-                              float* logits_dbg, TascVerifyTail* tail, hipStream_t st);
+                              float* logits_dbg, const TascVerifyTail* tail, hipStream_t st);
 // true if the model has the shapes the tiled kernels serve
 bool tasc_tiled_fits(const tasc_model_desc& c);
 
