@@ -118,74 +118,68 @@ template <typename T>
 tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M, int n_sel, float* logits_dbg, const TascVerifyTail* tail, hipStream_t st) {
     const tasc_model_desc& c = m->desc;
     const TascSessDev& d = s->d;
-    tasc_status rc = prepare_verify(m, s, tail, st);
-    if (rc != TASC_OK) return rc;
     const int D = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
-    const int nqkv = (H + 2 * Hkv) * hd, nqo = H * hd;
-    KvGeom gm{H, Hkv, hd, s->max_blocks, s->page_elems, d.row_seq, d.row0, 0};
+    const int pairs = (H + 2 * Hkv) * (hd / 2), nqo = H * hd;
+    const KvGeom gm{H, Hkv, hd, s->max_blocks, s->page_elems, d.row_seq, d.row0, 0};
+    const GenericRope rope{m->rope_cos, m->rope_sin, d.n_rows, d.pos0, d.block_tab, gm, c.max_pos, tail ? nq : 0};
     const float scale = 1.0f / sqrtf((float)hd);
+    const size_t att_lds = ((size_t)(ATTN_GENERIC_THREADS / 64) * hd + (size_t)ATTN_GENERIC_UNITS * (hd + 2)) * sizeof(float);
+    const unsigned chunks = (unsigned)std::min((M + 7) / 8, 64);      // chunks of rows side by side
     {
         PROF(TASC_KC_PREPARE);
-        k_embed<T><<<dim3(M), dim3(64), 0, st>>>((const T*)m->embed, d.row_tok, D, d.x);
+        k_embed<T><<<dim3(M), dim3(64), 0, st>>>((const T*)m->embed, d.row_tok, D, d.x, step_rows(m, s, tail));
     }
     TASC_LAUNCH_CHECK();
     for (int l = 0; l < c.n_layers; ++l) {
         const TascLayerW& w = m->layers[l];
         T* kv_layer = (T*)s->kv_pool + (size_t)l * s->kv_layer_stride;
         {
-            PROF(TASC_KC_NORM);
-            k_rmsnorm<T><<<dim3(M), dim3(64), 0, st>>>(d.x, w.g1, nullptr, D, c.rms_eps, (T*)d.h);
-        }
-        {
             PROF(TASC_KC_GEMM_QKV);
-            k_gemm_generic<T, EPI_STORE><<<dim3((nqkv + 3) / 4), dim3(256), 0, st>>>((const T*)d.h, (const T*)w.wqkv, M, nqkv, D,
-                                                                                  d.qkv, nullptr);
-        }
-        {
-            PROF(TASC_KC_ROPE_KV);
-            k_rope_kv<T><<<dim3(M), dim3(256), 0, st>>>(d.qkv, m->rope_cos, m->rope_sin, c.max_pos, d.n_rows, d.pos0, d.block_tab,
-                                                      gm, (T*)d.q, kv_layer);
+            k_gemm_generic<T, EPI_ROPE, true><<<dim3((pairs + 3) / 4, chunks), dim3(256), 0, st>>>(d.x, (const T*)w.wqkv, M, pairs, D, w.g1, c.rms_eps,
+                                                                                            nullptr, (T*)d.q, kv_layer, rope);
         }
         {
             PROF(TASC_KC_ATTN);
-            k_attn_generic<T><<<dim3(s->batch, H), dim3(ATTN_GENERIC_THREADS), (size_t)nq * hd * sizeof(float), st>>>(
-                (const T*)d.q, kv_layer, d.n_rows, d.pos0, d.block_tab, gm, scale, (T*)d.att);
+            k_attn_generic<T><<<dim3(s->batch, H, nq <= 16 ? 1 : (nq + 7) / 8), dim3(ATTN_GENERIC_THREADS), att_lds, st>>>(
+                (const T*)d.q, kv_layer, d.n_rows, d.pos0, d.block_tab, gm, scale, tail ? nq : 0, (T*)d.att);
         }
         {
             PROF(TASC_KC_GEMM_O);
-            k_gemm_generic<T, EPI_RESID><<<dim3((D + 3) / 4), dim3(256), 0, st>>>((const T*)d.att, (const T*)w.wo, M, D, nqo, d.x,
-                                                                              nullptr);
-        }
-        {
-            PROF(TASC_KC_NORM);
-            k_rmsnorm<T><<<dim3(M), dim3(64), 0, st>>>(d.x, w.g2, nullptr, D, c.rms_eps, (T*)d.h);
+            k_gemm_generic<T, EPI_RESID, false><<<dim3((D + 3) / 4, chunks), dim3(256), 0, st>>>(d.att, (const T*)w.wo, M, D, nqo, nullptr, 0.f, d.x, nullptr,
+                                                                                      nullptr, GenericRope{});
         }
         {
             PROF(TASC_KC_GEMM_GU);
-            k_gemm_generic<T, EPI_SWIGLU><<<dim3((F + 3) / 4), dim3(256), 0, st>>>((const T*)d.h, (const T*)w.wgu, M, F, D, nullptr,
-                                                                               (T*)d.act);
+            k_gemm_generic<T, EPI_SWIGLU, true><<<dim3((F + 3) / 4, chunks), dim3(256), 0, st>>>(d.x, (const T*)w.wgu, M, F, D, w.g2, c.rms_eps, nullptr,
+                                                                                      (T*)d.act, nullptr, GenericRope{});
         }
         {
             PROF(TASC_KC_GEMM_D);
-            k_gemm_generic<T, EPI_RESID><<<dim3((D + 3) / 4), dim3(256), 0, st>>>((const T*)d.act, (const T*)w.wd, M, D, F, d.x,
-                                                                              nullptr);
+            k_gemm_generic<T, EPI_RESID, false><<<dim3((D + 3) / 4, chunks), dim3(256), 0, st>>>(d.act, (const T*)w.wd, M, D, F, nullptr, 0.f, d.x, nullptr,
+                                                                                      nullptr, GenericRope{});
         }
         TASC_LAUNCH_CHECK();
     }
     if (n_sel > 0) {
-        {
-            PROF(TASC_KC_NORM);
-            k_rmsnorm<T><<<dim3(n_sel), dim3(64), 0, st>>>(d.x, m->gf, d.sel_rows, D, c.rms_eps, (T*)d.h);
-        }
-        BiasCsr bias{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base};
+        const BiasCsr bias{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base};
+        // Partial maxima of 16 columns where a vocabulary of few strips would leave the chip idle; they take the room of the q/k/v
+        // buffer, which these kernels do not use, so that must hold two of them per strip eighth.
+        constexpr int SPLIT = 8;
+        const bool split = s->n_strips * SPLIT * 2 <= (H + 2 * Hkv) * hd;
+        const int parts = s->n_strips * (split ? SPLIT : 1);
+        float* const pv = split ? d.qkv : d.part_val;
+        int32_t* const pi = split ? (int32_t*)(d.qkv + (size_t)n_sel * parts) : d.part_idx;
         {
             PROF(TASC_KC_LMHEAD);
-            k_lmhead_generic<T><<<dim3(s->n_strips), dim3(64 * LM_GENERIC_WAVES), 0, st>>>((const T*)d.h, (const T*)m->lm_head, d.sel_tok, n_sel,
-                                                                      c.vocab, D, bias, d.part_val, d.part_idx, s->n_strips,
-                                                                      logits_dbg);
+            if (split)
+                k_lmhead_generic<T, 4, TASC_LM_STRIP / SPLIT / 4><<<dim3(parts), dim3(64 * 5), 0, st>>>(
+                    d.x, d.sel_rows, m->gf, c.rms_eps, (const T*)m->lm_head, d.sel_tok, n_sel, c.vocab, D, bias, pv, pi, parts, logits_dbg);
+            else
+                k_lmhead_generic<T, 8, TASC_LM_STRIP / 8><<<dim3(parts), dim3(64 * 9), 0, st>>>(
+                    d.x, d.sel_rows, m->gf, c.rms_eps, (const T*)m->lm_head, d.sel_tok, n_sel, c.vocab, D, bias, pv, pi, parts, logits_dbg);
         }
         TASC_LAUNCH_CHECK();
-        return finish_rows(s, n_sel, s->n_strips, d.part_val, d.part_idx, tail, st);
+        return finish_rows(s, n_sel, parts, pv, pi, tail, st);
     }
     return TASC_OK;
 }
@@ -397,7 +391,7 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         } else {
             const tasc_status rc = prepare_verify(m, s, tail, st);
             if (rc != TASC_OK) return rc;
-            k_embed<BF16><<<dim3(M_all), dim3(64), 0, st>>>((const BF16*)m->embed, d.row_tok, D, d.x);
+            k_embed<BF16><<<dim3(M_all), dim3(64), 0, st>>>((const BF16*)m->embed, d.row_tok, D, d.x, StepRows{});
             if (bias_wgs) k_bias_ptr<<<dim3(bias_wgs), dim3(256), 0, st>>>(bc);
         }
     }

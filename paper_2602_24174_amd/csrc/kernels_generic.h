@@ -31,6 +31,15 @@ __device__ inline void load8(const BF16* __restrict__ p, float* o) {
     o[4] = bf2f(u.z & 0xFFFFu); o[5] = bf2f(u.z >> 16); o[6] = bf2f(u.w & 0xFFFFu); o[7] = bf2f(u.w >> 16);
 }
 
+__device__ inline void load4(const float* __restrict__ p, float* o) {
+    const float4 a = *reinterpret_cast<const float4*>(p);
+    o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+}
+__device__ inline void load4(const BF16* __restrict__ p, float* o) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    o[0] = bf2f(u.x & 0xFFFFu); o[1] = bf2f(u.x >> 16); o[2] = bf2f(u.y & 0xFFFFu); o[3] = bf2f(u.y >> 16);
+}
+
 __device__ inline float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
@@ -38,6 +47,21 @@ __device__ inline float wave_sum(float v) {
 __device__ inline float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
     return v;
+}
+
+// Sum over the 64 lanes with DPP row operations (a few cycles each; the ds_bpermute path of __shfl_xor costs an LDS
+// round trip per step).  The lanes are added in a fixed order, the same for every call.
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, false));   // row_half_mirror
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, false));   // row_mirror
+    // every lane now holds the sum of its row of 16; rows 0..3 are lanes 0-15, 16-31, 32-47, 48-63
+    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0));
+    const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 16));
+    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32));
+    const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 48));
+    return (r0 + r1) + (r2 + r3);
 }
 
 // ---------------------------------------------------------------- rows of a verify step
@@ -75,9 +99,10 @@ __global__ void k_prepare_verify(StepRows a, int rows) {
 
 // ---------------------------------------------------------------- embedding gather
 template <typename T>
-__global__ void k_embed(const T* __restrict__ E, const int32_t* __restrict__ row_tok, int d, float* __restrict__ x) {
-    const int r = blockIdx.x;
-    const T* e = E + (size_t)row_tok[r] * d;
+__global__ void k_embed(const T* __restrict__ E, const int32_t* row_tok, int d, float* __restrict__ x, StepRows step) {
+    const int r = blockIdx.x, t = step.tokens ? step_token(step, r) : row_tok[r];
+    if (step.tokens && threadIdx.x == 0) step_row(step, r, t);
+    const T* e = E + (size_t)t * d;
     for (int k = threadIdx.x * 8; k < d; k += blockDim.x * 8) {
         float v[8];
         load8(e + k, v);
@@ -114,64 +139,6 @@ __global__ __launch_bounds__(64) void k_rmsnorm(const float* __restrict__ x, con
     }
 }
 
-// ---------------------------------------------------------------- generic GEMM  out[M, N] = A[M, K] W[N, K]^T
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
-
-// One wave per output column (per FFN feature for EPI_SWIGLU), rows in chunks of 8.  Every lane sums
-// its own k-slices in ascending order, then a butterfly adds the 64 partial sums.
-template <typename T, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_generic(const T* __restrict__ A, const T* __restrict__ W, int M, int N, int K,
-                                                      float* __restrict__ outf, T* __restrict__ outT) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * 4 + wave;
-    if (col >= N) return;
-    const T* w0;
-    const T* w1 = nullptr;
-    if (EPI == EPI_SWIGLU) {
-        w0 = W + (size_t)((col >> 4) * 32 + (col & 15)) * K;
-        w1 = w0 + (size_t)16 * K;
-    } else {
-        w0 = W + (size_t)col * K;
-    }
-    for (int r0 = 0; r0 < M; r0 += 8) {
-        float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, acu[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int k = lane * 8; k < K; k += 512) {
-            float wv[8], uv[8];
-            load8(w0 + k, wv);
-            if (EPI == EPI_SWIGLU) load8(w1 + k, uv);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if (r0 + r < M) {
-                    float av[8];
-                    load8(A + (size_t)(r0 + r) * K + k, av);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        acc[r] = fmaf(av[e], wv[e], acc[r]);
-                        if (EPI == EPI_SWIGLU) acu[r] = fmaf(av[e], uv[e], acu[r]);
-                    }
-                }
-            }
-        }
-        float mine = 0.f, mine_u = 0.f;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            float v = wave_sum(acc[r]);
-            if (lane == r) mine = v;
-            if (EPI == EPI_SWIGLU) {
-                float u = wave_sum(acu[r]);
-                if (lane == r) mine_u = u;
-            }
-        }
-        const int row = r0 + lane;
-        if (lane < 8 && row < M) {
-            if (EPI == EPI_STORE) outf[(size_t)row * N + col] = mine;
-            if (EPI == EPI_RESID) outf[(size_t)row * N + col] += mine;
-            if (EPI == EPI_SWIGLU) outT[(size_t)row * N + col] = from_f<T>(mine / (1.0f + expf(-mine)) * mine_u);
-        }
-    }
-}
-
-// ---------------------------------------------------------------- RoPE + KV append
 // Rows of a forward: sequence b has the n_rows[b] rows row0[b] .. row0[b] + n_rows[b] - 1, row_seq[r] = the sequence of row r.
 // Rows that belong to no sequence (the persistent kernels' prompt chunks) have i >= n_rows[b].
 struct KvGeom {
@@ -184,6 +151,148 @@ struct KvGeom {
     __device__ int index(int r, int b) const { return r + first - row0[b]; }
 };
 
+// ---------------------------------------------------------------- generic GEMM  out[M, N] = A[M, K] W[N, K]^T
+// EPI_RESID: outf += A W^T.  EPI_SWIGLU: outT = silu(gate) up, a wave per feature (weight rows in blocks of 16 gate, 16 up).
+// EPI_ROPE: the fused q/k/v projection, a wave per pair of features half a head apart: q and k rotated at the row's position, q to
+// outT, new k and v rows to their cache pages (k_rope_kv's arithmetic).
+enum { EPI_RESID = 1, EPI_SWIGLU = 2, EPI_ROPE = 3 };
+
+struct GenericRope {          // EPI_ROPE only
+    const float* cosT;        // [max_pos][hd / 2]
+    const float* sinT;
+    const int32_t* n_rows;
+    const int32_t* pos0;
+    const int32_t* block_tab;
+    KvGeom gm;
+    int32_t max_pos, nq;      // nq: rows of every sequence, all active, in a verify step; 0: look them up
+};
+
+// The products of up to 8 rows (R of them, from row0 on) with one weight row, or two, by one wave: every lane sums its own k-slices in
+// ascending order, then the 64 partial sums are added in the order of wave_sum_dpp.  Lane r < 8 returns with row r's.  NORM: A is the
+// residual stream and the product is with its RMSNorm (gain g): the sum of squares is taken along with the products, of weights
+// already multiplied by the gain.
+struct RowDots { float v, u; };
+template <typename T, bool PAIR, bool NORM>
+__device__ __forceinline__ RowDots row_dots(const void* __restrict__ A_, int row0, int R, const T* __restrict__ w0, const T* __restrict__ w1, int K,
+                                            const float* __restrict__ g, float eps, int lane) {
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, acu[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ss[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 2
+    for (int k = lane * 4; k < K; k += 256) {
+        float wv[4], uv[4], gv[4];
+        load4(w0 + k, wv);
+        if (PAIR) load4(w1 + k, uv);
+        if (NORM) {
+            load4(g + k, gv);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                wv[e] *= gv[e];
+                if (PAIR) uv[e] *= gv[e];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            if (r < R) {
+                float av[4];
+                if constexpr (NORM) load4(reinterpret_cast<const float*>(A_) + (size_t)(row0 + r) * K + k, av);
+                else load4(reinterpret_cast<const T*>(A_) + (size_t)(row0 + r) * K + k, av);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[r] = fmaf(av[e], wv[e], acc[r]);
+                    if (PAIR) acu[r] = fmaf(av[e], uv[e], acu[r]);
+                    if (NORM) ss[r] = fmaf(av[e], av[e], ss[r]);
+                }
+            }
+        }
+    }
+    float v = 0.f, u = 0.f, q = 0.f;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        if (r < R) {
+            const float a = wave_sum_dpp(acc[r]), b = PAIR ? wave_sum_dpp(acu[r]) : 0.f, c = NORM ? wave_sum_dpp(ss[r]) : 0.f;
+            v = lane == r ? a : v;
+            u = lane == r ? b : u;
+            q = lane == r ? c : q;
+        }
+    }
+    if (NORM) {
+        const float rinv = 1.0f / sqrtf(q / (float)K + eps);
+        v *= rinv;
+        u *= rinv;
+    }
+    return RowDots{v, u};
+}
+// a row's pair of features (e0 and half a head on) of a q, k or v head -> its rotation, its place
+template <typename T>
+__device__ __forceinline__ void rope_store(const GenericRope& rp, int head, int e0, int row, int pos, T* page, RowDots d, float cs, float sn,
+                                           T* __restrict__ q_out) {
+    const KvGeom& gm = rp.gm;
+    const int half = gm.hd / 2, slot = pos % TASC_KV_BLOCK;
+    if (head < gm.H + gm.Hkv) {
+        const float ra = fmaf(d.v, cs, -(d.u * sn)), rc = fmaf(d.u, cs, d.v * sn);
+        T* o = head < gm.H ? q_out + ((size_t)row * gm.H + head) * gm.hd + e0
+                           : page ? page + (size_t)((head - gm.H) * TASC_KV_BLOCK + slot) * gm.hd + e0 : nullptr;
+        if (o) {
+            o[0] = from_f<T>(ra);
+            o[half] = from_f<T>(rc);
+        }
+    } else if (page) {
+        T* vt = page + (size_t)gm.Hkv * TASC_KV_BLOCK * gm.hd + (size_t)((head - gm.H - gm.Hkv) * gm.hd + e0) * TASC_KV_BLOCK + slot;
+        vt[0] = from_f<T>(d.v);
+        vt[(size_t)half * TASC_KV_BLOCK] = from_f<T>(d.u);
+    }
+}
+
+// One wave per output column (or pair), rows in chunks of 8, blockIdx.y and gridDim.y chunks on.
+// Of a small model's step each launch is a few dependent loads and its own start and end (fp32, d 128, 5 rows: 4.6 to 5.4 us; 4.1 to
+// 4.9 with norm, rotation and cache append as launches of 2.4 and 2.8 us beside it): so those ride along, and what an epilogue needs
+// is requested before the products.  (The projection inside the attention's workgroups was slower: 22.8 us against 5.4 + 7.8.)
+template <typename T, int EPI, bool NORM>
+__global__ __launch_bounds__(256) void k_gemm_generic(const void* __restrict__ A, const T* __restrict__ W, int M, int N, int K,
+                                                      const float* __restrict__ g, float eps, float* outf, T* __restrict__ outT,
+                                                      T* __restrict__ kv_layer, GenericRope rp) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = blockIdx.x * 4 + wave;
+    if (col >= N) return;
+    const KvGeom& gm = rp.gm;
+    const int half = EPI == EPI_ROPE ? gm.hd / 2 : 1, head = col / half, e0 = col % half;        // EPI_ROPE: the pair's place
+    const T *w0, *w1;
+    if (EPI == EPI_SWIGLU) {
+        w0 = W + (size_t)((col >> 4) * 32 + (col & 15)) * K;
+        w1 = w0 + (size_t)16 * K;
+    } else if (EPI == EPI_ROPE) {
+        w0 = W + (size_t)(head * gm.hd + e0) * K;
+        w1 = w0 + (size_t)half * K;
+    } else {
+        w0 = w1 = W + (size_t)col * K;
+    }
+    for (int r0 = 8 * blockIdx.y; r0 < M; r0 += 8 * gridDim.y) {
+        // what lane r < 8 needs for row r0 + r at the end
+        const int row = r0 + lane;
+        const bool own = lane < 8 && row < M;
+        float old = 0.f, cs = 1.f, sn = 0.f;
+        T* page = nullptr;
+        int pos = 0;
+        if (own && EPI == EPI_RESID) old = outf[(size_t)row * N + col];
+        if (own && EPI == EPI_ROPE) {
+            const int b = rp.nq ? row / rp.nq : gm.seq(row), i = rp.nq ? row - b * rp.nq : gm.index(row, b);
+            const bool active = rp.nq != 0 || i < rp.n_rows[b];
+            pos = rp.pos0[b] + i;
+            if (head < gm.H + gm.Hkv) {
+                const int tpos = pos < rp.max_pos ? pos : rp.max_pos - 1;
+                cs = rp.cosT[(size_t)tpos * half + e0];
+                sn = rp.sinT[(size_t)tpos * half + e0];
+            }
+            if (active) page = kv_layer + (size_t)rp.block_tab[(size_t)b * gm.max_blocks + pos / TASC_KV_BLOCK] * gm.page_elems;
+        }
+        const RowDots d = row_dots<T, EPI != EPI_RESID, NORM>(A, r0, min(8, M - r0), w0, w1, K, g, eps, lane);
+        if (!own) continue;
+        if (EPI == EPI_RESID) outf[(size_t)row * N + col] = old + d.v;
+        if (EPI == EPI_SWIGLU) outT[(size_t)row * N + col] = from_f<T>(d.v / (1.0f + expf(-d.v)) * d.u);
+        if (EPI == EPI_ROPE) rope_store<T>(rp, head, e0, row, pos, page, d, cs, sn, outT);
+    }
+}
+
+// ---------------------------------------------------------------- RoPE + KV append
 // Row r = (sequence b, i) sits at position pos0[b] + i.  q is rotated into `q_out`; k is rotated and
 // written to the K half of its page, v to the transposed V half.  Rows beyond n_rows[b] write nothing.
 // `qkv` may be n_slices partial sums [n_slices][rows][nqkv] (slice_stride elements apart), added here in slice order.
@@ -229,84 +338,143 @@ __global__ void k_rope_kv(const float* __restrict__ qkv, const float* __restrict
 }
 
 // ---------------------------------------------------------------- generic attention over the paged cache
-// One workgroup per (sequence, query head); a wave per query row.  Keys are visited in tiles of 64 at
-// absolute positions 0, 64, ...; running max / sum (online softmax) in fp32.  A lane holds one dimension of the output and
-// reads the 16 tokens of a value page in one go (they are contiguous), all pages of the tile ahead of the first product: with a
-// load per key, one sequence of 100 tokens took 46 us, nearly all of it waiting.
+// One workgroup per (sequence, query head).  Keys are taken in tiles of 64 at absolute positions 0, 64, ...; a tile gives a row its
+// maximum, the sum of its exponentials and their products with the values (a lane holds one dimension of the output and reads the 16
+// tokens of a value page in one go, ahead of the scores), and the tiles are added in ascending order, rescaled to the larger
+// maximum: the same arithmetic whoever computes a tile.  nq: rows of every sequence in a verify step, 0: look them up.  Where a sequence's (row, tile) pairs are few, every wave takes pairs of
+// its own and the tiles of a row meet in LDS; otherwise a wave takes whole rows.  fp32, one sequence of 100 tokens, 5 rows: 9 us
+// with a wave per row.
 #define ATTN_GENERIC_THREADS 512
+#define ATTN_GENERIC_UNITS 32      // (row, tile) pairs that meet in LDS
+struct AttnTile {
+    float m, l, acc[4];            // maximum, sum, output dimensions lane, lane + 64, ..
+};
+template <typename T>
+__device__ __forceinline__ AttnTile attn_tile(const float* qi, const T* __restrict__ kv_layer, const int32_t* __restrict__ bt, int first_pages,
+                                              const KvGeom& gm, int g, int t0, int L, float scale, int lane) {
+    const int hd = gm.hd, key = t0 + lane, nk = min(64, L - t0);
+    const size_t v_off = (size_t)gm.Hkv * TASC_KV_BLOCK * hd;
+    const T* pages[4];
+#pragma unroll
+    for (int pg = 0; pg < 4; ++pg) {           // (pages past the row's position are not read, slots past it do not count)
+        const int at = min(t0 + TASC_KV_BLOCK * pg, L - 1) / TASC_KV_BLOCK;
+        pages[pg] = kv_layer + (size_t)(t0 < 64 * TASC_KV_BLOCK ? __builtin_amdgcn_readlane(first_pages, at & 63) : bt[at]) * gm.page_elems;
+    }
+    const T* mine = lane < 16 ? pages[0] : lane < 32 ? pages[1] : lane < 48 ? pages[2] : pages[3];
+    const T* kp = mine + (size_t)(g * TASC_KV_BLOCK + (key < L ? key : L - 1) % TASC_KV_BLOCK) * hd;
+    float v[4][TASC_KV_BLOCK];
+    auto load_v = [&](int e) __attribute__((always_inline)) {
+#pragma unroll
+        for (int pg = 0; pg < 4; ++pg) {
+            const T* vt = pages[pg] + v_off + (size_t)(g * hd + min(e, hd - 1)) * TASC_KV_BLOCK;
+            load8(vt, v[pg]);
+            load8(vt + 8, v[pg] + 8);
+        }
+    };
+    load_v(lane);
+    float dot = 0.f;
+#pragma unroll 4
+    for (int e = 0; e < hd; e += 8) {
+        float kvv[8];
+        load8(kp + e, kvv);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) dot = fmaf(qi[e + u], kvv[u], dot);
+    }
+    AttnTile o;
+    const float s = key < L ? dot * scale : -INFINITY;
+    o.m = wave_max(s);
+    const float p = key < L ? expf(s - o.m) : 0.f;
+    o.l = wave_sum_dpp(p);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        o.acc[c] = 0.f;
+        if (64 * c >= hd) continue;
+        if (c > 0) load_v(lane + 64 * c);
+#pragma unroll
+        for (int pg = 0; pg < 4; ++pg) {
+            if (TASC_KV_BLOCK * pg >= nk) break;
+#pragma unroll
+            for (int q = 0; q < TASC_KV_BLOCK; ++q) {
+                const float vq = TASC_KV_BLOCK * pg + q < nk ? v[pg][q] : 0.f;
+                o.acc[c] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), TASC_KV_BLOCK * pg + q)), vq, o.acc[c]);
+            }
+        }
+    }
+    return o;
+}
+__device__ __forceinline__ void attn_add(float& m, float& l, float& acc, float tm, float tl, float ta) {
+    const float mn = fmaxf(m, tm), c1 = expf(m - mn), c2 = expf(tm - mn);
+    l = fmaf(l, c1, tl * c2);
+    acc = fmaf(acc, c1, ta * c2);
+    m = mn;
+}
 template <typename T>
 __global__ __launch_bounds__(ATTN_GENERIC_THREADS) void k_attn_generic(const T* __restrict__ q, const T* __restrict__ kv_layer,
                                                       const int32_t* __restrict__ n_rows, const int32_t* __restrict__ pos0,
-                                                      const int32_t* __restrict__ block_tab, KvGeom gm, float scale,
+                                                      const int32_t* __restrict__ block_tab, KvGeom gm, float scale, int nq,
                                                       T* __restrict__ att) {
-    extern __shared__ float s_q[];   // [most rows of a sequence][hd]
+    extern __shared__ float s_q[];             // [waves][hd], then [units][hd + 2]
+    constexpr int NW = ATTN_GENERIC_THREADS / 64;
     const int b = blockIdx.x, j = blockIdx.y, g = (j * gm.Hkv) / gm.H;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int hd = gm.hd, nr = n_rows[b], p0 = pos0[b];
-    const size_t qstride = (size_t)gm.H * hd, row0 = gm.row0[b];
-    for (int idx = threadIdx.x; idx < nr * hd; idx += blockDim.x) {
-        const int i = idx / hd, e = idx % hd;
-        s_q[idx] = to_f(q[(row0 + i) * qstride + j * hd + e]);
+    const int32_t* const bt = block_tab + (size_t)b * gm.max_blocks;
+    const int first_pages = bt[min(lane, gm.max_blocks - 1)];          // in one go with the position
+    const int hd = gm.hd, nr = nq ? nq : n_rows[b], p0 = pos0[b];
+    const size_t row0 = nq ? (size_t)b * nq : (size_t)gm.row0[b];
+    const size_t qstride = (size_t)gm.H * hd;
+    float* const qi = s_q + wave * hd;         // the wave's own query row
+    auto load_q = [&](int i) __attribute__((always_inline)) {
+        __builtin_amdgcn_wave_barrier();
+        for (int e = lane; e < hd; e += 64) qi[e] = to_f(q[(row0 + i) * qstride + j * hd + e]);
+        __builtin_amdgcn_wave_barrier();
+    };
+    const int tiles = (p0 + nr + 63) / 64;     // of the last row, the most of any
+    float* const s_part = s_q + NW * hd;
+    if (gridDim.z == 1 && nr * tiles <= ATTN_GENERIC_UNITS) {
+        for (int u = wave; u < nr * tiles; u += NW) {
+            const int i = u / tiles, t0 = 64 * (u % tiles), L = p0 + i + 1;
+            if (t0 >= L) continue;
+            load_q(i);
+            const AttnTile o = attn_tile(qi, kv_layer, bt, first_pages, gm, g, t0, L, scale, lane);
+            float* part = s_part + u * (hd + 2);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (lane + 64 * c < hd) part[lane + 64 * c] = o.acc[c];
+            if (lane == 0) {
+                part[hd] = o.m;
+                part[hd + 1] = o.l;
+            }
+        }
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < nr * hd; idx += ATTN_GENERIC_THREADS) {
+            const int i = idx / hd, e = idx % hd;
+            float m = -INFINITY, l = 0.f, acc = 0.f;
+            for (int t = 0; 64 * t < p0 + i + 1; ++t) {
+                const float* part = s_part + (i * tiles + t) * (hd + 2);
+                attn_add(m, l, acc, part[hd], part[hd + 1], part[e]);
+            }
+            att[(row0 + i) * qstride + j * hd + e] = from_f<T>(acc / l);
+        }
+        return;
     }
-    __syncthreads();
-    const int32_t* bt = block_tab + (size_t)b * gm.max_blocks;
-    const size_t v_off = (size_t)gm.Hkv * TASC_KV_BLOCK * hd;
-    for (int i = wave; i < nr; i += ATTN_GENERIC_THREADS / 64) {
-        T* out = att + (row0 + i) * qstride + j * hd;
-        const float* qi = s_q + i * hd;
+    for (int i = NW * blockIdx.z + wave; i < nr; i += NW * gridDim.z) {
+        load_q(i);
         const int L = p0 + i + 1;
         float m = -INFINITY, l = 0.f, acc[4] = {0, 0, 0, 0};
         for (int t0 = 0; t0 < L; t0 += 64) {
-            const int key = t0 + lane;
-            float s = -INFINITY;
-            if (key < L) {
-                const T* kp = kv_layer + (size_t)bt[key / TASC_KV_BLOCK] * gm.page_elems +
-                              (size_t)(g * TASC_KV_BLOCK + key % TASC_KV_BLOCK) * hd;
-                float dot = 0.f;
-#pragma unroll 4
-                for (int e = 0; e < hd; e += 8) {
-                    float kvv[8];
-                    load8(kp + e, kvv);
+            const AttnTile o = attn_tile(qi, kv_layer, bt, first_pages, gm, g, t0, L, scale, lane);
+            const float m0 = m, l0 = l;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) dot = fmaf(qi[e + u], kvv[u], dot);
-                }
-                s = dot * scale;
-            }
-            const float m_new = fmaxf(m, wave_max(s));
-            const float corr = expf(m - m_new);
-            const float p = key < L ? expf(s - m_new) : 0.f;
-            l = l * corr + wave_sum(p);
-            m = m_new;
-            const int nk = min(64, L - t0);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                acc[c] *= corr;
-                const int e = lane + 64 * c;
-                if (64 * c >= hd) break;
-                // (pages past the row's position are not read, slots past it do not count)
-                float v[4][TASC_KV_BLOCK];
-#pragma unroll
-                for (int pg = 0; pg < 4; ++pg) {
-                    const int kpos = min(t0 + TASC_KV_BLOCK * pg, L - 1);
-                    const T* vt = kv_layer + (size_t)bt[kpos / TASC_KV_BLOCK] * gm.page_elems + v_off + (size_t)(g * hd + min(e, hd - 1)) * TASC_KV_BLOCK;
-                    load8(vt, v[pg]);
-                    load8(vt + 8, v[pg] + 8);
-                }
-#pragma unroll
-                for (int pg = 0; pg < 4; ++pg) {
-                    if (TASC_KV_BLOCK * pg >= nk) break;
-#pragma unroll
-                    for (int q = 0; q < TASC_KV_BLOCK; ++q) {
-                        const float vq = TASC_KV_BLOCK * pg + q < nk ? v[pg][q] : 0.f;
-                        acc[c] = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), TASC_KV_BLOCK * pg + q)), vq, acc[c]);
-                    }
-                }
+            for (int c = 0; c < 4; ++c) {      // (the same maximum and sum for every dimension)
+                m = m0;
+                l = l0;
+                attn_add(m, l, acc[c], o.m, o.l, o.acc[c]);
             }
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int e = lane + 64 * c;
-            if (e < hd) out[e] = from_f<T>(acc[c] / l);
+            if (e < hd) att[(row0 + i) * qstride + j * hd + e] = from_f<T>(acc[c] / l);
         }
     }
 }
@@ -319,100 +487,130 @@ struct BiasCsr {
     const float* base;
 };
 
-// h: [n_rows, d] normalised hidden rows; row r was fed token tok[r] (bias row).  A workgroup covers a
-// strip of TASC_LM_STRIP vocabulary columns, 8 per wave, and leaves, per row, the best (value, index)
-// of its strip; index ties go to the lowest column.  logits (nullable) receives every logit.  Four columns
-// at a time: the 32 sums over the wave are independent chains (one column at a time and 32 columns a wave, a vocabulary of
-// 512 took 50 us, all of it the chains' latency).
-#define LM_GENERIC_WAVES 16
-template <typename T>
-__global__ __launch_bounds__(64 * LM_GENERIC_WAVES) void k_lmhead_generic(const T* __restrict__ h, const T* __restrict__ W,
+// x: [rows, d] residual stream; LM-head row r is the final RMSNorm (gain gf) of row sel[r] (negative: row 0) and was fed token tok[r]
+// (its bias row).  WAVES waves take CW columns each, four at a time, and leave per row the best (value, index) of the workgroup's
+// columns; index ties go to the lowest.  logits (nullable) receives every logit.  The norm's sum of squares is taken along with
+// the products.  One more wave looks up the rows' seen successors among the columns, eight lanes a row, while the others multiply,
+// and leaves their bias in LDS.  Few columns a workgroup for a vocabulary of few strips: 512 columns in four workgroups of 16 waves, a
+// binary search by one lane per row in front, took 24 us, all of it latency; 6.3 us now.
+template <typename T, int WAVES, int CW>
+__global__ __launch_bounds__(64 * (WAVES + 1)) void k_lmhead_generic(const float* __restrict__ x, const int32_t* __restrict__ sel,
+                                                        const float* __restrict__ gf, float eps, const T* __restrict__ W,
                                                         const int32_t* __restrict__ tok, int n_rows, int V, int d,
                                                         BiasCsr bias, float* __restrict__ part_val,
-                                                        int32_t* __restrict__ part_idx, int n_strips,
+                                                        int32_t* __restrict__ part_idx, int n_parts,
                                                         float* __restrict__ logits) {
-    constexpr int CW = TASC_LM_STRIP / LM_GENERIC_WAVES, CB = 4;      // columns of a wave, and at a time
-    __shared__ float s_v[LM_GENERIC_WAVES][8];
-    __shared__ int32_t s_i[LM_GENERIC_WAVES][8];
+    constexpr int CB = 4, COLS = WAVES * CW;                          // columns at a time, and of the workgroup
+    __shared__ float s_bias[8][COLS];
+    __shared__ float s_v[WAVES][8];
+    __shared__ int32_t s_i[WAVES][8];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int strip = blockIdx.x;
-    const int c0 = strip * TASC_LM_STRIP + wave * CW;
+    const int first = blockIdx.x * COLS, c0 = first + wave * CW;
     for (int r0 = 0; r0 < n_rows; r0 += 8) {
         const int row = r0 + lane;
         const bool own = lane < 8 && row < n_rows;
-        float best = -INFINITY;
-        int32_t best_i = 0x7FFFFFFF;
-        int64_t bp = 0, be = 0;
-        float base = 0.f;
-        if (own && bias.rowptr) {
-            const int u = tok[row];
-            int64_t lo = bias.rowptr[u];
-            be = bias.rowptr[u + 1];
-            int64_t hi = be;
-            while (lo < hi) {   // first entry of the row with column >= c0
-                int64_t mid = (lo + hi) >> 1;
-                if (bias.col[mid] < c0) lo = mid + 1; else hi = mid;
+        float z[CW];                                                  // lane r: the row's logits without bias
+        if (wave == WAVES) {
+            const int r = lane >> 3, q = lane & 7;
+            float base = 0.f;
+            int64_t lo = 0, hi = 0, end = 0;
+            if (bias.rowptr && r0 + r < n_rows) {
+                const int u = tok[r0 + r];
+                base = bias.base[u];
+                lo = bias.rowptr[u];
+                hi = end = bias.rowptr[u + 1];
             }
-            bp = lo;
-            base = bias.base[u];
-        }
-        for (int cb = c0; cb < c0 + CW && cb < V; cb += CB) {
-            float acc[CB][8];
+            for (int c = q; c < COLS; c += 8) s_bias[r][c] = base;
+            // first entry of the row with a column >= first: the range in nine parts per look
+            while (__ballot(hi - lo > 0) != 0) {
+                const int64_t n = hi - lo, at = lo + n * (q + 1) / 9;          // (below hi)
+                const bool below = n > 0 && bias.col[at] < first;
+                const int k = __popc((u32)(__ballot(below) >> (8 * r)) & 0xFF);        // ascending: the first k are
+                const int64_t from = k > 0 ? lo + n * k / 9 + 1 : lo;
+                if (k < 8) hi = lo + n * (k + 1) / 9;
+                lo = n > 0 ? from : lo;
+                hi = hi > lo ? hi : lo;
+            }
+            __builtin_amdgcn_wave_barrier();
+            for (int64_t p = lo + q; p < end; p += 8) {
+                const int c = bias.col[p] - first;
+                if (c >= COLS) break;
+                s_bias[r][c] = bias.val[p];
+            }
+        } else {
 #pragma unroll
-            for (int u = 0; u < CB; ++u)
-#pragma unroll
-                for (int r = 0; r < 8; ++r) acc[u][r] = 0.f;
-            for (int k = lane * 8; k < d; k += 512) {
-                float wv[CB][8];
-#pragma unroll
-                for (int u = 0; u < CB; ++u) load8(W + (size_t)min(cb + u, V - 1) * d + k, wv[u]);
+            for (int cb = 0; cb < CW; cb += CB) {
+                float acc[CB][8], ss[8];
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    if (r0 + r < n_rows) {
-                        float av[8];
-                        load8(h + (size_t)(r0 + r) * d + k, av);
+                    ss[r] = 0.f;
 #pragma unroll
-                        for (int u = 0; u < CB; ++u)
+                    for (int u = 0; u < CB; ++u) acc[u][r] = 0.f;
+                }
+                const float* xr[8];
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) acc[u][r] = fmaf(av[e], wv[u][e], acc[u][r]);
+                for (int r = 0; r < 8; ++r) xr[r] = x + (size_t)max(sel[min(r0 + r, n_rows - 1)], 0) * d;
+                for (int k = lane * 4; k < d; k += 256) {
+                    float wv[CB][4], gv[4];
+                    load4(gf + k, gv);
+#pragma unroll
+                    for (int u = 0; u < CB; ++u) load4(W + (size_t)min(c0 + cb + u, V - 1) * d + k, wv[u]);
+#pragma unroll
+                    for (int u = 0; u < CB; ++u)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) wv[u][e] *= gv[e];
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        if (r0 + r < n_rows) {
+                            float av[4];
+                            load4(xr[r] + k, av);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                ss[r] = fmaf(av[e], av[e], ss[r]);
+#pragma unroll
+                                for (int u = 0; u < CB; ++u) acc[u][r] = fmaf(av[e], wv[u][e], acc[u][r]);
+                            }
+                        }
                     }
                 }
-            }
-            float mine[CB];
+                float mine[CB] = {0.f, 0.f, 0.f, 0.f}, mine_s = 0.f;
 #pragma unroll
-            for (int u = 0; u < CB; ++u) mine[u] = 0.f;
+                for (int r = 0; r < 8; ++r) {
+                    const float q = wave_sum_dpp(ss[r]);
+                    mine_s = lane == r ? q : mine_s;
 #pragma unroll
-            for (int r = 0; r < 8; ++r)
-#pragma unroll
-                for (int u = 0; u < CB; ++u) {
-                    const float v = wave_sum(acc[u][r]);
-                    if (lane == r) mine[u] = v;
-                }
-#pragma unroll
-            for (int u = 0; u < CB; ++u) {
-                const int c = cb + u;
-                if (own && c < V) {
-                    float z = mine[u];
-                    if (bias.rowptr) {
-                        if (bp < be && bias.col[bp] == c) z += bias.val[bp++];
-                        else z += base;
+                    for (int u = 0; u < CB; ++u) {
+                        const float v = wave_sum_dpp(acc[u][r]);
+                        mine[u] = lane == r ? v : mine[u];
                     }
-                    if (logits) logits[(size_t)row * V + c] = z;
-                    if (z > best) { best = z; best_i = c; }
                 }
+                const float rinv = 1.0f / sqrtf(mine_s / (float)d + eps);
+#pragma unroll
+                for (int u = 0; u < CB; ++u) z[cb + u] = mine[u] * rinv;
             }
         }
-        if (lane < 8) { s_v[wave][lane] = best; s_i[wave][lane] = best_i; }
+        __syncthreads();
+        float best = -INFINITY;
+        int32_t best_i = 0x7FFFFFFF;
+        if (wave < WAVES && own) {
+#pragma unroll
+            for (int u = 0; u < CW; ++u) {
+                const int c = c0 + u;
+                if (c >= V) break;
+                const float y = z[u] + s_bias[lane][wave * CW + u];
+                if (logits) logits[(size_t)row * V + c] = y;
+                if (y > best) { best = y; best_i = c; }
+            }
+            s_v[wave][lane] = best;
+            s_i[wave][lane] = best_i;
+        }
         __syncthreads();
         if (wave == 0 && own) {
-            float bv = s_v[0][lane];
-            int32_t bi = s_i[0][lane];
-            for (int w = 1; w < LM_GENERIC_WAVES; ++w)
-                if (s_v[w][lane] > bv) { bv = s_v[w][lane]; bi = s_i[w][lane]; }
-            part_val[(size_t)row * n_strips + strip] = bv;
-            part_idx[(size_t)row * n_strips + strip] = bi;
+            for (int w = 1; w < WAVES; ++w)
+                if (s_v[w][lane] > best) { best = s_v[w][lane]; best_i = s_i[w][lane]; }
+            part_val[(size_t)row * n_parts + blockIdx.x] = best;
+            part_idx[(size_t)row * n_parts + blockIdx.x] = best_i;
         }
-        __syncthreads();
     }
 }
 
