@@ -258,11 +258,14 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
     // padding (25 x 49152 x 896 106 | 108, 25 x 151936 x 896 165 | 169).
     const bool large = EPI == TEPI_LMHEAD ? M > 32 && small_wgs > cus : (M >= kLargeTileRows && large_wgs >= 128) || (M > 128 && large_wgs >= 512);
     if (large) {
-        // 192-row tiles where they cover the rows with less padding and no more tiles (the tile shape never changes a
-        // row's result)
+        // Tiles of 192 rows where their rounds over the compute units are shorter in all (the tile shape never changes a row's result):
+        // fewer padded rows (576 = 3 x 192), or a last round that larger tiles would leave half empty.  They read the weights more
+        // often, so they have to win by a twentieth (us, 256 | 192: down 6336 x 1536 x 8960, 150 | 198 tiles 187 | 174; 12288 x 2048 x 11008,
+        // 384 | 512 tiles 557 | 498).
         const int mt256 = (M + 255) / 256, mt192 = (M + 191) / 192;
         const int nt = (N + 255) / 256;
-        const bool mid = mt192 <= mt256 && mt192 * 192 < mt256 * 256;
+        auto rounds = [&](int mt) { return ((long)mt * nt * slices + cus - 1) / cus; };
+        const bool mid = rounds(mt192) * 192 * 20 < rounds(mt256) * 256 * 19;
         const int tiles = (mid ? mt192 : mt256) * nt * slices;
         if (EPI == TEPI_LMHEAD || (tiles > cus && !(EPI == TEPI_ROPE && mid))) {   // (that rotation needs whole heads in a wave's features: 128, not 64)
             if constexpr (EPI != TEPI_ROPE) {
