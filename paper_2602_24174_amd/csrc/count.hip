@@ -15,25 +15,6 @@
 
 namespace {
 
-// The hash: a bijection of lo for every hi, of few multiplications (each of 64 bits is four instructions of a quarter of the rate).
-constexpr u64 kMulHi = 0x9E3779B97F4A7C15ull, kMulA = 0xBF58476D1CE4E5B9ull, kMulB = 0x94D049BB133111EBull;
-constexpr u64 kUnmulA = 0x96DE1B173F119089ull, kUnmulB = 0x319642B2D24D8EC3ull;          // their inverses modulo 2^64
-__device__ __forceinline__ u64 count_hash(u64 lo, u64 hi, bool wide) {
-    u64 x = wide ? lo + hi * kMulHi : lo;
-    x ^= x >> 32;
-    x *= kMulA;
-    x ^= x >> 29;
-    return x * kMulB;
-}
-__device__ __forceinline__ u64 key_lo_of(u64 hash, u64 hi) {
-    u64 x = hash * kUnmulB;
-    x ^= (x >> 29) ^ (x >> 58);
-    x *= kUnmulA;
-    x ^= x >> 32;
-    return x - hi * kMulHi;
-}
-static_assert(kMulA * kUnmulA == 1 && kMulB * kUnmulB == 1, "inverses");
-
 // A record is {low 56 bits of the hash : 56, count - 1 : 8}, followed by the key's upper half where keys have more than 64 bits;
 // larger counts of a chunk take several.  The upper 8 bits of the hash follow from the partition: at least TASC_COUNT_MIN_PARTS =
 // 256 ranges of the hash's upper 32 bits, so a range is no longer than 2^24.
@@ -152,7 +133,7 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
         hi[w] = 0;
 #pragma unroll
         for (int j = 0; j < N; ++j) tasc_key_put(lo, hi[w], j, bits, at[j]);
-        hash[w] = count_hash(lo, hi[w], wide);
+        hash[w] = tasc_hash_key(lo, hi[w]);
         rank[w] = atomicAdd(&s_hist[part_of(hash[w], parts)], (cnt[w] + 255) / 256);
     }
     __syncthreads();
@@ -415,7 +396,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
                 const u64 key = s_key[i];
                 if (key == 0 || s_cnt[i] != most) continue;
                 const u64 hi = hi_of(key, i);
-                const TascGram g{key_lo_of(hash_of(key, part, a.parts), hi), hi, most, (u32)a.n};
+                const TascGram g{tasc_hash_lo(hash_of(key, part, a.parts), hi), hi, most, (u32)a.n};
                 if (tasc_gram_before(g, best, a.bits)) best = g;
             }
         }
@@ -434,7 +415,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
                     const u32 c = s_cnt[i];
                     if (key == 0 || c < a.p_min) continue;
                     const u64 hi = hi_of(key, i);
-                    a.kept.lo[to] = key_lo_of(hash_of(key, part, a.parts), hi);
+                    a.kept.lo[to] = tasc_hash_lo(hash_of(key, part, a.parts), hi);
                     a.kept.hi[to] = hi;
                     a.kept.count[to] = c;
                     ++to;

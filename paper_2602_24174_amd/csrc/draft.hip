@@ -3,10 +3,9 @@
 //     p_mixed(x|c) = lambda p_corp(x|c) + (1 - lambda) p_prompt(x|c),
 // each source queried in descending order of n, first match wins, most frequent token if none).
 //
-// One wave per sequence.  The sequence's committed tokens sit in LDS; the context drafter is
-// not a stored table but a scan: for the running suffix, every position of the sequence gets the
-// length of its match with the suffix, the longest match gives the context's order, and the tokens
-// that follow the matching positions are its successor multiset.  Exact integer scores.
+// The sequence's committed tokens sit in LDS; the context drafter is not a stored table: for the running suffix, the places of
+// its last token get the length of their match with it, the longest match gives the context's order, and the tokens that
+// follow the matching positions are its successor multiset.  Exact integer scores.
 #include "tasc_internal.h"
 
 namespace {
@@ -20,8 +19,8 @@ struct DraftArgs {
     int32_t* drafts;          // [B, k]
 };
 
-__device__ inline bool probe(const TascSlot* __restrict__ tab, u64 mask, u64 lo, u64 hi, int ntok, TascSlot& out) {
-    u64 idx = tasc_hash_key(lo, hi, ntok) & mask;
+__device__ inline bool probe(const TascSlot* __restrict__ tab, u64 mask, u64 lo, u64 hi, TascSlot& out) {
+    u64 idx = tasc_slot_of(tasc_hash_key(lo, hi), mask);
     for (u64 p = 0; p <= mask; ++p) {
         TascSlot s = tab[idx];
         if (s.a == 0) return false;
@@ -34,24 +33,23 @@ __device__ inline bool probe(const TascSlot* __restrict__ tab, u64 mask, u64 lo,
     return false;
 }
 
-// One WAVE per sequence: every exchange between lanes is a ballot, a lane read or an LDS access of the same wave, so
-// the k sequential proposals cross no workgroup barrier.  What bounds it is that chain of dependent steps and not memory
-// (64 sequences of 64 to 2,300 tokens, k = 8: 56 us, 92 before; its tokens and slots are 0.7 MB).  Per proposal, in cycles of
-// that workload:
+// One workgroup per sequence.  All its waves bring the tokens to LDS and sort the positions into buckets by their token; then one
+// WAVE makes the k sequential proposals: every exchange between lanes is a ballot, a lane read or an LDS access of the
+// same wave, so they cross no workgroup barrier.  What bounds it is that chain of dependent steps and not memory (64 sequences of 64
+// to 2,300 tokens, k = 8: 35 us, 55 with one wave and a pass over the sequence per proposal, and no longer at any length from 60 tokens on; its tokens and slots
+// are 0.7 MB):
 //   * the running suffix comes from LDS into registers, all tokens of it at once, and keys are shifted together from it
-//     without a loop over LDS;
-//   * corpus source (1,400 with the keys): lanes 0 .. n_max-2 request the first slot of one order each, and the answers are
-//     only looked at after the context phase, so the round trip runs under it;
-//   * context source (5,100): one pass over the sequence, 4 tokens per lane and read, lists the positions that follow an
-//     occurrence of the last token (29 on average), then only those are compared with the rest of the suffix.  Carrying every
-//     position's match length from proposal to proposal instead cost three more passes over LDS.  The successors of the longest
-//     matches (900) are counted with a ballot per distinct one while the list fits the wave's lanes, else in a hash table in LDS
+//     without a loop over LDS; what a lane asks for in every proposal (its order, that order's tables) is looked up once;
+//   * corpus source: lanes 0 .. n_max-2 request the first slot of one order each, and the answers are only looked at after the
+//     context phase, so the round trip runs under it;
+//   * context source: the bucket of the last token, a lane per position; only the positions of the last token
+//     are compared with the rest of the suffix.  The successors of the longest
+//     matches are counted with a ballot per distinct one while the list fits the wave's lanes, else in a hash table in LDS
 //     (token -> multiplicity; entries carry a generation number, so the table is never cleared); the distinct ones are the
 //     candidates;
-//   * the candidates' corpus counts (1,000) are requested at EVERY order before the corpus context is known (a second round
+//   * the candidates' corpus counts are requested at EVERY order before the corpus context is known (a second round
 //     trip that would otherwise wait for the first), and the ones of the matching order are used;
-//   * the argmax over (score, smallest token) is a reduction over neighbouring lanes (DPP, no LDS round trips); with the two
-//     answers 3,000.
+//   * the argmax over (score, smallest token) is a reduction over neighbouring lanes (DPP, no LDS round trips).
 constexpr int kHashSlots = 2 * TASC_DRAFT_MAX_LEN;        // more than any sequence has successors
 static_assert(TASC_DRAFT_MAX_LEN <= 4096 && TASC_DRAFT_MAX_LEN % 4 == 0 && TASC_MAX_ORDER <= 16, "list entries, token reads");
 
@@ -114,36 +112,77 @@ __device__ __forceinline__ void key_of(const u32* t, int m, int bits, u64& lo, u
     }
 }
 
-__global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
+constexpr int kDraftWaves = 8, kDraftThreads = 64 * kDraftWaves;
+constexpr int kBuckets = 1024;                            // of positions by their token
+__device__ __forceinline__ u32 bucket_of(u32 tok) { return (tok * 0x9E3779B1u) >> 22; }
+static_assert(kBuckets == 1 << 10 && kBuckets == 2 * kDraftThreads, "bucket_of, two buckets per thread");
+
+__global__ __launch_bounds__(kDraftThreads) void k_draft(DraftArgs a) {
     __shared__ __attribute__((aligned(16))) int32_t s_tok[TASC_DRAFT_MAX_LEN];
+    __shared__ uint16_t s_index[TASC_DRAFT_MAX_LEN];      // positions that a token follows, by bucket of their token
+    __shared__ __attribute__((aligned(16))) u32 s_bucket[kBuckets + 1];                // the buckets' first places
     __shared__ uint16_t s_pos[TASC_DRAFT_MAX_LEN];        // positions of the last token before the end; of lists beyond 64: {match length - 1 : 4, position : 12}
     __shared__ __attribute__((aligned(16))) u64 s_tab[kHashSlots];   // {generation : 16, multiplicity : 16, token : 32}
     __shared__ uint16_t s_dl[TASC_DRAFT_MAX_LEN];         // slots of the distinct successors of the current generation
     __shared__ int32_t s_d[TASC_MAX_K];                   // the proposals so far
+    __shared__ u32 s_wave[kDraftWaves];
     __shared__ int s_nd;
     __shared__ TascSlot s_hit[TASC_MAX_ORDER + 1];
 
-    const int b = blockIdx.x, lane = threadIdx.x;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const u64 lt_mask = (1ull << lane) - 1;
     const int N = a.n_tok[b];
     const int Nctx = a.ctx_gen ? N : min(N, a.n_prompt[b]);   // tokens the context statistics cover
     const int32_t* seq = a.tokens + (size_t)b * a.max_len;
-    for (int i0 = 0; i0 < N; i0 += 1024) {                 // sixteen loads in flight per lane
-        int32_t v[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = seq[min(i0 + 64 * u + lane, N - 1)];
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (i0 + 64 * u + lane < N) s_tok[i0 + 64 * u + lane] = v[u];
-    }
+    const u64 q = (u64)a.q16, qb = (u64)(65536 - a.q16);
     u32 tab_mask = 127;                                    // slots of the hash table: at least twice the successors there can be
     while (tab_mask + 1 < 2 * (u32)Nctx) tab_mask = 2 * tab_mask + 1;
-    for (u32 i = 2 * lane; i <= tab_mask; i += 128) *reinterpret_cast<ulonglong2*>(&s_tab[i]) = make_ulonglong2(0, 0);   // generation 0 = never used
-    const u64 q = (u64)a.q16, qb = (u64)(65536 - a.q16);
-    const int n_max = a.ng.n_max, bits = a.ng.bits;
+
+    // ---- all waves: tokens to LDS; positions sorted by bucket
+    {
+        constexpr int PER = TASC_DRAFT_MAX_LEN / kDraftThreads;
+        int32_t t[PER];
+        u32 rank[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) t[u] = seq[min(u * kDraftThreads + tid, N - 1)];
+        for (u32 i = 2 * tid; i <= tab_mask; i += 2 * kDraftThreads) *reinterpret_cast<ulonglong2*>(&s_tab[i]) = make_ulonglong2(0, 0);   // generation 0 = never used
+        *reinterpret_cast<uint2*>(&s_bucket[2 * tid]) = make_uint2(0, 0);
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u * kDraftThreads + tid < N) s_tok[u * kDraftThreads + tid] = t[u];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u * kDraftThreads + tid < Nctx - 1) rank[u] = atomicAdd(&s_bucket[bucket_of((u32)t[u])], 1u);
+        __syncthreads();
+        const uint2 n = *reinterpret_cast<const uint2*>(&s_bucket[2 * tid]);
+        u32 at = n.x + n.y;
+        for (int o = 1; o < 64; o <<= 1) {
+            const u32 v = __shfl_up(at, o);
+            if (lane >= o) at += v;
+        }
+        if (lane == 63) s_wave[tid >> 6] = at;
+        __syncthreads();
+        for (int w = 0; w < (tid >> 6); ++w) at += s_wave[w];
+        *reinterpret_cast<uint2*>(&s_bucket[2 * tid]) = make_uint2(at - n.x - n.y, at - n.y);
+        if (tid == kDraftThreads - 1) s_bucket[kBuckets] = at;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u * kDraftThreads + tid < Nctx - 1) s_index[s_bucket[bucket_of((u32)t[u])] + rank[u]] = (uint16_t)(u * kDraftThreads + tid);
+        __syncthreads();
+    }
+    if (tid >= 64) return;
+
+    // ---- the first wave: the proposals, one after the other
+    const int n_max = a.ng.n_max, bits = a.ng.bits, n_ord = n_max - 1;
     u32 gen = 0;
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    // what the lane asks for in every proposal: contexts of my_n - 1 tokens, and counts of f_ord-grams
+    const int my_n = max(n_max - lane, 2), f_ord = n_max - lane % n_ord;
+    const TascSlot* const my_ctx = a.ng.ord[my_n].ctx;
+    const u64 my_ctx_mask = a.ng.ord[my_n].ctx_mask;
+    const TascSlot* const f_full = a.ng.ord[f_ord].full;
+    const u64 f_full_mask = a.ng.ord[f_ord].full_mask;
 
     for (int j = 0; j < a.k; ++j) {
         const int wlen = N + j;
@@ -155,14 +194,13 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
         for (int i = 0; i < TASC_MAX_ORDER - 1; ++i) suf[i] = (u32)(i < j ? s_d[j - 1 - i] : s_tok[max(N - 1 - (i - j), 0)]);
 
         // ---- corpus source: the first slot of every order is requested now and examined after the context phase
-        const int my_n = n_max - lane;                     // lane l probes the contexts of n - 1 = n_max - 1 - l tokens
-        const bool c_probe = q > 0 && lane < n_max - 1 && my_n - 1 <= nsuf && a.ng.ord[my_n < 2 ? 2 : my_n].ctx != nullptr;
+        const bool c_probe = q > 0 && lane < n_max - 1 && my_n - 1 <= nsuf && my_ctx != nullptr;
         u64 c_lo = 0, c_hi = 0, c_idx = 0;
         TascSlot c_slot = {0, 0, 0, 0, 0, 0};
         if (c_probe) {
             key_of(suf, my_n - 1, bits, c_lo, c_hi);
-            c_idx = tasc_hash_key(c_lo, c_hi, my_n - 1) & a.ng.ord[my_n].ctx_mask;
-            c_slot = slot_load(a.ng.ord[my_n].ctx + c_idx);
+            c_idx = tasc_slot_of(tasc_hash_key(c_lo, c_hi), my_ctx_mask);
+            c_slot = slot_load(my_ctx + c_idx);
         }
 
         // ---- context source
@@ -170,18 +208,19 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
         bool in_regs = false;                              // the candidates are (cand_x, cand_c) of the lanes below n_dist, else in the table
         int cand_x = 0, cand_c = 0;
         if (qb > 0) {
-            int n_list = 0, my_ml = 0;
-            // the places of the last token, 4 tokens per lane and read ...
-            for (int p0 = 0; p0 < Nctx - 1; p0 += 256) {
-                const int t0 = p0 + 4 * lane;
-                const int4 t = *reinterpret_cast<const int4*>(&s_tok[min(t0, TASC_DRAFT_MAX_LEN - 4)]);
-                const u32 tv[4] = {(u32)t.x, (u32)t.y, (u32)t.z, (u32)t.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool hit = t0 + u + 1 < Nctx && tv[u] == suf[0];
+            int n_list = 0, my_ml = 0, e_at = 0;
+            // the places of the last token: those of its bucket that are it ...
+            const u32 bk = bucket_of(suf[0]);
+            const int from = (int)s_bucket[bk], to = (int)s_bucket[bk + 1];
+            const bool direct = to - from <= 64;           // a lane each, no list
+            if (direct) {
+                e_at = from + lane < to ? s_index[from + lane] : 0;
+            } else {
+                for (int p0 = from; p0 < to; p0 += 64) {
+                    const int at = s_index[min(p0 + lane, to - 1)];
+                    const bool hit = p0 + lane < to && (u32)s_tok[at] == suf[0];
                     const u64 m = __ballot(hit);
-                    if (m == 0) continue;
-                    if (hit) s_pos[n_list + __popcll(m & lt_mask)] = (uint16_t)(t0 + u);
+                    if (hit) s_pos[n_list + __popcll(m & lt_mask)] = (uint16_t)at;
                     n_list += __popcll(m);
                 }
             }
@@ -189,8 +228,7 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
             __builtin_amdgcn_wave_barrier();
             // ... and how much of the suffix before it matches there
             int e_ml = 0, e_x = 0;                         // the lane's (last) list entry: match length and successor
-            for (int e0 = 0; e0 < n_list; e0 += 64) {
-                const int at = s_pos[min(e0 + lane, n_list - 1)];
+            auto match = [&](int at) __attribute__((always_inline)) {
                 int before[TASC_MAX_ORDER - 2];
 #pragma unroll
                 for (int i = 1; i < TASC_MAX_ORDER - 1; ++i) before[i - 1] = s_tok[max(at - i, 0)];
@@ -202,9 +240,21 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
                     on = on && i < nsuf && at - i >= 0 && (u32)before[i - 1] == suf[i];
                     ml += on ? 1 : 0;
                 }
-                e_ml = e0 + lane < n_list ? ml : 0;
-                my_ml = max(my_ml, e_ml);
-                if (n_list > 64 && e_ml) s_pos[e0 + lane] = (uint16_t)(((ml - 1) << 12) | at);
+                return ml;
+            };
+            if (direct) {
+                const bool hit = from + lane < to && (u32)s_tok[e_at] == suf[0];
+                const int ml = match(e_at);
+                e_ml = hit ? ml : 0;
+                my_ml = e_ml;
+                n_list = __popcll(__ballot(hit));
+            } else {
+                for (int e0 = 0; e0 < n_list; e0 += 64) {
+                    const int at = s_pos[min(e0 + lane, n_list - 1)], ml = match(at);
+                    e_ml = e0 + lane < n_list ? ml : 0;
+                    my_ml = max(my_ml, e_ml);
+                    if (n_list > 64 && e_ml) s_pos[e0 + lane] = (uint16_t)(((ml - 1) << 12) | at);
+                }
             }
             int lmax = 0;
             if (n_list > 0) {
@@ -214,7 +264,7 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
             }
             __builtin_amdgcn_s_waitcnt(0);
             __builtin_amdgcn_wave_barrier();
-            in_regs = n_list <= 64;
+            in_regs = direct || n_list <= 64;
             // back off from the longest matching context until one has a kept successor
             for (int n = lmax + 1; n >= 2 && !n_ctx; --n) {
                 int t = 0;
@@ -293,7 +343,6 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
         };
 
         // ---- the candidates' corpus counts, requested at every order a corpus context could match (pair = candidate x order)
-        const int n_ord = n_max - 1;
         const bool spec = q > 0 && n_ctx && n_dist * n_ord <= 64;
         u64 f_lo = 0, f_hi = 0, f_idx = 0;
         TascSlot f_slot = {0, 0, 0, 0, 0, 0};
@@ -301,21 +350,19 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
         if (spec) {
             candidate(lane / n_ord, f_x, f_c);
             if (lane < n_dist * n_ord) {
-                f_n = n_max - lane % n_ord;
-                if (f_c >= a.p_min_ctx && f_n - 1 <= nsuf && a.ng.ord[f_n].full != nullptr) {
+                if (f_c >= a.p_min_ctx && f_ord - 1 <= nsuf && f_full != nullptr) {
+                    f_n = f_ord;
                     run[0] = (u32)f_x;
                     key_of(run, f_n, bits, f_lo, f_hi);
-                    f_idx = tasc_hash_key(f_lo, f_hi, f_n) & a.ng.ord[f_n].full_mask;
-                    f_slot = slot_load(a.ng.ord[f_n].full + f_idx);
-                } else {
-                    f_n = 0;
+                    f_idx = tasc_slot_of(tasc_hash_key(f_lo, f_hi), f_full_mask);
+                    f_slot = slot_load(f_full + f_idx);
                 }
             }
         }
 
         // ---- the corpus context: the highest order whose probe hits
         bool found = false;
-        if (c_probe && probe_finish(a.ng.ord[my_n].ctx, a.ng.ord[my_n].ctx_mask, c_lo, c_hi, c_idx, c_slot)) {
+        if (c_probe && probe_finish(my_ctx, my_ctx_mask, c_lo, c_hi, c_idx, c_slot)) {
             s_hit[my_n] = c_slot;
             found = true;
         }
@@ -337,11 +384,11 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
             if (spec) {
                 // one lane per (candidate, order): the lanes of the matching order (or, without a corpus match, of the
                 // highest order: one per candidate) score
-                const bool scorer = lane < n_dist * n_ord && f_c >= a.p_min_ctx && (n_corp ? (n_max - lane % n_ord) == n_corp : lane % n_ord == 0);
+                const bool scorer = lane < n_dist * n_ord && f_c >= a.p_min_ctx && (n_corp ? f_ord == n_corp : f_ord == n_max);
                 if (scorer) {
                     u64 sc;
                     if (n_corp) {
-                        const u64 c_corp = (f_n == n_corp && probe_finish(a.ng.ord[f_n].full, a.ng.ord[f_n].full_mask, f_lo, f_hi, f_idx, f_slot)) ? f_slot.a : 0;
+                        const u64 c_corp = (f_n == n_corp && probe_finish(f_full, f_full_mask, f_lo, f_hi, f_idx, f_slot)) ? f_slot.a : 0;
                         sc = q * c_corp * (u64)T_ctx + qb * (u64)f_c * T_corp;
                     } else {
                         sc = (u64)f_c;
@@ -361,7 +408,7 @@ __global__ __launch_bounds__(64) void k_draft(DraftArgs a) {
                         u64 lo = lo0, hi = hi0;
                         tasc_key_put(lo, hi, n_corp - 1, bits, (u32)xe);
                         TascSlot hit;
-                        const u64 c_corp = probe(a.ng.ord[n_corp].full, a.ng.ord[n_corp].full_mask, lo, hi, n_corp, hit) ? hit.a : 0;
+                        const u64 c_corp = probe(a.ng.ord[n_corp].full, a.ng.ord[n_corp].full_mask, lo, hi, hit) ? hit.a : 0;
                         sc = q * c_corp * (u64)T_ctx + qb * (u64)c * T_corp;
                     } else {
                         sc = (u64)c;
@@ -417,7 +464,7 @@ extern "C" tasc_status tasc_draft(const tasc_ngram* ng, tasc_session* s, const t
     a.drafts = drafts;
     {
         TascProfScope ps(TASC_KC_DRAFT, (hipStream_t)stream);
-        k_draft<<<dim3(s->batch), dim3(64), 0, (hipStream_t)stream>>>(a);
+        k_draft<<<dim3(s->batch), dim3(kDraftThreads), 0, (hipStream_t)stream>>>(a);
     }
     TASC_LAUNCH_CHECK();
     return TASC_OK;

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreadsKeep) void k_keep(TascKept kept, u64 n_kept
     const u32 cnt = on ? kept.count[i] : 0;
     if (on) {
         // full table: keys are distinct, so claiming a slot (count 0 -> cnt) is all the synchronisation needed
-        u64 idx = tasc_hash_key(lo, hi, n) & full_mask;
+        u64 idx = tasc_slot_of(tasc_hash_key(lo, hi), full_mask);
         for (u64 probe = 0; probe <= full_mask; ++probe) {
             if (atomicCAS(&full[idx].a, 0u, cnt) == 0u) {
                 full[idx].lo = lo;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreadsKeep) void k_keep(TascKept kept, u64 n_kept
     s_lo[tid] = lo;
     s_hi[tid] = hi;
     __syncthreads();
-    const u64 hash = tasc_hash_key(lo, hi, n - 1);
+    const u64 hash = tasc_hash_key(lo, hi);
     int own = -1;
     if (on) {
         u32 at = (u32)(hash >> 40) & (SLOTS - 1);
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kThreadsKeep) void k_keep(TascKept kept, u64 n_kept
     }
     __syncthreads();
     if (own < 0) return;
-    u64 idx = hash & ctx_mask;
+    u64 idx = tasc_slot_of(hash, ctx_mask);
     for (u64 probe = 0; probe <= ctx_mask; ++probe) {
         u32 q = __hip_atomic_load(&ctx[idx].ref1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (q == 0) q = atomicCAS(&ctx[idx].ref1, 0u, (u32)(i + 1));

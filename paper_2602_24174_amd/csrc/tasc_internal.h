@@ -132,9 +132,23 @@ __host__ __device__ inline u64 tasc_mix64(u64 x) {
     x ^= x >> 31;
     return x;
 }
-__host__ __device__ inline u64 tasc_hash_key(u64 lo, u64 hi, int ntok) {
-    return tasc_mix64(lo ^ tasc_mix64(hi + 0x9E3779B97F4A7C15ull * (u64)(ntok + 1)));
+// Hash of a packed key: for every hi a bijection of lo (tasc_hash_lo undoes it), of few multiplications (one of 64 bits is four
+// instructions of a quarter of the rate).  Its upper half is the better one.
+__host__ __device__ inline u64 tasc_hash_key(u64 lo, u64 hi) {
+    u64 x = lo + hi * 0x9E3779B97F4A7C15ull;
+    x ^= x >> 32; x *= 0xBF58476D1CE4E5B9ull;
+    x ^= x >> 29;
+    return x * 0x94D049BB133111EBull;
 }
+__host__ __device__ inline u64 tasc_hash_lo(u64 hash, u64 hi) {
+    u64 x = hash * 0x319642B2D24D8EC3ull;                  // the constants' inverses modulo 2^64
+    x ^= (x >> 29) ^ (x >> 58); x *= 0x96DE1B173F119089ull;
+    x ^= x >> 32;
+    return x - hi * 0x9E3779B97F4A7C15ull;
+}
+static_assert(0xBF58476D1CE4E5B9ull * 0x96DE1B173F119089ull == 1 && 0x94D049BB133111EBull * 0x319642B2D24D8EC3ull == 1, "inverses");
+// slot of a finished table (TascSlot) where the key's probe sequence begins
+__host__ __device__ inline u64 tasc_slot_of(u64 hash, u64 mask) { return (hash >> 28) & mask; }
 // appends token t as element j of a packed key
 __host__ __device__ inline void tasc_key_put(u64& lo, u64& hi, int j, int bits, u32 t) {
     int sh = j * bits;
