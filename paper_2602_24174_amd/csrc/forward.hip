@@ -470,13 +470,18 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
             if (ks_qkv > 1) {
                 // the k-slices of a split projection are added inside the rotation kernel (same order as the reduction kernel)
                 PROF(TASC_KC_ROPE_KV);
-                k_rope_kv<BF16><<<dim3(M), dim3(256), 0, st>>>(part, m->rope_cos, m->rope_sin, c.max_pos, n_rows,
-                                                             pos0, block_tab, gm, q, kv_layer, ks_qkv, (size_t)M * nqkv);
+                switch (ks_qkv) {
+#define ROPE_CASE(NS) case NS: k_rope_kv<NS><<<dim3(M), dim3(256), 0, st>>>(part, m->rope_cos, m->rope_sin, c.max_pos, n_rows, pos0, block_tab, gm, \
+                                                                          decode ? nq : 0, q, kv_layer, (size_t)M * nqkv); break;
+                    ROPE_CASE(2) ROPE_CASE(3) ROPE_CASE(4) ROPE_CASE(5) ROPE_CASE(6) ROPE_CASE(7)
+                    default: ROPE_CASE(8)
+#undef ROPE_CASE
+                }
             }
             {
                 PROF(TASC_KC_ATTN);
                 AttnArgs aa{q, att, kv_layer, n_rows, pos0, block_tab, d.row0, b0, (int32_t)r0, M, nq, H, Hkv,
-                            s->max_blocks, s->page_elems, 1.0f / sqrtf((float)hd)};
+                            s->max_blocks, decode ? 1 : 0, s->page_elems, 1.0f / sqrtf((float)hd)};
                 if (hd == 32 || s->max_blocks > TA_MAX_BLOCKS) {
                     if (hd == 64) k_attn_tiled<2><<<attn_grid, dim3(SMALL_THREADS), 0, st>>>(aa);
                     else if (hd == 128) k_attn_tiled<4><<<attn_grid, dim3(SMALL_THREADS), 0, st>>>(aa);
@@ -491,7 +496,10 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
                     else k_attn_staged<4><<<grid, dim3(SMALL_THREADS), TA_LDS_BYTES(128) + 4 * s->max_blocks, st>>>(sa);
                     if (att_chunks > 1) {
                         const size_t n = rows_all * H * hd / 4;
-                        k_attn_merge<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(sa.part_o, sa.part_ml, att_chunks, rows_all, H, hd, att);
+                        const dim3 mg((unsigned)((n + 255) / 256));
+                        if (att_chunks == 2) k_attn_merge<2><<<mg, dim3(256), 0, st>>>(sa.part_o, sa.part_ml, rows_all, H, hd, att);
+                        else if (att_chunks == 3) k_attn_merge<3><<<mg, dim3(256), 0, st>>>(sa.part_o, sa.part_ml, rows_all, H, hd, att);
+                        else k_attn_merge<4><<<mg, dim3(256), 0, st>>>(sa.part_o, sa.part_ml, rows_all, H, hd, att);
                     }
                 }
             }

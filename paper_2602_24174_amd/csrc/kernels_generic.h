@@ -154,7 +154,7 @@ struct KvGeom {
 // ---------------------------------------------------------------- generic GEMM  out[M, N] = A[M, K] W[N, K]^T
 // EPI_RESID: outf += A W^T.  EPI_SWIGLU: outT = silu(gate) up, a wave per feature (weight rows in blocks of 16 gate, 16 up).
 // EPI_ROPE: the fused q/k/v projection, a wave per pair of features half a head apart: q and k rotated at the row's position, q to
-// outT, new k and v rows to their cache pages (k_rope_kv's arithmetic).
+// outT, new k and v rows to their cache pages.
 enum { EPI_RESID = 1, EPI_SWIGLU = 2, EPI_ROPE = 3 };
 
 struct GenericRope {          // EPI_ROPE only
@@ -289,51 +289,6 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const void* __restrict__ A
         if (EPI == EPI_RESID) outf[(size_t)row * N + col] = old + d.v;
         if (EPI == EPI_SWIGLU) outT[(size_t)row * N + col] = from_f<T>(d.v / (1.0f + expf(-d.v)) * d.u);
         if (EPI == EPI_ROPE) rope_store<T>(rp, head, e0, row, pos, page, d, cs, sn, outT);
-    }
-}
-
-// ---------------------------------------------------------------- RoPE + KV append
-// Row r = (sequence b, i) sits at position pos0[b] + i.  q is rotated into `q_out`; k is rotated and
-// written to the K half of its page, v to the transposed V half.  Rows beyond n_rows[b] write nothing.
-// `qkv` may be n_slices partial sums [n_slices][rows][nqkv] (slice_stride elements apart), added here in slice order.
-template <typename T>
-__global__ void k_rope_kv(const float* __restrict__ qkv, const float* __restrict__ cosT, const float* __restrict__ sinT,
-                          int max_pos, const int32_t* __restrict__ n_rows, const int32_t* __restrict__ pos0,
-                          const int32_t* __restrict__ block_tab, KvGeom gm, T* __restrict__ q_out, T* __restrict__ kv_layer,
-                          int n_slices = 1, size_t slice_stride = 0) {
-    const int r = blockIdx.x, b = gm.seq(r), i = gm.index(r, b);
-    const bool active = i < n_rows[b];
-    const int pos = pos0[b] + i;
-    const int tpos = pos < max_pos ? pos : max_pos - 1;
-    const int half = gm.hd / 2, nqkv = (gm.H + 2 * gm.Hkv) * gm.hd;
-    const float* src = qkv + (size_t)r * nqkv;
-    T* page = nullptr;
-    const int slot = pos % TASC_KV_BLOCK;
-    if (active) page = kv_layer + (size_t)block_tab[(size_t)b * gm.max_blocks + pos / TASC_KV_BLOCK] * gm.page_elems;
-    for (int idx = threadIdx.x; idx < (gm.H + 2 * gm.Hkv) * half; idx += blockDim.x) {
-        const int head = idx / half, e = idx % half;
-        float a = src[head * gm.hd + e], c = src[head * gm.hd + e + half];
-        for (int sl = 1; sl < n_slices; ++sl) {            // k-slices of a split projection, added in slice order
-            a += src[(size_t)sl * slice_stride + head * gm.hd + e];
-            c += src[(size_t)sl * slice_stride + head * gm.hd + e + half];
-        }
-        if (head < gm.H + gm.Hkv) {
-            const float cs = cosT[(size_t)tpos * half + e], sn = sinT[(size_t)tpos * half + e];
-            const float ra = a * cs - c * sn, rc = c * cs + a * sn;
-            if (head < gm.H) {
-                q_out[(size_t)r * gm.H * gm.hd + head * gm.hd + e] = from_f<T>(ra);
-                q_out[(size_t)r * gm.H * gm.hd + head * gm.hd + e + half] = from_f<T>(rc);
-            } else if (active) {
-                const int g = head - gm.H;
-                page[(size_t)(g * TASC_KV_BLOCK + slot) * gm.hd + e] = from_f<T>(ra);
-                page[(size_t)(g * TASC_KV_BLOCK + slot) * gm.hd + e + half] = from_f<T>(rc);
-            }
-        } else if (active) {
-            const int g = head - gm.H - gm.Hkv;
-            T* vt = page + (size_t)gm.Hkv * TASC_KV_BLOCK * gm.hd;
-            vt[(size_t)(g * gm.hd + e) * TASC_KV_BLOCK + slot] = from_f<T>(a);
-            vt[(size_t)(g * gm.hd + e + half) * TASC_KV_BLOCK + slot] = from_f<T>(c);
-        }
     }
 }
 
