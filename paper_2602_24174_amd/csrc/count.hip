@@ -10,6 +10,13 @@
 // Partitions are ranges of the key's 64-bit hash.  With the upper half `hi` of the 128-bit key given, the hash is a bijection of the
 // lower half, so (hash, hi) is the key itself: records and LDS slots hold 8 bytes for keys of up to 64 bits and 16 beyond, the
 // comparison is exact, and nothing looks at the corpus again.
+// Both kernels live on dependent LDS round trips: a hash probe is an exchange, a comparison and an addition, and a wave that takes one
+// window or record per lane at a time waits for its unluckiest lane at each.  So a lane that is done with one takes its next at once.
+// And of the orders above the second, a window whose first or last n - 1 tokens occur once in the corpus occurs once itself: a map of
+// the (n-1)-grams that occur more often (a few per cent of the distinct ones) takes a third to half of the windows out.
+// 32 M tokens, orders 2 to 5, us: 2107 / 2302 / 2348 / 2378 with a table in memory; k_partition 311 / 472 / 528 / 541, k_turn 12 to 26,
+// k_tables 313 / 208 / 296 / 272 (414 / 530 / 566 and 332 / 565 / 610 for orders 3 to 5 without the map).  Both wait for LDS and L2
+// with one or two workgroups a compute unit: the vector units are busy 40 % of the time, the LDS 20 %.
 #include "tasc_internal.h"
 #include <algorithm>
 
@@ -48,12 +55,20 @@ __device__ __forceinline__ u32 block_scan(u32 v, u32* s_wave, u32& total) {
     return before + at - v;
 }
 
+// A hash of n tokens that costs two instructions a token; good enough for a chunk's table, and for the map of n-grams that occur twice
+__device__ __forceinline__ u32 light_step(u32 h, u32 tok, int j) { return h ^ (j == 0 ? tok : (tok << (13 * j % 32)) | (tok >> (32 - 13 * j % 32))); }   // (never by 0 or 32)
+__device__ __forceinline__ u32 light_end(u32 h) { return h * 0x9E3779B1u; }
+
 // LDS (dynamic): tokens [C + 8], slots [2 C] of {position in the chunk + 1 : 16, count : 16}, partition counters [parts], wave sums, the
 // windows' slots [C].  A few rotations of the tokens make a hash that is good enough for the chunk's table; the key and its hash are
 // computed once per window that is left.
+//
+// twice (nullable): a bit per range of the (N - 1)-grams' light hash, set for those that occur at least twice.  A window that begins or ends with
+// one that occurs once occurs once itself: it is counted and leaves no record.
 template <int N, int C, int TH>
 __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, u64 T, int bits, u32 parts,
-                                                u64* __restrict__ rec, uint16_t* __restrict__ offs) {
+                                                const u32* __restrict__ twice, int twice_bits, u64* distinct, u64* __restrict__ rec,
+                                                uint16_t* __restrict__ offs) {
     constexpr int W = C / TH;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     u32* s_slot = reinterpret_cast<u32*>(lds);
@@ -77,6 +92,41 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
     for (int i = tid; i < 2 * C / 4; i += TH) reinterpret_cast<uint4*>(s_slot)[i] = make_uint4(0, 0, 0, 0);
     for (u32 i = tid; i < parts; i += TH) s_hist[i] = 0;
     __syncthreads();
+    if (N > 2 && twice) {
+        u32 word[W], bit[W], word64[W], bit64[W];          // of the lane's positions, and (lane 0) of the one past the wave's 64
+        auto where = [&](int i, u32& word_, u32& bit_) __attribute__((always_inline)) {
+            u32 h = 0;
+#pragma unroll
+            for (int j = 0; j < N - 1; ++j) h = light_step(h, s_tok[i + j], j);
+            h = light_end(h) >> (32 - twice_bits);
+            word_ = twice[h >> 5];
+            bit_ = h & 31;
+        };
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            where(w * TH + tid, word[w], bit[w]);
+            word64[w] = bit64[w] = 0;
+            if (lane == 0) where(w * TH + tid + 64, word64[w], bit64[w]);
+        }
+        u32 gone = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const u64 here = __ballot((word[w] >> bit[w]) & 1);
+            const u64 next = __ballot((word64[w] >> bit64[w]) & 1);
+            const u64 both = here & ((here >> 1) | (next << 63));
+            if (((inside >> w) & 1) && !((both >> lane) & 1)) gone |= 1u << w;
+        }
+        inside &= ~gone;
+        u32 n = (u32)__popc(gone);
+        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+        if (lane == 0) s_wave[tid >> 6] = n;
+        __syncthreads();
+        if (tid == 0) {
+            u32 all = 0;
+            for (int w = 0; w < TH / 64; ++w) all += s_wave[w];
+            if (all) atomicAdd(distinct, (u64)all);
+        }
+    }
 
     // ---- equal windows merged: a lane probes once per turn and takes its next window as soon as it is done with one
     u32 mine = 0;                                          // bit w: the window claimed a slot, s_claim[w TH + tid]
@@ -90,10 +140,10 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
                 inside &= inside - 1;
 #pragma unroll
                 for (int j = 0; j < N; ++j) t[j] = s_tok[i + j];
-                u32 h = t[0];
+                u32 h = 0;
 #pragma unroll
-                for (int j = 1; j < N; ++j) h ^= (t[j] << (13 * j % 32)) | (t[j] >> (32 - 13 * j % 32));      // (never by 0 or 32)
-                idx = (h * 0x9E3779B1u) >> (31 - __builtin_ctz(C));
+                for (int j = 0; j < N; ++j) h = light_step(h, t[j], j);
+                idx = light_end(h) >> (31 - __builtin_ctz(C));
                 busy = true;
             }
             if (__ballot(busy) == 0) break;
@@ -181,6 +231,9 @@ struct PartitionArgs {
     u64 T;
     int32_t bits, n0;          // n0 + blockIdx.y = order of the launch's block
     u32 parts, row;            // row = parts + 1, rounded up: a chunk's offsets
+    const u32* twice;          // nullable: [2^twice_bits / 32], see partition_chunk
+    int32_t twice_bits;
+    u64* distinct;             // += n-grams that left no record
     size_t order_recs;         // 8-byte words of an order's records
     u64* rec;                  // [orders][chunks C] of 8 bytes, or 16 for keys of more than 64 bits
     uint16_t* offs;            // [orders][chunks][row]
@@ -193,13 +246,13 @@ __global__ __launch_bounds__(TH) void k_partition(PartitionArgs a) {
     u64* const rec = a.rec + blockIdx.y * a.order_recs;
     uint16_t* const offs = a.offs + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * a.row;
     switch (n) {
-        case 2: partition_chunk<2, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
-        case 3: partition_chunk<3, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
-        case 4: partition_chunk<4, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
-        case 5: partition_chunk<5, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
-        case 6: partition_chunk<6, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
-        case 7: partition_chunk<7, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
-        default: partition_chunk<8, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, rec, offs); break;
+        case 2: partition_chunk<2, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 3: partition_chunk<3, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 4: partition_chunk<4, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 5: partition_chunk<5, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 6: partition_chunk<6, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 7: partition_chunk<7, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        default: partition_chunk<8, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
     }
 }
 
@@ -240,6 +293,8 @@ struct TablesArgs {
     u32 p_min, rounds;         // rounds: ranges that a partition is cut into from the start
     u64* counters;             // [0] distinct n-grams, [1] kept n-grams, [TASC_COUNT_FAILED] set where a partition could not be cut fine enough
     TascKept kept;
+    u32* twice;                // nullable: see k_partition
+    int32_t twice_bits;
     TascGram* best;            // [orders][parts] the partition's n-gram with the largest count, smallest tuple among equals
 };
 
@@ -259,7 +314,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     u64* s_hi = s_key + SLOTS;                                                 // WIDE only: {1 : 7, low 57 bits of hi}; 0 = nobody's yet
     u32* s_cnt = reinterpret_cast<u32*>(s_key + RW * SLOTS);
     u64* s_rec = reinterpret_cast<u64*>(lds + table_bytes<WIDE>());            // first where they are, then the records
-    __shared__ u32 s_full, s_wave[2][kTabThreads / 64];
+    __shared__ u32 s_full, s_nn, s_wave[2][kTabThreads / 64];
     __shared__ u64 s_at;
     const int tid = threadIdx.x, lane = tid & 63;
     auto hi_of = [&](u64 key, int i) { return WIDE ? ((key & 0x7F) << 57) | (s_hi[i] & kLow57) : 0ull; };
@@ -271,7 +326,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     u32 den = a.rounds, num = 0;                           // the range of the partition that is being counted: num / den
     while (num < den) {
         for (int i = tid; i < table_bytes<WIDE>() / 16; i += kTabThreads) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
-        if (tid == 0) s_full = 0;
+        if (tid == 0) s_full = s_nn = 0;
         for (u32 c0 = 0; c0 < a.chunks; c0 += runs * kTabThreads) {
             // the thread's runs and their place among the records of these chunks
             u32 at[kRuns], len[kRuns], sum = 0, total;
@@ -378,6 +433,16 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
             continue;
         }
         u32 keep = 0, most = 0;
+        auto set_bit = [&](int i) {
+            const u64 hi = hi_of(s_key[i], i), lo = tasc_hash_lo(hash_of(s_key[i], part, a.parts), hi);
+            u32 h = 0;
+            for (int j = 0; j < a.n; ++j) {
+                const u32 t = tasc_key_get(lo, hi, j, a.bits), r = 13 * j % 32;
+                h ^= r == 0 ? t : (t << r) | (t >> (32 - r));
+            }
+            h = light_end(h) >> (32 - a.twice_bits);
+            atomicOr(&a.twice[h >> 5], 1u << (h & 31));
+        };
 #pragma unroll
         for (int s = 0; s < PER; ++s) {
             const int i = s * kTabThreads + tid;
@@ -385,6 +450,15 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
             ++distinct;
             if (s_cnt[i] >= a.p_min) ++keep;
             most = max(most, s_cnt[i]);
+            if (!BEST && a.twice && s_cnt[i] > 1) {
+                const u32 q = atomicAdd(&s_nn, 1u);
+                if (q < (u32)STAGE) reinterpret_cast<u32*>(s_rec)[q] = i;
+                else set_bit(i);
+            }
+        }
+        if (!BEST && a.twice) {                            // (few slots have a bit to set: one a lane, once they are known)
+            __syncthreads();
+            for (u32 q = tid; q < min(s_nn, (u32)STAGE); q += kTabThreads) set_bit((int)reinterpret_cast<const u32*>(s_rec)[q]);
         }
         if (BEST) {
             // only what has the largest count is taken apart
@@ -478,12 +552,12 @@ u32 up64(u32 v) { return (v + 63) / 64 * 64; }
 // Chunks of 8192 positions merge more windows (of 32 M tokens 0.55 / 0.84 of the 2- / 5-grams are left, 0.65 / 0.89 with 2048)
 // and leave longer runs of a partition, but they need 2 M tokens to fill the chip.  A partition is as many windows as there
 // are LDS slots: about half of a corpus' windows are distinct (0.21 to 0.51 of the 2- to 5-grams of 24 M tokens), and where
-// nearly all are, it is cut in two.  Offsets are turned round where there are many chunks.
-TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide) {
+// nearly all are, it is cut in two; twice as many where most of the unique ones leave no record.  Offsets are turned round where there are many chunks.
+TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide, bool pruned) {
     TascCountPlan p;
     p.chunk = T >= (u64)256 * kChunkLarge ? kChunkLarge : kChunkSmall;
     p.chunks = (u32)((T + p.chunk - 1) / p.chunk);
-    const u64 per = wide ? kSlotsWide : kSlotsNarrow;
+    const u64 slots = wide ? kSlotsWide : kSlotsNarrow, per = pruned ? 2 * slots : slots;
     p.parts = (u32)std::clamp<u64>((windows + per - 1) / per, TASC_COUNT_MIN_PARTS, TASC_COUNT_MAX_PARTS);
     p.rounds = (u32)std::max<u64>(1, windows / p.parts / per);
     p.rec_bytes = (size_t)p.chunks * p.chunk * (wide ? 16 : 8);
@@ -491,10 +565,18 @@ TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide) {
     return p;
 }
 
+// a bit for every two tokens or so: of 24 M tokens' windows, the distinct n-grams that occur more than once are 2 to 3 %, and the map of 32 M
+// tokens lies in an XCD's L2 (8 instead of 2 MB: k_partition 498 / 563 / 583 us for orders 3 to 5, 469 / 523 / 533 so)
+int tasc_twice_bits(u64 T) {
+    int b = 16;
+    while (b < 32 && (1ull << b) < T / 2) ++b;
+    return b;
+}
+
 tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, const uint8_t* d_last, u64 T, const u64* d_T, int32_t n0,
-                                 int32_t n_orders, int32_t bits, const TascCountBufs& b, hipStream_t st) {
+                                 int32_t n_orders, int32_t bits, const TascCountBufs& b, const u32* d_twice, u64* d_counters, hipStream_t st) {
     const u32 row = up64(p.parts + 1);
-    PartitionArgs a{d_tok, d_T, d_last, T, bits, n0, p.parts, row, p.rec_bytes / sizeof(u64), b.rec, b.offs};
+    PartitionArgs a{d_tok, d_T, d_last, T, bits, n0, p.parts, row, d_twice, tasc_twice_bits(T), d_counters, p.rec_bytes / sizeof(u64), b.rec, b.offs};
     const size_t lds = partition_lds(p.chunk, p.parts);
     auto launch = [&](auto kernel, int threads) -> tasc_status {
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -521,12 +603,14 @@ static TablesArgs tables_args(const TascCountPlan& p, const u64* d_T, int32_t n,
     const bool turned = p.chunk == kChunkLarge;
     return TablesArgs{b.rec, turned ? b.offs + (size_t)n_orders * col * row : b.offs, p.rec_bytes / sizeof(u64),
                       turned ? (size_t)col * row : (size_t)p.chunks * row, turned ? 1 : row, turned ? col : 1,
-                      p.chunks, p.chunk, p.parts, d_T, n, bits, p_min, p.rounds, d_counters, kept, d_best};
+                      p.chunks, p.chunk, p.parts, d_T, n, bits, p_min, p.rounds, d_counters, kept, nullptr, 0, d_best};
 }
 
 tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u32 p_min, const TascCountBufs& b, u64* d_counters,
-                              const TascKept& kept, hipStream_t st) {
-    const TablesArgs a = tables_args(p, nullptr, n, 1, bits, p_min, b, d_counters, kept, nullptr);
+                              const TascKept& kept, u32* d_twice, u64 T, hipStream_t st) {
+    TablesArgs a = tables_args(p, nullptr, n, 1, bits, p_min, b, d_counters, kept, nullptr);
+    a.twice = d_twice;
+    a.twice_bits = tasc_twice_bits(T);
     auto launch = [&](auto kernel, int lds) -> tasc_status {
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         kernel<<<dim3(p.parts), dim3(kTabThreads), lds, st>>>(a);

@@ -260,16 +260,17 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
     while ((1ll << bits) < vocab) ++bits;
     TASC_REQUIRE(n_max * bits <= 128, "ngram_build: n_max %d x %d bits per token exceeds the 128-bit key", n_max, bits);
     TASC_REQUIRE(doc_offsets[0] == 0, "ngram_build: doc_offsets[0] != 0");
-    u64 windows[TASC_MAX_ORDER + 1] = {0};                     // per order, from the document lengths
+    u64 windows[TASC_MAX_ORDER + 1] = {0};                     // per order, from the document lengths: first what short documents lack
     for (int64_t d = 0; d < n_docs; ++d) {
         const int64_t len = doc_offsets[d + 1] - doc_offsets[d];
+        if (len >= n_max - 1) continue;
         TASC_REQUIRE(len >= 0, "ngram_build: doc_offsets decrease at %lld", (long long)d);
-        for (int n = 2; n <= n_max; ++n)
-            if (len >= n) windows[n] += (u64)(len - n + 1);
+        for (int n = 2; n <= n_max; ++n) windows[n] += (u64)std::max<int64_t>(0, n - 1 - len);
     }
     const u64 T = (u64)doc_offsets[n_docs];
     TASC_REQUIRE(T < 0xFFFFFFFFull, "ngram_build: corpus of %llu tokens is too large", T);
     TASC_REQUIRE(T == 0 || tokens != nullptr, "ngram_build: null tokens");
+    for (int n = 2; n <= n_max; ++n) windows[n] += T - (u64)(n - 1) * (u64)n_docs;
     hipStream_t st = (hipStream_t)stream;
 
     Cleanup tmp;
@@ -315,14 +316,16 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
     const size_t at_copies = carve(T > 0 ? (size_t)vocab * sizeof(u32) * uni_slices : 0);
     const bool any = windows[2] > 0;
     const size_t at_last = carve(any ? T : 0), at_off = carve(any ? (size_t)(n_docs + 1) * sizeof(int64_t) : 0);
+    // (with p_min 1 every n-gram is kept, the unique ones too)
+    const bool prune = p_min > 1;
     size_t rec_bytes = 0, offs_bytes = 0;
     for (int n = 2; n <= n_max; ++n) {
         if (windows[n] == 0) continue;
-        const TascCountPlan p = tasc_count_plan(T, windows[n], n * bits > 64);
+        const TascCountPlan p = tasc_count_plan(T, windows[n], n * bits > 64, prune && n > 2);
         rec_bytes = std::max(rec_bytes, p.rec_bytes);
         offs_bytes = std::max(offs_bytes, p.offs_bytes);
     }
-    const size_t at_rec = carve(rec_bytes), at_roff = carve(offs_bytes);
+    const size_t at_rec = carve(rec_bytes), at_roff = carve(offs_bytes), twice_bytes = any && prune ? ((size_t)1 << tasc_twice_bits(T)) / 8 : 0, at_twice = carve(2 * twice_bytes);
     const size_t list_bytes = (size_t)g_tasc_config.build_list_kib << 10;
     size_t at_list[TASC_MAX_ORDER + 1] = {0}, lists = 0, longest = 0;
     int group_end[TASC_MAX_ORDER + 2] = {0};                   // [n] = one past the last order of the group that n begins
@@ -392,10 +395,14 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
             if (windows[n] == 0) continue;
             TASC_TRY(event(&evc[n][0]));
             TASC_TRY(event(&evc[n][1]));
-            const TascCountPlan p = tasc_count_plan(T, windows[n], n * bits > 64);
+            const TascCountPlan p = tasc_count_plan(T, windows[n], n * bits > 64, prune && n > 2);
+            // the map of the order below is read while this order's is filled, if there is one above it
+            u32* const below = prune && n > 2 ? (u32*)(arena + at_twice + (n & 1) * twice_bytes) : nullptr;
+            u32* const mine = prune && n < n_max ? (u32*)(arena + at_twice + (1 - (n & 1)) * twice_bytes) : nullptr;
             TASC_HIP(hipEventRecord(evc[n][0], st));
-            TASC_TRY(tasc_count_partition(p, d_tok, d_last, T, nullptr, n, 1, bits, bufs, st));
-            TASC_TRY(tasc_count_tables(p, n, bits, (u32)p_min, bufs, d_counters[n], kept_of(n), st));
+            if (mine) TASC_HIP(hipMemsetAsync(mine, 0, twice_bytes, st));
+            TASC_TRY(tasc_count_partition(p, d_tok, d_last, T, nullptr, n, 1, bits, bufs, below, &d_counters[n][0], st));
+            TASC_TRY(tasc_count_tables(p, n, bits, (u32)p_min, bufs, d_counters[n], kept_of(n), mine, T, st));
             TASC_HIP(hipEventRecord(evc[n][1], st));
         }
         TASC_HIP(hipMemcpyAsync(h_counters, d_counters, sizeof h_counters, hipMemcpyDeviceToHost, st));

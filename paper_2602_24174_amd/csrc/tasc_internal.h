@@ -111,15 +111,18 @@ struct TascGram {             // one n-gram; count 0 = none
     u64 lo, hi;
     u32 count, n;
 };
-// wide: keys of more than 64 bits (a call of several orders takes the plan of its longest)
-TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide);
+// wide: keys of more than 64 bits (a call of several orders takes the plan of its longest); pruned: with the order below at hand
+TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide, bool pruned);
+int tasc_twice_bits(u64 T);   // log2 of the bits of a `twice` map
 // Records of the orders n0 .. n0 + n_orders - 1.  last[i] = 1 where position i ends a document, as the corpus' last one does;
-// d_T (nullable): the corpus' length in device memory, no more than T.
+// d_T (nullable): the corpus' length in device memory, no more than T.  d_twice (nullable, one order only): the map that
+// tasc_count_tables filled for the order below; n-grams that it shows to occur once leave no record but are added to d_counters[0].
 tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, const uint8_t* d_last, u64 T, const u64* d_T, int32_t n0,
-                                 int32_t n_orders, int32_t bits, const TascCountBufs& b, hipStream_t st);
-// Finished counts of one order: d_counters[0] += distinct n-grams, [1] += those of at least p_min, which go to `kept`
+                                 int32_t n_orders, int32_t bits, const TascCountBufs& b, const u32* d_twice, u64* d_counters, hipStream_t st);
+// Finished counts of one order: d_counters[0] += distinct n-grams, [1] += those of at least p_min, which go to `kept`; d_twice
+// (nullable, cleared): a bit is set for every n-gram that occurs more than once
 tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u32 p_min, const TascCountBufs& b, u64* d_counters,
-                              const TascKept& kept, hipStream_t st);
+                              const TascKept& kept, u32* d_twice, u64 T, hipStream_t st);
 // The most frequent n-gram of every partition (smallest tuple among equals): d_best[n_orders][parts]
 tasc_status tasc_count_best(const TascCountPlan& p, const u64* d_T, int32_t n0, int32_t n_orders, int32_t bits, const TascCountBufs& b,
                             u64* d_counters, TascGram* d_best, hipStream_t st);

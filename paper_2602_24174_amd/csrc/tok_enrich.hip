@@ -301,7 +301,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     u64 windows = 0;                                         // of order 2, the most of any
     for (int64_t d = 0; d < n_docs; ++d) windows += (u64)std::max<int64_t>(0, doc_offsets[d + 1] - doc_offsets[d] - 1);
     const int orders = n_max - 1;
-    const TascCountPlan plan = tasc_count_plan(T0, windows, n_max * bits > 64);
+    const TascCountPlan plan = tasc_count_plan(T0, windows, n_max * bits > 64, false);
     const bool run = budget > 0 && T0 > 0;
     Arena ar;
     const size_t at_state = ar.carve(sizeof(State)), at_counters = ar.carve(8 * sizeof(u64)), at_len = ar.carve(((size_t)budget + 1) * sizeof(u64));
@@ -346,7 +346,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         for (; done < end; ++done) {
             int32_t* const cur = tok[done & 1];
             const uint8_t* const cur_last = last[done & 1];
-            TOK_TRY(tasc_count_partition(p, cur, cur_last, T, len + done, 2, orders, bits, bufs, st));
+            TOK_TRY(tasc_count_partition(p, cur, cur_last, T, len + done, 2, orders, bits, bufs, nullptr, counters, st));
             TOK_TRY(tasc_count_best(p, len + done, 2, orders, bits, bufs, counters, best, st));
             k_pick<<<dim3(1), dim3(kPickThreads), 0, st>>>(best, (u32)orders * p.parts, bits, vocab, counters, state, d_merges);
             k_select<<<grid1, dim3(kThreads), 0, st>>>(cur, cur_last, len + done, state, sel);

@@ -84,3 +84,23 @@ def test_enrichment_of_a_long_corpus():
     assert merges[0][0] == (9, 9), merges
     tok, off = _corpus("phrases", 6000, 50)
     _run_and_compare(T, [tok[a:b].tolist() for a, b in zip(off[:-1], off[1:])], 50, 3, 40)
+
+
+@pytest.mark.parametrize("length", [8191, 8192, 8256, 70_001])
+def test_unique_grams_leave_no_record(length):
+    """p_min 1 keeps every n-gram, p_min 2 counts the unique ones of the higher orders without looking at them: the same distinct
+    n-grams, the same counts, whatever lies across a wave's 64 positions or a chunk's end."""
+    import paper_2602_24174_amd as T
+    rng = np.random.default_rng(length)
+    tok = rng.integers(0, 40, length)
+    tok[rng.random(length) < 0.3] = rng.integers(0, 100_000)
+    hit = rng.random(length) < 0.1
+    tok[hit] = rng.integers(0, 100_000, int(hit.sum()))
+    off = np.concatenate([[0], np.sort(rng.integers(0, length, 30)), [length]]).astype(np.int64)
+    tok = tok.astype(np.int32)
+    a, b = (T.tasc_ngram_build(tok, off, 100_000, 7, p) for p in (1, 2))
+    sa, sb = T.tasc_ngram_get_stats(a), T.tasc_ngram_get_stats(b)
+    for n in range(2, 8):
+        ra, ca = T.tasc_ngram_export(a, n)
+        rb, cb = T.tasc_ngram_export(b, n)
+        assert sa.distinct[n] == sb.distinct[n] == len(ca) and (ra[ca > 1] == rb).all() and (ca[ca > 1] == cb).all()
