@@ -321,6 +321,8 @@ tasc_status tiled_ready(int* cus) {
     if ((rc = tiled_attrs<TEPI_ROPE>()) != TASC_OK) return rc;
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_staged<2>), hipFuncAttributeMaxDynamicSharedMemorySize, TA_LDS_BYTES(64) + 4 * TA_MAX_BLOCKS));
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_staged<4>), hipFuncAttributeMaxDynamicSharedMemorySize, TA_LDS_BYTES(128) + 4 * TA_MAX_BLOCKS));
+    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_prompt<2>), hipFuncAttributeMaxDynamicSharedMemorySize, TA_LDS_BYTES(64) + 4 * TA_MAX_BLOCKS));
+    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_prompt<4>), hipFuncAttributeMaxDynamicSharedMemorySize, TA_LDS_BYTES(128) + 4 * TA_MAX_BLOCKS));
     ds.tiled_ready = true;
     return TASC_OK;
 }
@@ -383,6 +385,12 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
     const int att_passes = decode ? 1 : (s->prompt_ref / s->batch * (H / Hkv) + 63) / 64;
     int att_chunks = 512 / (s->batch * Hkv * att_passes);
     att_chunks = att_chunks < 1 ? 1 : (att_chunks > 4 ? 4 : att_chunks);
+    // Prompt chunks that need no key chunks go 128 (row, head) pairs a workgroup where that is a workgroup per compute unit; a session
+    // constant as well (the two kernels' sums are not the same bits).  2 layers of the 0.5B, 1.5B and 3B shapes, 64 | 128 pairs: from 256
+    // workgroups on 0.99 to 1.32 times as fast (1 prompt of 8192: 1479 | 1119, 2610 | 2141, 3667 | 3085 us; 32 of 64: 320 | 321, 531 | 534,
+    // 798 | 793), with 146 to 224 of them 0.98 to 1.02 times (4 of 512: 354 | 354, 558 | 564, 811 | 825; 1 of 2048: 423 | 414, 725 | 712, 955 | 932).
+    const int prompt_passes = (s->prompt_ref / s->batch * (H / Hkv) + TAP_ROWS - 1) / TAP_ROWS;
+    const bool prompt_attn = !decode && att_chunks == 1 && s->batch * Hkv * prompt_passes >= cus;
     const BiasCursors bc{BiasCsr{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base}, d.sel_tok,
                          m->bias_rowptr ? n_sel * (s->n_strips + 1) : 0, s->n_strips, d.bias_ptr, d.bias_first, d.bias_base};
     const unsigned bias_wgs = (unsigned)((bc.n + 255) / 256);
@@ -486,6 +494,10 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
                     if (hd == 64) k_attn_tiled<2><<<attn_grid, dim3(SMALL_THREADS), 0, st>>>(aa);
                     else if (hd == 128) k_attn_tiled<4><<<attn_grid, dim3(SMALL_THREADS), 0, st>>>(aa);
                     else k_attn_tiled<1><<<attn_grid, dim3(SMALL_THREADS), 0, st>>>(aa);
+                } else if (prompt_attn) {
+                    const dim3 grid(nb * Hkv, (nq * (H / Hkv) + TAP_ROWS - 1) / TAP_ROWS);
+                    if (hd == 64) k_attn_prompt<2><<<grid, dim3(TAP_THREADS), TA_LDS_BYTES(64) + 4 * s->max_blocks, st>>>(aa);
+                    else k_attn_prompt<4><<<grid, dim3(TAP_THREADS), TA_LDS_BYTES(128) + 4 * s->max_blocks, st>>>(aa);
                 } else {
                     // keys and values staged in LDS, 64 rows per pass; the key tiles are dealt to att_chunks workgroups, a
                     // number fixed by the session's batch (it sets the order in which a row's keys are added)

@@ -1063,6 +1063,200 @@ __global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(4
     }
 }
 
+// ---------------------------------------------------------------- attention of long prompt chunks
+// One workgroup per (sequence, KV head, pass of 128 (row, head) pairs), all its keys; a wave has 32 pairs, two workgroups fit a compute
+// unit.  Key tiles of 64 at absolute positions.  S^T = K Q^T and O^T = V^T P^T with 32x32x16 MFMAs: a lane holds 32 scores of one pair,
+// so a maximum takes one exchange between lane halves a tile, and the key rows are parked so that a lane's scores are those of 8
+// consecutive keys twice per block of 32, which is how the second product takes them from its registers.
+// What costs k_attn_staged its time: a wave has 16 pairs by 32 keys of a tile, corrects 8 sums per lane for every 8 scores, masks every
+// tile and waits for each of its products.  Here
+//  - the loop runs one tile ahead with the scores: their products are issued between this tile's exponentials (the order is fixed by
+//    hand, operands are read from LDS three products early);
+//  - a pair's sums are corrected when its maximum has grown by more than 8 (the weights then are at most 2^8, which costs no
+//    precision: they and their sums are floating point), decided for each pair by itself, so its bits do not depend on its neighbours;
+//  - only tiles that reach past a wave's first position are masked;
+//  - workgroup x of pass y takes sequence and head x + y, so that one sequence's passes are spread over the dies: where only some
+//    prompts are long the dies that hold the others' rows would be idle (the last chunk of the figures below: 156 -> 105 us).
+// 1.5B shape, 16 prompts of 1024 to 2048 tokens, four layers: k_attn_staged 1950 us, this one 1043.  What bounds it: LDS reads (a product of
+// 32 cycles takes 1 KB of keys or values, and four SIMDs' products take all that LDS delivers); a tile takes about twice as long as
+// that, and the 608 workgroups of an even chunk are 1.2 rounds of the 512 that fit.  Tried: 64 pairs a wave, one wave a SIMD (half the
+// LDS reads, but 400 registers: 1.6 times the time); lines of a tile requested three tiles early (no gain); 8 waves a workgroup (the same).
+#define TAP_ROWS 128
+#define TAP_THREADS 256
+template <int NKS>
+__global__ __launch_bounds__(TAP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_prompt(AttnArgs a) {
+    constexpr int hd = 32 * NKS, KS = hd / 16, DB = hd / 32;         // k-steps of the first product, blocks of 32 output dimensions
+    constexpr int KLD = hd + TA_KPAD, VLD = 64 + TA_KPAD;
+    constexpr int LPT = 64 * hd / 8 / TAP_THREADS;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    uint16_t* sK = reinterpret_cast<uint16_t*>(lds);                 // [2][64][KLD]
+    uint16_t* sV = sK + 2 * 64 * KLD;                                // [2][hd][VLD]
+    int32_t* s_bt = reinterpret_cast<int32_t*>(lds + TA_LDS_BYTES(hd));
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 31, h = lane >> 5;
+    const int Gq = a.H / a.Hkv;
+    const int y = gridDim.y - 1 - blockIdx.y, xg = (blockIdx.x + y) % gridDim.x;          // the longest first; a sequence's passes on several dies
+    const int b = a.b0 + xg / a.Hkv, g = xg % a.Hkv;
+    const int r0 = y * TAP_ROWS;
+    const int nr = a.n_rows[b], p0 = a.pos0[b], row_b = a.row0[b] - a.first, R = nr * Gq;
+    if (r0 >= R) return;                                             // a shorter sequence: no rows in this pass
+    const int32_t* bt = a.block_tab + (size_t)b * a.max_blocks;
+    const size_t v_off = (size_t)a.Hkv * TASC_KV_BLOCK * hd;
+    const int n_tiles = (p0 + (min(r0 + TAP_ROWS, R) - 1) / Gq) / 64 + 1;
+    for (int i = tid; i < min(4 * n_tiles, a.max_blocks); i += TAP_THREADS) s_bt[i] = bt[i];
+    // the lane's pair; past the end the last one again, which nobody stores
+    const int w0 = r0 + 32 * wave, r = w0 + m, rc = min(r, R - 1), qi = p0 + rc / Gq;
+    const int first = p0 + min(w0, R - 1) / Gq;                                     // (position of the wave's first pair)
+    const size_t out_at = ((size_t)(row_b + rc / Gq) * a.H + g * Gq + rc % Gq) * hd;
+    bf16x8 qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(a.q + out_at + 16 * ks + 8 * h);
+    __syncthreads();
+    const int pg_last = min(4 * n_tiles, a.max_blocks) - 1;
+    u32x4 rk[LPT], rv[LPT];
+    // a wave's chunks u of the keys and of the values are of one page
+    auto page_of = [&](int t, int u) __attribute__((always_inline)) {
+        const int id = __builtin_amdgcn_readfirstlane(s_bt[min(4 * t + (64 * wave + TAP_THREADS * u) / (2 * hd), pg_last)]);
+        return a.kv_layer + (size_t)id * a.page_elems;
+    };
+    auto fetch_k = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const int q = tid + TAP_THREADS * u, key = q / (hd / 8), dch = q % (hd / 8);
+            rk[u] = *reinterpret_cast<const u32x4*>(page_of(t, u) + g * TASC_KV_BLOCK * hd + (key % TASC_KV_BLOCK) * hd + 8 * dch);
+        }
+    };
+    auto fetch_v = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const int q = tid + TAP_THREADS * u, dim = (q % (2 * hd)) / 2, half = q % 2;
+            rv[u] = *reinterpret_cast<const u32x4*>(page_of(t, u) + v_off + g * hd * TASC_KV_BLOCK + dim * TASC_KV_BLOCK + 8 * half);
+        }
+    };
+    auto park_k = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const int q = tid + TAP_THREADS * u, key = q / (hd / 8), dch = q % (hd / 8);
+            const int krow = (key & 0x33) | ((key & 4) << 1) | ((key & 8) >> 1);         // rows 8 b + 4 h + x of 16 hold keys 8 h + 4 b + x
+            *reinterpret_cast<u32x4*>(sK + (size_t)(buf * 64 + krow) * KLD + 8 * dch) = rk[u];
+        }
+    };
+    auto park_v = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const int q = tid + TAP_THREADS * u, vp = q / (2 * hd), dim = (q % (2 * hd)) / 2, half = q % 2;
+            *reinterpret_cast<u32x4*>(sV + (size_t)(buf * hd + dim) * VLD + TASC_KV_BLOCK * vp + 8 * half) = rv[u];
+        }
+    };
+    const float c = a.scale * 1.44269504088896f;                     // scores in units of log2 e
+    float mx = -3.4028235e38f, lsum = 0.f;                           // the pair's maximum (finite: a difference from -inf stays -inf); the lane half's share of its sum
+    f32x16 o[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[d][e] = 0.f;
+    auto scores = [&](int buf, int k, f32x16& s) __attribute__((always_inline)) {
+        const uint16_t* kb = sK + (size_t)(buf * 64 + 32 * k + m) * KLD + 8 * h;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kb + 16 * ks), qf[ks], s, 0, 0, 0);
+    };
+    // tile t's scores are in s; leaves those of tile t + 1 there
+    f32x16 s[2];
+    auto multiply = [&](int t, auto masked) __attribute__((always_inline)) {
+        if (masked) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int key = 64 * t + 32 * k + 16 * (e >> 3) + 8 * h + (e & 7);
+                    if (key > qi) s[k][e] = -INFINITY;
+                }
+        }
+        float tm = s[0][0];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) tm = fmaxf(tm, s[k][e]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tm), __float_as_uint(tm), false, false);
+        tm = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c;
+        if (__ballot(tm > mx + 8.f) != 0) {
+            const float mn = tm > mx + 8.f ? tm : mx, corr = __builtin_amdgcn_exp2f(mx - mn);
+            lsum *= corr;
+#pragma unroll
+            for (int d = 0; d < DB; ++d) o[d] *= corr;
+            mx = mn;
+        }
+        // products in the order: scores of the next tile's first 32 keys, the sums of this tile's weights, scores of the next 32 keys
+        constexpr int N = 2 * KS + 4 * DB;
+        const uint16_t* kb = sK + (size_t)(((t + 1) & 1) * 64 + m) * KLD + 8 * h;
+        const uint16_t* vb = sV + (size_t)((t & 1) * hd + m) * VLD + 8 * h;
+        auto operand = [&](int i) __attribute__((always_inline)) {
+            const uint16_t* at = i < KS ? kb + 16 * i
+                               : i < KS + 4 * DB ? vb + (size_t)32 * ((i - KS) % DB) * VLD + 16 * ((i - KS) / DB) : kb + (size_t)32 * KLD + 16 * (i - KS - 4 * DB);
+            return *reinterpret_cast<const bf16x8*>(at);
+        };
+        f32x16 next, zero;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+        uint32_t w[16];
+        bf16x8 fr[4];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) fr[i] = operand(i);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (i + 3 < N) fr[(i + 3) & 3] = operand(i + 3);
+            const bf16x8 f = fr[i & 3];
+            if (i < KS) next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[i], i ? next : zero, 0, 0, 0);
+            else if (i < KS + 4 * DB) {
+                const int d = (i - KS) % DB, x = (i - KS) / DB;
+                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, as_bf16x8(w[4 * x], w[4 * x + 1], w[4 * x + 2], w[4 * x + 3]), o[d], 0, 0, 0);
+            } else s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[i - KS - 4 * DB], i > KS + 4 * DB ? s[1] : zero, 0, 0, 0);
+            // 16 pairs of weights over the first KS + 3 DB products: those of a sum are ready when its turn comes
+#pragma unroll
+            for (int j = 16 * i / (KS + 3 * DB); j < 16 && j < 16 * (i + 1) / (KS + 3 * DB); ++j) {
+                const int k = j / 8, e = 2 * (j % 8);
+                w[j] = f2bf_pair(__builtin_amdgcn_exp2f(fmaf(s[k][e], c, -mx)), __builtin_amdgcn_exp2f(fmaf(s[k][e + 1], c, -mx)));
+                lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(tasc_bf16x2, w[j]), __builtin_bit_cast(tasc_bf16x2, 0x3F803F80u), lsum, false);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        s[0] = next;
+    };
+    fetch_k(0);
+    fetch_v(0);
+    park_k(0);
+    park_v(0);
+    fetch_k(1);
+    park_k(1);
+    __syncthreads();
+    scores(0, 0, s[0]);
+    scores(0, 1, s[1]);
+    __syncthreads();
+    auto tile = [&](int t, auto masked) __attribute__((always_inline)) {
+        fetch_k(t + 2);
+        fetch_v(t + 1);
+        multiply(t, masked);
+        park_k(t & 1);
+        park_v((t + 1) & 1);
+        __syncthreads();
+    };
+    const int n_whole = min((first + 1) / 64, n_tiles);
+    int t = 0;
+    for (; t < n_whole; ++t) tile(t, std::false_type{});
+    for (; t < n_tiles; ++t) tile(t, std::true_type{});
+    lsum += __shfl_xor(lsum, 32);
+    if (r >= R) return;
+    const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;                // (0: every score was -inf)
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<u32x2*>(a.att + out_at + 32 * d + 8 * q + 4 * h) =
+                pack_bf16x4(o[d][4 * q] * inv, o[d][4 * q + 1] * inv, o[d][4 * q + 2] * inv, o[d][4 * q + 3] * inv);
+}
+
 // adds the key chunks of k_attn_staged in the order c = 0, 1, ..: one thread per (row, head, 4 dims), all its loads at once (a chunk
 // after the other 3.8 us for 224 rows of 896, 2.6 to 4.5 so)
 template <int C>
