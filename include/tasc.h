@@ -409,8 +409,8 @@ tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem where, int3
  *   corpus_len          HOST int64[budget + 1]: corpus length before merge i; entry *n_merges = final.
  *   n_merges            HOST: merges performed (<= budget).
  * Limits: n_max in [2, TASC_MAX_ORDER], n_max * ceil(log2(vocab + budget)) <= 128, corpus < 2^32 - 1
- * tokens.  Synchronous (two host round trips per merge: the pick, and the new offsets); allocates about 20 bytes of device
- * scratch per corpus token plus one counting table (8-byte slots, 1.5 to 3 per 2-gram window).  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
+ * tokens.  Synchronous (the host looks at the device once per 16 merges); about 14 bytes of device scratch per corpus token
+ * plus 8 per 2-gram window (16 for keys of more than 64 bits).  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
  * ---------------------------------------------------------------------------------------- */
 tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs, int32_t vocab,
                             int32_t n_max, int32_t budget, tasc_mem where, void* stream, int32_t* merges,
