@@ -338,7 +338,7 @@ __device__ __forceinline__ AttnTile attn_tile(const float* qi, const T* __restri
     AttnTile o;
     const float s = key < L ? dot * scale : -INFINITY;
     o.m = wave_max(s);
-    const float p = key < L ? expf(s - o.m) : 0.f;
+    const float p = key < L ? expf(s - (o.m == -INFINITY ? 0.f : o.m)) : 0.f;      // (every product of a tile can overflow to -inf: weights of 0)
     o.l = wave_sum_dpp(p);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -358,7 +358,7 @@ __device__ __forceinline__ AttnTile attn_tile(const float* qi, const T* __restri
     return o;
 }
 __device__ __forceinline__ void attn_add(float& m, float& l, float& acc, float tm, float tl, float ta) {
-    const float mn = fmaxf(m, tm), c1 = expf(m - mn), c2 = expf(tm - mn);
+    const float mn = fmaxf(m, tm), at = mn == -INFINITY ? 0.f : mn, c1 = expf(m - at), c2 = expf(tm - at);
     l = fmaf(l, c1, tl * c2);
     acc = fmaf(acc, c1, ta * c2);
     m = mn;
