@@ -281,6 +281,18 @@ constexpr int kStageNarrow = 1536, kStageWide = 768;       // records on their w
 constexpr int kRuns = 4;                                   // chunks of a thread at a time
 constexpr u64 kLow57 = (1ull << 57) - 1;
 constexpr int kMaxProbe = 128;                             // a longer probe sequence means a table that is as good as full
+// A range that overflows is cut in two, by the hash down to kFinest ranges of a partition (one value of the hash's upper half each), then
+// by the rest of the key: (hash, hi) is the key, so a range of the finest kind holds one n-gram, and no corpus can fail.  Behind
+// a dense spot the ranges grow again, up to kCoarse times as many as at the start.
+constexpr u32 kFinest = 1u << 24, kCoarse = 8;
+typedef unsigned __int128 u128;
+template <bool WIDE>
+constexpr u128 kPlaces = (u128)1 << (WIDE ? 120 : 56);
+template <bool WIDE>
+__device__ __forceinline__ u128 place_of(u64 rec, u64 hi) {                // of a key among those of one value of the hash's upper half
+    const u64 low = rec >> 8, h = ((low << 24) | (low >> 32)) & ((1ull << 56) - 1);      // (the bits that still differ first)
+    return WIDE ? ((u128)(hi * 0x9E3779B97F4A7C15ull) << 56) | h : h;
+}
 
 struct TablesArgs {
     const u64* rec;
@@ -291,7 +303,7 @@ struct TablesArgs {
     const u64* d_T;            // nullable, as above (chunks is then an upper bound)
     int32_t n, bits;
     u32 p_min, rounds;         // rounds: ranges that a partition is cut into from the start
-    u64* counters;             // [0] distinct n-grams, [1] kept n-grams, [TASC_COUNT_FAILED] set where a partition could not be cut fine enough
+    u64* counters;             // [0] distinct n-grams, [1] kept n-grams
     TascKept kept;
     u32* twice;                // nullable: see k_partition
     int32_t twice_bits;
@@ -316,6 +328,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     u64* s_rec = reinterpret_cast<u64*>(lds + table_bytes<WIDE>());            // first where they are, then the records
     __shared__ u32 s_full, s_nn, s_wave[2][kTabThreads / 64];
     __shared__ u64 s_at;
+    __shared__ u128 s_place, s_places;                     // the part of a finest range that is being counted
     const int tid = threadIdx.x, lane = tid & 63;
     auto hi_of = [&](u64 key, int i) { return WIDE ? ((key & 0x7F) << 57) | (s_hi[i] & kLow57) : 0ull; };
     TascGram best{0, 0, 0, 0};
@@ -324,6 +337,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     const uint16_t* const offs = a.offs + (size_t)part * a.part_step;
 
     u32 den = a.rounds, num = 0;                           // the range of the partition that is being counted: num / den
+    bool within = false;                                   // only s_place .. of it
     while (num < den) {
         for (int i = tid; i < table_bytes<WIDE>() / 16; i += kTabThreads) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
         if (tid == 0) s_full = s_nn = 0;
@@ -388,6 +402,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
                         if (den > 1) {                     // where in the partition: the lower half of the product that chose it
                             const u32 upper = (u32)(hash_of(r, part, a.parts) >> 32);
                             busy = (u32)(((u64)(upper * a.parts) * den) >> 32) == num;
+                            if (within) busy = busy && place_of<WIDE>(r, hi) - s_place < s_places;
                         }
                         key = (r & ~0xFFull) | 0x80 | (hi >> 57);
                         hv = (hi & kLow57) | ~kLow57;
@@ -421,15 +436,16 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
         __syncthreads();
         if (s_full) {                                      // more n-grams than slots: the range in two halves
             __syncthreads();
-            if (den >= 1u << 24) {                         // (n-grams whose hashes agree in all bits that cut partitions: not a corpus)
+            if (den < kFinest) {
+                den *= 2;
+                num *= 2;
+            } else {
                 if (tid == 0) {
-                    atomicOr(&a.counters[TASC_COUNT_FAILED], 1ull);
-                    if (BEST) *best_out = TascGram{0, 0, 0, 0};
+                    if (!within) s_place = 0;
+                    s_places = within ? s_places / 2 : kPlaces<WIDE> / 2;
                 }
-                return;
+                within = true;
             }
-            den *= 2;
-            num *= 2;
             continue;
         }
         u32 keep = 0, most = 0;
@@ -496,8 +512,22 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
                 }
             }
         }
-        ++num;
         __syncthreads();
+        if (within) {                                      // on to the next part, of the largest size that begins there
+            if (tid == 0) {
+                s_place += s_places;
+                s_places = s_place & (~s_place + 1);
+            }
+            __syncthreads();
+            within = s_place != kPlaces<WIDE>;
+            __syncthreads();
+            if (within) continue;
+        }
+        ++num;
+        while (den > kCoarse * a.rounds && num % 2 == 0) {
+            den /= 2;
+            num /= 2;
+        }
     }
     if (BEST) {
         TascGram* s_best = reinterpret_cast<TascGram*>(lds);
@@ -621,8 +651,8 @@ tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u
 }
 
 tasc_status tasc_count_best(const TascCountPlan& p, const u64* d_T, int32_t n0, int32_t n_orders, int32_t bits, const TascCountBufs& b,
-                            u64* d_counters, TascGram* d_best, hipStream_t st) {
-    const TablesArgs a = tables_args(p, d_T, n0, n_orders, bits, 1, b, d_counters, TascKept{}, d_best);
+                            TascGram* d_best, hipStream_t st) {
+    const TablesArgs a = tables_args(p, d_T, n0, n_orders, bits, 1, b, nullptr, TascKept{}, d_best);
     constexpr int lds = std::max(tables_lds<false>(), tables_lds<true>());
     TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tables_best), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     k_tables_best<<<dim3(p.parts, (unsigned)n_orders), dim3(kTabThreads), lds, st>>>(a);

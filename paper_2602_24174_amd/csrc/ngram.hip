@@ -411,10 +411,6 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
         // the finished tables of the group in one block; their context tables are built in the records' memory
         u64 fcap[TASC_MAX_ORDER + 1] = {0}, total = 0, most = 0;
         for (int n = n0; n < group_end[n0]; ++n) {
-            if (h_counters[n][TASC_COUNT_FAILED] != 0) {
-                tasc_set_error("ngram_build: too many %d-grams of one hash", n);
-                return TASC_ESTATE;
-            }
             ng->stats.distinct[n] = (int64_t)h_counters[n][0];
             ng->stats.kept[n] = (int64_t)h_counters[n][1];
             if (h_counters[n][1] == 0) continue;

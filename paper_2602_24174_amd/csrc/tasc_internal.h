@@ -91,7 +91,6 @@ struct tasc_ngram {
 // ---------------------------------------------------------------- exact n-gram counts (count.hip)
 #define TASC_COUNT_MIN_PARTS 256
 #define TASC_COUNT_MAX_PARTS 11264  // their counters fit a workgroup's LDS beside a chunk
-#define TASC_COUNT_FAILED 5         // of an order's counters: a partition that could not be cut fine enough
 
 struct TascCountPlan {
     u32 chunk, chunks;        // corpus positions of a workgroup, and how many such chunks
@@ -125,7 +124,7 @@ tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u
                               const TascKept& kept, u32* d_twice, u64 T, hipStream_t st);
 // The most frequent n-gram of every partition (smallest tuple among equals): d_best[n_orders][parts]
 tasc_status tasc_count_best(const TascCountPlan& p, const u64* d_T, int32_t n0, int32_t n_orders, int32_t bits, const TascCountBufs& b,
-                            u64* d_counters, TascGram* d_best, hipStream_t st);
+                            TascGram* d_best, hipStream_t st);
 // last[0..T) as above (ngram.hip)
 tasc_status tasc_mark_ends(const int64_t* d_off, int64_t n_docs, u64 T, uint8_t* d_last, hipStream_t st);
 

@@ -26,8 +26,8 @@ struct Merge {           // one line of the result, as the caller's arrays have 
     u32 freq;
 };
 struct State {
-    u32 merges, done;    // merges so far; 1: nothing left to merge, or a failure: every later step does nothing
-    u32 bad, failed;     // a token outside the vocabulary; the counting stage gave up
+    u32 merges, done;    // merges so far; 1: nothing left to merge: every later step does nothing
+    u32 bad;             // a token outside the vocabulary
     u32 n, overlaps;     // the running merge: its n-gram, and whether two occurrences of it can overlap
     int32_t t[TASC_MAX_ORDER], new_id;
 };
@@ -41,8 +41,7 @@ __global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __rest
 
 // the best of the partitions' candidates becomes merge number st->merges
 constexpr int kPickThreads = 1024;
-__global__ __launch_bounds__(kPickThreads) void k_pick(const TascGram* __restrict__ cands, u32 count, int bits, int vocab, const u64* __restrict__ counters,
-                                                   State* st, Merge* merges) {
+__global__ __launch_bounds__(kPickThreads) void k_pick(const TascGram* __restrict__ cands, u32 count, int bits, int vocab, State* st, Merge* merges) {
     if (st->done) return;
     TascGram best{0, 0, 0, 0};
     for (u32 i = threadIdx.x; i < count; i += kPickThreads)
@@ -56,9 +55,7 @@ __global__ __launch_bounds__(kPickThreads) void k_pick(const TascGram* __restric
     }
     if (threadIdx.x != 0) return;
     best = s_c[0];
-    const bool failed = counters[TASC_COUNT_FAILED] != 0;
-    if (failed || best.count == 0) {
-        st->failed = failed;
+    if (best.count == 0) {
         st->done = 1;
         return;
     }
@@ -304,7 +301,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     const TascCountPlan plan = tasc_count_plan(T0, windows, n_max * bits > 64, false);
     const bool run = budget > 0 && T0 > 0;
     Arena ar;
-    const size_t at_state = ar.carve(sizeof(State)), at_counters = ar.carve(8 * sizeof(u64)), at_len = ar.carve(((size_t)budget + 1) * sizeof(u64));
+    const size_t at_state = ar.carve(sizeof(State)), at_len = ar.carve(((size_t)budget + 1) * sizeof(u64));
     const size_t at_sel = ar.carve(T0 * sizeof(u32)), zeroed = ar.used;
     const size_t at_tok[2] = {ar.carve(T0 * sizeof(int32_t)), ar.carve(T0 * sizeof(int32_t))}, at_last[2] = {ar.carve(T0), ar.carve(T0)};
     const size_t at_off = ar.carve(((size_t)n_docs + 1) * sizeof(int64_t)), at_ends = ar.carve((size_t)n_docs * sizeof(u32));
@@ -313,7 +310,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     const size_t at_rec = ar.carve(run ? orders * plan.rec_bytes : 0), at_roff = ar.carve(run ? orders * plan.offs_bytes : 0);
     TOK_TRY(ar.get(ar.used));
     State* const state = (State*)(ar.p + at_state);
-    u64 *const counters = (u64*)(ar.p + at_counters), *const len = (u64*)(ar.p + at_len);
+    u64* const len = (u64*)(ar.p + at_len);
     int32_t* const tok[2] = {(int32_t*)(ar.p + at_tok[0]), (int32_t*)(ar.p + at_tok[1])};
     uint8_t *const last[2] = {(uint8_t*)(ar.p + at_last[0]), (uint8_t*)(ar.p + at_last[1])};
     int64_t* const d_off = (int64_t*)(ar.p + at_off);
@@ -346,9 +343,9 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         for (; done < end; ++done) {
             int32_t* const cur = tok[done & 1];
             const uint8_t* const cur_last = last[done & 1];
-            TOK_TRY(tasc_count_partition(p, cur, cur_last, T, len + done, 2, orders, bits, bufs, nullptr, counters, st));
-            TOK_TRY(tasc_count_best(p, len + done, 2, orders, bits, bufs, counters, best, st));
-            k_pick<<<dim3(1), dim3(kPickThreads), 0, st>>>(best, (u32)orders * p.parts, bits, vocab, counters, state, d_merges);
+            TOK_TRY(tasc_count_partition(p, cur, cur_last, T, len + done, 2, orders, bits, bufs, nullptr, nullptr, st));
+            TOK_TRY(tasc_count_best(p, len + done, 2, orders, bits, bufs, best, st));
+            k_pick<<<dim3(1), dim3(kPickThreads), 0, st>>>(best, (u32)orders * p.parts, bits, vocab, state, d_merges);
             k_select<<<grid1, dim3(kThreads), 0, st>>>(cur, cur_last, len + done, state, sel);
             k_sums<<<grid2, dim3(kThreads), 0, st>>>(cur, cur_last, sel, len + done, state, bsum);
             if (grid2.x > kScanFrom) k_scan<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, grid2.x);
@@ -359,10 +356,6 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         TASC_HIP(hipMemcpyAsync(&lens[begin + 1], len + begin + 1, (size_t)(end - begin) * sizeof(u64), hipMemcpyDeviceToHost, st));
         TASC_HIP(hipStreamSynchronize(st));
         TASC_REQUIRE(h.bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
-        if (h.failed) {
-            tasc_set_error("tok_enrich: too many n-grams of one hash");
-            return TASC_ESTATE;
-        }
         T = lens[h.merges];
     }
     const int n_done = (int)h.merges;
