@@ -404,6 +404,7 @@ tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem where, int3
  *   tokens, out_tokens  HOST or DEVICE (`where`, both alike) int32; out_tokens has room for the input
  *                       length and receives the final corpus (corpus_len[*n_merges] tokens).
  *   doc_offsets         HOST int64[n_docs + 1]; out_offsets HOST int64[n_docs + 1] (final boundaries).
+ *                       out_tokens may be tokens, and out_offsets doc_offsets.
  *   merges              HOST int32[budget][1 + TASC_MAX_ORDER]: n, then the n tokens (over the vocabulary
  *                       of that step), then -1 padding; merge_freq HOST int64[budget]: freq of the pick.
  *   corpus_len          HOST int64[budget + 1]: corpus length before merge i; entry *n_merges = final.

@@ -296,7 +296,12 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
 
     // Nothing of the device is looked at before the first kBatch merges are on their way, a token outside the vocabulary included.
     u64 windows = 0;                                         // of order 2, the most of any
-    for (int64_t d = 0; d < n_docs; ++d) windows += (u64)std::max<int64_t>(0, doc_offsets[d + 1] - doc_offsets[d] - 1);
+    std::vector<uint8_t> empty((size_t)n_docs);              // (out_offsets may be doc_offsets: looked at before anything is written)
+    for (int64_t d = 0; d < n_docs; ++d) {
+        const int64_t n = doc_offsets[d + 1] - doc_offsets[d];
+        windows += (u64)std::max<int64_t>(0, n - 1);
+        empty[d] = n == 0;
+    }
     const int orders = n_max - 1;
     const TascCountPlan plan = tasc_count_plan(T0, windows, n_max * bits > 64, false);
     const bool run = budget > 0 && T0 > 0;
@@ -382,6 +387,6 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     for (int i = 0; i <= n_done; ++i) corpus_len[i] = (int64_t)lens[i];
     out_offsets[0] = 0;
     for (int64_t d = 0, e = 0; d < n_docs; ++d)              // (an output that had tokens keeps at least one)
-        out_offsets[d + 1] = doc_offsets[d] < doc_offsets[d + 1] ? (int64_t)h_ends[e++] : out_offsets[d];
+        out_offsets[d + 1] = empty[d] ? out_offsets[d] : (int64_t)h_ends[e++];
     return TASC_OK;
 }

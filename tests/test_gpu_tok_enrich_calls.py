@@ -1,0 +1,26 @@
+"""tasc_tok_enrich called in ways the binding does not: results written over the corpus."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from oracle import tok_enrich as OT
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("docs", [[[], [1, 2, 1, 2, 3], [], [], [1, 2], [5], []], [[1, 2, 1, 2, 1, 2], [4], [1, 2]]])
+def test_in_place(docs):
+    import paper_2602_24174_amd as T
+    from paper_2602_24174_amd import binding as B
+    vocab, n_max, budget = 8, 3, 2
+    tok = np.array([t for d in docs for t in d], dtype=np.int32)
+    off = np.cumsum([0] + [len(d) for d in docs]).astype(np.int64)
+    rows, freq = np.zeros((budget, 1 + T.TASC_MAX_ORDER), np.int32), np.zeros(budget, np.int64)
+    lens, n = np.zeros(budget + 1, np.int64), C.c_int32(0)
+    B._check(B.lib().tasc_tok_enrich(B._ptr(tok), B._ptr(off), len(docs), vocab, n_max, budget, B.TASC_MEM_HOST, B._stream(None), B._ptr(rows),
+                                     B._ptr(freq), B._ptr(lens), B._ptr(tok), B._ptr(off), C.byref(n)))
+    want_m, want_docs, want_l = OT.enrich(docs, vocab, n_max, budget)
+    assert n.value == len(want_m) and lens[:n.value + 1].tolist() == want_l
+    assert off.tolist() == np.cumsum([0] + [len(d) for d in want_docs]).tolist()
+    assert tok[:off[-1]].tolist() == [t for d in want_docs for t in d]
