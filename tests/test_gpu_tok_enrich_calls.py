@@ -16,7 +16,7 @@ def test_in_place(docs):
     vocab, n_max, budget = 8, 3, 2
     tok = np.array([t for d in docs for t in d], dtype=np.int32)
     off = np.cumsum([0] + [len(d) for d in docs]).astype(np.int64)
-    rows, freq = np.zeros((budget, 1 + T.TASC_MAX_ORDER), np.int32), np.zeros(budget, np.int64)
+    rows, freq = np.zeros((budget, 1 + B.TASC_MAX_ORDER), np.int32), np.zeros(budget, np.int64)
     lens, n = np.zeros(budget + 1, np.int64), C.c_int32(0)
     B._check(B.lib().tasc_tok_enrich(B._ptr(tok), B._ptr(off), len(docs), vocab, n_max, budget, B.TASC_MEM_HOST, B._stream(None), B._ptr(rows),
                                      B._ptr(freq), B._ptr(lens), B._ptr(tok), B._ptr(off), C.byref(n)))
