@@ -102,32 +102,70 @@ __device__ __forceinline__ bool matches(const int32_t* tok, const uint8_t* __res
 }
 
 // Left-to-right choice among occurrences that can overlap (the others are all taken, and found where they are needed): sel[i] =
-// number of the merge.  An occurrence with none in the n - 1 positions before it ("head") is always taken; from it, one thread
+// number of the merge.  An occurrence with none in the n - 1 positions before it ("head") is always taken; from it, one lane
 // walks the run of occurrences that overlap each other, taking the first at or after the end of the last taken one, and stops when
-// that one is a head itself (its own thread takes it) or lies beyond the reach of an overlap.  The walk ends at the latest at
-// the end of the corpus.
+// that one is a head itself (its own lane takes it) or lies beyond the reach of an overlap.  A walk is a chain of dependent loads, and
+// a long run of one token is one walk: after kLaneSteps steps the wave takes it over, 64 positions at a time, and the steps among them
+// are a few instructions (200,000 equal tokens, four merges of two: 176 ms with the lane alone; 61 with a byte per
+// position to read instead of the tokens; 16 so).  The walk ends at the latest at the end of the corpus.
 constexpr unsigned kSelectBlocks = 1024;
+constexpr int kLaneSteps = 8;
 __global__ __launch_bounds__(kThreads) void k_select(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, const u64* __restrict__ len,
                                                      const State* __restrict__ st, u32* sel) {
     if (st->done || !st->overlaps) return;
     const u64 T = *len;
     const Gram g = running(st);
-    const int n = (int)g.n;
+    const int n = (int)g.n, lane = threadIdx.x & 63;
     auto is_head = [&](u64 p) {
         for (int j = 1; j < n; ++j)
             if (p >= (u64)j && matches(tok + (p - j), last, T, p - j, g)) return false;
         return true;
     };
-    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < T; i += (u64)gridDim.x * kThreads) {
-        if (!matches(tok + i, last, T, i, g) || !is_head(i)) continue;
+    // bit l: an occurrence starts at p + l
+    auto starts = [&](u64 p) {
+        const u64 i = p + lane;
+        bool ok = i + n <= T;
+        const u64 at = ok ? i : 0;                           // (all of a lane's loads at once)
+#pragma unroll
+        for (int j = 0; j < TASC_MAX_ORDER; ++j)
+            if (j < n) {
+                const int32_t t = tok[at + j];
+                const uint8_t e = last[at + j];
+                ok = ok & (t == g.t[j]) & (j + 1 == n || !e);
+            }
+        return __ballot(ok);
+    };
+    for (u64 i0 = (u64)blockIdx.x * kThreads + threadIdx.x - lane; i0 < T; i0 += (u64)gridDim.x * kThreads) {
+        const u64 i = i0 + lane;
         u64 cur = i;
-        for (;;) {
+        bool walking = i < T && matches(tok + i, last, T, i, g) && is_head(i);
+        for (int s = 0; walking && s < kLaneSteps; ++s) {
             sel[cur] = st->merges;
             u64 next = T;
             for (u64 p = cur + n; p < cur + 2 * (u64)n - 1 && p < T; ++p)
                 if (matches(tok + p, last, T, p, g)) { next = p; break; }
-            if (next >= T || is_head(next)) break;
+            walking = next < T && !is_head(next);
             cur = next;
+        }
+        // (the last step's `next` of a lane that is still walking is an occurrence that has to be taken)
+        for (u64 todo = __ballot(walking); todo != 0; todo &= todo - 1) {
+            u64 at = __shfl(cur, __ffsll(todo) - 1);         // taken; the next one lies n to 2 n - 2 positions on
+            if (lane == 0) sel[at] = g.merges;
+            for (bool on = true; on;) {
+                const u64 base = at + 1, here = starts(base);
+                u64 taken = 0;
+                int c = -1;                                  // the last taken one, from base
+                while (c + 2 * n - 2 < 64) {
+                    const u64 reach = ((here >> (c + n)) & ((1ull << (n - 1)) - 1)) << (c + n);
+                    const int next = __ffsll(reach) - 1;
+                    // none, or a head: no occurrence between the last taken one and it
+                    if (next < 0 || (here & ((1ull << next) - 1) & (~0ull << (next - n + 1))) == 0) { on = false; break; }
+                    taken |= 1ull << next;
+                    c = next;
+                }
+                if ((taken >> lane) & 1) sel[base + lane] = g.merges;
+                at = base + c;
+            }
         }
     }
 }

@@ -24,3 +24,17 @@ def test_in_place(docs):
     assert n.value == len(want_m) and lens[:n.value + 1].tolist() == want_l
     assert off.tolist() == np.cumsum([0] + [len(d) for d in want_docs]).tolist()
     assert tok[:off[-1]].tolist() == [t for d in want_docs for t in d]
+
+
+@pytest.mark.parametrize("n_max", [2, 3, 5, 8])
+@pytest.mark.parametrize("period", [1, 2, 3])
+def test_long_runs_of_overlapping_occurrences(period, n_max):
+    """Runs that end around the 64 positions a wave takes at a time, inside one output and over several, with a break now and then."""
+    import paper_2602_24174_amd as T
+    from test_gpu_tok_enrich import _run_and_compare
+    rng = np.random.default_rng(10 * period + n_max)
+    docs = [[int(t) for t in np.arange(n + 1) % period] for n in (0, 62, 63, 64, 65, 130, 700)]
+    noisy = np.arange(1500) % period
+    noisy[rng.integers(0, 1500, 8)] = 5
+    docs += [noisy.tolist(), [7] * 300, [3, 4]]
+    _run_and_compare(T, docs, 9, n_max, 6, device=True)
