@@ -355,6 +355,7 @@ tasc_status tasc_session_get_tokens(const tasc_session* s, int32_t b, int32_t* t
  *   TASC_CFG_BUILD_LIST_KIB
  *                        KiB of kept-n-gram lists a table build holds at a time (default 8 GiB; one order's list is always
  *                        held): less memory for one host round trip more per group of orders.  Tables do not depend on it.
+ *                        It also bounds the records that an enrichment holds at a time (2 GiB unless it is less; one order's always).
  */
 enum {
     TASC_CFG_SMALL_PATH = 0, TASC_CFG_SMALL_GRID = 1, TASC_CFG_SMALL_LAYER_WGS = 2, TASC_CFG_SMALL_LAYER_STRIDE = 3,
@@ -410,8 +411,9 @@ tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem where, int3
  *   corpus_len          HOST int64[budget + 1]: corpus length before merge i; entry *n_merges = final.
  *   n_merges            HOST: merges performed (<= budget).
  * Limits: n_max in [2, TASC_MAX_ORDER], n_max * ceil(log2(vocab + budget)) <= 128, corpus < 2^32 - 1
- * tokens.  Synchronous (the host looks at the device once per 16 merges); about 14 bytes of device scratch per corpus token
- * plus 8 per 2-gram window (16 for keys of more than 64 bits).  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
+ * tokens.  Synchronous (the host looks at the device once per 16 merges); 14 bytes of device scratch per corpus token, plus
+ * 8 to 14 per token (16 to 22 for keys of more than 64 bits) for each order that is counted together with others: all of them up
+ * to 2 GiB (or TASC_CFG_BUILD_LIST_KIB, if that is less), one at least.  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
  * ---------------------------------------------------------------------------------------- */
 tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs, int32_t vocab,
                             int32_t n_max, int32_t budget, tasc_mem where, void* stream, int32_t* merges,
