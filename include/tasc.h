@@ -69,7 +69,7 @@ const char* tasc_last_error(void);
  * An element (c, x) of M_n is kept iff count(c, x) >= p_min; per kept context c the table holds
  * T(c) = sum of kept counts and its most frequent kept successor (smallest id among equals).
  * Synchronous: allocates device memory, runs on `stream` and waits for it.  While it runs it holds, in one allocation,
- * 13 to 22 bytes (and the token, from host memory) per corpus token and, for all orders together, 20 bytes per window / p_min
+ * 13 to 24 bytes (and the token, from host memory) per corpus token and, for all orders together, 20 bytes per window / p_min
  * (orders are taken in groups where that exceeds TASC_CFG_BUILD_LIST_KIB).  One such allocation of up to 2 GiB per device
  * stays with the library for the next build or enrichment while the process holds a model or a table; it is also given
  * back when an allocation of the library finds no memory.  *out is owned by the library until tasc_ngram_destroy.
@@ -411,7 +411,7 @@ tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem where, int3
  *   corpus_len          HOST int64[budget + 1]: corpus length before merge i; entry *n_merges = final.
  *   n_merges            HOST: merges performed (<= budget).
  * Limits: n_max in [2, TASC_MAX_ORDER], n_max * ceil(log2(vocab + budget)) <= 128, corpus < 2^32 - 1
- * tokens.  Synchronous (the host looks at the device once per 16 merges); 14 bytes of device scratch per corpus token, plus
+ * tokens.  Synchronous (the host looks at the device once per 16 merges); 14 to 16 bytes of device scratch per corpus token, plus
  * 8 to 14 per token (16 to 22 for keys of more than 64 bits) for each order that is counted together with others: all of them up
  * to 2 GiB (or TASC_CFG_BUILD_LIST_KIB, if that is less), one at least.  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
  * ---------------------------------------------------------------------------------------- */

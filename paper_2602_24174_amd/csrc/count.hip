@@ -6,7 +6,7 @@
 //     writes what is left, ordered by partition, as records into the chunk's own region, with the partitions' offsets beside
 //     it: no exchange between workgroups, nothing to reserve, and the regions are as large as the corpus whatever its n-grams are;
 //   * k_tables: one partition, all chunks: a workgroup gathers the partition's records into a hash table in its LDS and
-//     reads the finished counts off it.
+//     reads the finished counts off it; of more windows than partitions can take, in several rounds (tasc_count_plan).
 // Partitions are ranges of the key's 64-bit hash.  With the upper half `hi` of the 128-bit key given, the hash is a bijection of the
 // lower half, so (hash, hi) is the key itself: records and LDS slots hold 8 bytes for keys of up to 64 bits and 16 beyond, the
 // comparison is exact, and nothing looks at the corpus again.
@@ -281,6 +281,7 @@ constexpr int kStageNarrow = 1536, kStageWide = 768;       // records on their w
 constexpr int kRuns = 4;                                   // chunks of a thread at a time
 constexpr u64 kLow57 = (1ull << 57) - 1;
 constexpr int kMaxProbe = 128;                             // a longer probe sequence means a table that is as good as full
+constexpr u32 kMostRounds = 256;
 // A range that overflows is cut in two, by the hash down to kFinest ranges of a partition (one value of the hash's upper half each), then
 // by the rest of the key: (hash, hi) is the key, so a range of the finest kind holds one n-gram, and no corpus can fail.  Behind
 // a dense spot the ranges grow again, up to kCoarse times as many as at the start.
@@ -308,6 +309,8 @@ struct TablesArgs {
     u32* twice;                // nullable: see k_partition
     int32_t twice_bits;
     TascGram* best;            // [orders][parts] the partition's n-gram with the largest count, smallest tuple among equals
+    u64* deal;                 // room for deal_recs records per workgroup
+    u32 deal_recs;
 };
 
 template <bool WIDE>
@@ -315,11 +318,14 @@ constexpr int table_bytes() { return WIDE ? kSlotsWide * 20 : kSlotsNarrow * 12;
 template <bool WIDE>
 constexpr int tables_lds() { return table_bytes<WIDE>() + (WIDE ? kStageWide * 16 : kStageNarrow * 8); }
 
-// BEST: no list, but the most frequent n-gram of the workgroup's partition
-template <bool WIDE, bool BEST>
+// BEST: no list, but the most frequent n-gram of the workgroup's partition.
+// A partition is counted in `rounds` ranges, one table after the other, and each gathers all of the partition's records and drops those
+// of the others.  DEAL, for many rounds: the records are gathered twice, to count those of every round and to lay them out round by
+// round in memory of the workgroup's own, as many rounds at a time as fit there (one that does not fit alone gathers for itself).
+template <bool WIDE, bool BEST, bool DEAL>
 __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, TascGram* best_out) {
     constexpr int SLOTS = WIDE ? kSlotsWide : kSlotsNarrow, PRIME = WIDE ? kPrimeWide : kPrimeNarrow, PER = SLOTS / kTabThreads;
-    constexpr int STAGE = WIDE ? kStageWide : kStageNarrow, RW = WIDE ? 2 : 1;
+    constexpr int STAGE = WIDE ? kStageWide : kStageNarrow, RW = WIDE ? 2 : 1, MINE = STAGE / kTabThreads;
     static_assert(SLOTS % kTabThreads == 0 && STAGE % kTabThreads == 0 && table_bytes<WIDE>() % 16 == 0, "slots and records per thread; clearing");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     u64* s_key = reinterpret_cast<u64*>(lds);                                  // {low 56 bits of the hash, 1, upper 7 bits of hi}; 0 = free
@@ -329,18 +335,92 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     __shared__ u32 s_full, s_nn, s_wave[2][kTabThreads / 64];
     __shared__ u64 s_at;
     __shared__ u128 s_place, s_places;                     // the part of a finest range that is being counted
+    __shared__ u32 s_len[DEAL ? kMostRounds : 1], s_end[DEAL ? kMostRounds : 1], s_next;      // DEAL: rounds' records; the end of what is laid out of them; end of the laid out rounds
     const int tid = threadIdx.x, lane = tid & 63;
     auto hi_of = [&](u64 key, int i) { return WIDE ? ((key & 0x7F) << 57) | (s_hi[i] & kLow57) : 0ull; };
     TascGram best{0, 0, 0, 0};
     u32 distinct = 0;                                      // (a thread's are fewer than the corpus' positions)
     const u32 runs = a.chunks > 2 * kTabThreads ? kRuns : a.chunks > kTabThreads ? 2 : 1;
     const uint16_t* const offs = a.offs + (size_t)part * a.part_step;
+    u64* const deal = DEAL ? a.deal + (size_t)blockIdx.x * a.deal_recs * RW : nullptr;
 
-    u32 den = a.rounds, num = 0;                           // the range of the partition that is being counted: num / den
+    u32 fine = 1, num = 0;                                 // the range that is being counted: num of rounds x fine
     bool within = false;                                   // only s_place .. of it
-    while (num < den) {
-        for (int i = tid; i < table_bytes<WIDE>() / 16; i += kTabThreads) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
-        if (tid == 0) s_full = s_nn = 0;
+    bool dealt = false;                                    // its round's records lie in `deal`
+    // which of den ranges: from the lower half of the product that chose the partition
+    auto range_of = [&](u64 r, u32 den) { return (u32)(((u64)((u32)(hash_of(r, part, a.parts) >> 32) * a.parts) * den) >> 32); };
+
+    // every thread inserts the records of s_rec that it put there; a lane probes once per turn
+    auto insert = [&](u32 here) __attribute__((always_inline)) {
+        u32 e = tid, idx = 0, step = 0, c = 0;
+        int probes = 0;
+        u64 key = 0, hv = 0;
+        bool busy = false;
+        for (;;) {
+            if (!busy && e < here) {
+                const u64 r = s_rec[RW * e];
+                const u64 hi = WIDE ? s_rec[RW * e + RW - 1] : 0;
+                e += kTabThreads;
+                busy = true;
+                if ((DEAL && dealt ? 1 : a.rounds) * fine > 1) {
+                    busy = range_of(r, a.rounds * fine) == num;
+                    if (within) busy = busy && place_of<WIDE>(r, hi) - s_place < s_places;
+                }
+                key = (r & ~0xFFull) | 0x80 | (hi >> 57);
+                hv = (hi & kLow57) | ~kLow57;
+                c = (u32)(r & 0xFF) + 1;
+                idx = __umulhi((u32)(r >> 8), (u32)PRIME);
+                step = ((u32)(r >> 20) & 1023) + 1;
+                probes = 0;
+            }
+            if (__ballot(busy || e < here) == 0) break;
+            if (!busy) continue;
+            // Nobody waits for anybody: a slot whose hash is there without its hi takes the hi of whoever comes first, and the
+            // one that claimed it goes on where that was another's.
+            const u64 k = atomicCAS(&s_key[idx], 0ull, key);
+            bool mine = k == 0 || k == key;
+            if (WIDE && mine) {
+                const u64 v = atomicCAS(&s_hi[idx], 0ull, hv);
+                mine = v == 0 || v == hv;
+            }
+            if (mine) atomicAdd(&s_cnt[idx], c);
+            busy = !mine;
+            idx += step;
+            idx -= idx >= (u32)PRIME ? PRIME : 0;
+            if (busy && ++probes == kMaxProbe) {
+                s_full = 1;
+                busy = false;
+            }
+        }
+    };
+    // the records src[e] of `from`, e < here, through s_rec into the table
+    auto load_insert = [&](const u64* from, u32 here, auto src) __attribute__((always_inline)) {
+        u64 r[MINE][RW];
+#pragma unroll
+        for (int k = 0; k < MINE; ++k) {
+            const u32 e = k * kTabThreads + tid;
+            if (e < here) {
+                if constexpr (WIDE) {
+                    const ulonglong2 v = reinterpret_cast<const ulonglong2*>(from)[src(e)];
+                    r[k][0] = v.x;
+                    r[k][1] = v.y;
+                } else {
+                    r[k][0] = from[src(e)];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < MINE; ++k) {
+            const u32 e = k * kTabThreads + tid;
+            if (e < here) {
+                if constexpr (WIDE) reinterpret_cast<ulonglong2*>(s_rec)[e] = make_ulonglong2(r[k][0], r[k][1]);
+                else s_rec[e] = r[k][0];
+            }
+        }
+        insert(here);
+    };
+    // all records of the partition, STAGE at a time: use(how many), with where they are in s_rec
+    auto gather = [&](auto use) __attribute__((always_inline)) {
         for (u32 c0 = 0; c0 < a.chunks; c0 += runs * kTabThreads) {
             // the thread's runs and their place among the records of these chunks
             u32 at[kRuns], len[kRuns], sum = 0, total;
@@ -362,171 +442,170 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
                     for (u32 j = 0; j < len[u]; ++j, ++to)
                         if (to - first < (u32)STAGE) reinterpret_cast<u32*>(s_rec + RW * (to - first))[0] = (c0 + tid * runs + u) * a.chunk + at[u] + j;
                 __syncthreads();
-                const u32 here = min(total - first, (u32)STAGE);
-                {
-                    u64 r[STAGE / kTabThreads][RW];
-#pragma unroll
-                    for (int k = 0; k < STAGE / kTabThreads; ++k) {
-                        const u32 e = k * kTabThreads + tid;
-                        if (e < here) {
-                            const u32 src = reinterpret_cast<const u32*>(s_rec + RW * e)[0];
-                            if constexpr (WIDE) {
-                                const ulonglong2 v = reinterpret_cast<const ulonglong2*>(a.rec)[src];
-                                r[k][0] = v.x;
-                                r[k][1] = v.y;
-                            } else {
-                                r[k][0] = a.rec[src];
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int k = 0; k < STAGE / kTabThreads; ++k) {
-                        const u32 e = k * kTabThreads + tid;
-                        if (e < here) {
-                            if constexpr (WIDE) reinterpret_cast<ulonglong2*>(s_rec)[e] = make_ulonglong2(r[k][0], r[k][1]);
-                            else s_rec[e] = r[k][0];
-                        }
-                    }
-                }
-                // every thread inserts the records that it fetched; a lane probes once per turn
-                u32 e = tid, idx = 0, step = 0, c = 0;
-                int probes = 0;
-                u64 key = 0, hv = 0;
-                bool busy = false;
-                for (;;) {
-                    if (!busy && e < here) {
-                        const u64 r = s_rec[RW * e];
-                        const u64 hi = WIDE ? s_rec[RW * e + RW - 1] : 0;
-                        e += kTabThreads;
-                        busy = true;
-                        if (den > 1) {                     // where in the partition: the lower half of the product that chose it
-                            const u32 upper = (u32)(hash_of(r, part, a.parts) >> 32);
-                            busy = (u32)(((u64)(upper * a.parts) * den) >> 32) == num;
-                            if (within) busy = busy && place_of<WIDE>(r, hi) - s_place < s_places;
-                        }
-                        key = (r & ~0xFFull) | 0x80 | (hi >> 57);
-                        hv = (hi & kLow57) | ~kLow57;
-                        c = (u32)(r & 0xFF) + 1;
-                        idx = __umulhi((u32)(r >> 8), (u32)PRIME);
-                        step = ((u32)(r >> 20) & 1023) + 1;
-                        probes = 0;
-                    }
-                    if (__ballot(busy || e < here) == 0) break;
-                    if (!busy) continue;
-                    // Nobody waits for anybody: a slot whose hash is there without its hi takes the hi of whoever comes first, and the
-                    // one that claimed it goes on where that was another's.
-                    const u64 k = atomicCAS(&s_key[idx], 0ull, key);
-                    bool mine = k == 0 || k == key;
-                    if (WIDE && mine) {
-                        const u64 v = atomicCAS(&s_hi[idx], 0ull, hv);
-                        mine = v == 0 || v == hv;
-                    }
-                    if (mine) atomicAdd(&s_cnt[idx], c);
-                    busy = !mine;
-                    idx += step;
-                    idx -= idx >= (u32)PRIME ? PRIME : 0;
-                    if (busy && ++probes == kMaxProbe) {
-                        s_full = 1;
-                        busy = false;
-                    }
-                }
+                use(min(total - first, (u32)STAGE));
                 __syncthreads();
             }
         }
-        __syncthreads();
-        if (s_full) {                                      // more n-grams than slots: the range in two halves
-            __syncthreads();
-            if (den < kFinest) {
-                den *= 2;
-                num *= 2;
-            } else {
-                if (tid == 0) {
-                    if (!within) s_place = 0;
-                    s_places = within ? s_places / 2 : kPlaces<WIDE> / 2;
-                }
-                within = true;
-            }
-            continue;
-        }
-        u32 keep = 0, most = 0;
-        auto set_bit = [&](int i) {
-            const u64 hi = hi_of(s_key[i], i), lo = tasc_hash_lo(hash_of(s_key[i], part, a.parts), hi);
-            u32 h = 0;
-            for (int j = 0; j < a.n; ++j) {
-                const u32 t = tasc_key_get(lo, hi, j, a.bits), r = 13 * j % 32;
-                h ^= r == 0 ? t : (t << r) | (t >> (32 - r));
-            }
-            h = light_end(h) >> (32 - a.twice_bits);
-            atomicOr(&a.twice[h >> 5], 1u << (h & 31));
-        };
+    };
+    auto gathered = [&](u32 e) { return reinterpret_cast<const u32*>(s_rec + RW * e)[0]; };
+
+    for (u32 round = 0, end; round < a.rounds; round = end) {
+        end = a.rounds;
+        if (DEAL) {
+            if (round == 0) {
+                for (u32 i = tid; i < a.rounds; i += kTabThreads) s_len[i] = 0;
+                gather([&](u32 here) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < PER; ++s) {
-            const int i = s * kTabThreads + tid;
-            if (s_key[i] == 0) continue;
-            ++distinct;
-            if (s_cnt[i] >= a.p_min) ++keep;
-            most = max(most, s_cnt[i]);
-            if (!BEST && a.twice && s_cnt[i] > 1) {
-                const u32 q = atomicAdd(&s_nn, 1u);
-                if (q < (u32)STAGE) reinterpret_cast<u32*>(s_rec)[q] = i;
-                else set_bit(i);
+                    for (int k = 0; k < MINE; ++k) {
+                        const u32 e = k * kTabThreads + tid;
+                        if (e < here) atomicAdd(&s_len[range_of(a.rec[(size_t)RW * gathered(e)], a.rounds)], 1u);
+                    }
+                });
             }
-        }
-        if (!BEST && a.twice) {                            // (few slots have a bit to set: one a lane, once they are known)
-            __syncthreads();
-            for (u32 q = tid; q < min(s_nn, (u32)STAGE); q += kTabThreads) set_bit((int)reinterpret_cast<const u32*>(s_rec)[q]);
-        }
-        if (BEST) {
-            // only what has the largest count is taken apart
-            for (int o = 32; o > 0; o >>= 1) most = max(most, (u32)__shfl_xor((int)most, o));
-            if (lane == 0) s_wave[0][tid >> 6] = most;
-            __syncthreads();
-            for (int w = 0; w < kTabThreads / 64; ++w) most = max(most, s_wave[0][w]);
-            for (int i = tid; i < SLOTS && most >= best.count; i += kTabThreads) {
-                const u64 key = s_key[i];
-                if (key == 0 || s_cnt[i] != most) continue;
-                const u64 hi = hi_of(key, i);
-                const TascGram g{tasc_hash_lo(hash_of(key, part, a.parts), hi), hi, most, (u32)a.n};
-                if (tasc_gram_before(g, best, a.bits)) best = g;
-            }
-        }
-        if (!BEST) {
-            // the kept n-grams behind those of other workgroups: one addition per workgroup and range
-            u32 all;
-            const u32 before = block_scan<kTabThreads>(keep, s_wave[0], all);
-            if (tid == 0) s_at = all ? atomicAdd(&a.counters[1], (u64)all) : 0;
-            __syncthreads();
-            u64 to = s_at + before;
-            if (keep) {
-#pragma unroll
-                for (int s = 0; s < PER; ++s) {
-                    const int i = s * kTabThreads + tid;
-                    const u64 key = s_key[i];
-                    const u32 c = s_cnt[i];
-                    if (key == 0 || c < a.p_min) continue;
-                    const u64 hi = hi_of(key, i);
-                    a.kept.lo[to] = tasc_hash_lo(hash_of(key, part, a.parts), hi);
-                    a.kept.hi[to] = hi;
-                    a.kept.count[to] = c;
-                    ++to;
-                }
-            }
-        }
-        __syncthreads();
-        if (within) {                                      // on to the next part, of the largest size that begins there
             if (tid == 0) {
-                s_place += s_places;
-                s_places = s_place & (~s_place + 1);
+                u32 r = round;
+                for (u32 sum = 0; r < a.rounds && s_len[r] <= a.deal_recs - sum; ++r) {
+                    s_end[r] = sum;
+                    sum += s_len[r];
+                }
+                s_next = r;
             }
             __syncthreads();
-            within = s_place != kPlaces<WIDE>;
-            __syncthreads();
-            if (within) continue;
+            dealt = s_next > round;
+            end = dealt ? s_next : round + 1;
+            if (dealt) {
+                gather([&](u32 here) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int k = 0; k < MINE; ++k) {
+                        const u32 e = k * kTabThreads + tid;
+                        if (e >= here) continue;
+                        const u32 src = gathered(e);
+                        u64 r, hi = 0;
+                        if constexpr (WIDE) {
+                            const ulonglong2 v = reinterpret_cast<const ulonglong2*>(a.rec)[src];
+                            r = v.x;
+                            hi = v.y;
+                        } else {
+                            r = a.rec[src];
+                        }
+                        const u32 to = range_of(r, a.rounds);
+                        if (to < round || to >= end) continue;
+                        const u32 at = atomicAdd(&s_end[to], 1u);
+                        if constexpr (WIDE) reinterpret_cast<ulonglong2*>(deal)[at] = make_ulonglong2(r, hi);
+                        else deal[at] = r;
+                    }
+                });
+            }
         }
-        ++num;
-        while (den > kCoarse * a.rounds && num % 2 == 0) {
-            den /= 2;
-            num /= 2;
+        fine = 1;
+        num = round;
+        while (num < end * fine) {
+            for (int i = tid; i < table_bytes<WIDE>() / 16; i += kTabThreads) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
+            if (tid == 0) s_full = s_nn = 0;
+            if (DEAL && dealt) {
+                const u32 n = s_len[num / fine];
+                const u64* const from = deal + (size_t)RW * (s_end[num / fine] - n);
+                __syncthreads();
+                for (u32 first = 0; first < n; first += STAGE)           // (a thread's records are its own: no barriers)
+                    load_insert(from + (size_t)RW * first, min(n - first, (u32)STAGE), [](u32 e) { return e; });
+            } else {
+                gather([&](u32 here) __attribute__((always_inline)) { load_insert(a.rec, here, gathered); });
+            }
+            __syncthreads();
+            if (s_full) {                                      // more n-grams than slots: the range in two halves
+                __syncthreads();
+                if (a.rounds * fine < kFinest) {
+                    fine *= 2;
+                    num *= 2;
+                } else {
+                    if (tid == 0) {
+                        if (!within) s_place = 0;
+                        s_places = within ? s_places / 2 : kPlaces<WIDE> / 2;
+                    }
+                    within = true;
+                }
+                continue;
+            }
+            u32 keep = 0, most = 0;
+            auto set_bit = [&](int i) {
+                const u64 hi = hi_of(s_key[i], i), lo = tasc_hash_lo(hash_of(s_key[i], part, a.parts), hi);
+                u32 h = 0;
+                for (int j = 0; j < a.n; ++j) {
+                    const u32 t = tasc_key_get(lo, hi, j, a.bits), r = 13 * j % 32;
+                    h ^= r == 0 ? t : (t << r) | (t >> (32 - r));
+                }
+                h = light_end(h) >> (32 - a.twice_bits);
+                atomicOr(&a.twice[h >> 5], 1u << (h & 31));
+            };
+#pragma unroll
+            for (int s = 0; s < PER; ++s) {
+                const int i = s * kTabThreads + tid;
+                if (s_key[i] == 0) continue;
+                ++distinct;
+                if (s_cnt[i] >= a.p_min) ++keep;
+                most = max(most, s_cnt[i]);
+                if (!BEST && a.twice && s_cnt[i] > 1) {
+                    const u32 q = atomicAdd(&s_nn, 1u);
+                    if (q < (u32)STAGE) reinterpret_cast<u32*>(s_rec)[q] = i;
+                    else set_bit(i);
+                }
+            }
+            if (!BEST && a.twice) {                            // (few slots have a bit to set: one a lane, once they are known)
+                __syncthreads();
+                for (u32 q = tid; q < min(s_nn, (u32)STAGE); q += kTabThreads) set_bit((int)reinterpret_cast<const u32*>(s_rec)[q]);
+            }
+            if (BEST) {
+                // only what has the largest count is taken apart
+                for (int o = 32; o > 0; o >>= 1) most = max(most, (u32)__shfl_xor((int)most, o));
+                if (lane == 0) s_wave[0][tid >> 6] = most;
+                __syncthreads();
+                for (int w = 0; w < kTabThreads / 64; ++w) most = max(most, s_wave[0][w]);
+                for (int i = tid; i < SLOTS && most >= best.count; i += kTabThreads) {
+                    const u64 key = s_key[i];
+                    if (key == 0 || s_cnt[i] != most) continue;
+                    const u64 hi = hi_of(key, i);
+                    const TascGram g{tasc_hash_lo(hash_of(key, part, a.parts), hi), hi, most, (u32)a.n};
+                    if (tasc_gram_before(g, best, a.bits)) best = g;
+                }
+            }
+            if (!BEST) {
+                // the kept n-grams behind those of other workgroups: one addition per workgroup and range
+                u32 all;
+                const u32 before = block_scan<kTabThreads>(keep, s_wave[0], all);
+                if (tid == 0) s_at = all ? atomicAdd(&a.counters[1], (u64)all) : 0;
+                __syncthreads();
+                u64 to = s_at + before;
+                if (keep) {
+#pragma unroll
+                    for (int s = 0; s < PER; ++s) {
+                        const int i = s * kTabThreads + tid;
+                        const u64 key = s_key[i];
+                        const u32 c = s_cnt[i];
+                        if (key == 0 || c < a.p_min) continue;
+                        const u64 hi = hi_of(key, i);
+                        a.kept.lo[to] = tasc_hash_lo(hash_of(key, part, a.parts), hi);
+                        a.kept.hi[to] = hi;
+                        a.kept.count[to] = c;
+                        ++to;
+                    }
+                }
+            }
+            __syncthreads();
+            if (within) {                                      // on to the next part, of the largest size that begins there
+                if (tid == 0) {
+                    s_place += s_places;
+                    s_places = s_place & (~s_place + 1);
+                }
+                __syncthreads();
+                within = s_place != kPlaces<WIDE>;
+                __syncthreads();
+                if (within) continue;
+            }
+            ++num;
+            while (fine > kCoarse && num % 2 == 0) {
+                fine /= 2;
+                num /= 2;
+            }
         }
     }
     if (BEST) {
@@ -552,25 +631,39 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     }
 }
 
-// The partition of a workgroup: the dispatcher deals ids to the 8 XCDs in turn, and each XCD takes one contiguous range of the
-// partitions, so that the records of neighbouring partitions, which share cache lines, are read into one L2.
-__device__ inline u32 my_part(u32 parts) {
-    const u32 xcd = blockIdx.x % 8;
-    return xcd * (parts / 8) + min(xcd, parts % 8) + blockIdx.x / 8;
+// The partition number i, i % 8 the XCD of its workgroup (the dispatcher deals ids to the 8 XCDs in turn): each XCD takes one contiguous
+// range of the partitions, so that the records of neighbouring partitions, which share cache lines, are read into one L2.
+__device__ inline u32 my_part(u32 i, u32 parts) {
+    const u32 xcd = i % 8;
+    return xcd * (parts / 8) + min(xcd, parts % 8) + i / 8;
 }
-template <bool WIDE>
-__global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_tables(TablesArgs a) { partition_table<WIDE, false>(a, my_part(a.parts), nullptr); }
+// A partition per workgroup, or, with records dealt, one after the other in the workgroup's memory
+constexpr u32 kDealWgs = 512;                              // two per compute unit; a multiple of 8
+template <bool WIDE, bool DEAL>
+__global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_tables(TablesArgs a) {
+    if (!DEAL) partition_table<WIDE, false, false>(a, my_part(blockIdx.x, a.parts), nullptr);
+    else
+        for (u32 i = blockIdx.x; i < a.parts; i += gridDim.x) {
+            partition_table<WIDE, false, true>(a, my_part(i, a.parts), nullptr);
+            __syncthreads();
+        }
+}
 
-// every order n + blockIdx.y
+// every order n + blockIdx.y (one order only with records dealt)
+template <bool DEAL>
 __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_tables_best(TablesArgs a) {
     const u32 y = blockIdx.y;
     a.n += (int32_t)y;
     a.rec += y * a.order_recs;
     a.offs += y * a.order_offs;
-    a.best += (size_t)y * gridDim.x + blockIdx.x;
+    a.best += (size_t)y * a.parts;
     if (a.d_T) a.chunks = (u32)((*a.d_T + a.chunk - 1) / a.chunk);
-    if (a.n * a.bits > 64) partition_table<true, true>(a, my_part(a.parts), a.best);
-    else partition_table<false, true>(a, my_part(a.parts), a.best);
+    for (u32 i = blockIdx.x; i < a.parts; i += gridDim.x) {
+        if (a.n * a.bits > 64) partition_table<true, true, DEAL>(a, my_part(i, a.parts), a.best + i);
+        else partition_table<false, true, DEAL>(a, my_part(i, a.parts), a.best + i);
+        if (!DEAL) return;
+        __syncthreads();
+    }
 }
 
 constexpr int kChunkLarge = 8192, kThreadsLarge = 1024, kChunkSmall = 2048, kThreadsSmall = 512;
@@ -583,6 +676,12 @@ u32 up64(u32 v) { return (v + 63) / 64 * 64; }
 // and leave longer runs of a partition, but they need 2 M tokens to fill the chip.  A partition is as many windows as there
 // are LDS slots: about half of a corpus' windows are distinct (0.21 to 0.51 of the 2- to 5-grams of 24 M tokens), and where
 // nearly all are, it is cut in two; twice as many where most of the unique ones leave no record.  Offsets are turned round where there are many chunks.
+// The partitions' counters fit LDS up to TASC_COUNT_MAX_PARTS of them; what a larger corpus has more is counted in rounds.  Where every
+// round gathers a partition's records for itself, the time grows with the square of the corpus; records that are laid out by round cost
+// two gatherings, a write and a read whatever the rounds are.  Builds of orders 2 to 5, every round for itself | laid out from kDealFrom rounds on, ms:
+// 320 M tokens of a phrase corpus 70.6 | 61.0, 640 M 258 | 136, 1.28 G 999 | 277, 4.2 G 10440 | 972; random ones 640 M 250 | 87.
+// With two rounds it is no gain unless nearly all windows are distinct (160 M 24.3 | 27.8, random 30.9 | 18.0).
+constexpr u64 kDealFrom = 3;
 TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide, bool pruned) {
     TascCountPlan p;
     p.chunk = T >= (u64)256 * kChunkLarge ? kChunkLarge : kChunkSmall;
@@ -591,6 +690,12 @@ TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide, bool pruned) {
     p.parts = (u32)std::clamp<u64>((windows + per - 1) / per, TASC_COUNT_MIN_PARTS, TASC_COUNT_MAX_PARTS);
     p.rounds = (u32)std::max<u64>(1, windows / p.parts / per);
     p.rec_bytes = (size_t)p.chunks * p.chunk * (wide ? 16 : 8);
+    p.deal_recs = 0;
+    if (windows >= (u64)kDealFrom * per * p.parts) {
+        p.rounds = (u32)std::min<u64>(kMostRounds, (windows + per * p.parts - 1) / (per * p.parts));
+        p.deal_recs = (u32)(2 * windows / p.parts);
+    }
+    p.deal_bytes = (size_t)kDealWgs * p.deal_recs * (wide ? 16 : 8);
     p.offs_bytes = (size_t)up64(p.chunks) * up64(p.parts + 1) * sizeof(uint16_t) * (p.chunk == kChunkLarge ? 2 : 1);
     return p;
 }
@@ -633,7 +738,7 @@ static TablesArgs tables_args(const TascCountPlan& p, const u64* d_T, int32_t n,
     const bool turned = p.chunk == kChunkLarge;
     return TablesArgs{b.rec, turned ? b.offs + (size_t)n_orders * col * row : b.offs, p.rec_bytes / sizeof(u64),
                       turned ? (size_t)col * row : (size_t)p.chunks * row, turned ? 1 : row, turned ? col : 1,
-                      p.chunks, p.chunk, p.parts, d_T, n, bits, p_min, p.rounds, d_counters, kept, nullptr, 0, d_best};
+                      p.chunks, p.chunk, p.parts, d_T, n, bits, p_min, p.rounds, d_counters, kept, nullptr, 0, d_best, b.deal, p.deal_recs};
 }
 
 tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u32 p_min, const TascCountBufs& b, u64* d_counters,
@@ -643,19 +748,33 @@ tasc_status tasc_count_tables(const TascCountPlan& p, int32_t n, int32_t bits, u
     a.twice_bits = tasc_twice_bits(T);
     auto launch = [&](auto kernel, int lds) -> tasc_status {
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        kernel<<<dim3(p.parts), dim3(kTabThreads), lds, st>>>(a);
+        kernel<<<dim3(p.deal_recs ? std::min(p.parts, kDealWgs) : p.parts), dim3(kTabThreads), lds, st>>>(a);
         TASC_LAUNCH_CHECK();
         return TASC_OK;
     };
-    return n * bits > 64 ? launch(&k_tables<true>, tables_lds<true>()) : launch(&k_tables<false>, tables_lds<false>());
+    if (n * bits > 64) return p.deal_recs ? launch(&k_tables<true, true>, tables_lds<true>()) : launch(&k_tables<true, false>, tables_lds<true>());
+    return p.deal_recs ? launch(&k_tables<false, true>, tables_lds<false>()) : launch(&k_tables<false, false>, tables_lds<false>());
 }
 
 tasc_status tasc_count_best(const TascCountPlan& p, const u64* d_T, int32_t n0, int32_t n_orders, int32_t bits, const TascCountBufs& b,
                             TascGram* d_best, hipStream_t st) {
     const TablesArgs a = tables_args(p, d_T, n0, n_orders, bits, 1, b, nullptr, TascKept{}, d_best);
     constexpr int lds = std::max(tables_lds<false>(), tables_lds<true>());
-    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tables_best), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    k_tables_best<<<dim3(p.parts, (unsigned)n_orders), dim3(kTabThreads), lds, st>>>(a);
-    TASC_LAUNCH_CHECK();
+    auto launch = [&](auto kernel, const TablesArgs& one, dim3 grid) -> tasc_status {
+        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        kernel<<<grid, dim3(kTabThreads), lds, st>>>(one);
+        TASC_LAUNCH_CHECK();
+        return TASC_OK;
+    };
+    if (!p.deal_recs) return launch(&k_tables_best<false>, a, dim3(p.parts, (unsigned)n_orders));
+    for (int y = 0; y < n_orders; ++y) {                   // (in turn: they deal into the same memory)
+        TablesArgs one = a;
+        one.n += y;
+        one.rec += y * a.order_recs;
+        one.offs += y * a.order_offs;
+        one.best += (size_t)y * p.parts;
+        const tasc_status rc = launch(&k_tables_best<true>, one, dim3(std::min(p.parts, kDealWgs)));
+        if (rc != TASC_OK) return rc;
+    }
     return TASC_OK;
 }

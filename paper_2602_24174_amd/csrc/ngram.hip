@@ -318,14 +318,15 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
     const size_t at_last = carve(any ? T : 0), at_off = carve(any ? (size_t)(n_docs + 1) * sizeof(int64_t) : 0);
     // (with p_min 1 every n-gram is kept, the unique ones too)
     const bool prune = p_min > 1;
-    size_t rec_bytes = 0, offs_bytes = 0;
+    size_t rec_bytes = 0, offs_bytes = 0, deal_bytes = 0;
     for (int n = 2; n <= n_max; ++n) {
         if (windows[n] == 0) continue;
         const TascCountPlan p = tasc_count_plan(T, windows[n], n * bits > 64, prune && n > 2);
         rec_bytes = std::max(rec_bytes, p.rec_bytes);
         offs_bytes = std::max(offs_bytes, p.offs_bytes);
+        deal_bytes = std::max(deal_bytes, p.deal_bytes);
     }
-    const size_t at_rec = carve(rec_bytes), at_roff = carve(offs_bytes), twice_bytes = any && prune ? ((size_t)1 << tasc_twice_bits(T)) / 8 : 0, at_twice = carve(2 * twice_bytes);
+    const size_t at_rec = carve(rec_bytes), at_roff = carve(offs_bytes), at_deal = carve(deal_bytes), twice_bytes = any && prune ? ((size_t)1 << tasc_twice_bits(T)) / 8 : 0, at_twice = carve(2 * twice_bytes);
     const size_t list_bytes = (size_t)g_tasc_config.build_list_kib << 10;
     size_t at_list[TASC_MAX_ORDER + 1] = {0}, lists = 0, longest = 0;
     int group_end[TASC_MAX_ORDER + 2] = {0};                   // [n] = one past the last order of the group that n begins
@@ -376,7 +377,7 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
         TASC_LAUNCH_CHECK();
     }
     uint8_t* const d_last = (uint8_t*)(arena + at_last);
-    const TascCountBufs bufs{(u64*)(arena + at_rec), (uint16_t*)(arena + at_roff)};
+    const TascCountBufs bufs{(u64*)(arena + at_rec), (uint16_t*)(arena + at_roff), (u64*)(arena + at_deal)};
     auto kept_of = [&](int n) {
         u64* const lo = (u64*)(arena + at_list[n]);
         const size_t most = windows[n] / (u64)p_min;

@@ -96,10 +96,13 @@ struct TascCountPlan {
     u32 chunk, chunks;        // corpus positions of a workgroup, and how many such chunks
     u32 parts, rounds;        // hash ranges, and how many a range is cut into once more
     size_t rec_bytes, offs_bytes;   // buffers of one order
+    u32 deal_recs;            // records that a workgroup has room for to lay a partition's rounds out; 0: every round gathers for itself
+    size_t deal_bytes;        // room of all workgroups
 };
-struct TascCountBufs {        // of every order of a call, one behind the other
-    u64* rec;
+struct TascCountBufs {
+    u64* rec;                 // of every order of a call, one behind the other
     uint16_t* offs;
+    u64* deal;                // for one order at a time
 };
 struct TascKept {             // n-grams with their packed keys and counts
     u64* lo;

@@ -357,6 +357,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     const size_t most = std::min(kMostRecords, (size_t)g_tasc_config.build_list_kib << 10);
     const int together = (int)std::clamp<size_t>(most / std::max<size_t>(1, plan.rec_bytes + plan.offs_bytes), 1, orders);
     const size_t at_rec = ar.carve(run ? together * plan.rec_bytes : 0), at_roff = ar.carve(run ? together * plan.offs_bytes : 0);
+    const size_t at_deal = ar.carve(run ? plan.deal_bytes : 0);
     TOK_TRY(ar.get(ar.used));
     State* const state = (State*)(ar.p + at_state);
     u64* const len = (u64*)(ar.p + at_len);
@@ -366,7 +367,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     u32 *const bsum = (u32*)(ar.p + at_bsum), *const sel = (u32*)(ar.p + at_sel), *const ends = (u32*)(ar.p + at_ends);
     Merge* const d_merges = (Merge*)(ar.p + at_merges);
     TascGram* const best = (TascGram*)(ar.p + at_best);
-    const TascCountBufs bufs{(u64*)(ar.p + at_rec), (uint16_t*)(ar.p + at_roff)};
+    const TascCountBufs bufs{(u64*)(ar.p + at_rec), (uint16_t*)(ar.p + at_roff), (u64*)(ar.p + at_deal)};
 
     TASC_HIP(hipMemsetAsync(ar.p, 0, zeroed, st));
     TASC_HIP(hipMemcpyAsync(len, &T0, sizeof T0, hipMemcpyHostToDevice, st));
