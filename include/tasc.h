@@ -71,8 +71,8 @@ const char* tasc_last_error(void);
  * Synchronous: allocates device memory, runs on `stream` and waits for it.  While it runs it holds, in one allocation,
  * 13 to 24 bytes (and the token, from host memory) per corpus token and, for all orders together, 20 bytes per window / p_min
  * (orders are taken in groups where that exceeds TASC_CFG_BUILD_LIST_KIB).  One such allocation of up to 2 GiB per device
- * stays with the library for the next build or enrichment while the process holds a model or a table; it is also given
- * back when an allocation of the library finds no memory.  *out is owned by the library until tasc_ngram_destroy.
+ * (TASC_CFG_KEEP_SCRATCH_KIB) stays with the library for the next build or enrichment while the process holds a model or a table; it
+ * is also given back when an allocation of the library finds no memory.  *out is owned by the library until tasc_ngram_destroy.
  */
 tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs,
                              int32_t vocab, int32_t n_max, int32_t p_min, tasc_mem where,
@@ -356,11 +356,16 @@ tasc_status tasc_session_get_tokens(const tasc_session* s, int32_t b, int32_t* t
  *                        KiB of kept-n-gram lists a table build holds at a time (default 8 GiB; one order's list is always
  *                        held): less memory for one host round trip more per group of orders.  Tables do not depend on it.
  *                        It also bounds the records that an enrichment holds at a time (2 GiB unless it is less; one order's always).
+ *   TASC_CFG_KEEP_SCRATCH_KIB
+ *                        KiB of scratch that a table build or an enrichment may leave to the next one, per device (0 .. 2 GiB, the
+ *                        default); setting it gives back what is kept beyond, so 0 and the value before free it for other users of the
+ *                        device.  Results do not depend on it.
  */
 enum {
     TASC_CFG_SMALL_PATH = 0, TASC_CFG_SMALL_GRID = 1, TASC_CFG_SMALL_LAYER_WGS = 2, TASC_CFG_SMALL_LAYER_STRIDE = 3,
     TASC_CFG_TILED_PATH = 4, TASC_CFG_SMALL_XCD_LOCAL = 5, TASC_CFG_SMALL_LAYER_WORKERS = 6, TASC_CFG_SMALL_KERNEL = 7,
-    TASC_CFG_PIPE_SHARE = 8, TASC_CFG_CHAINS = 9, TASC_CFG_STEP_GRAPH = 10, TASC_CFG_BUILD_LIST_KIB = 11
+    TASC_CFG_PIPE_SHARE = 8, TASC_CFG_CHAINS = 9, TASC_CFG_STEP_GRAPH = 10, TASC_CFG_BUILD_LIST_KIB = 11,
+    TASC_CFG_KEEP_SCRATCH_KIB = 12
 };
 tasc_status tasc_config_set(int32_t key, int32_t value);
 

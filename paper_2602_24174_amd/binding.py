@@ -408,6 +408,7 @@ TASC_CFG_PIPE_SHARE = 8
 TASC_CFG_CHAINS = 9
 TASC_CFG_STEP_GRAPH = 10
 TASC_CFG_BUILD_LIST_KIB = 11
+TASC_CFG_KEEP_SCRATCH_KIB = 12
 
 
 def tasc_config_set(key: int, value: int):

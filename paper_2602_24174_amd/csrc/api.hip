@@ -157,8 +157,7 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
     const size_t D = c.d_model, HD = (size_t)c.n_heads * c.head_dim, KD = (size_t)c.n_kv_heads * c.head_dim, F = c.d_ffn;
 
     auto dev_alloc = [&](size_t bytes, void** p) -> tasc_status {
-        const tasc_status rc = tasc_device_malloc(p, std::max<size_t>(bytes, 16));
-        if (rc != TASC_OK) return rc;
+        TASC_ALLOC(p, std::max<size_t>(bytes, 16));
         m->allocs.push_back(*p);
         return TASC_OK;
     };
@@ -192,7 +191,7 @@ extern "C" tasc_status tasc_model_create(const tasc_model_desc* desc, const tasc
     // Gate and up pass through device memory in whole matrices and are interleaved there.  (hipMemcpy2D straight into place left every
     // layer's matrices zero, and reported success, in models created after a first one had run under rocprofv3.)
     struct Staging { void* p = nullptr; ~Staging() { if (p) (void)hipFree(p); } } gate_up;
-    TASC_HIP(hipMalloc(&gate_up.p, 2 * F * D * es));
+    TASC_ALLOC(&gate_up.p, 2 * F * D * es);
     for (int l = 0; l < c.n_layers; ++l) {
         TASC_REQUIRE(w->wq[l] && w->wk[l] && w->wv[l] && w->wo[l] && w->wg[l] && w->wu[l] && w->wd[l] && w->g1[l] && w->g2[l],
                      "model_create: null weight pointer in layer %d", l);
@@ -503,7 +502,8 @@ extern "C" tasc_status tasc_session_prefill(const tasc_model* m, tasc_session* s
     const int32_t* d_prompts = prompts;
     if (where == TASC_MEM_HOST) {
         void* p;
-        TASC_HIP(hipMalloc(&p, total * 4)); tmp.p.push_back(p);
+        TASC_ALLOC(&p, total * 4);
+        tmp.p.push_back(p);
         TASC_HIP(hipMemcpyAsync(p, prompts, total * 4, hipMemcpyHostToDevice, st));
         d_prompts = (const int32_t*)p;
     }

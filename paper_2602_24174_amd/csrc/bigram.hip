@@ -36,7 +36,7 @@ extern "C" tasc_status tasc_model_bigram(const tasc_model* m, tasc_session* s, i
     hipStream_t st = (hipStream_t)stream;
     const int B = s->batch, V = m->desc.vocab;
     DevBuf prompts;
-    TASC_HIP(hipMalloc(&prompts.p, (size_t)B * sizeof(int32_t)));
+    TASC_ALLOC(&prompts.p, (size_t)B * sizeof(int32_t));
     std::vector<int64_t> offs(B + 1);
     for (int b = 0; b <= B; ++b) offs[b] = b;
     for (int first = 0; first < V; first += B) {
@@ -61,11 +61,11 @@ extern "C" tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem 
     DevBuf staged, pairs;
     const int32_t* d_next = next_tok;
     if (where == TASC_MEM_HOST) {
-        TASC_HIP(hipMalloc(&staged.p, (size_t)vocab * sizeof(int32_t)));
+        TASC_ALLOC(&staged.p, (size_t)vocab * sizeof(int32_t));
         TASC_HIP(hipMemcpyAsync(staged.p, next_tok, (size_t)vocab * sizeof(int32_t), hipMemcpyHostToDevice, st));
         d_next = (const int32_t*)staged.p;
     }
-    TASC_HIP(hipMalloc(&pairs.p, (size_t)vocab * 2 * sizeof(int32_t)));
+    TASC_ALLOC(&pairs.p, (size_t)vocab * 2 * sizeof(int32_t));
     k_bigram_pairs<<<dim3((vocab + 255) / 256), dim3(256), 0, st>>>(d_next, vocab, (int32_t*)pairs.p);
     TASC_LAUNCH_CHECK();
     std::vector<int64_t> offs((size_t)vocab + 1);

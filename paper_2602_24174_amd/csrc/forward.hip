@@ -70,6 +70,9 @@ extern "C" tasc_status tasc_config_set(int32_t key, int32_t value) {
     } else if (key == TASC_CFG_BUILD_LIST_KIB) {
         TASC_REQUIRE(value >= 0, "config_set: build list size %d KiB", value);
         g_tasc_config.build_list_kib = value;
+    } else if (key == TASC_CFG_KEEP_SCRATCH_KIB) {
+        TASC_REQUIRE(value >= 0 && value <= 2 << 20, "config_set: kept scratch %d KiB outside [0, %d]", value, 2 << 20);
+        tasc_scratch_limit((size_t)value << 10);
     } else if (key == TASC_CFG_PIPE_SHARE) {
         TASC_REQUIRE(value >= 1 && value <= 3, "config_set: pipeline share %d outside [1, 3]", value);
         g_tasc_config.pipe_share = value;
@@ -857,9 +860,9 @@ extern "C" tasc_status tasc_calibration_gemm(int32_t M, int32_t N, int32_t K, in
     if (rc != TASC_OK) return rc;
     const size_t a_bytes = (size_t)M * K * 2, w_bytes = (size_t)N * K * 2, o_bytes = (size_t)M * N * 4 * slices;
     struct Tmp { void* p[3] = {nullptr, nullptr, nullptr}; ~Tmp() { for (void* q : p) if (q) (void)hipFree(q); } } t;
-    TASC_HIP(hipMalloc(&t.p[0], a_bytes));
-    TASC_HIP(hipMalloc(&t.p[1], w_bytes));
-    TASC_HIP(hipMalloc(&t.p[2], o_bytes));
+    TASC_ALLOC(&t.p[0], a_bytes);
+    TASC_ALLOC(&t.p[1], w_bytes);
+    TASC_ALLOC(&t.p[2], o_bytes);
     TASC_HIP(hipMemsetAsync(t.p[0], 0x3c, a_bytes, st));       // bf16 0x3c3c = 0.0115: finite sums and SwiGLU arguments
     TASC_HIP(hipMemsetAsync(t.p[1], 0x3c, w_bytes, st));
     TASC_HIP(hipMemsetAsync(t.p[2], 0, o_bytes, st));

@@ -122,7 +122,7 @@ extern "C" tasc_status tasc_calibration_mfma(int32_t iters, void* stream, double
     TASC_HIP(hipGetDevice(&dev));
     TASC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     float* sink = nullptr;
-    TASC_HIP(hipMalloc((void**)&sink, sizeof(float)));
+    TASC_ALLOC(&sink, sizeof(float));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -177,7 +177,7 @@ extern "C" tasc_status tasc_calibration_read(const void* src, size_t bytes, int3
     const size_t steps = (n_blocks * (size_t)passes + wgs - 1) / wgs;
     TASC_REQUIRE(steps <= ((size_t)1 << 26), "calibration_read: %zu blocks x %d passes is too much work for one launch", n_blocks, passes);
     unsigned* sink = nullptr;
-    TASC_HIP(hipMalloc((void**)&sink, sizeof(unsigned)));
+    TASC_ALLOC(&sink, sizeof(unsigned));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -301,7 +301,7 @@ extern "C" tasc_status tasc_calibration_handover(int32_t n_workgroups, int32_t s
     const int units = bytes / 8, mode = with_flags ? 1 : 0;
     const size_t words = (size_t)kHandoverPhases * units;
     u64* buf = nullptr;
-    TASC_HIP(hipMalloc((void**)&buf, words * 8 + 4096 + 64));
+    TASC_ALLOC(&buf, words * 8 + 4096 + 64);
     u32* flags = reinterpret_cast<u32*>(buf + words);
     u32* err = flags + 1024 - 16;
     u64* ticks = reinterpret_cast<u64*>(flags + 1024);

@@ -2,13 +2,14 @@
 //
 // A build of 32 M tokens needs 1.2 GB for 5 ms.  Memory that goes back to the driver is cleared before it is handed out again, at
 // about 80 GB/s: allocated on each call, that build takes 5.6 ms until the cleared memory of the card is used up and 15 ms from
-// then on.  So one block per device, of kMostKept at most, stays with the library between calls, as long as the process
-// holds a model or a table; it goes with the last of them, and when the device has no memory left for something else.
+// then on.  So one block per device, of TASC_CFG_KEEP_SCRATCH_KIB at most, stays with the library between calls, as long as the process
+// holds a model or a table; it goes with the last of them, when the option is set to less, and when the device has no memory left
+// for something else of the library's.
 #include "tasc_internal.h"
 #include <mutex>
 
 namespace {
-constexpr size_t kMostKept = (size_t)2 << 30;
+size_t g_most = (size_t)2 << 30;
 constexpr int kDevices = 16;
 struct Kept { char* p; size_t bytes; };
 Kept g_kept[kDevices];
@@ -31,6 +32,13 @@ void tasc_handles_add(int n) {
     g_handles += n;
     if (g_handles == 0)
         for (int d = 0; d < kDevices; ++d) drop(d);
+}
+
+void tasc_scratch_limit(size_t bytes) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    g_most = bytes;
+    for (int d = 0; d < kDevices; ++d)
+        if (g_kept[d].bytes > bytes) drop(d);
 }
 
 tasc_status tasc_device_malloc(void** p, size_t bytes) {
@@ -67,7 +75,7 @@ tasc_status TascScratch::get(size_t need) {
 void TascScratch::keep() {
     std::lock_guard<std::mutex> lock(g_mu);
     const int dev = device();
-    if (dev < 0 || g_handles == 0 || bytes > kMostKept || bytes <= g_kept[dev].bytes) return;      // (the destructor frees it)
+    if (dev < 0 || g_handles == 0 || bytes > g_most || bytes <= g_kept[dev].bytes) return;      // (the destructor frees it)
     drop(dev);
     g_kept[dev] = Kept{p, bytes};
     p = nullptr;

@@ -209,7 +209,7 @@ extern "C" tasc_status tasc_ngram_entropy(const tasc_ngram* ng, int32_t order, i
     const TableSpan t = table_span(ng, order);
     const int blocks = stat_blocks(t.n);
     unsigned char* scratch = nullptr;
-    TASC_HIP(hipMalloc(&scratch, stat_scratch_bytes(blocks)));
+    TASC_ALLOC(&scratch, stat_scratch_bytes(blocks));
     tasc_table_entropy* res = nullptr;
     tasc_status rc = enqueue_entropy(t, blocks, coverage_ppm, scratch, st, &res);
     tasc_table_entropy host;

@@ -30,6 +30,12 @@ void tasc_set_error(const char* fmt, ...);
         }                                  \
     } while (0)
 
+#define TASC_ALLOC(p, bytes)                                            \
+    do {                                                                \
+        tasc_status _rc = tasc_device_malloc((void**)(p), (bytes));     \
+        if (_rc != TASC_OK) return _rc;                                 \
+    } while (0)
+
 #define TASC_LAUNCH_CHECK()                                                          \
     do {                                                                             \
         hipError_t _e = hipGetLastError();                                           \
@@ -52,8 +58,10 @@ struct TascScratch {
     TascScratch& operator=(const TascScratch&) = delete;
     ~TascScratch();
 };
-// hipMalloc that gives kept scratch back where memory runs out
+// Every device allocation of the library: hipMalloc that gives kept scratch back where memory runs out
 tasc_status tasc_device_malloc(void** p, size_t bytes);
+// the most bytes a call may leave to later ones; what is kept beyond goes at once
+void tasc_scratch_limit(size_t bytes);
 // models and tables that exist: kept scratch is freed with the last of them
 void tasc_handles_add(int n);
 
