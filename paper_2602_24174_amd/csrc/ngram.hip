@@ -94,14 +94,13 @@ __global__ __launch_bounds__(kThreads) void k_unigram(const int32_t* __restrict_
 
 // hist = the sum of the copies; best[0] = max over tokens of (count << 32) | (0xFFFFFFFF - token): largest count, smallest id
 __global__ void k_unigram_argmax(const u32* copies, int n_copies, int vocab, u32* hist, u64* best) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
     u64 v = 0;
-    for (; i < vocab; i += gridDim.x * blockDim.x) {
+    for (u32 i = blockIdx.x * blockDim.x + threadIdx.x; i < (u32)vocab; i += gridDim.x * blockDim.x) {
         u32 n = 0;
 #pragma unroll 8
         for (int q = 0; q < n_copies; ++q) n += copies[(size_t)q * vocab + i];
         hist[i] = n;
-        u64 c = ((u64)n << 32) | (u64)(0xFFFFFFFFu - (u32)i);
+        u64 c = ((u64)n << 32) | (u64)(0xFFFFFFFFu - i);
         v = c > v ? c : v;
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -310,7 +309,7 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
     size_t used = 0;
     auto carve = [&](size_t bytes) { const size_t at = used; used += (bytes + 255) / 256 * 256; return at; };
     const size_t at_counters = carve((TASC_MAX_ORDER + 1) * 8 * sizeof(u64));
-    const int uni_ranges = (vocab + kUniRange - 1) / kUniRange, uni_range = (vocab + uni_ranges - 1) / uni_ranges;
+    const int uni_ranges = (int)(((int64_t)vocab + kUniRange - 1) / kUniRange), uni_range = (int)(((int64_t)vocab + uni_ranges - 1) / uni_ranges);
     // slices of kUniSlice tokens or more, eight at a time and no more workgroups than a round
     const u32 uni_slices = uni_ranges > kUniRanges ? kUniCopies : 8 * (u32)std::clamp<u64>((T + 8 * kUniSlice - 1) / (8 * kUniSlice), 1, std::max(1, 32 / uni_ranges));
     const size_t at_copies = carve(T > 0 ? (size_t)vocab * sizeof(u32) * uni_slices : 0);
@@ -372,7 +371,7 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
             k_unigram<<<dim3(grid), dim3(kThreads), 0, st>>>(d_tok, T, vocab, d_copies, (u32*)&d_counters[0][4]);
         }
         TASC_LAUNCH_CHECK();
-        k_unigram_argmax<<<dim3((unsigned)std::min((vocab + kThreads - 1) / kThreads, 1024)), dim3(kThreads), 0, st>>>(
+        k_unigram_argmax<<<dim3((unsigned)std::min<int64_t>(((int64_t)vocab + kThreads - 1) / kThreads, 1024)), dim3(kThreads), 0, st>>>(
             d_copies, (int)uni_slices, vocab, ng->unigram, &d_counters[0][3]);
         TASC_LAUNCH_CHECK();
     }
