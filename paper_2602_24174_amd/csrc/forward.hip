@@ -262,13 +262,16 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
     const bool large = EPI == TEPI_LMHEAD ? M > 32 && small_wgs > cus : (M >= kLargeTileRows && large_wgs >= 128) || (M > 128 && large_wgs >= 512);
     if (large) {
         // Tiles of 192 rows where their rounds over the compute units are shorter in all (the tile shape never changes a row's result):
-        // fewer padded rows (576 = 3 x 192), or a last round that larger tiles would leave half empty.  They read the weights more
-        // often, so they have to win by a twentieth (us, 256 | 192: down 6336 x 1536 x 8960, 150 | 198 tiles 187 | 174; 12288 x 2048 x 11008,
-        // 384 | 512 tiles 557 | 498).
+        // fewer padded rows (576 = 3 x 192), a last round that larger tiles would leave half empty, or idle units in the only one.
+        // They read the weights more often, so they have to win by a twelfth.  165 products of 384 to 8192 rows, all epilogues,
+        // by the rounds of 192 / 256 rows: as many of both 1.06 to 1.34 times as fast (us, 256 | 192: down 6336 x 1536 x 8960 187 | 174; 3072 x 2048 x
+        // 11008 in four slices 121 | 100), 6 / 5 1.11 times (gate and up 3072 x 22016 x 2048 223 | 201), but 5 / 4 between 0.92 (6336 x 2048 x
+        // 11008 in four slices 270 | 295) and 1.07.  LM head, 200 and 256 rows x 16640 to 32768, 480 to 700 rows x 12288 to 20480: 1.01
+        // to 1.12 times (200 x 16640 x 1536 53.8 | 48.8, 256 x 32768 x 2048 73.6 | 72.2).
         const int mt256 = (M + 255) / 256, mt192 = (M + 191) / 192;
         const int nt = (N + 255) / 256;
         auto rounds = [&](int mt) { return ((long)mt * nt * slices + cus - 1) / cus; };
-        const bool mid = rounds(mt192) * 192 * 20 < rounds(mt256) * 256 * 19;
+        const bool mid = rounds(mt192) * 192 * 12 < rounds(mt256) * 256 * 11;
         const int tiles = (mid ? mt192 : mt256) * nt * slices;
         if (EPI == TEPI_LMHEAD || (tiles > cus && !(EPI == TEPI_ROPE && mid))) {   // (that rotation needs whole heads in a wave's features: 128, not 64)
             if constexpr (EPI != TEPI_ROPE) {
