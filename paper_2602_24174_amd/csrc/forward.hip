@@ -165,17 +165,14 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
     }
     if (n_sel > 0) {
         const BiasCsr bias{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base};
-        // Partial maxima of 16 columns where a vocabulary of few strips would leave the chip idle; they take the room of the q/k/v
-        // buffer, which these kernels do not use, so that must hold two of them per strip eighth.
-        constexpr int SPLIT = 8;
-        const bool split = s->n_strips * SPLIT * 2 <= (H + 2 * Hkv) * hd;
-        const int parts = s->n_strips * (split ? SPLIT : 1);
-        float* const pv = split ? d.qkv : d.part_val;
-        int32_t* const pi = split ? (int32_t*)(d.qkv + (size_t)n_sel * parts) : d.part_idx;
+        const bool split = tasc_generic_lm_split(s->n_strips) > 1;
+        const int parts = s->n_strips * tasc_generic_lm_split(s->n_strips);
+        float* const pv = d.part_val;
+        int32_t* const pi = d.part_idx;
         {
             PROF(TASC_KC_LMHEAD);
             if (split)
-                k_lmhead_generic<T, 4, TASC_LM_STRIP / SPLIT / 4><<<dim3(parts), dim3(64 * 5), 0, st>>>(
+                k_lmhead_generic<T, 4, TASC_LM_STRIP / 8 / 4><<<dim3(parts), dim3(64 * 5), 0, st>>>(
                     d.x, d.sel_rows, m->gf, c.rms_eps, (const T*)m->lm_head, d.sel_tok, n_sel, c.vocab, D, bias, pv, pi, parts, logits_dbg);
             else
                 k_lmhead_generic<T, 8, TASC_LM_STRIP / 8><<<dim3(parts), dim3(64 * 9), 0, st>>>(

@@ -263,12 +263,11 @@ struct TascSessDev {
     // activations
     float* x;            // [M_max, d] residual stream
     void* h;             // [M_max, d]   normalised activations, model dtype
-    float* qkv;          // [M_max, (H + 2Hkv) hd]
     void* q;             // [M_max, H hd] rotated queries, model dtype
     void* att;           // [M_max, H hd]
     void* act;           // [M_max, F]
-    float* part_val;     // [M_lm, n_strips]
-    int32_t* part_idx;   // [M_lm, n_strips]
+    float* part_val;     // [M_lm, n_strips], or as many parts of the strips as tasc_generic_lm_split says
+    int32_t* part_idx;
     int32_t* amax;       // [M_lm] argmax token of every LM-head row
     float* att_part;     // attention split partials
     char* small_ws;      // the small-batch kernel's per-phase / per-layer activation buffers (tasc_small_ws_bytes)
@@ -322,6 +321,11 @@ struct tasc_session {
 #define TASC_CTR_BARB 26      // whole-grid barrier arrival counter
 #define TASC_CTR_XCD_STEPS 28 // steps of the persistent kernel whose layer group used XCD-local barriers
 #define TASC_CTR_XCC 27       // XCDs the layer group of the running step found itself on (low 32 bits)
+
+// Into how many parts the type-generic LM head cuts a strip of TASC_LM_STRIP columns, a workgroup each.  Few columns a workgroup where
+// whole strips would leave the chip idle (us with whole strips | with eighths, 5 rows, d 128: vocabulary of 512 26.8 | 9.3, 8192 27.0 | 10.3,
+// 16384 27.0 | 17.9, 32768 28.0 | 26.2 and 2 more for the larger argmax; d 512: 31.6 | 10.8, 31.9 | 11.9, 34.7 | 24.4, 36.6 | 36.8).
+inline int tasc_generic_lm_split(int n_strips) { return n_strips <= 128 ? 8 : 1; }
 
 // what makes a forward a verify step: its rows are the sequences' pending tokens and the drafts, and it ends with the acceptance
 struct TascVerifyTail {
