@@ -143,7 +143,7 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
         }
         {
             PROF(TASC_KC_ATTN);
-            k_attn_generic<T><<<dim3(s->batch, H, nq <= 16 ? 1 : (nq + 7) / 8), dim3(ATTN_GENERIC_THREADS), att_lds, st>>>(
+            k_attn_generic<T><<<dim3(s->batch, H, nq <= ATTN_GENERIC_ROWS ? 1 : (nq + 7) / 8), dim3(ATTN_GENERIC_THREADS), att_lds, st>>>(
                 (const T*)d.q, kv_layer, d.n_rows, d.pos0, d.block_tab, gm, scale, tail ? nq : 0, (T*)d.att);
         }
         {

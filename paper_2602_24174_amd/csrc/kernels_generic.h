@@ -296,11 +296,15 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const void* __restrict__ A
 // One workgroup per (sequence, query head).  Keys are taken in tiles of 64 at absolute positions 0, 64, ...; a tile gives a row its
 // maximum, the sum of its exponentials and their products with the values (a lane holds one dimension of the output and reads the 16
 // tokens of a value page in one go, ahead of the scores), and the tiles are added in ascending order, rescaled to the larger
-// maximum: the same arithmetic whoever computes a tile.  nq: rows of every sequence in a verify step, 0: look them up.  Where a sequence's (row, tile) pairs are few, every wave takes pairs of
-// its own and the tiles of a row meet in LDS; otherwise a wave takes whole rows.  Latency bounds it: fp32, one sequence of 100
-// tokens, 5 rows 7.8 us, 9.0 with a wave per row and the values requested after the scores.
+// maximum: the same arithmetic whoever computes a tile.  nq: rows of every sequence in a verify step, 0: look them up.  A wave takes
+// whole rows, or, in a step whose rows would leave ATTN_GENERIC_IDLE waves or more without one at the end, or whose (row, tile) pairs
+// are few, pairs of its own: the tiles of a row meet in LDS, as many of each row at a time as fit.  Latency bounds it (fp32, 32 dimensions,
+// one sequence, us, a wave per row | pairs: 100 tokens and 5 rows 9.0 | 7.8, 2000 and 1 row 68 | 23, 3 rows 84 | 61, 9 rows 174 | 157; bf16, 128
+// dimensions, 2000 tokens, 3 rows 204 | 108, 9 rows 372 | 300; with one or two waves idle the exchange costs more than they give).
 #define ATTN_GENERIC_THREADS 512
-#define ATTN_GENERIC_UNITS 32      // (row, tile) pairs that meet in LDS
+#define ATTN_GENERIC_UNITS 32      // (row, tile) pairs that meet in LDS at a time
+#define ATTN_GENERIC_ROWS 16       // most rows of a sequence that are taken by pairs
+#define ATTN_GENERIC_IDLE 3
 struct AttnTile {
     float m, l, acc[4];            // maximum, sum, output dimensions lane, lane + 64, ..
 };
@@ -383,23 +387,24 @@ __global__ __launch_bounds__(ATTN_GENERIC_THREADS) void k_attn_generic(const T* 
         for (int e = lane; e < hd; e += 64) qi[e] = to_f(q[(row0 + i) * qstride + j * hd + e]);
         __builtin_amdgcn_wave_barrier();
     };
-    const int tiles = (p0 + nr + 63) / 64;     // of the last row, the most of any
     float* const s_part = s_q + NW * hd;
-    if (gridDim.z == 1 && nr * tiles <= ATTN_GENERIC_UNITS) {
-        for (int u = wave; u < nr * tiles; u += NW) {
-            const int i = u / tiles, t0 = 64 * (u % tiles), L = p0 + i + 1;
-            if (t0 >= L) continue;
-            load_q(i);
-            const AttnTile o = attn_tile(qi, kv_layer, bt, first_pages, gm, g, t0, L, scale, lane);
-            float* part = s_part + u * (hd + 2);
+    const int tiles = (p0 + nr + 63) / 64;     // of the last row, the most of any
+    auto pair = [&](int u, int i, int t0) __attribute__((always_inline)) {       // row i's tile at t0, to place u
+        const int L = p0 + i + 1;
+        if (t0 >= L) return;
+        load_q(i);
+        const AttnTile o = attn_tile(qi, kv_layer, bt, first_pages, gm, g, t0, L, scale, lane);
+        float* part = s_part + u * (hd + 2);
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (lane + 64 * c < hd) part[lane + 64 * c] = o.acc[c];
-            if (lane == 0) {
-                part[hd] = o.m;
-                part[hd + 1] = o.l;
-            }
+        for (int c = 0; c < 4; ++c)
+            if (lane + 64 * c < hd) part[lane + 64 * c] = o.acc[c];
+        if (lane == 0) {
+            part[hd] = o.m;
+            part[hd + 1] = o.l;
         }
+    };
+    if (gridDim.z == 1 && nr * tiles <= ATTN_GENERIC_UNITS) {
+        for (int u = wave; u < nr * tiles; u += NW) pair(u, u / tiles, 64 * (u % tiles));
         __syncthreads();
         for (int idx = threadIdx.x; idx < nr * hd; idx += ATTN_GENERIC_THREADS) {
             const int i = idx / hd, e = idx % hd;
@@ -409,6 +414,37 @@ __global__ __launch_bounds__(ATTN_GENERIC_THREADS) void k_attn_generic(const T* 
                 attn_add(m, l, acc, part[hd], part[hd + 1], part[e]);
             }
             att[(row0 + i) * qstride + j * hd + e] = from_f<T>(acc / l);
+        }
+        return;
+    }
+    if (gridDim.z == 1 && (NW - nr % NW) % NW >= ATTN_GENERIC_IDLE) {            // (at most ATTN_GENERIC_ROWS rows, and one)
+        const int per = ATTN_GENERIC_UNITS / nr;                                 // tiles of each row at a time
+        constexpr int OWN = ATTN_GENERIC_ROWS * 256 / ATTN_GENERIC_THREADS;                     // (row, dimension) pairs of a thread
+        float m[OWN], l[OWN], acc[OWN];
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            m[o] = -INFINITY;
+            l[o] = acc[o] = 0.f;
+        }
+        for (int tp = 0; tp < tiles; tp += per) {
+            const int np = min(per, tiles - tp);
+            for (int u = wave; u < nr * np; u += NW) pair(u, u / np, 64 * (tp + u % np));
+            __syncthreads();
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) {
+                const int idx = threadIdx.x + o * ATTN_GENERIC_THREADS, i = idx / hd, e = idx % hd;
+                if (idx >= nr * hd) break;
+                for (int t = 0; t < np && 64 * (tp + t) < p0 + i + 1; ++t) {
+                    const float* part = s_part + (i * np + t) * (hd + 2);
+                    attn_add(m[o], l[o], acc[o], part[hd], part[hd + 1], part[e]);
+                }
+            }
+            if (tp + per < tiles) __syncthreads();
+        }
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const int idx = threadIdx.x + o * ATTN_GENERIC_THREADS, i = idx / hd, e = idx % hd;
+            if (idx < nr * hd) att[(row0 + i) * qstride + j * hd + e] = from_f<T>(acc[o] / l[o]);
         }
         return;
     }
