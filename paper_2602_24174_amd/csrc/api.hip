@@ -299,7 +299,7 @@ size_t slice_rows(size_t ml, size_t m) { return std::max({8 * ml, std::min<size_
 WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows, int64_t chunk_rows) {
     const size_t ML = (size_t)B * max_rows, M = (size_t)chunk_rows, es = elt_size(c.dtype);
     const size_t HD = (size_t)c.n_heads * c.head_dim, KD = (size_t)c.n_kv_heads * c.head_dim;
-    const size_t n_strips = ((size_t)c.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP, n_parts = n_strips * tasc_generic_lm_split((int)n_strips);
+    const size_t n_strips = ((size_t)c.vocab + TASC_LM_STRIP - 1) / TASC_LM_STRIP, n_parts = n_strips * tasc_generic_lm_split((int)n_strips, c.d_model);
     const size_t max_blocks = ((size_t)max_len + TASC_KV_BLOCK - 1) / TASC_KV_BLOCK;
     const size_t sizes[] = {
         (size_t)B * max_len * 4,  // tokens
@@ -310,7 +310,7 @@ WsLayout ws_layout(const tasc_model_desc& c, int B, int max_len, int max_rows, i
         ML * 4, ML * 4,                                              // sel_rows sel_tok
         TASC_N_COUNTERS * 8,                                         // counters (+ barrier flags)
         M * c.d_model * 4,                                           // x
-        M * std::max<size_t>(c.d_model, 1) * es,                     // h
+        M * c.d_model * 4,                                           // h
         M * HD * es, M * HD * es,                                    // q att
         M * (size_t)c.d_ffn * es,                                    // act
         ML * n_parts * 4, ML * n_parts * 4, ML * 4,                  // part_val part_idx amax

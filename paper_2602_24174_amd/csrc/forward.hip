@@ -133,13 +133,35 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
         k_embed<T><<<dim3(M), dim3(64), 0, st>>>((const T*)m->embed, d.row_tok, D, d.x, step_rows(m, s, tail));
     }
     TASC_LAUNCH_CHECK();
+    // a product of the residual stream's norm, or of `in`; lanes take 8 columns at a time where that leaves none of them out
+    const bool along = D <= kNormAlong;
+    float* const h = (float*)d.h;
+    auto product = [&](auto epi, const auto* in, const float* gain, const void* weights, int n, int k, float* outf, T* outT, T* kv_layer, const GenericRope& rp) {
+        constexpr int EPI = decltype(epi)::value;
+        using AT = std::remove_cv_t<std::remove_pointer_t<decltype(in)>>;
+        const dim3 grid((n + 3) / 4, chunks);
+        if (gain && along) {
+            if constexpr (std::is_same_v<AT, float>)
+                k_gemm_generic<T, AT, EPI, true, 4><<<grid, dim3(256), 0, st>>>(in, (const T*)weights, M, n, k, gain, c.rms_eps, outf, outT, kv_layer, rp);
+        } else if (k < 512) {
+            k_gemm_generic<T, AT, EPI, false, 4><<<grid, dim3(256), 0, st>>>(in, (const T*)weights, M, n, k, nullptr, 0.f, outf, outT, kv_layer, rp);
+        } else {
+            k_gemm_generic<T, AT, EPI, false, 8><<<grid, dim3(256), 0, st>>>(in, (const T*)weights, M, n, k, nullptr, 0.f, outf, outT, kv_layer, rp);
+        }
+    };
+    auto norm = [&](const float* gain, const int32_t* sel, int rows) {
+        if (along) return;
+        PROF(TASC_KC_NORM);
+        k_rmsnorm<float><<<dim3(rows), dim3(64), 0, st>>>(d.x, gain, sel, D, c.rms_eps, h);
+    };
+    const float* const rows_in = along ? d.x : h;
     for (int l = 0; l < c.n_layers; ++l) {
         const TascLayerW& w = m->layers[l];
         T* kv_layer = (T*)s->kv_pool + (size_t)l * s->kv_layer_stride;
+        norm(w.g1, nullptr, M);
         {
             PROF(TASC_KC_GEMM_QKV);
-            k_gemm_generic<T, EPI_ROPE, true><<<dim3((pairs + 3) / 4, chunks), dim3(256), 0, st>>>(d.x, (const T*)w.wqkv, M, pairs, D, w.g1, c.rms_eps,
-                                                                                            nullptr, (T*)d.q, kv_layer, rope);
+            product(std::integral_constant<int, EPI_ROPE>{}, rows_in, w.g1, w.wqkv, pairs, D, nullptr, (T*)d.q, kv_layer, rope);
         }
         {
             PROF(TASC_KC_ATTN);
@@ -148,38 +170,37 @@ tasc_status forward_generic(const tasc_model* m, tasc_session* s, int nq, int M,
         }
         {
             PROF(TASC_KC_GEMM_O);
-            k_gemm_generic<T, EPI_RESID, false><<<dim3((D + 3) / 4, chunks), dim3(256), 0, st>>>(d.att, (const T*)w.wo, M, D, nqo, nullptr, 0.f, d.x, nullptr,
-                                                                                      nullptr, GenericRope{});
+            product(std::integral_constant<int, EPI_RESID>{}, (const T*)d.att, nullptr, w.wo, D, nqo, d.x, nullptr, nullptr, GenericRope{});
         }
+        norm(w.g2, nullptr, M);
         {
             PROF(TASC_KC_GEMM_GU);
-            k_gemm_generic<T, EPI_SWIGLU, true><<<dim3((F + 3) / 4, chunks), dim3(256), 0, st>>>(d.x, (const T*)w.wgu, M, F, D, w.g2, c.rms_eps, nullptr,
-                                                                                      (T*)d.act, nullptr, GenericRope{});
+            product(std::integral_constant<int, EPI_SWIGLU>{}, rows_in, w.g2, w.wgu, F, D, nullptr, (T*)d.act, nullptr, GenericRope{});
         }
         {
             PROF(TASC_KC_GEMM_D);
-            k_gemm_generic<T, EPI_RESID, false><<<dim3((D + 3) / 4, chunks), dim3(256), 0, st>>>(d.act, (const T*)w.wd, M, D, F, nullptr, 0.f, d.x, nullptr,
-                                                                                      nullptr, GenericRope{});
+            product(std::integral_constant<int, EPI_RESID>{}, (const T*)d.act, nullptr, w.wd, D, F, d.x, nullptr, nullptr, GenericRope{});
         }
         TASC_LAUNCH_CHECK();
     }
     if (n_sel > 0) {
         const BiasCsr bias{m->bias_rowptr, m->bias_col, m->bias_val, m->bias_base};
-        const bool split = tasc_generic_lm_split(s->n_strips) > 1;
-        const int parts = s->n_strips * tasc_generic_lm_split(s->n_strips);
-        float* const pv = d.part_val;
-        int32_t* const pi = d.part_idx;
+        const int split = tasc_generic_lm_split(s->n_strips, D), parts = s->n_strips * split;
+        norm(m->gf, d.sel_rows, n_sel);
         {
             PROF(TASC_KC_LMHEAD);
-            if (split)
-                k_lmhead_generic<T, 4, TASC_LM_STRIP / 8 / 4><<<dim3(parts), dim3(64 * 5), 0, st>>>(
-                    d.x, d.sel_rows, m->gf, c.rms_eps, (const T*)m->lm_head, d.sel_tok, n_sel, c.vocab, D, bias, pv, pi, parts, logits_dbg);
-            else
-                k_lmhead_generic<T, 8, TASC_LM_STRIP / 8><<<dim3(parts), dim3(64 * 9), 0, st>>>(
-                    d.x, d.sel_rows, m->gf, c.rms_eps, (const T*)m->lm_head, d.sel_tok, n_sel, c.vocab, D, bias, pv, pi, parts, logits_dbg);
+            auto head = [&](auto kernel, int threads) {
+                kernel<<<dim3(parts), dim3(threads), 0, st>>>(rows_in, d.sel_rows, m->gf, c.rms_eps, (const T*)m->lm_head, d.sel_tok, n_sel, c.vocab, D, bias,
+                                                             d.part_val, d.part_idx, parts, logits_dbg);
+            };
+            constexpr int strip = TASC_LM_STRIP;
+            if (split == 8) along ? head(&k_lmhead_generic<T, 4, strip / 32, true, true, 4>, 320) : D < 512 ? head(&k_lmhead_generic<T, 4, strip / 32, true, false, 4>, 320)
+                                                                                                  : head(&k_lmhead_generic<T, 4, strip / 32, true, false, 8>, 320);
+            else along ? head(&k_lmhead_generic<T, 16, strip / 16, false, true, 4>, 1024) : D < 512 ? head(&k_lmhead_generic<T, 16, strip / 16, false, false, 4>, 1024)
+                                                                                        : head(&k_lmhead_generic<T, 16, strip / 16, false, false, 8>, 1024);
         }
         TASC_LAUNCH_CHECK();
-        return finish_rows(s, n_sel, parts, pv, pi, tail, st);
+        return finish_rows(s, n_sel, parts, d.part_val, d.part_idx, tail, st);
     }
     return TASC_OK;
 }

@@ -40,6 +40,12 @@ __device__ inline void load4(const BF16* __restrict__ p, float* o) {
     o[0] = bf2f(u.x & 0xFFFFu); o[1] = bf2f(u.x >> 16); o[2] = bf2f(u.y & 0xFFFFu); o[3] = bf2f(u.y >> 16);
 }
 
+template <int VEC, typename T>
+__device__ inline void load_n(const T* __restrict__ p, float* o) {
+    if constexpr (VEC == 8) load8(p, o);
+    else load4(p, o);
+}
+
 __device__ inline float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
@@ -167,24 +173,29 @@ struct GenericRope {          // EPI_ROPE only
     int32_t max_pos, nq;      // nq: rows of every sequence, all active, in a verify step; 0: look them up
 };
 
-// The products of up to 8 rows (R of them, from row0 on) with one weight row, or two, by one wave: every lane sums its own k-slices in
-// ascending order, then the 64 partial sums are added in the order of wave_sum_dpp.  Lane r < 8 returns with row r's.  NORM: A is the
+// Up to this width the norms ride along with the products behind them: a small model's launches are what it waits for.  Beyond, every
+// column's wave would sum the squares and scale the weights again for nothing (verify steps, fp32, two layers, us, norms in launches of their
+// own | along: 5 rows, d 128 73 | 67, 256 78 | 72, 384 103 | 95, 2048 275 | 281; 224 rows 254 | 280, 330 | 364, 566 | 622, 3960 | 4930).
+constexpr int kNormAlong = 256;
+
+// The products of up to 8 rows (R of them, from row0 on) with one weight row, or two, by one wave: every lane sums its own k-slices (VEC
+// wide) in ascending order, then the 64 partial sums are added in the order of wave_sum_dpp.  Lane r < 8 returns with row r's.  NORM: A is the
 // residual stream and the product is with its RMSNorm (gain g): the sum of squares is taken along with the products, of weights
 // already multiplied by the gain.
 struct RowDots { float v, u; };
-template <typename T, bool PAIR, bool NORM>
-__device__ __forceinline__ RowDots row_dots(const void* __restrict__ A_, int row0, int R, const T* __restrict__ w0, const T* __restrict__ w1, int K,
+template <typename T, typename AT, bool PAIR, bool NORM, int VEC>
+__device__ __forceinline__ RowDots row_dots(const AT* __restrict__ A, int row0, int R, const T* __restrict__ w0, const T* __restrict__ w1, int K,
                                             const float* __restrict__ g, float eps, int lane) {
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, acu[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ss[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll 2
-    for (int k = lane * 4; k < K; k += 256) {
-        float wv[4], uv[4], gv[4];
-        load4(w0 + k, wv);
-        if (PAIR) load4(w1 + k, uv);
+    for (int k = lane * VEC; k < K; k += 64 * VEC) {
+        float wv[VEC], uv[VEC], gv[VEC];
+        load_n<VEC>(w0 + k, wv);
+        if (PAIR) load_n<VEC>(w1 + k, uv);
         if (NORM) {
-            load4(g + k, gv);
+            load_n<VEC>(g + k, gv);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < VEC; ++e) {
                 wv[e] *= gv[e];
                 if (PAIR) uv[e] *= gv[e];
             }
@@ -192,11 +203,10 @@ __device__ __forceinline__ RowDots row_dots(const void* __restrict__ A_, int row
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             if (r < R) {
-                float av[4];
-                if constexpr (NORM) load4(reinterpret_cast<const float*>(A_) + (size_t)(row0 + r) * K + k, av);
-                else load4(reinterpret_cast<const T*>(A_) + (size_t)(row0 + r) * K + k, av);
+                float av[VEC];
+                load_n<VEC>(A + (size_t)(row0 + r) * K + k, av);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
+                for (int e = 0; e < VEC; ++e) {
                     acc[r] = fmaf(av[e], wv[e], acc[r]);
                     if (PAIR) acu[r] = fmaf(av[e], uv[e], acu[r]);
                     if (NORM) ss[r] = fmaf(av[e], av[e], ss[r]);
@@ -246,8 +256,8 @@ __device__ __forceinline__ void rope_store(const GenericRope& rp, int head, int 
 // Of a small model's step each launch is a few dependent loads and its own start and end (fp32, d 128, 5 rows: 4.6 to 5.4 us; 4.1 to
 // 4.9 with norm, rotation and cache append as launches of 2.4 and 2.8 us beside it): so those ride along, and what an epilogue needs
 // is requested before the products.  (The projection inside the attention's workgroups was slower: 22.8 us against 5.4 + 7.8.)
-template <typename T, int EPI, bool NORM>
-__global__ __launch_bounds__(256) void k_gemm_generic(const void* __restrict__ A, const T* __restrict__ W, int M, int N, int K,
+template <typename T, typename AT, int EPI, bool NORM, int VEC>
+__global__ __launch_bounds__(256) void k_gemm_generic(const AT* __restrict__ A, const T* __restrict__ W, int M, int N, int K,
                                                       const float* __restrict__ g, float eps, float* outf, T* __restrict__ outT,
                                                       T* __restrict__ kv_layer, GenericRope rp) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -284,7 +294,7 @@ __global__ __launch_bounds__(256) void k_gemm_generic(const void* __restrict__ A
             }
             if (active) page = kv_layer + (size_t)rp.block_tab[(size_t)b * gm.max_blocks + pos / TASC_KV_BLOCK] * gm.page_elems;
         }
-        const RowDots d = row_dots<T, EPI != EPI_RESID, NORM>(A, r0, min(8, M - r0), w0, w1, K, g, eps, lane);
+        const RowDots d = row_dots<T, AT, EPI != EPI_RESID, NORM, VEC>(A, r0, min(8, M - r0), w0, w1, K, g, eps, lane);
         if (!own) continue;
         if (EPI == EPI_RESID) outf[(size_t)row * N + col] = old + d.v;
         if (EPI == EPI_SWIGLU) outT[(size_t)row * N + col] = from_f<T>(d.v / (1.0f + expf(-d.v)) * d.u);
@@ -478,14 +488,13 @@ struct BiasCsr {
     const float* base;
 };
 
-// x: [rows, d] residual stream; LM-head row r is the final RMSNorm (gain gf) of row sel[r] (negative: row 0) and was fed token tok[r]
-// (its bias row).  WAVES waves take CW columns each, four at a time, and leave per row the best (value, index) of the workgroup's
-// columns; index ties go to the lowest.  logits (nullable) receives every logit.  The norm's sum of squares is taken along with
-// the products.  One more wave looks up the rows' seen successors among the columns, eight lanes a row, while the others multiply,
+// x: NORM: [rows, d] residual stream, LM-head row r is the final RMSNorm (gain gf) of row sel[r] (negative: row 0); else the normalised
+// rows themselves.  Row r was fed token tok[r] (its bias row).  WAVES waves take CW columns each, four at a time, and leave per row the best (value, index) of the workgroup's
+// columns; index ties go to the lowest.  logits (nullable) receives every logit.  One more wave looks up the rows' seen successors among the columns, eight lanes a row, while the others multiply,
 // and leaves their bias in LDS.  Few columns a workgroup for a vocabulary of few strips: 512 columns in four workgroups of 16 waves, a
 // binary search by one lane per row in front, took 24 us, all of it latency; 6.3 us now.
-template <typename T, int WAVES, int CW>
-__global__ __launch_bounds__(64 * (WAVES + 1)) void k_lmhead_generic(const float* __restrict__ x, const int32_t* __restrict__ sel,
+template <typename T, int WAVES, int CW, bool LOOKUP, bool NORM, int VEC>
+__global__ __launch_bounds__(64 * (WAVES + LOOKUP)) void k_lmhead_generic(const float* __restrict__ x, const int32_t* __restrict__ sel,
                                                         const float* __restrict__ gf, float eps, const T* __restrict__ W,
                                                         const int32_t* __restrict__ tok, int n_rows, int V, int d,
                                                         BiasCsr bias, float* __restrict__ part_val,
@@ -500,9 +509,11 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void k_lmhead_generic(const float
     for (int r0 = 0; r0 < n_rows; r0 += 8) {
         const int row = r0 + lane;
         const bool own = lane < 8 && row < n_rows;
-        float z[CW];                                                  // lane r: the row's logits without bias
-        if (wave == WAVES) {
-            const int r = lane >> 3, q = lane & 7;
+        float best = -INFINITY;
+        int32_t best_i = 0x7FFFFFFF;
+        // the bias of row r0 + r at the workgroup's columns, by G lanes, this one number q
+        auto row_bias = [&](int r, int q, auto group) __attribute__((always_inline)) {
+            constexpr int G = decltype(group)::value;
             float base = 0.f;
             int64_t lo = 0, hi = 0, end = 0;
             if (bias.rowptr && r0 + r < n_rows) {
@@ -511,87 +522,113 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void k_lmhead_generic(const float
                 lo = bias.rowptr[u];
                 hi = end = bias.rowptr[u + 1];
             }
-            for (int c = q; c < COLS; c += 8) s_bias[r][c] = base;
-            // first entry of the row with a column >= first: the range in nine parts per look
+            for (int c = q; c < COLS; c += G) s_bias[r][c] = base;
+            // first entry of the row with a column >= first: the range in G + 1 parts per look
             while (__ballot(hi - lo > 0) != 0) {
-                const int64_t n = hi - lo, at = lo + n * (q + 1) / 9;          // (below hi)
-                const bool below = n > 0 && bias.col[at] < first;
-                const int k = __popc((u32)(__ballot(below) >> (8 * r)) & 0xFF);        // ascending: the first k are
-                const int64_t from = k > 0 ? lo + n * k / 9 + 1 : lo;
-                if (k < 8) hi = lo + n * (k + 1) / 9;
+                const int64_t n = hi - lo, at = lo + n * (q + 1) / (G + 1);          // (below hi)
+                const u64 below = __ballot(n > 0 && bias.col[at] < first) >> (lane - q);
+                const int k = __popcll(G < 64 ? below & ((1ull << (G & 63)) - 1) : below);        // ascending: the first k are
+                const int64_t from = k > 0 ? lo + n * k / (G + 1) + 1 : lo;
+                if (k < G) hi = lo + n * (k + 1) / (G + 1);
                 lo = n > 0 ? from : lo;
                 hi = hi > lo ? hi : lo;
             }
             __builtin_amdgcn_wave_barrier();
-            for (int64_t p = lo + q; p < end; p += 8) {
+            for (int64_t p = lo + q; p < end; p += G) {
                 const int c = bias.col[p] - first;
                 if (c >= COLS) break;
                 s_bias[r][c] = bias.val[p];
             }
-        } else {
+        };
+        // lane r: row r0 + r's logits without bias at columns at .. at + CB - 1
+        auto columns = [&](int at, float* z) __attribute__((always_inline)) {
+            float acc[CB][8], ss[8];
 #pragma unroll
-            for (int cb = 0; cb < CW; cb += CB) {
-                float acc[CB][8], ss[8];
+            for (int r = 0; r < 8; ++r) {
+                ss[r] = 0.f;
+#pragma unroll
+                for (int u = 0; u < CB; ++u) acc[u][r] = 0.f;
+            }
+            size_t from[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) from[r] = (size_t)(NORM ? max(sel[min(r0 + r, n_rows - 1)], 0) : r0 + r) * d;
+            for (int k = lane * VEC; k < d; k += 64 * VEC) {
+                float wv[CB][VEC], gv[VEC];
+                if (NORM) load_n<VEC>(gf + k, gv);
+#pragma unroll
+                for (int u = 0; u < CB; ++u) load_n<VEC>(W + (size_t)min(at + u, V - 1) * d + k, wv[u]);
+#pragma unroll
+                for (int u = 0; u < CB; ++u)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        if (NORM) wv[u][e] *= gv[e];
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    ss[r] = 0.f;
+                    if (r0 + r < n_rows) {
+                        float av[VEC];
+                        load_n<VEC>(x + from[r] + k, av);
 #pragma unroll
-                    for (int u = 0; u < CB; ++u) acc[u][r] = 0.f;
-                }
-                const float* xr[8];
+                        for (int e = 0; e < VEC; ++e) {
+                            if (NORM) ss[r] = fmaf(av[e], av[e], ss[r]);
 #pragma unroll
-                for (int r = 0; r < 8; ++r) xr[r] = x + (size_t)max(sel[min(r0 + r, n_rows - 1)], 0) * d;
-                for (int k = lane * 4; k < d; k += 256) {
-                    float wv[CB][4], gv[4];
-                    load4(gf + k, gv);
-#pragma unroll
-                    for (int u = 0; u < CB; ++u) load4(W + (size_t)min(c0 + cb + u, V - 1) * d + k, wv[u]);
-#pragma unroll
-                    for (int u = 0; u < CB; ++u)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) wv[u][e] *= gv[e];
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        if (r0 + r < n_rows) {
-                            float av[4];
-                            load4(xr[r] + k, av);
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                ss[r] = fmaf(av[e], av[e], ss[r]);
-#pragma unroll
-                                for (int u = 0; u < CB; ++u) acc[u][r] = fmaf(av[e], wv[u][e], acc[u][r]);
-                            }
+                            for (int u = 0; u < CB; ++u) acc[u][r] = fmaf(av[e], wv[u][e], acc[u][r]);
                         }
                     }
                 }
-                float mine[CB] = {0.f, 0.f, 0.f, 0.f}, mine_s = 0.f;
+            }
+            float mine_s = 0.f;
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
+            for (int u = 0; u < CB; ++u) z[u] = 0.f;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                if (NORM) {
                     const float q = wave_sum_dpp(ss[r]);
                     mine_s = lane == r ? q : mine_s;
-#pragma unroll
-                    for (int u = 0; u < CB; ++u) {
-                        const float v = wave_sum_dpp(acc[u][r]);
-                        mine[u] = lane == r ? v : mine[u];
-                    }
                 }
+#pragma unroll
+                for (int u = 0; u < CB; ++u) {
+                    const float v = wave_sum_dpp(acc[u][r]);
+                    z[u] = lane == r ? v : z[u];
+                }
+            }
+            if (NORM) {
                 const float rinv = 1.0f / sqrtf(mine_s / (float)d + eps);
 #pragma unroll
-                for (int u = 0; u < CB; ++u) z[cb + u] = mine[u] * rinv;
+                for (int u = 0; u < CB; ++u) z[u] *= rinv;
+            }
+        };
+        auto take = [&](int c, float z) __attribute__((always_inline)) {
+            if (!own || c >= V) return;
+            const float y = z + s_bias[lane][c - first];
+            if (logits) logits[(size_t)row * V + c] = y;
+            if (y > best) { best = y; best_i = c; }
+        };
+        if constexpr (LOOKUP) {                            // one more wave looks the bias up meanwhile
+            float z[CW];
+            if (wave == WAVES) {
+                row_bias(lane >> 3, lane & 7, std::integral_constant<int, 8>{});
+            } else {
+#pragma unroll
+                for (int cb = 0; cb < CW; cb += CB) columns(c0 + cb, z + cb);
+            }
+            __syncthreads();
+            if (wave < WAVES) {
+#pragma unroll
+                for (int u = 0; u < CW; ++u) take(c0 + u, z[u]);
+            }
+        } else {                                           // the first eight waves do, a row each, in front
+            static_assert(WAVES >= 8, "a wave per row");
+            if (wave < 8) row_bias(wave, lane, std::integral_constant<int, 64>{});
+            __syncthreads();
+#pragma unroll 1
+            for (int cb = 0; cb < CW && c0 + cb < V; cb += CB) {
+                float z[CB];
+                columns(c0 + cb, z);
+#pragma unroll
+                for (int u = 0; u < CB; ++u) take(c0 + cb + u, z[u]);
             }
         }
-        __syncthreads();
-        float best = -INFINITY;
-        int32_t best_i = 0x7FFFFFFF;
         if (wave < WAVES && own) {
-#pragma unroll
-            for (int u = 0; u < CW; ++u) {
-                const int c = c0 + u;
-                if (c >= V) break;
-                const float y = z[u] + s_bias[lane][wave * CW + u];
-                if (logits) logits[(size_t)row * V + c] = y;
-                if (y > best) { best = y; best_i = c; }
-            }
             s_v[wave][lane] = best;
             s_i[wave][lane] = best_i;
         }

@@ -262,7 +262,7 @@ struct TascSessDev {
     u64* counters;
     // activations
     float* x;            // [M_max, d] residual stream
-    void* h;             // [M_max, d]   normalised activations, model dtype
+    void* h;             // [M_max, d]   normalised activations, model dtype (the type-generic kernels: fp32)
     void* q;             // [M_max, H hd] rotated queries, model dtype
     void* att;           // [M_max, H hd]
     void* act;           // [M_max, F]
@@ -322,10 +322,10 @@ struct tasc_session {
 #define TASC_CTR_XCD_STEPS 28 // steps of the persistent kernel whose layer group used XCD-local barriers
 #define TASC_CTR_XCC 27       // XCDs the layer group of the running step found itself on (low 32 bits)
 
-// Into how many parts the type-generic LM head cuts a strip of TASC_LM_STRIP columns, a workgroup each.  Few columns a workgroup where
-// whole strips would leave the chip idle (us with whole strips | with eighths, 5 rows, d 128: vocabulary of 512 26.8 | 9.3, 8192 27.0 | 10.3,
-// 16384 27.0 | 17.9, 32768 28.0 | 26.2 and 2 more for the larger argmax; d 512: 31.6 | 10.8, 31.9 | 11.9, 34.7 | 24.4, 36.6 | 36.8).
-inline int tasc_generic_lm_split(int n_strips) { return n_strips <= 128 ? 8 : 1; }
+// Into how many parts the type-generic LM head cuts a strip of TASC_LM_STRIP columns, a workgroup each: few columns a workgroup where
+// whole strips would leave the chip idle (us, whole strips | eighths, 5 rows: d 128, vocabulary of 8192 25 | 10, 16384 25 | 18, 32768
+// 24 | 26; d 2048, 8192 38 | 21, 16384 38 | 45).
+inline int tasc_generic_lm_split(int n_strips, int d) { return n_strips <= (d <= 1024 ? 128 : 64) ? 8 : 1; }
 
 // what makes a forward a verify step: its rows are the sequences' pending tokens and the drafts, and it ends with the acceptance
 struct TascVerifyTail {
