@@ -73,22 +73,33 @@ def test_tables(vocab, length, n_max, p_min):
         assert torch.equal(ref.key_of(rows), keys[keep]) and (counts[keep].cpu().numpy() == got).all()
 
 
-def test_enrichment():
-    import paper_2602_24174_amd as T
-    vocab, length = 100_000, 150_000_000
-    tok, off = _corpus(length, vocab)
-    g = np.random.default_rng(1)
+@pytest.mark.parametrize("vocab,length", [(3000, 2_300_000), (90_000, 2_100_000), (100_000, 150_000_000)])
+def test_enrichment(vocab, length):
+    """From 2 M tokens on chunks are long and their offsets turned, of all orders at once (keys of 48 and of 68 bits); the longest corpus goes order
+    by order, in rounds."""
     import torch
-    at = torch.from_numpy(240 * g.permutation(length // 240)[:60_000] + 100).cuda()      # one 4-gram often enough to be the best
-    for j, t in enumerate((1, 99_999, 50_000, 1)):
+    import paper_2602_24174_amd as T
+    tok, off = _corpus(length, vocab)
+    docs = length // 240
+    at = torch.from_numpy(240 * np.random.default_rng(1).permutation(docs)[:max(docs * 2 // 3, 60_000 if docs > 100_000 else 0)] + 100).cuda()
+    for j, t in enumerate((1, vocab - 1, vocab // 2, 1)):     # one 4-gram often, and one of three in every output but the last
         tok[at + j] = t
-    merges, out, out_off, lens = T.tasc_tok_enrich(tok, off, vocab, 4, 1)
-    ref = Counts(tok, off, vocab)
-    best = []
-    for n in (2, 3, 4):
-        keys, counts = ref.of(n)
-        i = int(torch.nonzero(counts == counts.max())[0])  # (the first, so the smallest)
-        best.append((-int(counts[i]) * (n - 1), n, ref.tokens_of(keys[i], n), int(counts[i])))
-        del keys, counts
-    _, n, gram, freq = min(best)
-    assert n == 4 and merges[0][:2] == (gram, freq) and lens[1] == length - freq * (n - 1)
+    for j, t in enumerate((5, 6, vocab - 2)):
+        tok[240 * torch.arange(docs, device="cuda") + 7 + j] = t
+    merges, _, _, lens = T.tasc_tok_enrich(tok, off, vocab, 4, 2)
+    text, bounds = tok, off
+    for i in range(2):
+        ref = Counts(text, bounds, vocab + 2)
+        best = []
+        for n in (2, 3, 4):
+            keys, counts = ref.of(n)
+            first = int(torch.nonzero(counts == counts.max())[0])      # (the smallest)
+            best.append((-int(counts[first]) * (n - 1), n, ref.tokens_of(keys[first], n), int(counts[first])))
+            del keys, counts
+        _, n, gram, freq = min(best)
+        print(f"{length} tokens, merge {i}: {gram} {freq} times", flush=True)
+        assert merges[i][:2] == (gram, freq) and lens[i] == text.numel()
+        del ref
+        done, text, bounds, _ = T.tasc_tok_enrich(tok, off, vocab, 4, i + 1)
+        assert done == merges[:i + 1]
+    assert lens[2] == text.numel() == bounds[-1]
