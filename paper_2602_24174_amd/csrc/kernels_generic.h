@@ -489,10 +489,13 @@ struct BiasCsr {
 };
 
 // x: NORM: [rows, d] residual stream, LM-head row r is the final RMSNorm (gain gf) of row sel[r] (negative: row 0); else the normalised
-// rows themselves.  Row r was fed token tok[r] (its bias row).  WAVES waves take CW columns each, four at a time, and leave per row the best (value, index) of the workgroup's
-// columns; index ties go to the lowest.  logits (nullable) receives every logit.  One more wave looks up the rows' seen successors among the columns, eight lanes a row, while the others multiply,
-// and leaves their bias in LDS.  Few columns a workgroup for a vocabulary of few strips: 512 columns in four workgroups of 16 waves, a
-// binary search by one lane per row in front, took 24 us, all of it latency; 6.3 us now.
+// rows themselves.  Row r was fed token tok[r] (its bias row).  WAVES waves take CW columns each, four at a time, and leave per row the
+// best (value, index) of the workgroup's columns; index ties go to the lowest.  logits (nullable) receives every logit.
+// LOOKUP, few columns a workgroup (vocabularies of few strips): one more wave looks up the rows' seen successors among the columns, eight
+// lanes a row, while the others multiply, and leaves their bias in LDS: latency bounds it (512 columns in four workgroups of 16 waves, a
+// binary search by one lane per row in front, took 24 us; 6.3 us so).  Else whole strips: the registers hold 16 waves a compute unit and
+// no seventeenth, so eight of them look a row up each, in front, and a column's logits are taken as they come (d 2048, vocabulary of 32000,
+// fp32, 5 rows 58 us, 62 with a binary search per lane, 70 with 8 waves beside one that looks up; bf16 43 and 69 of the latter two).
 template <typename T, int WAVES, int CW, bool LOOKUP, bool NORM, int VEC>
 __global__ __launch_bounds__(64 * (WAVES + LOOKUP)) void k_lmhead_generic(const float* __restrict__ x, const int32_t* __restrict__ sel,
                                                         const float* __restrict__ gf, float eps, const T* __restrict__ W,
