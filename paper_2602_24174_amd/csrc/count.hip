@@ -321,7 +321,8 @@ constexpr int tables_lds() { return table_bytes<WIDE>() + (WIDE ? kStageWide * 1
 // BEST: no list, but the most frequent n-gram of the workgroup's partition.
 // A partition is counted in `rounds` ranges, one table after the other, and each gathers all of the partition's records and drops those
 // of the others.  DEAL, for many rounds: the records are gathered twice, to count those of every round and to lay them out round by
-// round in memory of the workgroup's own, as many rounds at a time as fit there (one that does not fit alone gathers for itself).
+// round in memory of the workgroup's own, as many rounds at a time as fit there (one that does not fit alone gathers for itself).  Where all
+// of them together are more than that, a few n-grams may be most of the corpus: the whole partition is tried in one table first, until that is full.
 template <bool WIDE, bool BEST, bool DEAL>
 __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, TascGram* best_out) {
     constexpr int SLOTS = WIDE ? kSlotsWide : kSlotsNarrow, PRIME = WIDE ? kPrimeWide : kPrimeNarrow, PER = SLOTS / kTabThreads;
@@ -347,6 +348,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
     u32 fine = 1, num = 0;                                 // the range that is being counted: num of rounds x fine
     bool within = false;                                   // only s_place .. of it
     bool dealt = false;                                    // its round's records lie in `deal`
+    bool whole = false;                                    // DEAL: the whole partition is tried in one
     // which of den ranges: from the lower half of the product that chose the partition
     auto range_of = [&](u64 r, u32 den) { return (u32)(((u64)((u32)(hash_of(r, part, a.parts) >> 32) * a.parts) * den) >> 32); };
 
@@ -362,7 +364,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
                 const u64 hi = WIDE ? s_rec[RW * e + RW - 1] : 0;
                 e += kTabThreads;
                 busy = true;
-                if ((DEAL && dealt ? 1 : a.rounds) * fine > 1) {
+                if ((DEAL && (dealt || whole) ? 1 : a.rounds) * fine > 1) {
                     busy = range_of(r, a.rounds * fine) == num;
                     if (within) busy = busy && place_of<WIDE>(r, hi) - s_place < s_places;
                 }
@@ -419,8 +421,9 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
         }
         insert(here);
     };
-    // all records of the partition, STAGE at a time: use(how many), with where they are in s_rec
+    // all records of the partition, STAGE at a time: use(how many), with where they are in s_rec; returns how many in all
     auto gather = [&](auto use) __attribute__((always_inline)) {
+        u32 all = 0;
         for (u32 c0 = 0; c0 < a.chunks; c0 += runs * kTabThreads) {
             // the thread's runs and their place among the records of these chunks
             u32 at[kRuns], len[kRuns], sum = 0, total;
@@ -438,30 +441,41 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
             for (u32 first = 0; first < total; first += STAGE) {
                 u32 to = before;
 #pragma unroll
-                for (int u = 0; u < kRuns; ++u)
-                    for (u32 j = 0; j < len[u]; ++j, ++to)
-                        if (to - first < (u32)STAGE) reinterpret_cast<u32*>(s_rec + RW * (to - first))[0] = (c0 + tid * runs + u) * a.chunk + at[u] + j;
+                for (int u = 0; u < kRuns; ++u) {
+                    // (only the part of a run that belongs here: an n-gram that fills its chunks has 32 records in each)
+                    u32 from = 0, end = len[u];
+                    if (total > (u32)STAGE) {
+                        from = min(max(to, first) - to, end);
+                        end = min(max(first + STAGE, to) - to, end);
+                    }
+                    for (u32 j = from; j < end; ++j) reinterpret_cast<u32*>(s_rec + RW * (to + j - first))[0] = (c0 + tid * runs + u) * a.chunk + at[u] + j;
+                    to += len[u];
+                }
                 __syncthreads();
                 use(min(total - first, (u32)STAGE));
                 __syncthreads();
+                if (DEAL && whole && s_full) return all;
             }
+            all += total;
         }
+        return all;
     };
     auto gathered = [&](u32 e) { return reinterpret_cast<const u32*>(s_rec + RW * e)[0]; };
 
+    if (DEAL) {
+        for (u32 i = tid; i < a.rounds; i += kTabThreads) s_len[i] = 0;
+        whole = gather([&](u32 here) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < MINE; ++k) {
+                const u32 e = k * kTabThreads + tid;
+                if (e < here) atomicAdd(&s_len[range_of(a.rec[(size_t)RW * gathered(e)], a.rounds)], 1u);
+            }
+        }) > a.deal_recs;                                  // (more records than it should have: few n-grams, maybe, often)
+    }
     for (u32 round = 0, end; round < a.rounds; round = end) {
         end = a.rounds;
-        if (DEAL) {
-            if (round == 0) {
-                for (u32 i = tid; i < a.rounds; i += kTabThreads) s_len[i] = 0;
-                gather([&](u32 here) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int k = 0; k < MINE; ++k) {
-                        const u32 e = k * kTabThreads + tid;
-                        if (e < here) atomicAdd(&s_len[range_of(a.rec[(size_t)RW * gathered(e)], a.rounds)], 1u);
-                    }
-                });
-            }
+        dealt = false;
+        if (DEAL && !whole) {
             if (tid == 0) {
                 u32 r = round;
                 for (u32 sum = 0; r < a.rounds && s_len[r] <= a.deal_recs - sum; ++r) {
@@ -499,7 +513,7 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
         }
         fine = 1;
         num = round;
-        while (num < end * fine) {
+        while (num < (DEAL && whole ? 1 : end * fine)) {
             for (int i = tid; i < table_bytes<WIDE>() / 16; i += kTabThreads) reinterpret_cast<ulonglong2*>(lds)[i] = make_ulonglong2(0, 0);
             if (tid == 0) s_full = s_nn = 0;
             if (DEAL && dealt) {
@@ -514,6 +528,11 @@ __device__ __forceinline__ void partition_table(const TablesArgs& a, u32 part, T
             __syncthreads();
             if (s_full) {                                      // more n-grams than slots: the range in two halves
                 __syncthreads();
+                if (DEAL && whole) {                       // they are not few: round by round after all
+                    whole = false;
+                    end = 0;
+                    break;
+                }
                 if (a.rounds * fine < kFinest) {
                     fine *= 2;
                     num *= 2;
@@ -679,8 +698,10 @@ u32 up64(u32 v) { return (v + 63) / 64 * 64; }
 // The partitions' counters fit LDS up to TASC_COUNT_MAX_PARTS of them; what a larger corpus has more is counted in rounds.  Where every
 // round gathers a partition's records for itself, the time grows with the square of the corpus; records that are laid out by round cost
 // two gatherings, a write and a read whatever the rounds are.  Builds of orders 2 to 5, every round for itself | laid out from kDealFrom rounds on, ms:
-// 320 M tokens of a phrase corpus 70.6 | 61.0, 640 M 258 | 136, 1.28 G 999 | 277, 4.2 G 10440 | 972; random ones 640 M 250 | 87.
+// 320 M tokens of a phrase corpus 70.6 | 57.8, 640 M 258 | 136, 1.28 G 999 | 281, 4.2 G 10440 | 978; random ones 640 M 250 | 87.
 // With two rounds it is no gain unless nearly all windows are distinct (160 M 24.3 | 27.8, random 30.9 | 18.0).
+// (A few n-grams that are the whole corpus leave most partitions empty: 1 G tokens of four values 93, of one alone 286, 600 before whole
+// partitions were tried; a table of atomics in memory 234 and 100.)
 constexpr u64 kDealFrom = 3;
 TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide, bool pruned) {
     TascCountPlan p;

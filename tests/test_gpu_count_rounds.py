@@ -1,6 +1,6 @@
 """Corpora whose partitions are counted in two rounds, or in several with the records laid out round by round, keys of up to 64 bits and more, for the
 tables and for the enrichment: bit-exact against sorted keys.  Half of the tokens are of a few: their n-grams leave a record in nearly every
-chunk, so that some partitions, and some rounds, hold more records than a workgroup has room for."""
+chunk, so that some partitions, and some rounds, hold more records than a workgroup has room for; of four tokens alone all do."""
 import numpy as np
 import pytest
 
@@ -56,7 +56,7 @@ class Counts:
         return tuple(out + ([int(key) % self.vocab] if n == 3 else []))
 
 
-@pytest.mark.parametrize("vocab,length,n_max,p_min", [(50_000, 140_000_000, 2, 40), (50_000, 250_000_000, 2, 60), (131_072, 290_000_000, 4, 3)])
+@pytest.mark.parametrize("vocab,length,n_max,p_min", [(50_000, 140_000_000, 2, 40), (50_000, 250_000_000, 2, 60), (131_072, 290_000_000, 4, 3), (4, 200_000_000, 3, 1)])
 def test_tables(vocab, length, n_max, p_min):
     import torch
     import paper_2602_24174_amd as T
