@@ -33,7 +33,8 @@ __device__ inline bool probe(const TascSlot* __restrict__ tab, u64 mask, u64 lo,
     return false;
 }
 
-// One workgroup per sequence.  All its waves bring the tokens to LDS and sort the positions into buckets by their token; then one
+// One workgroup per sequence.  All its waves bring the tokens to LDS and sort the positions into buckets by their token (or leave
+// them in order where that costs more than it saves: kUnsorted); then one
 // WAVE makes the k sequential proposals: every exchange between lanes is a ballot, a lane read or an LDS access of the
 // same wave, so they cross no workgroup barrier.  What bounds it is that chain of dependent steps and not memory (64 sequences of 64
 // to 2,300 tokens, k = 8: 35 us, 55 with one wave and a pass over the sequence per proposal, and no longer at any length from 60 tokens on; its tokens and slots
@@ -114,9 +115,16 @@ __device__ __forceinline__ void key_of(const u32* t, int m, int bits, u64& lo, u
 
 constexpr int kDraftWaves = 8, kDraftThreads = 64 * kDraftWaves;
 constexpr int kBuckets = 1024;                            // of positions by their token
+// Sorting takes 0.5 to 1.5 us.  It is left out where nothing is looked for in the context (lambda 1: a proposal 6.6 | 6.0 us, eight
+// 13.3 | 12.0, one sequence) and where the proposals, times 64 positions that a sequence has room for, are no more than this: each
+// then reads all positions (one proposal, room for 480: 30 tokens with orders to 5 6.9 | 6.0, 256 sequences of 300 8.3 | 7.6; over 256
+// sequences of 3900 a pass over all of them took 15.2, the sort and one bucket 9.4).
+constexpr int kUnsorted = 8;
 __device__ __forceinline__ u32 bucket_of(u32 tok) { return (tok * 0x9E3779B1u) >> 22; }
 static_assert(kBuckets == 1 << 10 && kBuckets == 2 * kDraftThreads, "bucket_of, two buckets per thread");
 
+// SORTED: positions in buckets by their token; else all of them in order, in one
+template <bool SORTED>
 __global__ __launch_bounds__(kDraftThreads) void k_draft(DraftArgs a) {
     __shared__ __attribute__((aligned(16))) int32_t s_tok[TASC_DRAFT_MAX_LEN];
     __shared__ uint16_t s_index[TASC_DRAFT_MAX_LEN];      // positions that a token follows, by bucket of their token
@@ -146,31 +154,33 @@ __global__ __launch_bounds__(kDraftThreads) void k_draft(DraftArgs a) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) t[u] = seq[min(u * kDraftThreads + tid, N - 1)];
         for (u32 i = 2 * tid; i <= tab_mask; i += 2 * kDraftThreads) *reinterpret_cast<ulonglong2*>(&s_tab[i]) = make_ulonglong2(0, 0);   // generation 0 = never used
-        *reinterpret_cast<uint2*>(&s_bucket[2 * tid]) = make_uint2(0, 0);
+        if (SORTED) *reinterpret_cast<uint2*>(&s_bucket[2 * tid]) = make_uint2(0, 0);
 #pragma unroll
         for (int u = 0; u < PER; ++u)
             if (u * kDraftThreads + tid < N) s_tok[u * kDraftThreads + tid] = t[u];
         __syncthreads();
+        if constexpr (SORTED) {
 #pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (u * kDraftThreads + tid < Nctx - 1) rank[u] = atomicAdd(&s_bucket[bucket_of((u32)t[u])], 1u);
-        __syncthreads();
-        const uint2 n = *reinterpret_cast<const uint2*>(&s_bucket[2 * tid]);
-        u32 at = n.x + n.y;
-        for (int o = 1; o < 64; o <<= 1) {
-            const u32 v = __shfl_up(at, o);
-            if (lane >= o) at += v;
+            for (int u = 0; u < PER; ++u)
+                if (u * kDraftThreads + tid < Nctx - 1) rank[u] = atomicAdd(&s_bucket[bucket_of((u32)t[u])], 1u);
+            __syncthreads();
+            const uint2 n = *reinterpret_cast<const uint2*>(&s_bucket[2 * tid]);
+            u32 at = n.x + n.y;
+            for (int o = 1; o < 64; o <<= 1) {
+                const u32 v = __shfl_up(at, o);
+                if (lane >= o) at += v;
+            }
+            if (lane == 63) s_wave[tid >> 6] = at;
+            __syncthreads();
+            for (int w = 0; w < (tid >> 6); ++w) at += s_wave[w];
+            *reinterpret_cast<uint2*>(&s_bucket[2 * tid]) = make_uint2(at - n.x - n.y, at - n.y);
+            if (tid == kDraftThreads - 1) s_bucket[kBuckets] = at;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (u * kDraftThreads + tid < Nctx - 1) s_index[s_bucket[bucket_of((u32)t[u])] + rank[u]] = (uint16_t)(u * kDraftThreads + tid);
+            __syncthreads();
         }
-        if (lane == 63) s_wave[tid >> 6] = at;
-        __syncthreads();
-        for (int w = 0; w < (tid >> 6); ++w) at += s_wave[w];
-        *reinterpret_cast<uint2*>(&s_bucket[2 * tid]) = make_uint2(at - n.x - n.y, at - n.y);
-        if (tid == kDraftThreads - 1) s_bucket[kBuckets] = at;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (u * kDraftThreads + tid < Nctx - 1) s_index[s_bucket[bucket_of((u32)t[u])] + rank[u]] = (uint16_t)(u * kDraftThreads + tid);
-        __syncthreads();
     }
     if (tid >= 64) return;
 
@@ -211,13 +221,14 @@ __global__ __launch_bounds__(kDraftThreads) void k_draft(DraftArgs a) {
             int n_list = 0, my_ml = 0, e_at = 0;
             // the places of the last token: those of its bucket that are it ...
             const u32 bk = bucket_of(suf[0]);
-            const int from = (int)s_bucket[bk], to = (int)s_bucket[bk + 1];
+            const int from = SORTED ? (int)s_bucket[bk] : 0, to = SORTED ? (int)s_bucket[bk + 1] : max(Nctx - 1, 0);
+            auto place = [&](int i) { return SORTED ? (int)s_index[i] : i; };
             const bool direct = to - from <= 64;           // a lane each, no list
             if (direct) {
-                e_at = from + lane < to ? s_index[from + lane] : 0;
+                e_at = from + lane < to ? place(from + lane) : 0;
             } else {
                 for (int p0 = from; p0 < to; p0 += 64) {
-                    const int at = s_index[min(p0 + lane, to - 1)];
+                    const int at = place(min(p0 + lane, to - 1));
                     const bool hit = p0 + lane < to && (u32)s_tok[at] == suf[0];
                     const u64 m = __ballot(hit);
                     if (hit) s_pos[n_list + __popcll(m & lt_mask)] = (uint16_t)at;
@@ -464,7 +475,8 @@ extern "C" tasc_status tasc_draft(const tasc_ngram* ng, tasc_session* s, const t
     a.drafts = drafts;
     {
         TascProfScope ps(TASC_KC_DRAFT, (hipStream_t)stream);
-        k_draft<<<dim3(s->batch), dim3(kDraftThreads), 0, (hipStream_t)stream>>>(a);
+        const bool sorted = p->lambda_q16 < 65536 && p->k * ((s->max_len + 63) / 64) > kUnsorted;
+        (sorted ? k_draft<true> : k_draft<false>)<<<dim3(s->batch), dim3(kDraftThreads), 0, (hipStream_t)stream>>>(a);
     }
     TASC_LAUNCH_CHECK();
     return TASC_OK;
