@@ -13,6 +13,8 @@
 #include "kernels_pipe.h"
 #include "kernels_tiled.h"
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 TascConfig g_tasc_config = {/*small_path*/ 2, /*small_grid*/ 0, /*layer_wgs*/ 0, /*layer_stride*/ 0, /*tiled_path*/ 1, /*xcd_local*/ 1,
                              /*layer_workers*/ 0, /*small_kernel*/ 1, /*pipe_share*/ 1, /*chains*/ 0, /*step_graph*/ 1, /*build_list_kib*/ 8 << 20};
@@ -213,48 +215,68 @@ bool tasc_tiled_fits(const tasc_model_desc& c) {
 }
 namespace {
 
-// tile shapes: 128 x 128 on 4 waves, and 256 x 256 on 8 waves for row counts where the GEMMs are MFMA-bound.
-// All reduce every output element over k in the same order, so the choice may depend on the row count.
+// Tile shapes (output features x rows, waves along each): 128 x 128, and 256 x 256 or 256 x 192 for row counts where the GEMMs are
+// MFMA-bound.  All reduce every output element over k in the same order, so the choice may depend on the row count.
 #define TILE_SMALL 128, 128, 2, 2
-#define TILE_LARGE 256, 256, 2, 4
 #define TILE_MID 256, 192, 4, 2        // 192 rows per tile where that leaves fewer padded rows than 256 (576 = 3 x 192)
 #define TILE_NARROW 64, 128, 1, 4      // few rows and a narrow output: twice the workgroups of the small tile
-// Launches of more large tiles than compute units take the streaming kernel (kernels_gemm.h), one workgroup per compute unit:
-// it hides a tile's start, first fetch and stores under its neighbours in the stream.  With one tile per workgroup there is no
-// neighbour, and the two-steps-ahead register staging of the other kernel fills faster (us, in the forwards; one per workgroup |
-// streaming: gate/up 576 x 17920 x 1536 37.9 | 42.3, down in slices 1280 x 2048 x 11008 59.1 | 59.4; more tiles than units:
-// gate/up 16384 x 22016 x 2048 1327 | 1248, 1280 x 22016 x 2048 114 | 111, q/k/v 16384 x 2560 x 2048 240 | 206).
-// Stages of 64 of k, two in LDS, against stages of 32, four in LDS (random operands, us): gate/up 16384 x 22016 x 2048
-// 1245 / 1310, down 16384 x 2048 x 11008 635 / 681 -- half the barriers; but the LM head 1280 x 49152 x 2048 262 / 235, whose
-// longer epilogue leaves a following fetch less time.
+// k_gemm (kernels_gemm.h) takes all launches but these, which fill their LDS through registers (kernels_tiled.h): one round of tiles over at
+// most kFewRows rows, whose weights come from memory for a few row tiles only and are fetched further ahead there (us, registers | straight to
+// LDS: gate/up 576 x 17920 x 1536 in 256 x 192 tiles 38.4 | 42.8, 224 x 9728 x 896 in 128 x 128 ones 12.3 | 12.7, 224 x 896 x 4864 in
+// six slices of 64 x 128 ones 8.5 | 8.8; with more row tiles gate/up 1000 x 9728 x 896 27.2 | 26.8, output 6336 x 1536 x 1536 46.4 | 42.2), the
+// narrow tile, and the 128 x 128 tile's SwiGLU and rotation in one round.  The last two have spans of 64 or 128 features a wave, and so four
+// waves of 64 x 64; the other epilogues take eight of 32 x 64 (us, four waves through registers | eight straight to LDS: 1280 x 2048 x 2048
+// with residual 25.4 | 21.5, 3072 x 1536 x 8960 151 | 134, 576 x 2048 x 1536 in two slices 11.1 | 10.5, 576 x 1536 x 8960 in four 23.8 | 24.1).
+// Stages of 64 of k, two in LDS for the large tiles, four for the small one: a stage of 32 of k is half a cache line of a row, and each half is
+// a request of its own (128 x 128, 1280 x 2560 x 2048, eight stages of 32 | four of 64: 29.4 | 23.1).  The LM head has stages of 32, four in LDS: its
+// longer epilogue leaves a following fetch less time (1280 x 49152 x 2048, two of 64 | four of 32: 262 | 235).
+#define GEMM_SMALL 128, 128, 4, 2, 64, 4
+#define GEMM_SMALL_GU 128, 128, 2, 4, 64, 4
+#define GEMM_SMALL_ROPE 128, 128, 1, 4, 64, 4
 #define GEMM_LARGE 256, 256, 2, 4, 64, 2
 #define GEMM_LARGE_LM 256, 256, 2, 4, 32, 4
 #define GEMM_MID 256, 192, 4, 2, 64, 2
+constexpr int kFewRows = 768;
 constexpr int kLargeTileRows = 384;
 
-template <int EPI>
-constexpr int kLdsLarge = EPI == TEPI_LMHEAD ? gemm_lds_bytes(GEMM_LARGE_LM) : gemm_lds_bytes(GEMM_LARGE);
-template <int EPI>
-constexpr auto k_gemm_large() {
-    if constexpr (EPI == TEPI_LMHEAD) return &k_gemm<EPI, GEMM_LARGE_LM>;
-    else return &k_gemm<EPI, GEMM_LARGE>;
+// kernel and LDS; the head size is the rotation's only
+template <int EPI, int HD>
+constexpr auto gemm_large() {
+    if constexpr (EPI == TEPI_LMHEAD) return std::pair(&k_gemm<EPI, GEMM_LARGE_LM>, gemm_lds_bytes(GEMM_LARGE_LM));
+    else return std::pair(&k_gemm<EPI, GEMM_LARGE, HD>, gemm_lds_bytes(GEMM_LARGE));
 }
+template <int EPI, int HD>
+constexpr auto gemm_small() {
+    if constexpr (EPI == TEPI_SWIGLU) return std::pair(&k_gemm<EPI, GEMM_SMALL_GU>, gemm_lds_bytes(GEMM_SMALL_GU));
+    else if constexpr (EPI == TEPI_ROPE) return std::pair(&k_gemm<EPI, GEMM_SMALL_ROPE, HD>, gemm_lds_bytes(GEMM_SMALL_ROPE));
+    else return std::pair(&k_gemm<EPI, GEMM_SMALL>, gemm_lds_bytes(GEMM_SMALL));
+}
+// f(head_dim as a type), 0 where the epilogue has no use for it
+template <int EPI>
+auto with_head_dim(int hd, auto f) {
+    if constexpr (EPI != TEPI_ROPE) return f(std::integral_constant<int, 0>{});
+    else return hd == 128 ? f(std::integral_constant<int, 128>{}) : hd == 64 ? f(std::integral_constant<int, 64>{}) : f(std::integral_constant<int, 32>{});
+}
+constexpr bool small_in_registers(int epi) { return epi == TEPI_SWIGLU || epi == TEPI_ROPE; }
 
 template <int EPI>
 tasc_status tiled_attrs() {
-    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_SMALL>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TG_LDS_BYTES(128, 128)));
-    TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_large<EPI>()), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLarge<EPI>));
-    if constexpr (EPI != TEPI_ROPE)
-        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm<EPI, GEMM_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     gemm_lds_bytes(GEMM_MID)));
+    auto lds = [](auto kernel, int bytes) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
+    for (int hd : {32, 64, 128})
+        TASC_HIP(with_head_dim<EPI>(hd, [&](auto h) {
+            constexpr auto large = gemm_large<EPI, decltype(h)::value>();
+            const hipError_t rc = lds(large.first, large.second);
+            if constexpr (EPI == TEPI_LMHEAD) return rc;
+            else {
+                constexpr auto small = gemm_small<EPI, decltype(h)::value>();
+                return rc != hipSuccess ? rc : lds(small.first, small.second);
+            }
+        }));
+    if constexpr (EPI != TEPI_ROPE) TASC_HIP(lds(&k_gemm<EPI, GEMM_MID>, gemm_lds_bytes(GEMM_MID)));
+    if constexpr (EPI == TEPI_LMHEAD || small_in_registers(EPI)) TASC_HIP(lds(&k_gemm_tiled<EPI, TILE_SMALL>, TG_LDS_BYTES(128, 128)));
     if constexpr (EPI != TEPI_LMHEAD) {
-        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_LARGE>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     TG_LDS_BYTES(256, 256)));
-        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_MID>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     TG_LDS_BYTES(256, 192)));
-        TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tiled<EPI, TILE_NARROW>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     TG_LDS_BYTES(64, 128)));
+        TASC_HIP(lds(&k_gemm_tiled<EPI, TILE_NARROW>, TG_LDS_BYTES(64, 128)));
+        TASC_HIP(lds(&k_gemm_tiled<EPI, TILE_MID>, TG_LDS_BYTES(256, 192)));
     }
     return TASC_OK;
 }
@@ -290,38 +312,47 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
         const int nt = (N + 255) / 256;
         auto rounds = [&](int mt) { return ((long)mt * nt * slices + cus - 1) / cus; };
         const bool mid = rounds(mt192) * 192 * 12 < rounds(mt256) * 256 * 11;
-        const int tiles = (mid ? mt192 : mt256) * nt * slices;
-        if (EPI == TEPI_LMHEAD || (tiles > cus && !(EPI == TEPI_ROPE && mid))) {   // (that rotation needs whole heads in a wave's features: 128, not 64)
-            if constexpr (EPI != TEPI_ROPE) {
-                if (mid) {
-                    k_gemm<EPI, GEMM_MID><<<dim3((unsigned)cus), dim3(512), gemm_lds_bytes(GEMM_MID), st>>>(A, (const BF16*)Wm, M, N, K, slices, outf,
-                                                                                                           outb, lm, rp);
+        if (mid) {
+            if constexpr (EPI != TEPI_LMHEAD) {
+                // (the other kernel's rotation needs whole heads in a wave's features: 128, not 64)
+                if (EPI == TEPI_ROPE || ((long)mt192 * nt * slices <= cus && M <= kFewRows)) {
+                    k_gemm_tiled<EPI, TILE_MID><<<dim3((unsigned)(mt192 * nt), (unsigned)slices), dim3(512), TG_LDS_BYTES(256, 192), st>>>(
+                        A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
                     return;
                 }
             }
-            k_gemm_large<EPI>()<<<dim3((unsigned)cus), dim3(512), kLdsLarge<EPI>, st>>>(A, (const BF16*)Wm, M, N, K, slices, outf, outb, lm, rp);
+            if constexpr (EPI != TEPI_ROPE) {
+                k_gemm<EPI, GEMM_MID><<<dim3((unsigned)cus), dim3(512), gemm_lds_bytes(GEMM_MID), st>>>(A, (const BF16*)Wm, M, N, K, slices, outf, outb, lm, rp);
+                return;
+            }
+        }
+        with_head_dim<EPI>(rp.gm.hd, [&](auto h) {
+            constexpr auto k = gemm_large<EPI, decltype(h)::value>();
+            k.first<<<dim3((unsigned)cus), dim3(512), k.second, st>>>(A, (const BF16*)Wm, M, N, K, slices, outf, outb, lm, rp);
+        });
+        return;
+    }
+    if constexpr (EPI == TEPI_LMHEAD) {
+        dim3 g((unsigned)(((M + 127) / 128) * ((N + 127) / 128)), 1);
+        k_gemm_tiled<EPI, TILE_SMALL><<<g, dim3(256), TG_LDS_BYTES(128, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
+    } else {
+        // (the rotation epilogue needs whole heads inside a tile)
+        if (small_wgs <= 128 && !(EPI == TEPI_ROPE && rp.gm.hd > 64)) {         // half of the compute units idle: halve the tile's width (a workgroup each, still)
+            dim3 g((unsigned)(((M + 127) / 128) * ((N + 63) / 64)), (unsigned)slices);
+            k_gemm_tiled<EPI, TILE_NARROW><<<g, dim3(256), TG_LDS_BYTES(64, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
             return;
         }
-        if constexpr (EPI != TEPI_LMHEAD) {
-            if (mid) {
-                dim3 g((unsigned)(mt192 * nt), (unsigned)slices);
-                k_gemm_tiled<EPI, TILE_MID><<<g, dim3(512), TG_LDS_BYTES(256, 192), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
-                return;
-            }
-            dim3 g((unsigned)(mt256 * nt), (unsigned)slices);
-            k_gemm_tiled<EPI, TILE_LARGE><<<g, dim3(512), TG_LDS_BYTES(256, 256), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
-        }
-    } else {
-        if constexpr (EPI != TEPI_LMHEAD) {
-            // (the rotation epilogue needs whole heads inside a tile)
-            if (small_wgs <= 128 && !(EPI == TEPI_ROPE && rp.gm.hd > 64)) {     // half of the compute units idle: halve the tile's width (a workgroup each, still)
-                dim3 g((unsigned)(((M + 127) / 128) * ((N + 63) / 64)), (unsigned)slices);
-                k_gemm_tiled<EPI, TILE_NARROW><<<g, dim3(256), TG_LDS_BYTES(64, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
+        if constexpr (small_in_registers(EPI)) {
+            if (small_wgs <= cus) {
+                k_gemm_tiled<EPI, TILE_SMALL><<<dim3((unsigned)small_wgs), dim3(256), TG_LDS_BYTES(128, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
                 return;
             }
         }
-        dim3 g((unsigned)(((M + 127) / 128) * ((N + 127) / 128)), (unsigned)slices);
-        k_gemm_tiled<EPI, TILE_SMALL><<<g, dim3(256), TG_LDS_BYTES(128, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
+        with_head_dim<EPI>(rp.gm.hd, [&](auto h) {
+            constexpr auto k = gemm_small<EPI, decltype(h)::value>();
+            const dim3 grid((unsigned)std::min<long>(small_wgs, cus)), threads(EPI == TEPI_ROPE ? 256 : 512);
+            k.first<<<grid, threads, k.second, st>>>(A, (const BF16*)Wm, M, N, K, slices, outf, outb, lm, rp);
+        });
     }
 }
 
@@ -401,7 +432,9 @@ tasc_status forward_tiled(const tasc_model* m, tasc_session* s, int nq, int M_al
         ks = ks < nk / 4 ? ks : nk / 4;                       // slices of at least 4 k-steps
         ks = ks < TG_MAX_SLICES ? ks : TG_MAX_SLICES;
         if (!decode && ks > s->prompt_slices) ks = s->prompt_slices;
-        return ks < 1 ? 1 : ks;
+        if (ks < 1) return 1;
+        // no empty slice at the end: fewer of the same length (k_gemm has no stage to begin with in one)
+        return (nk + (nk + ks - 1) / ks - 1) / ((nk + ks - 1) / ks);
     };
     // Key chunks of the attention: two workgroups per compute unit in one round, but no more than 4 partial results to merge.
     // A session constant, since it fixes the order in which a row's keys are added; the one for prompts counts the row passes of

@@ -17,6 +17,13 @@
 // LDS cycles in conflicts.  In the forwards, before -> now: gate/up of a 16384-row prompt chunk (N 22016, k 2048) 1327 -> 1248 us,
 // q/k/v 240 -> 206; LM head with logits 1280 x 49152 x 2048 499 -> 296, 576 x 151936 x 1536 510 -> 357 (whole rows of 128 bytes per
 // store instead of 4-byte stores to 32 rows).
+// Loads are buffer loads: a lane's offset from its tile's first row is the same for every item, k is a scalar beside it, and past the
+// last item the buffer has no bytes, so the stream's end costs no traffic and the loop no branch.  With more than two stages in LDS they are spread
+// over the k-blocks of a stage: all at once, behind the barrier, every wave waited for the others' (128 x 128 x 64 of a stage 0.78 us, 0.55 so).
+// What bounds a 128 x 128 tile is that rate of lines into a compute unit: without the products 23.3 of 24.8 us for 576 x 1536 x 8960 in four slices
+// with cold weights, 18.5 with warm ones, 18.4 without the loads.  In the forwards, one tile per compute unit through registers | so, us: down
+// 1280 x 2048 x 11008 in six slices 61.5 | 59.0, 6336 x 1536 x 8960 195 | 189, output 1280 x 2048 x 2048 26.9 | 21.5, q/k/v of prompts 6336 x 2560 x 1536
+// 80 | 60.
 #pragma once
 #include "kernels_small.h"
 
@@ -57,6 +64,13 @@ struct LmEpi {            // TEPI_LMHEAD only
 // rows of the accumulator a lane holds: element i of a 32x32 tile is output feature 8 (i / 4) + 4 (lane / 32) + i % 4
 __device__ inline int tile_row(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 
+// The rotation of a feature and its partner half a head on.  Which product is rounded first is written out: launches of different row counts
+// rotate in different kernels, and a row has to have the same bits from all of them.
+__device__ __forceinline__ void rope_turn(float a, float b, float cs, float sn, float& ra, float& rb) {
+    ra = __builtin_fmaf(a, cs, -(b * sn));
+    rb = __builtin_fmaf(b, cs, a * sn);
+}
+
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));    // four floats at any 4-byte address
 typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(4)));
@@ -80,11 +94,12 @@ __device__ __forceinline__ void interleave() {
 }
 
 // BN x BM = output features x rows of the workgroup tile; WN x WM waves, each computing a (BN / WN) x (BM / WM) block as
-// TI x TJ MFMA tiles of 32 x 32; SK = k per stage, ST = stages in LDS.
-template <int EPI, int BN, int BM, int WN, int WM, int SK, int ST>
+// TI x TJ MFMA tiles of 32 x 32; SK = k per stage, ST = stages in LDS; HD = head_dim (rotation only).
+template <int EPI, int BN, int BM, int WN, int WM, int SK, int ST, int HD = 0>
 __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N, int K, int slices, float* __restrict__ outf,
             BF16* __restrict__ outb, LmEpi lm, RopeEpi rp) {
+#ifdef __HIP_DEVICE_COMPILE__                                     // (buffer resources are unknown to the host's pass)
     constexpr int NW = WN * WM;
     constexpr int SN = BN / WN, SM = BM / WM, TI = SN / 32, TJ = SM / 32, NS = SK / 16;
     constexpr int RB = SK * 2, CPR = SK / 8, RPI = 64 / CPR;      // bytes and 16-byte chunks of a tile row of one stage; rows per load instruction
@@ -92,6 +107,8 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
     constexpr int STAGE = (BN + BM) * RB;
     static_assert(SN % 32 == 0 && SM % 32 == 0 && NI % NW == 0 && BN % RPI == 0 && (NS == 2 || NS == 4), "tile shape");
     static_assert(LPW * (ST - 1) < 63, "the outstanding loads of a wave fit its counter");
+    constexpr int SPREAD = ST > 2 ? NS : 1;
+    constexpr auto part = [](int x) { return x >= SPREAD ? LPW : x * LPW / SPREAD; };      // loads of a stage requested before k-block x
     extern __shared__ __attribute__((aligned(128))) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave / WM, wm = wave % WM;
@@ -120,40 +137,38 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
     // r is parked at place c ^ swz(r) of its row, which spreads the rows a fragment read touches over all banks.  Rows past the
     // matrix are read from its last row; what they produce is never stored.
     auto swz = [](int r) __attribute__((always_inline)) { return SK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; };
-    const char* lbase[LPW];
-    uint32_t loff[LPW];
-    int l_it = x0 + blockIdx.x / 8, l_left = 0, issued = 0;       // item being loaded, its stages still to load, stages issued in all
-    uint32_t l_k = 0;
-    auto load_item = [&]() __attribute__((always_inline)) {       // addresses of the next item with stages
+    uint32_t loff[LPW];                                           // from the tile's first row: the same for every item
+#pragma unroll
+    for (int p = 0; p < LPW; ++p) {
+        const int i = wave * LPW + p, r = (i < BN / RPI ? i : i - BN / RPI) * RPI + lane / CPR;
+        loff[p] = (uint32_t)r * (uint32_t)(K * 2) + ((lane % CPR) ^ swz(r)) * 16;
+    }
+    __amdgpu_buffer_rsrc_t rs_w, rs_a;
+    int l_it = x0 + blockIdx.x / 8, l_left = 0, issued = 0;       // item being loaded, its stages still to load, stages requested in all
+    uint32_t l_k = 0, l_at = wave * (LPW * 1024);                 // its next k (bytes), and where that stage goes
+    auto load_item = [&]() __attribute__((always_inline)) {       // the next item with stages; past the last one, loads of nothing
         while (l_it < x1 && (l_left = item_stages(l_it)) == 0) l_it += step;
-        if (l_it >= x1) return;
-        int n0, m0, lane_ = lane;
-        asm volatile("" : "+v"(lane_));                           // (what follows from it is computed here, not kept in registers)
-        tile_of(l_it, n0, m0);
-        l_k = (uint32_t)(l_it / total) * per * (TG_BK * 2);
-#pragma unroll
-        for (int p = 0; p < LPW; ++p) {
-            const int i = wave * LPW + p;
-            const bool is_w = i < BN / RPI;
-            const int row0 = is_w ? i * RPI : (i - BN / RPI) * RPI, r = row0 + lane_ / CPR;
-            const int last = is_w ? N - 1 - n0 : M - 1 - m0;
-            lbase[p] = reinterpret_cast<const char*>(is_w ? W + (size_t)n0 * K : A + (size_t)m0 * K);
-            loff[p] = (uint32_t)min(r, last) * (uint32_t)(K * 2) + ((lane_ % CPR) ^ swz(r)) * 16;
-        }
+        int n0 = 0, m0 = 0;
+        const bool any = l_it < x1;
+        if (any) tile_of(l_it, n0, m0);
+        else l_left = 1 << 30;
+        l_k = any ? (uint32_t)(l_it / total) * per * (TG_BK * 2) : 0;
+        rs_w = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)n0 * K), 0, any ? min(BN, N - n0) * K * 2 : 0, 0x00027000);
+        rs_a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)m0 * K), 0, any ? min(BM, M - m0) * K * 2 : 0, 0x00027000);
     };
-    // requests the next stage of the stream (past the last item: the last stage again, which nobody reads, so that the count of
-    // loads in flight is the same at every wait)
-    auto issue = [&]() __attribute__((always_inline)) {
-        unsigned char* dst = lds + (issued % ST) * STAGE + wave * (LPW * 1024);
+    // requests loads P0 .. P1 of the next stage of the stream
+    auto issue = [&]<int P0, int P1>() __attribute__((always_inline)) {
 #pragma unroll
-        for (int p = 0; p < LPW; ++p)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(lbase[p] + l_k + loff[p]),
-                                             (__attribute__((address_space(3))) void*)(dst + p * 1024), 16, 0, 0);
+        for (int p = P0; p < P1; ++p)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wave * LPW + p < BN / RPI ? rs_w : rs_a, (__attribute__((address_space(3))) void*)(lds + l_at + p * 1024),
+                                                     16, loff[p], l_k, 0, 0);
     };
     auto advance = [&]() __attribute__((always_inline)) {
         ++issued;
-        if (--l_left > 0) l_k += RB;
-        else if (l_it < x1) {
+        l_at += STAGE;
+        if (l_at >= ST * STAGE) l_at -= ST * STAGE;
+        l_k += RB;
+        if (--l_left == 0) {
             l_it += step;
             load_item();
         }
@@ -161,18 +176,19 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
     load_item();
     if (l_it >= x1) return;                                       // no work at all
 #pragma unroll 1
-    for (int s = 0; s < ST; ++s) {
-        issue();
+    for (int s = 0; s + 1 < ST; ++s) {
+        issue.template operator()<0, LPW>();
         advance();
     }
+    issue.template operator()<0, part(1)>();
 
     // ---- fragments: lane l reads the 8 k of half l / 32 of row l % 32 of its 32-row tile; double-buffered, one k-block of 16 ahead
     const int frow = lane & 31, fx = swz(frow);
     const unsigned char* fw_base = lds + (wn * SN + frow) * RB;
     const unsigned char* fa_base = lds + (BN + wm * SM + frow) * RB;
     bf16x8 fw[2][TI], fa[2][TJ];
-    auto read_frags = [&](int set, int buf, int ks) __attribute__((always_inline)) {
-        const int off = buf * STAGE + ((2 * ks + (lane >> 5)) ^ fx) * 16;
+    auto read_frags = [&](int set, int at, int ks) __attribute__((always_inline)) {
+        const int off = at + ((2 * ks + (lane >> 5)) ^ fx) * 16;
 #pragma unroll
         for (int i = 0; i < TI; ++i) fw[set][i] = *reinterpret_cast<const bf16x8*>(fw_base + off + i * 32 * RB);
 #pragma unroll
@@ -185,8 +201,8 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
 #pragma unroll
             for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[set][i], fa[set][j], acc[i][j], 0, 0, 0);
     };
-    int stage = 0, landed = 0;          // stage being multiplied; every stage below `landed` is known to be in LDS
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPW * (ST - 1)) : "memory");
+    int stage = 0, landed = 0, at = 0;  // stage being multiplied and its place; every stage below `landed` is known to be in LDS
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPW * (ST - 2) + part(1)) : "memory");
     read_frags(0, 0, 0);
 
     unsigned char* const stg = lds + ST * STAGE + wave * 4096;    // the wave's 4 KB for turning its block around in the epilogue
@@ -219,27 +235,46 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                 }
             }
         }
+        // Rotation: where the lane's rows go, a chain of three dependent loads that ends under the first products
+        int32_t r_pos[TJ], r_slot[TJ], r_page[TJ];                // table position, slot in its page (-1: appends nothing), page
+        if constexpr (EPI == TEPI_ROPE) {
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int m = min(mwave + 32 * j + (lane & 31), M - 1), b = rp.gm.seq(m);
+                const int ir = rp.gm.index(m, b), pos = rp.pos0[b] + ir;
+                r_pos[j] = min(pos, rp.max_pos - 1);
+                r_slot[j] = ir < rp.n_rows[b] && mwave + 32 * j + (lane & 31) < M ? pos % TASC_KV_BLOCK : -1;
+                r_page[j] = r_slot[j] >= 0 ? rp.block_tab[(size_t)b * rp.gm.max_blocks + pos / TASC_KV_BLOCK] : 0;
+            }
+        }
         // One stage: the products of k-block ks run while the fragments of ks + 1 are read.  In front of the last k-block
         // every wave has read its last fragment of the stage and seen its own loads of the next stage land: after the barrier
         // the stage's buffer is refilled (ST stages ahead) and the next stage's first fragments are read under the last products.
+        // The refill's loads are spread over SPREAD k-blocks from there on.
 #pragma unroll 1
         for (int kt = item_stages(it); kt > 0; --kt) {
-            const int buf = stage % ST;
-#pragma unroll
-            for (int ks = 0; ks + 1 < NS; ++ks) {
-                read_frags((ks + 1) & 1, buf, ks + 1);
+            auto block = [&]<int ks>() __attribute__((always_inline)) {
+                read_frags((ks + 1) & 1, at, ks + 1);
+                issue.template operator()<part(ks + 1), part(ks + 2)>();
                 multiply(ks & 1);
-                interleave<TI + TJ, TI * TJ, 0>();
+                interleave<TI + TJ, TI * TJ, part(ks + 2) - part(ks + 1)>();
+            };
+            block.template operator()<0>();
+            if constexpr (NS == 4) {
+                block.template operator()<1>();
+                block.template operator()<2>();
             }
+            advance();
             // (loads return in order; the ones of the ST - 2 stages after the next may still be on their way)
             if (stage + 1 >= landed) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (ST - 2)) : "memory");
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             ++stage;
-            read_frags(0, stage % ST, 0);
-            issue();
+            at += STAGE;
+            if (at >= ST * STAGE) at -= ST * STAGE;
+            read_frags(0, at, 0);
+            issue.template operator()<0, part(1)>();
             multiply((NS - 1) & 1);
-            interleave<TI + TJ, TI * TJ, LPW>();
-            advance();
+            interleave<TI + TJ, TI * TJ, part(1)>();
         }
         // The loads in flight belong to the next item; after this wait none is older than the epilogue's stores, which so
         // never stand between a wait and the stage it is for until that stage is ST - 1 stages away.
@@ -498,45 +533,45 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
             }
         } else if constexpr (EPI == TEPI_ROPE) {
             // head_dim divides the wave's span, so the rotation partner of a register is a register of the same lane
-            // (half a head = 16, 32 or 64 features further on).  Same arithmetic as k_rope_kv.
+            // (half a head = 16, 32 or 64 features further on).
             const KvGeom& gm = rp.gm;
+            // the q and k heads of 32 rows, up to 32 of the lane's factors at a time
+            auto turn_rows = [&]<int j>() __attribute__((always_inline)) {
+                constexpr int HALF = HD / 2, NX = HALF < 32 ? HALF / 8 : 4, STEP = HD == 32 ? 0 : HALF / 32;       // the partner: STEP tiles on, or 8 registers
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) {
-                const int m = mwave + 32 * j + lr, mc = min(m, M - 1);
-                const int b = gm.seq(mc), ir = gm.index(mc, b), pos = rp.pos0[b] + ir;
-                const bool active = m < M && ir < rp.n_rows[b];
-                const int tpos = pos < rp.max_pos ? pos : rp.max_pos - 1, slot = pos % TASC_KV_BLOCK;
-                BF16* const page = rp.kv_layer + (active ? (size_t)rp.block_tab[(size_t)b * gm.max_blocks + pos / TASC_KV_BLOCK] * gm.page_elems : 0);
+                for (int x0 = 0; x0 < HALF / 8; x0 += NX) {
+                    f32x4 cs[NX], sn[NX];
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int n = nwave + 32 * i, head = n / gm.hd, e0 = n % gm.hd;      // wave-uniform
-                    const int half = gm.hd / 2;
-                    if (n >= N) continue;
-                    if (head >= gm.H + gm.Hkv || e0 >= half) continue;                   // values; or done with its partner
+                    for (int x = 0; x < NX; ++x) {
+                        cs[x] = *reinterpret_cast<const f32x4*>(rp.cosT + (size_t)r_pos[j] * HALF + 8 * (x0 + x) + 4 * lh);
+                        sn[x] = *reinterpret_cast<const f32x4*>(rp.sinT + (size_t)r_pos[j] * HALF + 8 * (x0 + x) + 4 * lh);
+                    }
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (half == 16 && q >= 2) continue;                              // head_dim 32: the partner is 8 registers on
-                        const int e = e0 + 8 * q + 4 * lh;
-                        const float4 cs = *reinterpret_cast<const float4*>(rp.cosT + (size_t)tpos * half + e);
-                        const float4 sn = *reinterpret_cast<const float4*>(rp.sinT + (size_t)tpos * half + e);
-                        const float c_[4] = {cs.x, cs.y, cs.z, cs.w}, s_[4] = {sn.x, sn.y, sn.z, sn.w};
-                        auto turn = [&](f32x16& x, int xe, f32x16& y, int ye, int u) __attribute__((always_inline)) {
-                            const float a_ = x[xe], b_ = y[ye];
-                            x[xe] = a_ * c_[u] - b_ * s_[u];
-                            y[ye] = b_ * c_[u] + a_ * s_[u];
-                        };
+                    for (int i = 0; i < TI; ++i) {
+                        if ((32 * i) % HD != 8 * x0 || i + STEP >= TI || (nwave + 32 * i) / HD >= gm.H + gm.Hkv) continue;
+                        f32x16 &a_ = acc[i][j], &b_ = acc[i + STEP < TI ? i + STEP : i][j];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int x = 4 * q + u;
-                            if (half == 64) { if (i + 2 < TI) turn(acc[i][j], x, acc[i + 2 < TI ? i + 2 : i][j], x, u); }
-                            else if (half == 32) { if (i + 1 < TI) turn(acc[i][j], x, acc[i + 1 < TI ? i + 1 : i][j], x, u); }
-                            else if (q < 2) turn(acc[i][j], x, acc[i][j], (x + 8) & 15, u);
+                        for (int e = 0; e < 4 * NX; ++e) {
+                            float ra, rb;
+                            rope_turn(a_[e], b_[HD == 32 ? e + 8 : e], cs[e / 4][e % 4], sn[e / 4][e % 4], ra, rb);
+                            a_[e] = ra;
+                            b_[HD == 32 ? e + 8 : e] = rb;
                         }
                     }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+            };
+            static_assert(TJ <= 2 && HD <= SN, "rows of a wave; whole heads");
+            turn_rows.template operator()<0>();
+            if constexpr (TJ > 1) turn_rows.template operator()<1>();
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int m = mwave + 32 * j + lr, slot = r_slot[j];
+                const bool active = slot >= 0;
+                BF16* const page = rp.kv_layer + (size_t)r_page[j] * gm.page_elems;
 #pragma unroll
                 for (int i = 0; i < TI; ++i) {
-                    const int n = nwave + 32 * i, head = n / gm.hd, e0 = n % gm.hd;
+                    const int n = nwave + 32 * i, head = n / HD, e0 = n % HD;
                     if (n >= N) continue;
                     if (head < gm.H + gm.Hkv) {
                         // bf16 [32 rows][32 features] = 64 bytes a row through LDS, 16 bytes of a row per lane
@@ -547,8 +582,8 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                                 pack_bf16x4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
                         // where the row goes: q rows by row index, k rows by page and slot
                         BF16* dst = nullptr;
-                        if (head < gm.H) { if (m < M) dst = outb + (size_t)m * gm.H * gm.hd + n; }
-                        else if (active) dst = page + (size_t)((head - gm.H) * TASC_KV_BLOCK + slot) * gm.hd + e0;
+                        if (head < gm.H) { if (m < M) dst = outb + (size_t)m * gm.H * HD + n; }
+                        else if (active) dst = page + (size_t)((head - gm.H) * TASC_KV_BLOCK + slot) * HD + e0;
                         __builtin_amdgcn_wave_barrier();
 #pragma unroll
                         for (int p = 0; p < 2; ++p) {
@@ -558,14 +593,67 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                             const uint64_t dr = (uint64_t)(uint32_t)__shfl((int)(uint32_t)d64, r) | ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(d64 >> 32), r) << 32);
                             if (dr) *reinterpret_cast<u32x4*>(reinterpret_cast<BF16*>(dr) + 8 * ch) = o;
                         }
-                    } else if (active) {
-                        // values transposed: consecutive lanes are consecutive rows, so a sequence's rows fill consecutive slots
-                        uint16_t* vt = reinterpret_cast<uint16_t*>(page) + (size_t)gm.Hkv * TASC_KV_BLOCK * gm.hd +
-                                       (size_t)((head - gm.H - gm.Hkv) * gm.hd + e0 + 4 * lh) * TASC_KV_BLOCK + slot;
+                    }
+                }
+            }
+            // Values go transposed: [feature][32 rows] of two tiles in the wave's LDS, a feature a lane, and from there runs of rows that are
+            // neighbours in a page, 8 slots, 2 or 1 at a time.  The columns of few workgroups hold all the values of a layer, so what they cost
+            // is added to the launch (q/k/v of prompts, 6336 x 2560 x 1536: two-byte stores straight from the registers 80 us, so 60, without values 56).
+            if ((nwave + SN - 1) / HD >= gm.H + gm.Hkv && nwave < N) {
+                static_assert(TI % 2 == 0, "tiles in pairs");
+#pragma unroll 1
+                for (int pass = 0; pass < TJ * TI / 2; ++pass) {
+                    const int v0 = nwave + 64 * (pass % (TI / 2)) - (gm.H + gm.Hkv) * HD;      // the pair's first value feature
+                    if (v0 <= -64) continue;
+                    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
+                    for (int t = 0; t < TJ * TI / 2; ++t) {
+                        if (t != pass) continue;
 #pragma unroll
-                            for (int u = 0; u < 4; ++u) vt[(8 * q + u) * TASC_KV_BLOCK] = f2bf(acc[i][j][4 * q + u]);
+                        for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) {
+                                const int f = 32 * ii + tile_row(e, el);
+                                *reinterpret_cast<uint16_t*>(stg + f * 64 + (((lr >> 3) ^ ((f >> 2) & 3)) * 16) + (lr & 7) * 2) =
+                                    f2bf(acc[2 * (t % (TI / 2)) + ii][t / (TI / 2)][e]);
+                            }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    int slot_l = r_slot[0], page_l = r_page[0];
+                    if constexpr (TJ > 1) {
+                        slot_l = pass < TI / 2 ? slot_l : r_slot[1];
+                        page_l = pass < TI / 2 ? page_l : r_page[1];
+                    }
+                    // bit r: row r + 1 follows row r in its page
+                    const uint32_t on = (uint32_t)__ballot(lr < 31 && slot_l >= 0 && __shfl(slot_l, (el + 1) & 63) == slot_l + 1 &&
+                                                           __shfl(page_l, (el + 1) & 63) == page_l);
+                    if (v0 + el >= 0 && nwave + 64 * (pass % (TI / 2)) + el < N) {
+                        BF16* const base = rp.kv_layer + (size_t)gm.Hkv * TASC_KV_BLOCK * HD + (size_t)(v0 + el) * TASC_KV_BLOCK;
+                        uint32_t v[17];                              // the feature's 32 rows
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const u32x4 w = *reinterpret_cast<const u32x4*>(stg + el * 64 + ((c ^ ((el >> 2) & 3)) * 16));
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) v[4 * c + u] = w[u];
+                        }
+                        v[16] = 0;
+                        auto two = [&](int r) { return (r & 1) ? __builtin_amdgcn_alignbit(v[min(r / 2 + 1, 16)], v[min(r / 2, 16)], 16) : v[min(r / 2, 16)]; };
+                        int next = 0;
+#pragma unroll
+                        for (int r = 0; r < 32; ++r) {
+                            const int slot = __builtin_amdgcn_readlane(slot_l, r);
+                            if (r < next || slot < 0) continue;
+                            uint16_t* const dst = reinterpret_cast<uint16_t*>(base + (size_t)__builtin_amdgcn_readlane(page_l, r) * gm.page_elems) + slot;
+                            if ((slot & 7) == 0 && ((on >> r) & 0x7F) == 0x7F) {             // (row 31 has no bit: never past the last row)
+                                *reinterpret_cast<u32x4*>(dst) = u32x4{two(r), two(r + 2), two(r + 4), two(r + 6)};
+                                next = r + 8;
+                            } else if ((slot & 1) == 0 && ((on >> r) & 1)) {
+                                *reinterpret_cast<uint32_t*>(dst) = two(r);
+                                next = r + 2;
+                            } else {
+                                *dst = (uint16_t)(v[r / 2] >> (16 * (r & 1)));
+                            }
+                        }
                     }
                 }
             }
@@ -607,6 +695,7 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
         __builtin_amdgcn_wave_barrier();
         // (the LM head's epilogue has other use for the registers of the next stage's first fragments, and they are read again here:
         // 40 bytes of spills otherwise, 874 instead of 860 us for 1280 x 151936 x 2048)
-        if constexpr (EPI == TEPI_LMHEAD) read_frags(0, stage % ST, 0);
+        if constexpr (EPI == TEPI_LMHEAD || EPI == TEPI_ROPE) read_frags(0, at, 0);
     }
+#endif
 }

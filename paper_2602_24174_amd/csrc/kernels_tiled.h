@@ -2,8 +2,9 @@
 // MFMA GEMM with fused epilogues (plain store, residual add, SwiGLU, LM-head bias + strip argmax) and a
 // paged GQA attention kernel on the same MFMA scheme as the small-batch kernel.
 //
-// GEMM: out[M, N] = A[M, K] W[N, K]^T, both operands k-contiguous.  A workgroup of 4 waves computes a
-// BN (n) x BM (m) tile, 128 x 128 on 4 waves or 256 x 256 on 8; each wave a block of v_mfma_f32_32x32x16_bf16 tiles with the
+// GEMM: out[M, N] = A[M, K] W[N, K]^T, both operands k-contiguous, for the launches whose weights are best fetched two stages ahead through
+// registers (launch_gemm; k_gemm has the others).  A workgroup computes a
+// BN (n) x BM (m) tile, 64 or 128 x 128 on 4 waves or 256 x 192 on 8; each wave a block of v_mfma_f32_32x32x16_bf16 tiles with the
 // WEIGHT rows as the A operand, so a lane ends up with runs of 4 consecutive output features of one row.
 // k advances in steps of 64 through double-buffered LDS tiles (global -> registers -> LDS while the MFMAs
 // of the previous step run).  A row's result depends only on its own data and the fixed k order, not on
@@ -13,7 +14,7 @@
 #include "kernels_gemm.h"
 
 #define TG_LD (TG_BK + 8)                                     // padded LDS row (elements)
-#define TG_LDS_BYTES(BN, BM) (2 * ((BN) + (BM)) * TG_LD * 2)   // 73728 for 128 x 128, 147456 for 256 x 256
+#define TG_LDS_BYTES(BN, BM) (2 * ((BN) + (BM)) * TG_LD * 2)   // 73728 for 128 x 128, 129024 for 256 x 192
 
 // BN x BM = output features x rows of the workgroup tile; WN x WM waves, each computing a
 // (BN / WN) x (BM / WM) block as TI x TJ MFMA tiles of 32 x 32.
@@ -348,7 +349,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1,
                 if (EPI == TEPI_ROPE) {
                     // The lane whose 4 features lie in the first half of a head also takes their partners half a head on
                     // (the same row, this wave's block or the block of a wave further along n: a tile holds whole heads)
-                    // and writes both.  Same arithmetic as k_rope_kv.
+                    // and writes both.
                     const int hd = rp.gm.hd, half = hd / 2, e = n % hd, head = n / hd;
                     if (m < M && n < N && e < half) {
                         const int nl = SN * wn + ch * 4 + half;                      // partner's feature inside the tile
@@ -364,10 +365,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1,
                             const float c_[4] = {cs.x, cs.y, cs.z, cs.w}, s_[4] = {sn.x, sn.y, sn.z, sn.w};
                             float ra[4], rc[4];
 #pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                ra[u] = a4[u] * c_[u] - c4[u] * s_[u];
-                                rc[u] = c4[u] * c_[u] + a4[u] * s_[u];
-                            }
+                            for (int u = 0; u < 4; ++u) rope_turn(a4[u], c4[u], c_[u], s_[u], ra[u], rc[u]);
                             BF16* dst = nullptr;
                             if (head < rp.gm.H) {
                                 dst = outb + (size_t)m * rp.gm.H * hd + head * hd + e;
@@ -621,10 +619,7 @@ __global__ __launch_bounds__(256) void k_rope_kv(const float* __restrict__ qkv, 
         if (head < gm.H + gm.Hkv) {
             float ra[4], rc[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                ra[u] = a[0][u] * cs[u] - c[0][u] * sn[u];
-                rc[u] = c[0][u] * cs[u] + a[0][u] * sn[u];
-            }
+            for (int u = 0; u < 4; ++u) rope_turn(a[0][u], c[0][u], cs[u], sn[u], ra[u], rc[u]);
             BF16* dst = nullptr;
             if (head < gm.H) dst = q_out + ((size_t)r * gm.H + head) * gm.hd + e;
             else if (active) dst = page + (size_t)((head - gm.H) * TASC_KV_BLOCK + slot) * gm.hd + e;

@@ -9,7 +9,7 @@
    operand shapes -- the attainable rate at these shapes, not part of the product path.
 3. The same four products at the rows of a full prompt chunk of the largest workload.
 
-Launches of more 256 x 256 (or 256 x 192) tiles than compute units run the streaming kernel k_gemm, the others k_gemm_tiled.  The
+Most launches run k_gemm (tiles straight from memory to LDS), those of few row tiles k_gemm_tiled (through registers): launch_gemm's rules.  The
 calibration operands are constant, which spares the matrix cores power: products of real data run at a lower clock.
 """
 import argparse
