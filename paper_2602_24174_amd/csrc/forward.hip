@@ -224,9 +224,10 @@ namespace {
 // most kFewRows rows, whose weights come from memory for a few row tiles only and are fetched further ahead there (us, registers | straight to
 // LDS: gate/up 576 x 17920 x 1536 in 256 x 192 tiles 38.4 | 42.8, 224 x 9728 x 896 in 128 x 128 ones 12.3 | 12.7, 224 x 896 x 4864 in
 // six slices of 64 x 128 ones 8.5 | 8.8; with more row tiles gate/up 1000 x 9728 x 896 27.2 | 26.8, output 6336 x 1536 x 1536 46.4 | 42.2), the
-// narrow tile, and the 128 x 128 tile's SwiGLU and rotation in one round.  The last two have spans of 64 or 128 features a wave, and so four
-// waves of 64 x 64; the other epilogues take eight of 32 x 64 (us, four waves through registers | eight straight to LDS: 1280 x 2048 x 2048
-// with residual 25.4 | 21.5, 3072 x 1536 x 8960 151 | 134, 576 x 2048 x 1536 in two slices 11.1 | 10.5, 576 x 1536 x 8960 in four 23.8 | 24.1).
+// narrow tile, and the 128 x 128 tile's SwiGLU, rotation and k-slices in one round.  The first two have spans of 64 or 128 features a wave, and so
+// four waves of 64 x 64; the other epilogues take eight of 32 x 64 (us, four waves through registers | eight straight to LDS: 1280 x 2048 x 2048
+// with residual 25.4 | 21.5, 3072 x 1536 x 8960 151 | 134; slices in one round: 1137 x 896 x 4864 in four 16.3 | 17.8 and the reduction behind them
+// 5.7 | 7.9, 576 x 1536 x 8960 in four 23.8 | 24.1, 576 x 2048 x 1536 in two 11.1 | 10.5; in more than one 1280 x 2048 x 11008 in six 89 | 81).
 // Stages of 64 of k, two in LDS for the large tiles, four for the small one: a stage of 32 of k is half a cache line of a row, and each half is
 // a request of its own (128 x 128, 1280 x 2560 x 2048, eight stages of 32 | four of 64: 29.4 | 23.1).  The LM head has stages of 32, four in LDS: its
 // longer epilogue leaves a following fetch less time (1280 x 49152 x 2048, two of 64 | four of 32: 262 | 235).
@@ -257,7 +258,7 @@ auto with_head_dim(int hd, auto f) {
     if constexpr (EPI != TEPI_ROPE) return f(std::integral_constant<int, 0>{});
     else return hd == 128 ? f(std::integral_constant<int, 128>{}) : hd == 64 ? f(std::integral_constant<int, 64>{}) : f(std::integral_constant<int, 32>{});
 }
-constexpr bool small_in_registers(int epi) { return epi == TEPI_SWIGLU || epi == TEPI_ROPE; }
+constexpr bool small_in_registers(int epi) { return epi == TEPI_SWIGLU || epi == TEPI_ROPE || epi == TEPI_PARTIAL; }
 
 template <int EPI>
 tasc_status tiled_attrs() {
@@ -344,7 +345,8 @@ void launch_gemm(const BF16* A, const void* Wm, int M, int N, int K, float* outf
         }
         if constexpr (small_in_registers(EPI)) {
             if (small_wgs <= cus) {
-                k_gemm_tiled<EPI, TILE_SMALL><<<dim3((unsigned)small_wgs), dim3(256), TG_LDS_BYTES(128, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
+                const dim3 g((unsigned)(((M + 127) / 128) * ((N + 127) / 128)), (unsigned)slices);
+                k_gemm_tiled<EPI, TILE_SMALL><<<g, dim3(256), TG_LDS_BYTES(128, 128), st>>>(A, (const BF16*)Wm, M, N, K, outf, outb, lm, rp);
                 return;
             }
         }
