@@ -229,22 +229,20 @@ namespace {
 // with residual 25.4 | 21.5, 3072 x 1536 x 8960 151 | 134; slices in one round: 1137 x 896 x 4864 in four 16.3 | 17.8 and the reduction behind them
 // 5.7 | 7.9, 576 x 1536 x 8960 in four 23.8 | 24.1, 576 x 2048 x 1536 in two 11.1 | 10.5; in more than one 1280 x 2048 x 11008 in six 89 | 81).
 // Stages of 64 of k, two in LDS for the large tiles, four for the small one: a stage of 32 of k is half a cache line of a row, and each half is
-// a request of its own (128 x 128, 1280 x 2560 x 2048, eight stages of 32 | four of 64: 29.4 | 23.1).  The LM head has stages of 32, four in LDS: its
-// longer epilogue leaves a following fetch less time (1280 x 49152 x 2048, two of 64 | four of 32: 262 | 235).
-#define GEMM_SMALL 128, 128, 4, 2, 64, 4
-#define GEMM_SMALL_GU 128, 128, 2, 4, 64, 4
-#define GEMM_SMALL_ROPE 128, 128, 1, 4, 64, 4
-#define GEMM_LARGE 256, 256, 2, 4, 64, 2
-#define GEMM_LARGE_LM 256, 256, 2, 4, 32, 4
-#define GEMM_MID 256, 192, 4, 2, 64, 2
+// a request of its own (128 x 128, 1280 x 2560 x 2048, eight stages of 32 | four of 64: 29.4 | 23.1).  (So for the LM head's large tile: 1280 x 49152 x 2048 without
+// logits, four stages of 32 | two of 64: 245 | 219, 1280 x 151936 x 2048 705 | 654.)
+#define GEMM_SMALL 128, 128, 4, 2, 4
+#define GEMM_SMALL_GU 128, 128, 2, 4, 4
+#define GEMM_SMALL_ROPE 128, 128, 1, 4, 4
+#define GEMM_LARGE 256, 256, 2, 4, 2
+#define GEMM_MID 256, 192, 4, 2, 2
 constexpr int kFewRows = 768;
 constexpr int kLargeTileRows = 384;
 
 // kernel and LDS; the head size is the rotation's only
 template <int EPI, int HD>
 constexpr auto gemm_large() {
-    if constexpr (EPI == TEPI_LMHEAD) return std::pair(&k_gemm<EPI, GEMM_LARGE_LM>, gemm_lds_bytes(GEMM_LARGE_LM));
-    else return std::pair(&k_gemm<EPI, GEMM_LARGE, HD>, gemm_lds_bytes(GEMM_LARGE));
+    return std::pair(&k_gemm<EPI, GEMM_LARGE, HD>, gemm_lds_bytes(GEMM_LARGE));
 }
 template <int EPI, int HD>
 constexpr auto gemm_small() {

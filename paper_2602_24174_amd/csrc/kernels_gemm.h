@@ -1,7 +1,7 @@
 // The tiled bf16 GEMM of forwards of more than 16 rows: out[M, N] = epilogue(A[M, K] W[N, K]^T), both operands k-contiguous.
 //
 // A workgroup computes BN (output features) x BM (rows) tiles with v_mfma_f32_32x32x16_bf16, the WEIGHT rows as the A operand,
-// so a lane ends up with runs of 4 consecutive features of one row.  k advances in stages of SK; ST stages sit in LDS at once,
+// so a lane ends up with runs of 4 consecutive features of one row.  k advances in stages of 64; ST stages sit in LDS at once,
 // filled by loads that go from memory to LDS without passing through registers.  The stages of a workgroup's tiles form ONE
 // stream: while the last stages of a tile are multiplied, and while its epilogue runs, the first stages of its next tile are
 // already on their way, so a tile pays neither a launch nor a cold first fetch, and the stores of its epilogue drain under
@@ -76,7 +76,7 @@ typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int gemm_lds_bytes(int BN, int BM, int WN, int WM, int SK, int ST) { return ST * (BN + BM) * SK * 2 + WN * WM * 4096; }
+constexpr int gemm_lds_bytes(int BN, int BM, int WN, int WM, int ST) { return ST * (BN + BM) * TG_BK * 2 + WN * WM * 4096; }
 
 // The order of a k-block of X products: its R fragment reads go out between the products of the first half (after the first one,
 // whose wait for the block's own fragments so covers no newer read; they have the second half to arrive), its L loads between
@@ -94,18 +94,19 @@ __device__ __forceinline__ void interleave() {
 }
 
 // BN x BM = output features x rows of the workgroup tile; WN x WM waves, each computing a (BN / WN) x (BM / WM) block as
-// TI x TJ MFMA tiles of 32 x 32; SK = k per stage, ST = stages in LDS; HD = head_dim (rotation only).
-template <int EPI, int BN, int BM, int WN, int WM, int SK, int ST, int HD = 0>
+// TI x TJ MFMA tiles of 32 x 32; ST = stages in LDS; HD = head_dim (rotation only).
+template <int EPI, int BN, int BM, int WN, int WM, int ST, int HD = 0>
 __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N, int K, int slices, float* __restrict__ outf,
             BF16* __restrict__ outb, LmEpi lm, RopeEpi rp) {
 #ifdef __HIP_DEVICE_COMPILE__                                     // (buffer resources are unknown to the host's pass)
     constexpr int NW = WN * WM;
+    constexpr int SK = TG_BK;                                     // k per stage: whole cache lines of the operands' rows
     constexpr int SN = BN / WN, SM = BM / WM, TI = SN / 32, TJ = SM / 32, NS = SK / 16;
     constexpr int RB = SK * 2, CPR = SK / 8, RPI = 64 / CPR;      // bytes and 16-byte chunks of a tile row of one stage; rows per load instruction
     constexpr int NI = (BN + BM) / RPI, LPW = NI / NW;            // load instructions per stage, and per wave
     constexpr int STAGE = (BN + BM) * RB;
-    static_assert(SN % 32 == 0 && SM % 32 == 0 && NI % NW == 0 && BN % RPI == 0 && (NS == 2 || NS == 4), "tile shape");
+    static_assert(SN % 32 == 0 && SM % 32 == 0 && NI % NW == 0 && BN % RPI == 0, "tile shape");
     static_assert(LPW * (ST - 1) < 63, "the outstanding loads of a wave fit its counter");
     constexpr int SPREAD = ST > 2 ? NS : 1;
     constexpr auto part = [](int x) { return x >= SPREAD ? LPW : x * LPW / SPREAD; };      // loads of a stage requested before k-block x
@@ -130,13 +131,13 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
     };
     auto item_stages = [&](int it) {                              // stages of an item (0: a slice past the end of k)
         const int kb = (it / total) * per;
-        return max(0, min(nk_all, kb + per) - kb) * (TG_BK / SK);
+        return max(0, min(nk_all, kb + per) - kb);
     };
 
     // ---- loads: a wave instruction brings 64 chunks of 16 bytes, RPI tile rows, to 1 KB of LDS in lane order; chunk c of row
     // r is parked at place c ^ swz(r) of its row, which spreads the rows a fragment read touches over all banks.  Rows past the
     // matrix are read from its last row; what they produce is never stored.
-    auto swz = [](int r) __attribute__((always_inline)) { return SK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; };
+    auto swz = [](int r) __attribute__((always_inline)) { return (r >> 1) & 7; };
     uint32_t loff[LPW];                                           // from the tile's first row: the same for every item
 #pragma unroll
     for (int p = 0; p < LPW; ++p) {
@@ -259,11 +260,10 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                 multiply(ks & 1);
                 interleave<TI + TJ, TI * TJ, part(ks + 2) - part(ks + 1)>();
             };
+            static_assert(NS == 4, "three k-blocks, and the last one behind the barrier");
             block.template operator()<0>();
-            if constexpr (NS == 4) {
-                block.template operator()<1>();
-                block.template operator()<2>();
-            }
+            block.template operator()<1>();
+            block.template operator()<2>();
             advance();
             // (loads return in order; the ones of the ST - 2 stages after the next may still be on their way)
             if (stage + 1 >= landed) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (ST - 2)) : "memory");
