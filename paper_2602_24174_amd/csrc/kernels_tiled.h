@@ -304,7 +304,7 @@ __global__ __launch_bounds__(64 * WN * WM) __attribute__((amdgpu_waves_per_eu(1,
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         const float g = acc[i][j][4 * q + u], up = acc[i][j][8 + 4 * q + u];
-                        o[u] = g / (1.0f + __expf(-g)) * up;
+                        o[u] = silu_times(g, up);
                     }
                     *reinterpret_cast<u32x2*>(rj + (size_t)(lane & 31) * LDO + (16 * i + 8 * q + 4 * (lane >> 5)) * 2) = pack_bf16x4(o[0], o[1], o[2], o[3]);
                 }
