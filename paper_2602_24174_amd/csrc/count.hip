@@ -14,9 +14,12 @@
 // window or record per lane at a time waits for its unluckiest lane at each.  So a lane that is done with one takes its next at once.
 // And of the orders above the second, a window whose first or last n - 1 tokens occur once in the corpus occurs once itself: a map of
 // the (n-1)-grams that occur more often (a few per cent of the distinct ones) takes a third to half of the windows out.
-// 32 M tokens, orders 2 to 5, us: 2107 / 2302 / 2348 / 2378 with a table in memory; k_partition 311 / 472 / 528 / 541, k_turn 12 to 26,
-// k_tables 313 / 208 / 296 / 272 (414 / 530 / 566 and 332 / 565 / 610 for orders 3 to 5 without the map).  Both wait for LDS and L2
-// with one or two workgroups a compute unit: the vector units are busy 40 % of the time, the LDS 20 %.
+// Whether that is so takes a look at the map for every position; what the order below saw of its windows, chunk by chunk, spares two looks in three.
+// 32 M tokens, orders 2 to 5 together, us: 9135 with a table in memory; k_partition 1300 (1840 with loads that wait for each other where a chunk
+// begins and all looks at the map), k_turn 90, k_tables 1020 (2540 and 1840 without the map).  All wait for LDS and L2 with one or two workgroups
+// a compute unit: a chunk of order 4 is 53 k cycles, 6 of them for its loads, 14 at the map, 11 to merge, 11 for keys and ranks, 11 to put in order.
+// Measured and left out: workgroups that go on to a next chunk with its loads ahead (registers: 369 / 409 / 386 for orders 3 to 5 and k_turn, 366 /
+// 402 / 378 so), chunks of 4096 two to a unit (an eighth less here, more in k_tables than that), the map's loads before the merging (no overlap).
 #include "tasc_internal.h"
 #include <algorithm>
 
@@ -59,14 +62,21 @@ __device__ __forceinline__ u32 block_scan(u32 v, u32* s_wave, u32& total) {
 __device__ __forceinline__ u32 light_step(u32 h, u32 tok, int j) { return h ^ (j == 0 ? tok : (tok << (13 * j % 32)) | (tok >> (32 - 13 * j % 32))); }   // (never by 0 or 32)
 __device__ __forceinline__ u32 light_end(u32 h) { return h * 0x9E3779B1u; }
 
+// marks: a byte a position.  With `twice`, what the order below found out of its windows in its own chunks spares most looks at the map:
+// each is a line of the L2 for one bit, and they arrive at a line every 2.5 cycles a compute unit, 21 k cycles a chunk of 8192 where all look.
+constexpr u32 kMarkEnd = 1;        // the document's last token
+constexpr u32 kMarkOnce = 2;       // the window that begins here occurs once, or is none
+constexpr u32 kMarkOften = 4;      // it occurs more than once in the chunk alone
+
 // LDS (dynamic): tokens [C + 8], slots [2 C] of {position in the chunk + 1 : 16, count : 16}, partition counters [parts], wave sums, the
-// windows' slots [C].  A few rotations of the tokens make a hash that is good enough for the chunk's table; the key and its hash are
+// windows' slots [C], marks, a bit a position [3][C / 8 + 8].  A few rotations of the tokens make a hash that is good enough for the chunk's table; the key and its hash are
 // computed once per window that is left.
+//
 //
 // twice (nullable): a bit per range of the (N - 1)-grams' light hash, set for those that occur at least twice.  A window that begins or ends with
 // one that occurs once occurs once itself: it is counted and leaves no record.
 template <int N, int C, int TH>
-__device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, u64 T, int bits, u32 parts,
+__device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok, uint8_t* marks, bool keep_marks, u64 T, int bits, u32 parts,
                                                 const u32* __restrict__ twice, int twice_bits, u64* distinct, u64* __restrict__ rec,
                                                 uint16_t* __restrict__ offs) {
     constexpr int W = C / TH;
@@ -74,45 +84,88 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
     u32* s_slot = reinterpret_cast<u32*>(lds);
     u32* s_tok = s_slot + 2 * C;
     u32* s_hist = s_tok + C + 8;
-    u32* s_wave = s_hist + parts;
+    u32* s_wave = s_hist + ((parts + 1) & ~1u);           // (8-byte words behind it)
     uint16_t* s_claim = reinterpret_cast<uint16_t*>(s_wave + TH / 64);
+    uint8_t* s_end = reinterpret_cast<uint8_t*>(s_claim + C);      // bit i of each: the mark of position i
+    uint8_t* s_once = s_end + C / 8 + 8;
+    uint8_t* s_often = s_once + C / 8 + 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const u64 base = (u64)blockIdx.x * C;
     const int n_here = (int)min((u64)(C + N - 1), T - base), n_win = (int)min((u64)C, T - base);
-    for (int i = tid; i < n_here; i += TH) s_tok[i] = (u32)tok[base + i];
-    // a window stays inside its document if none of its tokens but the last ends one: 64 windows of a wave from their ends' ballots
+    // The chunk is asked for at once: its tokens, eight positions' document ends a thread, and the N - 1 positions behind it.
+    u32 t_in[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) t_in[w] = (u32)tok[base + min(w * TH + tid, n_here - 1)];
+    const u32 t_tail = (u32)tok[base + min(C + min(tid, N - 2), n_here - 1)];
+    u64 e_in[C / 8 > TH ? C / 8 / TH : 1];
+    const bool marks_mine = C / 8 >= TH || tid < C / 8;
+#pragma unroll
+    for (int q = 0; q < (int)(sizeof e_in / 8); ++q) {
+        const u64 at = base + 8 * (q * TH + tid);
+        e_in[q] = 0;
+        if (!marks_mine) continue;
+        if (at + 8 <= T) e_in[q] = *reinterpret_cast<const u64*>(marks + at);
+        else
+            for (int e = 0; e < 8; ++e) e_in[q] |= at + e < T ? (u64)marks[at + e] << (8 * e) : 0;
+    }
+    const bool e_tail = tid < 8 && base + C + tid < T && (marks[base + C + tid] & kMarkEnd);
+    for (int i = tid; i < 2 * C / 4; i += TH) reinterpret_cast<uint4*>(s_slot)[i] = make_uint4(0, 0, 0, 0);
+    for (u32 i = tid; i < parts; i += TH) s_hist[i] = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) s_tok[w * TH + tid] = t_in[w];
+    if (tid < N - 1) s_tok[C + tid] = t_tail;
+    // (a bit of eight bytes into one)
+    auto plane = [](u64 v, u32 mark) __attribute__((always_inline)) { return (uint8_t)(((v / mark & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56); };
+    const bool pruned = N > 2 && twice;
+#pragma unroll
+    for (int q = 0; q < (int)(sizeof e_in / 8); ++q)
+        if (marks_mine) {
+            s_end[q * TH + tid] = plane(e_in[q], kMarkEnd);
+            if (pruned) s_once[q * TH + tid] = plane(e_in[q], kMarkOnce);
+            if (pruned) s_often[q * TH + tid] = plane(e_in[q], kMarkOften);
+        }
+    const u64 tail = __ballot(e_tail);
+    if (tid == 0) s_end[C / 8] = (uint8_t)tail;
+    __syncthreads();
+    // a window stays inside its document if none of its tokens but the last ends one
     u32 inside = 0;                                        // bit w: window w TH + tid
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         const int i = w * TH + tid;
-        const u64 here = __ballot(i < n_win && last[base + i]), then = __ballot(lane < N && base + i + 64 < T && last[base + i + 64]);
-        const u64 ends = lane == 0 ? here : (here >> lane) | (then << (64 - lane));
+        const u32* const e = reinterpret_cast<const u32*>(s_end) + (i >> 5);
+        const u32 ends = __funnelshift_r(e[0], e[1], i & 31);
         inside |= (i < n_win && (ends & ((1u << (N - 1)) - 1)) == 0) ? 1u << w : 0;      // (the corpus' last token ends a document)
     }
-    for (int i = tid; i < 2 * C / 4; i += TH) reinterpret_cast<uint4*>(s_slot)[i] = make_uint4(0, 0, 0, 0);
-    for (u32 i = tid; i < parts; i += TH) s_hist[i] = 0;
-    __syncthreads();
-    if (N > 2 && twice) {
-        u32 word[W], bit[W], word64[W], bit64[W];          // of the lane's positions, and (lane 0) of the one past the wave's 64
-        auto where = [&](int i, u32& word_, u32& bit_) __attribute__((always_inline)) {
+    if (pruned) {
+        auto word_of = [&](int i, u32& bit) __attribute__((always_inline)) {
             u32 h = 0;
 #pragma unroll
             for (int j = 0; j < N - 1; ++j) h = light_step(h, s_tok[i + j], j);
             h = light_end(h) >> (32 - twice_bits);
-            word_ = twice[h >> 5];
-            bit_ = h & 31;
+            bit = h & 31;
+            return twice[h >> 5];
         };
+        u32 word[W], bit[W], word_c = 0, bit_c = 0;        // of the lane's positions, and of the one past the chunk
+        u64 often[W], once[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            where(w * TH + tid, word[w], bit[w]);
-            word64[w] = bit64[w] = 0;
-            if (lane == 0) where(w * TH + tid + 64, word64[w], bit64[w]);
+            often[w] = reinterpret_cast<const u64*>(s_often)[(w * TH + tid) / 64];
+            once[w] = reinterpret_cast<const u64*>(s_once)[(w * TH + tid) / 64];
+            word[w] = bit[w] = 0;
+            if ((((often[w] | once[w]) >> lane) & 1) == 0) word[w] = word_of(w * TH + tid, bit[w]);
         }
+        if (tid == 0) word_c = word_of(C, bit_c);
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            often[w] |= __ballot((word[w] >> bit[w]) & 1);
+            if (lane == 0) reinterpret_cast<u64*>(s_often)[(w * TH + tid) / 64] = often[w];
+        }
+        if (tid == 0) reinterpret_cast<u64*>(s_often)[C / 64] = (word_c >> bit_c) & 1;
+        __syncthreads();
         u32 gone = 0;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            const u64 here = __ballot((word[w] >> bit[w]) & 1);
-            const u64 next = __ballot((word64[w] >> bit64[w]) & 1);
+            const u64 here = often[w], next = reinterpret_cast<const u64*>(s_often)[(w * TH + tid) / 64 + 1];
             const u64 both = here & ((here >> 1) | (next << 63));
             if (((inside >> w) & 1) && !((both >> lane) & 1)) gone |= 1u << w;
         }
@@ -129,7 +182,8 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
     }
 
     // ---- equal windows merged: a lane probes once per turn and takes its next window as soon as it is done with one
-    u32 mine = 0;                                          // bit w: the window claimed a slot, s_claim[w TH + tid]
+    u32 mine = 0;                                          // bit w: the window claimed its slot, s_claim[w TH + tid]
+    const u32 alive = inside;
     {
         u32 t[N], idx = 0;
         int i = 0;
@@ -159,7 +213,10 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
                     bool eq = true;
 #pragma unroll
                     for (int j = 0; j < N; ++j) eq = eq & (s_tok[p + j] == t[j]);
-                    if (eq) atomicAdd(&s_slot[idx], 1u);
+                    if (eq) {
+                        atomicAdd(&s_slot[idx], 1u);
+                        s_claim[i] = (uint16_t)idx;
+                    }
                     busy = !eq;
                     idx = (idx + 1) & (2 * C - 1);         // (twice as many slots as windows: one is free)
                 }
@@ -173,20 +230,44 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
     u64 hash[W], hi[W];
     u32 cnt[W], rank[W];
 #pragma unroll
+    for (int w = 0; w < W; ++w) cnt[w] = s_slot[s_claim[w * TH + tid] & (2 * C - 1)] & 0xFFFFu;      // (of a window that is not alive: anything)
+    if (keep_marks) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const u64 live = __ballot((alive >> w) & 1), many = __ballot(((alive >> w) & 1) && cnt[w] > 1);
+            if (lane == 0) {
+                reinterpret_cast<u64*>(s_once)[(w * TH + tid) / 64] = ~live;
+                reinterpret_cast<u64*>(s_often)[(w * TH + tid) / 64] = many;
+            }
+        }
+    }
+#pragma unroll
     for (int w = 0; w < W; ++w) {
-        cnt[w] = 0;
-        if (!((mine >> w) & 1)) continue;
-        const u32 sl = s_slot[s_claim[w * TH + tid]];
         const u32* at = s_tok + w * TH + tid;
-        cnt[w] = sl & 0xFFFFu;
         u64 lo = 0;
         hi[w] = 0;
 #pragma unroll
         for (int j = 0; j < N; ++j) tasc_key_put(lo, hi[w], j, bits, at[j]);
         hash[w] = tasc_hash_key(lo, hi[w]);
-        rank[w] = atomicAdd(&s_hist[part_of(hash[w], parts)], (cnt[w] + 255) / 256);
+        if (!((mine >> w) & 1)) cnt[w] = 0;
+        if (cnt[w]) rank[w] = atomicAdd(&s_hist[part_of(hash[w], parts)], (cnt[w] + 255) / 256);
     }
     __syncthreads();
+    if (keep_marks && marks_mine) {
+        // eight bits into eight bytes
+        auto spread = [](u64 b) __attribute__((always_inline)) {
+            return (((b * 0x0101010101010101ull & 0x8040201008040201ull) + 0x7F7F7F7F7F7F7F7Full) >> 7) & 0x0101010101010101ull;
+        };
+#pragma unroll
+        for (int q = 0; q < (int)(sizeof e_in / 8); ++q) {
+            const int g = q * TH + tid;
+            const u64 at = base + 8 * g, v = spread(s_end[g]) * kMarkEnd | spread(s_once[g]) * kMarkOnce | spread(s_often[g]) * kMarkOften;
+            if (at + 8 <= T) *reinterpret_cast<u64*>(marks + at) = v;
+            else
+                for (int e = 0; e < 8; ++e)
+                    if (at + e < T) marks[at + e] = (uint8_t)(v >> (8 * e));
+        }
+    }
     // exclusive scan of the partitions' record counts, a run of consecutive partitions per thread
     const u32 per = ((parts + TH - 1) / TH) | 1, p0 = min(tid * per, parts), p1 = min(p0 + per, parts);     // (odd: no bank conflicts)
     u32 sum = 0, total;
@@ -227,7 +308,8 @@ __device__ __forceinline__ void partition_chunk(const int32_t* __restrict__ tok,
 struct PartitionArgs {
     const int32_t* tok;
     const u64* d_T;            // nullable: the corpus' length, where the host does not know it (T is then no less)
-    const uint8_t* last;       // 1: the document's last token
+    uint8_t* marks;            // kMark... of a position
+    bool keep_marks;           // leave those for the order above
     u64 T;
     int32_t bits, n0;          // n0 + blockIdx.y = order of the launch's block
     u32 parts, row;            // row = parts + 1, rounded up: a chunk's offsets
@@ -246,13 +328,13 @@ __global__ __launch_bounds__(TH) void k_partition(PartitionArgs a) {
     u64* const rec = a.rec + blockIdx.y * a.order_recs;
     uint16_t* const offs = a.offs + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * a.row;
     switch (n) {
-        case 2: partition_chunk<2, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
-        case 3: partition_chunk<3, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
-        case 4: partition_chunk<4, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
-        case 5: partition_chunk<5, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
-        case 6: partition_chunk<6, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
-        case 7: partition_chunk<7, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
-        default: partition_chunk<8, C, TH>(a.tok, a.last, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 2: partition_chunk<2, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 3: partition_chunk<3, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 4: partition_chunk<4, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 5: partition_chunk<5, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 6: partition_chunk<6, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        case 7: partition_chunk<7, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
+        default: partition_chunk<8, C, TH>(a.tok, a.marks, a.keep_marks, a.T, a.bits, a.parts, a.twice, a.twice_bits, a.distinct, rec, offs); break;
     }
 }
 
@@ -686,7 +768,7 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(6, 
 }
 
 constexpr int kChunkLarge = 8192, kThreadsLarge = 1024, kChunkSmall = 2048, kThreadsSmall = 512;
-size_t partition_lds(u32 chunk, u32 parts) { return (size_t)(2 * chunk + chunk + 8 + parts + 16) * 4 + 2 * (size_t)chunk; }
+size_t partition_lds(u32 chunk, u32 parts) { return (size_t)(2 * chunk + chunk + 8 + parts + 1 + 16) * 4 + 2 * (size_t)chunk + 3 * (chunk / 8 + 8); }
 u32 up64(u32 v) { return (v + 63) / 64 * 64; }
 
 }  // namespace
@@ -729,10 +811,10 @@ int tasc_twice_bits(u64 T) {
     return b;
 }
 
-tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, const uint8_t* d_last, u64 T, const u64* d_T, int32_t n0,
+tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, uint8_t* d_marks, bool keep_marks, u64 T, const u64* d_T, int32_t n0,
                                  int32_t n_orders, int32_t bits, const TascCountBufs& b, const u32* d_twice, u64* d_counters, hipStream_t st) {
     const u32 row = up64(p.parts + 1);
-    PartitionArgs a{d_tok, d_T, d_last, T, bits, n0, p.parts, row, d_twice, tasc_twice_bits(T), d_counters, p.rec_bytes / sizeof(u64), b.rec, b.offs};
+    PartitionArgs a{d_tok, d_T, d_marks, keep_marks, T, bits, n0, p.parts, row, d_twice, tasc_twice_bits(T), d_counters, p.rec_bytes / sizeof(u64), b.rec, b.offs};
     const size_t lds = partition_lds(p.chunk, p.parts);
     auto launch = [&](auto kernel, int threads) -> tasc_status {
         TASC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

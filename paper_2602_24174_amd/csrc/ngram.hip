@@ -401,7 +401,7 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
             u32* const mine = prune && n < n_max ? (u32*)(arena + at_twice + (1 - (n & 1)) * twice_bytes) : nullptr;
             TASC_HIP(hipEventRecord(evc[n][0], st));
             if (mine) TASC_HIP(hipMemsetAsync(mine, 0, twice_bytes, st));
-            TASC_TRY(tasc_count_partition(p, d_tok, d_last, T, nullptr, n, 1, bits, bufs, below, &d_counters[n][0], st));
+            TASC_TRY(tasc_count_partition(p, d_tok, d_last, mine != nullptr, T, nullptr, n, 1, bits, bufs, below, &d_counters[n][0], st));
             TASC_TRY(tasc_count_tables(p, n, bits, (u32)p_min, bufs, d_counters[n], kept_of(n), mine, T, st));
             TASC_HIP(hipEventRecord(evc[n][1], st));
         }

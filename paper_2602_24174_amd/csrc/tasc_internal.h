@@ -124,10 +124,11 @@ struct TascGram {             // one n-gram; count 0 = none
 // wide: keys of more than 64 bits (a call of several orders takes the plan of its longest); pruned: with the order below at hand
 TascCountPlan tasc_count_plan(u64 T, u64 windows, bool wide, bool pruned);
 int tasc_twice_bits(u64 T);   // log2 of the bits of a `twice` map
-// Records of the orders n0 .. n0 + n_orders - 1.  last[i] = 1 where position i ends a document, as the corpus' last one does;
+// Records of the orders n0 .. n0 + n_orders - 1.  Bit 0 of marks[i] (8-byte aligned): position i ends a document, as the corpus' last one does;
+// keep_marks (one order only) leaves in the other bits what the order above can use, and a call with d_twice reads what that of the order below left;
 // d_T (nullable): the corpus' length in device memory, no more than T.  d_twice (nullable, one order only): the map that
 // tasc_count_tables filled for the order below; n-grams that it shows to occur once leave no record but are added to d_counters[0].
-tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, const uint8_t* d_last, u64 T, const u64* d_T, int32_t n0,
+tasc_status tasc_count_partition(const TascCountPlan& p, const int32_t* d_tok, uint8_t* d_marks, bool keep_marks, u64 T, const u64* d_T, int32_t n0,
                                  int32_t n_orders, int32_t bits, const TascCountBufs& b, const u32* d_twice, u64* d_counters, hipStream_t st);
 // Finished counts of one order: d_counters[0] += distinct n-grams, [1] += those of at least p_min, which go to `kept`; d_twice
 // (nullable, cleared): a bit is set for every n-gram that occurs more than once

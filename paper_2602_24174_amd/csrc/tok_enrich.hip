@@ -912,7 +912,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
             if (full) {
                 for (int n0 = 2; n0 <= n_max; n0 += together) {
                     const int here = std::min(together, n_max + 1 - n0);
-                    TOK_TRY(tasc_count_partition(p, tok[i & 1], last[i & 1], T, len + i, n0, here, bits, bufs, nullptr, nullptr, st));
+                    TOK_TRY(tasc_count_partition(p, tok[i & 1], last[i & 1], false, T, len + i, n0, here, bits, bufs, nullptr, nullptr, st));
                     TOK_TRY(tasc_count_best(p, len + i, n0, here, bits, bufs, best + (size_t)(n0 - 2) * p.parts, st));
                 }
                 k_pick<<<dim3(1), dim3(kThreads), 0, st>>>(best, (u32)orders * p.parts, bits, since, state, d_merges);
