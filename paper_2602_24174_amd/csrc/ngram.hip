@@ -127,17 +127,53 @@ __device__ inline void key_head(u64& lo, u64& hi, int m, int bits) {
     hi = b > 64 ? hi & ((1ull << (b - 64)) - 1) : 0;
 }
 
+// The finished tables of several orders in three launches, whose chains of dependent round trips (a probe each) run beside each other: one order has
+// 130 to 280 workgroups of them, half the chip's room, and their longest lanes decide.  The keys and their contexts, 32 M tokens, orders 2 to 5, with
+// clearing and k_materialize_ctx: 405 us order by order, 248 so (k_keep 166: about the rate of its atomics).
+struct Finish {
+    TascKept kept;
+    u64 n_kept;
+    TascSlot *full, *ctx;
+    CtxRef* ref;
+    u64 cap;                   // slots of each table
+    u64* n_contexts;
+    int32_t n;
+    u32 first;                 // k_keep: the order's first workgroup
+};
+struct FinishAll {
+    Finish order[TASC_MAX_ORDER - 1];
+    int32_t orders, bits;
+};
+
+__global__ __launch_bounds__(kThreads) void k_clear_tables(FinishAll all) {
+    const Finish& f = all.order[blockIdx.y];
+    static_assert(sizeof(TascSlot) == 32 && sizeof(CtxRef) == 16, "16 bytes a store");
+    uint4 *const full = reinterpret_cast<uint4*>(f.full), *const ref = reinterpret_cast<uint4*>(f.ref);
+    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < f.cap; i += (u64)gridDim.x * kThreads) {
+        full[i] = make_uint4(0, 0, 0, 0);
+        full[f.cap + i] = make_uint4(0, 0, 0, 0);
+        ref[i] = make_uint4(0, 0, 0, 0);
+    }
+}
+
 // Kept n-grams -> full table, and their contexts -> context table.  Frequent contexts have thousands of kept successors, whose
 // additions to one slot would wait for each other (32 M tokens, orders 2 to 5: 220 us an order); a workgroup merges those
-// of its kThreadsKeep n-grams in LDS first: 34 to 70 us.
+// of its kThreadsKeep n-grams in LDS first: 34 to 70 us an order alone.
 constexpr int kThreadsKeep = 1024;
-__global__ __launch_bounds__(kThreadsKeep) void k_keep(TascKept kept, u64 n_kept, int n, int bits, TascSlot* full, u64 full_mask,
-                                                       CtxRef* ctx, u64 ctx_mask) {
+__global__ __launch_bounds__(kThreadsKeep) void k_keep(FinishAll all) {
+    int o = 0;
+    while (o + 1 < all.orders && blockIdx.x >= all.order[o + 1].first) ++o;
+    const Finish& f = all.order[o];
+    const TascKept kept = f.kept;
+    const u64 n_kept = f.n_kept, full_mask = f.cap - 1, ctx_mask = f.cap - 1;
+    const int n = f.n, bits = all.bits;
+    TascSlot* const full = f.full;
+    CtxRef* const ctx = f.ref;
     constexpr int SLOTS = 2 * kThreadsKeep;
     __shared__ u64 s_lo[kThreadsKeep], s_hi[kThreadsKeep], s_best[SLOTS];
     __shared__ u32 s_ref[SLOTS], s_total[SLOTS];
     const int tid = threadIdx.x;
-    const u64 i = (u64)blockIdx.x * kThreadsKeep + tid;
+    const u64 i = (u64)(blockIdx.x - f.first) * kThreadsKeep + tid;
     for (int q = tid; q < SLOTS; q += kThreadsKeep) { s_ref[q] = 0; s_total[q] = 0; s_best[q] = 0; }
     const bool on = i < n_kept;
     u64 lo = on ? kept.lo[i] : 0, hi = on ? kept.hi[i] : 0;
@@ -202,8 +238,14 @@ __global__ __launch_bounds__(kThreadsKeep) void k_keep(TascKept kept, u64 n_kept
 }
 
 // gives every context slot its explicit key; same index, so the probe sequences stay valid
-__global__ __launch_bounds__(kThreads) void k_materialize_ctx(TascKept kept, const CtxRef* ref, u64 cap, int n_ctx_tok, int bits,
-                                                              TascSlot* out, u64* n_contexts) {
+__global__ __launch_bounds__(kThreads) void k_materialize_ctx(FinishAll all) {
+    const Finish& f = all.order[blockIdx.y];
+    const TascKept kept = f.kept;
+    const CtxRef* const ref = f.ref;
+    const u64 cap = f.cap;
+    const int n_ctx_tok = f.n - 1, bits = all.bits;
+    TascSlot* const out = f.ctx;
+    u64* const n_contexts = f.n_contexts;
     u32 n = 0;
     for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < cap; i += (u64)gridDim.x * kThreads) {
         CtxRef r = ref[i];
@@ -421,30 +463,48 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
         if (total == 0) continue;
         TASC_TRY(tasc_device_malloc((void**)&ng->tables[n0], total * sizeof(TascSlot)));
         CtxRef* ref = (CtxRef*)bufs.rec;
-        if (most * sizeof(CtxRef) > rec_bytes) {
+        u64 room = rec_bytes / sizeof(CtxRef);
+        if (most > room) {
             TASC_TRY(tasc_device_malloc((void**)&ref, most * sizeof(CtxRef)));
             tmp.ptrs.push_back(ref);
+            room = most;
         }
         TascSlot* at = ng->tables[n0];
+        FinishAll all{};
+        all.bits = bits;
+        u64 used_ref = 0, largest = 0;
+        u32 groups = 0;
+        auto finish = [&]() -> tasc_status {                   // the orders collected so far
+            if (all.orders == 0) return TASC_OK;
+            const dim3 grid((unsigned)std::min<u64>((largest + kThreads - 1) / kThreads, 2048), (unsigned)all.orders);
+            k_clear_tables<<<grid, dim3(kThreads), 0, st>>>(all);
+            TASC_LAUNCH_CHECK();
+            k_keep<<<dim3(groups), dim3(kThreadsKeep), 0, st>>>(all);
+            TASC_LAUNCH_CHECK();
+            k_materialize_ctx<<<grid, dim3(kThreads), 0, st>>>(all);
+            TASC_LAUNCH_CHECK();
+            all.orders = 0;
+            used_ref = largest = 0;
+            groups = 0;
+            return TASC_OK;
+        };
         for (int n = n0; n < group_end[n0]; ++n) {
             if (fcap[n] == 0) continue;
             TascSlot *full = at, *ctx = at + fcap[n];
             at += 2 * fcap[n];
-            TASC_HIP(hipMemsetAsync(full, 0, fcap[n] * sizeof(TascSlot), st));
-            TASC_HIP(hipMemsetAsync(ref, 0, fcap[n] * sizeof(CtxRef), st));
             const u64 kept = h_counters[n][1];
-            k_keep<<<dim3((unsigned)((kept + kThreadsKeep - 1) / kThreadsKeep)), dim3(kThreadsKeep), 0, st>>>(kept_of(n), kept, n, bits, full, fcap[n] - 1,
-                                                                                                         ref, fcap[n] - 1);
-            TASC_LAUNCH_CHECK();
-            k_materialize_ctx<<<dim3((unsigned)std::min<u64>((fcap[n] + kThreads - 1) / kThreads, 2048)), dim3(kThreads), 0, st>>>(
-                kept_of(n), ref, fcap[n], n - 1, bits, ctx, &d_counters[n][2]);
-            TASC_LAUNCH_CHECK();
+            if (used_ref + fcap[n] > room) TASC_TRY(finish()); // (the records' memory holds the contexts of all orders as a rule)
+            all.order[all.orders++] = Finish{kept_of(n), kept, full, ctx, ref + used_ref, fcap[n], &d_counters[n][2], n, groups};
+            used_ref += fcap[n];
+            largest = std::max(largest, fcap[n]);
+            groups += (u32)((kept + kThreadsKeep - 1) / kThreadsKeep);
             ng->slots[n][0] = ctx;
             ng->slots[n][1] = full;
             ng->view.ord[n].ctx = ctx;
             ng->view.ord[n].full = full;
             ng->view.ord[n].ctx_mask = ng->view.ord[n].full_mask = fcap[n] - 1;
         }
+        TASC_TRY(finish());
     }
     if (T > 0) ng->view.fallback = (int32_t)(0xFFFFFFFFu - (u32)h_counters[0][3]);
     TASC_HIP(hipMemcpyAsync(h_counters, d_counters, sizeof h_counters, hipMemcpyDeviceToHost, st));
