@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void k_unigram(const int32_t* __restrict_
 }
 
 // hist = the sum of the copies; best[0] = max over tokens of (count << 32) | (0xFFFFFFFF - token): largest count, smallest id
-__global__ void k_unigram_argmax(const u32* copies, int n_copies, int vocab, u32* hist, u64* best) {
+__global__ __launch_bounds__(kThreads) void k_unigram_argmax(const u32* copies, int n_copies, int vocab, u32* hist, u64* best) {
     u64 v = 0;
     for (u32 i = blockIdx.x * blockDim.x + threadIdx.x; i < (u32)vocab; i += gridDim.x * blockDim.x) {
         u32 n = 0;
@@ -107,7 +107,14 @@ __global__ void k_unigram_argmax(const u32* copies, int n_copies, int vocab, u32
         u64 w = __shfl_xor(v, o);
         v = w > v ? w : v;
     }
-    if ((threadIdx.x & 63) == 0) atomicMax(best, v);
+    // (additions and maxima to one address take 9 ns each, whoever makes them: a wave's each were 21 of 32 us at 151,936 tokens)
+    __shared__ u64 s_v[kThreads / 64];
+    if ((threadIdx.x & 63) == 0) s_v[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) v = s_v[w] > v ? s_v[w] : v;
+        atomicMax(best, v);
+    }
 }
 
 __global__ void k_mark_doc_ends(const int64_t* doc_off, int64_t n_docs, uint8_t* last) {
@@ -129,7 +136,7 @@ __device__ inline void key_head(u64& lo, u64& hi, int m, int bits) {
 
 // The finished tables of several orders in three launches, whose chains of dependent round trips (a probe each) run beside each other: one order has
 // 130 to 280 workgroups of them, half the chip's room, and their longest lanes decide.  The keys and their contexts, 32 M tokens, orders 2 to 5, with
-// clearing and k_materialize_ctx: 405 us order by order, 248 so (k_keep 166: about the rate of its atomics).
+// clearing and k_materialize_ctx: 405 us order by order, 212 so (k_keep 166: about the rate of its atomics).
 struct Finish {
     TascKept kept;
     u64 n_kept;
@@ -237,8 +244,10 @@ __global__ __launch_bounds__(kThreadsKeep) void k_keep(FinishAll all) {
     }
 }
 
-// gives every context slot its explicit key; same index, so the probe sequences stay valid
-__global__ __launch_bounds__(kThreads) void k_materialize_ctx(FinishAll all) {
+// gives every context slot its explicit key; same index, so the probe sequences stay valid.  Few and large workgroups: each adds once to the order's
+// number of contexts, and 2048 of 256 threads an order waited for that longer than for the tables (62 us, 32 so, four orders of 0.5 M to 1 M slots).
+constexpr int kThreadsCtx = 1024, kGroupsCtx = 256;
+__global__ __launch_bounds__(kThreadsCtx) void k_materialize_ctx(FinishAll all) {
     const Finish& f = all.order[blockIdx.y];
     const TascKept kept = f.kept;
     const CtxRef* const ref = f.ref;
@@ -247,7 +256,7 @@ __global__ __launch_bounds__(kThreads) void k_materialize_ctx(FinishAll all) {
     TascSlot* const out = f.ctx;
     u64* const n_contexts = f.n_contexts;
     u32 n = 0;
-    for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < cap; i += (u64)gridDim.x * kThreads) {
+    for (u64 i = (u64)blockIdx.x * kThreadsCtx + threadIdx.x; i < cap; i += (u64)gridDim.x * kThreadsCtx) {
         CtxRef r = ref[i];
         TascSlot s = {0, 0, 0, 0, 0, 0};
         if (r.ref1 != 0) {
@@ -261,13 +270,13 @@ __global__ __launch_bounds__(kThreads) void k_materialize_ctx(FinishAll all) {
         }
         out[i] = s;
     }
-    __shared__ u32 s_w[kThreads / 64];
+    __shared__ u32 s_w[kThreadsCtx / 64];
     for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = n;
     __syncthreads();
     if (threadIdx.x == 0) {                            // one addition per workgroup, not per context
         u64 sum = 0;
-        for (int w = 0; w < kThreads / 64; ++w) sum += s_w[w];
+        for (int w = 0; w < kThreadsCtx / 64; ++w) sum += s_w[w];
         if (sum) atomicAdd(n_contexts, sum);
     }
 }
@@ -481,7 +490,7 @@ extern "C" tasc_status tasc_ngram_build(const int32_t* tokens, const int64_t* do
             TASC_LAUNCH_CHECK();
             k_keep<<<dim3(groups), dim3(kThreadsKeep), 0, st>>>(all);
             TASC_LAUNCH_CHECK();
-            k_materialize_ctx<<<grid, dim3(kThreads), 0, st>>>(all);
+            k_materialize_ctx<<<dim3((unsigned)std::min<u64>((largest + kThreadsCtx - 1) / kThreadsCtx, kGroupsCtx), (unsigned)all.orders), dim3(kThreadsCtx), 0, st>>>(all);
             TASC_LAUNCH_CHECK();
             all.orders = 0;
             used_ref = largest = 0;
