@@ -18,8 +18,8 @@
 // q/k/v 240 -> 206; LM head with logits 1280 x 49152 x 2048 499 -> 296, 576 x 151936 x 1536 510 -> 357 (whole rows of 128 bytes per
 // store instead of 4-byte stores to 32 rows).
 // Loads are buffer loads: a lane's offset from its tile's first row is the same for every item, k is a scalar beside it, and past the
-// last item the buffer has no bytes, so the stream's end costs no traffic and the loop no branch.  With more than two stages in LDS they are spread
-// over the k-blocks of a stage: all at once, behind the barrier, every wave waited for the others' (128 x 128 x 64 of a stage 0.78 us, 0.55 so).
+// last item the buffer has no bytes, so the stream's end costs no traffic and the loop no branch.  They are spread over the k-blocks of
+// a stage (the first two of them with two stages in LDS): all at once, behind the barrier, every wave waited for the others' (128 x 128 x 64 of a stage 0.78 us, 0.55 so).
 // What bounds a 128 x 128 tile is that rate of lines into a compute unit: without the products 23.3 of 24.8 us for 576 x 1536 x 8960 in four slices
 // with cold weights, 18.5 with warm ones, 18.4 without the loads.  In the forwards, one tile per compute unit through registers | so, us: down
 // 1280 x 2048 x 11008 in six slices 61.5 | 59.0, 6336 x 1536 x 8960 195 | 189, output 1280 x 2048 x 2048 26.9 | 21.5, q/k/v of prompts 6336 x 2560 x 1536
