@@ -22,8 +22,8 @@
 // a stage (the first two of them with two stages in LDS): all at once, behind the barrier, every wave waited for the others' (128 x 128 x 64 of a stage 0.78 us, 0.55 so).
 // What bounds a 128 x 128 tile is that rate of lines into a compute unit: without the products 23.3 of 24.8 us for 576 x 1536 x 8960 in four slices
 // with cold weights, 18.5 with warm ones, 18.4 without the loads.  In the forwards, one tile per compute unit through registers | so, us: down
-// 1280 x 2048 x 11008 in six slices 61.5 | 59.0, 6336 x 1536 x 8960 195 | 189, output 1280 x 2048 x 2048 26.9 | 21.5, q/k/v of prompts 6336 x 2560 x 1536
-// 80 | 60.
+// 1280 x 2048 x 11008 in six slices 61.5 | 59.0, 6336 x 1536 x 8960 195 | 189, output 1280 x 2048 x 2048 26.9 | 21.5, q/k/v of prompts 6336 x 2048 x 1536
+// 80 | 54.
 #pragma once
 #include "kernels_small.h"
 
@@ -606,7 +606,7 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
             }
             // Values go transposed: [feature][32 rows] of two tiles in the wave's LDS, a feature a lane, and from there runs of rows that are
             // neighbours in a page, 8 slots, 2 or 1 at a time.  The columns of few workgroups hold all the values of a layer, so what they cost
-            // is added to the launch (q/k/v of prompts, 6336 x 2560 x 1536: two-byte stores straight from the registers 80 us, so 60, without values 56).
+            // is added to the launch (q/k/v of prompts, 6336 x 2048 x 1536: two-byte stores straight from the registers 80 us, so 54).
             if ((nwave + SN - 1) / HD >= gm.H + gm.Hkv && nwave < N) {
                 static_assert(TI % 2 == 0, "tiles in pairs");
 #pragma unroll 1
@@ -632,9 +632,10 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
                         slot_l = pass < TI / 2 ? slot_l : r_slot[1];
                         page_l = pass < TI / 2 ? page_l : r_page[1];
                     }
-                    // bit r: row r + 1 follows row r in its page
-                    const uint32_t on = (uint32_t)__ballot(lr < 31 && slot_l >= 0 && __shfl(slot_l, (el + 1) & 63) == slot_l + 1 &&
-                                                           __shfl(page_l, (el + 1) & 63) == page_l);
+                    // bit r: row r + 1 follows row r in its page.  (All lanes shuffle, before any condition: a lane that sits out reads as 0, and
+                    // page 0 is a page.)
+                    const int slot_n = __shfl(slot_l, (el + 1) & 63), page_n = __shfl(page_l, (el + 1) & 63);
+                    const uint32_t on = (uint32_t)__ballot(lr < 31 && slot_l >= 0 && slot_n == slot_l + 1 && page_n == page_l);
                     if (v0 + el >= 0 && nwave + 64 * (pass % (TI / 2)) + el < N) {
                         BF16* const base = rp.kv_layer + (size_t)gm.Hkv * TASC_KV_BLOCK * HD + (size_t)(v0 + el) * TASC_KV_BLOCK;
                         uint32_t v[17];                              // the feature's 32 rows
