@@ -24,16 +24,18 @@ constexpr int kBlock = kThreads * kItems;            // 4096
 constexpr int kFirst = 8, kBatch = 16;              // merges that the host launches before it looks: at first, and then
 constexpr size_t kMostRecords = (size_t)2 << 30;
 
-enum { kCountAll = 1, kTimeOut = 2 };
 struct Merge {           // one line of the result, as the caller's arrays have it
     int32_t row[1 + TASC_MAX_ORDER];
     u32 freq;
 };
+// Workgroups of one launch start at different times, and so do the waves of a workgroup: a field that a kernel returns early on is written in
+// that launch by no one, or only after all have read it (k_gather's last workgroup).
 struct State {
     u32 merges, done;    // merges so far; 1: nothing left to merge: every later step does nothing
-    u32 stuck;           // kCountAll: the sieve cannot tell the next merge (see below): every later step does nothing until the host has seen it
+    u32 stuck;           // 1: the sieve cannot tell the next merge (see below): every later step does nothing until the host has seen it
     u32 bad, foreign;    // a token outside the vocabulary, the new ids included: nothing is done; one of the new ids: the sieve is not used
-    u32 undo;            // 1: the last merge was the wrong one
+    u32 gave_up;         // k_sift's: its lists or tables are full, or most buckets pass; k_gather makes `stuck` of it
+    u32 undo, late;      // k_apply's: the last merge was the wrong one; a workgroup did not hear from another.  As `stuck` for later steps
     u32 arrived;         // workgroups of k_gather that are done with the running merge
     u32 top, taken;      // the fullest bucket of pairs; 1: there is a running merge
     u64 reward;          // of the last merge, or, where none was found for certain (retry), of the best n-gram that was
@@ -43,8 +45,8 @@ struct State {
     int32_t t[TASC_MAX_ORDER], new_id;
 };
 
-__device__ __forceinline__ bool idle(const State* st) { return (st->done | st->stuck | st->bad) != 0; }
-__device__ __forceinline__ bool no_merge(const State* st) { return (st->stuck | st->bad) != 0 || !st->taken; }      // (done: with the last one)
+__device__ __forceinline__ bool idle(const State* st) { return (st->done | st->stuck | st->bad | st->undo | st->late) != 0; }
+__device__ __forceinline__ bool no_merge(const State* st) { return !st->taken; }      // (after an idle k_sift or k_pick, too)
 
 // st->bad = 1 if a token lies outside [0, vocab_all), st->foreign = 1 if outside [0, vocab); and the corpus' length where the steps look for it
 __global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __restrict__ tok, u64 T, int vocab, int vocab_all, State* st, u64* len) {
@@ -55,7 +57,7 @@ __global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __rest
         foreign = foreign || (u32)tok[i] >= (u32)vocab;
     }
     if (bad) st->bad = 1;
-    if (foreign) st->foreign = st->stuck = kCountAll;
+    if (foreign) st->foreign = st->stuck = 1;
 }
 
 // The corpus: an even number of merges leaves it in the first of the two places, an odd one in the second.  The steps look for the number in
@@ -128,7 +130,10 @@ __device__ __forceinline__ TascGram best_of_wave(TascGram best, int bits) {
 
 // the best of the partitions' candidates
 __global__ __launch_bounds__(kThreads) void k_pick(const TascGram* __restrict__ cands, u32 count, int bits, Ends ends, State* st, Merge* merges) {
-    if (idle(st)) return;
+    if (idle(st)) {
+        if (threadIdx.x == 0) st->taken = 0;
+        return;
+    }
     TascGram best{0, 0, 0, 0};
     for (u32 i = threadIdx.x; i < count; i += kThreads)
         if (tasc_gram_before(cands[i], best, bits)) best = cands[i];
@@ -297,7 +302,7 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
     if (tid == 0) s_windows = s_total = 0;
     __syncthreads();
     if (s_open > kBuckets / 4) {                             // (nor is this)
-        if (tid == 0) st->stuck = kCountAll;
+        if (tid == 0) st->gave_up = 1;
         return;
     }
     auto passes = [&](int i) {
@@ -341,7 +346,7 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
                 return;
             }
         }
-        st->stuck = kCountAll;
+        st->gave_up = 1;
     };
     // Few positions have a window, and a window is a chain of LDS round trips: listed first, so that all lanes have one (a position a
     // lane, k_sift took 35 us); those of a quarter of the positions at a time where the list does not hold them all.
@@ -391,7 +396,7 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
     __syncthreads();
     if (tid < (int)lists.ranges) {
         const u32 n = s_listed[tid], to = n ? atomicAdd(&lists.listed[tid], n) : 0;
-        if (to + n > lists.most) st->stuck = kCountAll;
+        if (to + n > lists.most) st->gave_up = 1;
         s_listed[tid] = to + n > lists.most ? lists.most : to;
     }
     __syncthreads();
@@ -424,7 +429,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(Corpus corpus, Lists 
     __shared__ u64 s_most[kGatherThreads / 64];
     __shared__ u32 s_full, s_equals, s_equal[64];
     if (idle(st)) return;
-    const u32 all = lists.listed[blockIdx.x], lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    const bool gave_up = st->gave_up != 0;                   // (what is listed is not all, and may be more than there is room for)
+    const u32 all = gave_up ? 0 : lists.listed[blockIdx.x], lane = threadIdx.x & 63, wave = threadIdx.x / 64;
     const Found* __restrict__ const found = lists.found + (size_t)blockIdx.x * lists.most;
     for (int i = threadIdx.x; i < kGatherSlots; i += kGatherThreads) {
         s_key[i] = 0;
@@ -499,15 +505,15 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(Corpus corpus, Lists 
     if (lane != 0) return;
     const u64 reward = (u64)best.count * (best.n - 1);
     st->arrived = 0;
-    if (full) {
-        st->stuck = kCountAll;
+    if (full || gave_up) {
+        st->stuck = 1;
     } else if (best.count != 0 && reward > (u64)(n_max - 1) * (least - 1)) {
         take_merge(best, bits, ends, st, merges);
     } else if (best.count != 0 && !st->retry) {
         st->reward = reward;
         st->retry = 1;
     } else {
-        st->stuck = kCountAll;
+        st->stuck = 1;
     }
 }
 
@@ -730,7 +736,7 @@ __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __
             u32 spins = 0;
             do v = __hip_atomic_load(&told[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             while ((u32)(v >> 32) != launch && ++spins < kTellLimit);
-            if (spins == kTellLimit) st->stuck = kTimeOut;
+            if (spins == kTellLimit) st->late = 1;
             n = (u32)v;
         }
         block_scan(n, s_wave, &base);
@@ -739,10 +745,7 @@ __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         corpus.len[g.merges] = base + sum;
         // (of an n-gram that does not overlap itself every window is merged)
-        if (g.overlaps ? st->seen != g.freq : T - (base + sum) != (u64)g.freq * (g.n - 1)) {
-            st->stuck = kCountAll;
-            st->undo = 1;
-        }
+        if (g.overlaps ? st->seen != g.freq : T - (base + sum) != (u64)g.freq * (g.n - 1)) st->undo = 1;
     }
     for (u32 k = keep; k != 0; k &= k - 1, ++to) {
         const int e = __ffs((int)k) - 1;
@@ -895,7 +898,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     if (T0 && !run) TOK_TRY(look());
     u32 launch = 0;
     u32 full = 0, next_full = 4;                             // merges that are still counted in full; and how many the next time that the sieve gives up
-    for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck); batch = kBatch) {
+    for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck || h.undo); batch = kBatch) {
         const int begin = done, end = std::min(budget, done + (full ? (int)std::min<u32>(full, kBatch) : batch));
         if (full) TOK_TRY(full_counts());
         TascCountPlan p = plan;                              // (the records' strides are those of the whole corpus)
@@ -929,7 +932,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         }
         TOK_TRY(look());
         TASC_REQUIRE(h.bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
-        if (h.stuck == kTimeOut) {
+        if (h.late) {
             tasc_set_error("tok_enrich: workgroups of one launch did not hear from each other");
             return TASC_EHIP;
         }
@@ -937,7 +940,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         T = lens[done];
         if (full) {
             full -= (u32)(end - begin);
-        } else if (h.stuck) {
+        } else if (h.stuck || h.undo) {
             // (a look costs as much as the sieve gains on two or three merges; what it does not settle tends to come one after the other, and more
             // of it later)
             if (done - begin >= kFirst / 2) next_full = 4;
@@ -945,10 +948,9 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
             next_full = std::min(2 * next_full, 1u << 16);
             State again = h;
             again.merges = (u32)done;
-            again.stuck = again.undo = again.arrived = again.retry = again.taken = again.done = 0;
+            again.stuck = again.gave_up = again.undo = again.retry = again.taken = again.done = 0;
             again.reward = 0;                                // (the pairs are counted again, or k_pick leaves one)
             TASC_HIP(hipMemcpyAsync(state, &again, sizeof again, hipMemcpyHostToDevice, st));
-            TASC_HIP(hipMemsetAsync(lists.listed, 0, kGatherMost * sizeof(u32), st));
             TASC_HIP(hipStreamSynchronize(st));
         }
     }
