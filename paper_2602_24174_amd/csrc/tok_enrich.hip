@@ -538,7 +538,7 @@ __device__ __forceinline__ bool matches(const int32_t* tok, const uint8_t* __res
 }
 
 // Left-to-right choice among occurrences that can overlap (the others are all taken, and found where they are needed): sel[i] =
-// number of the merge.  An occurrence with none in the n - 1 positions before it ("head") is always taken; from it, one lane
+// number of the step, which no other one has (a merge's number comes again if it is taken back, and its marks stay).  An occurrence with none in the n - 1 positions before it ("head") is always taken; from it, one lane
 // walks the run of occurrences that overlap each other, taking the first at or after the end of the last taken one, and stops when
 // that one is a head itself (its own lane takes it) or lies beyond the reach of an overlap.  A walk is a chain of dependent loads, and
 // a long run of one token is one walk: after kLaneSteps steps the wave takes it over, 64 positions at a time, and the steps among them
@@ -546,7 +546,7 @@ __device__ __forceinline__ bool matches(const int32_t* tok, const uint8_t* __res
 // position to read instead of the tokens; 16 so).  The walk ends at the latest at the end of the corpus.
 constexpr unsigned kSelectBlocks = 256, kSelectThreads = 256;
 constexpr int kLaneSteps = 8;
-__global__ __launch_bounds__(kSelectThreads) void k_select(Corpus corpus, State* st, u32* sel) {
+__global__ __launch_bounds__(kSelectThreads) void k_select(Corpus corpus, State* st, u32* sel, u32 step) {
     __shared__ u32 s_seen;
     if (no_merge(st) || !st->overlaps) return;
     const Gram g = running(st);
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(Corpus corpus, State*
         seen += (u32)__popcll(__ballot(here));
         bool walking = here && is_head(i);
         for (int s = 0; walking && s < kLaneSteps; ++s) {
-            sel[cur] = st->merges;
+            sel[cur] = step;
             u64 next = T;
             for (u64 p = cur + n; p < cur + 2 * (u64)n - 1 && p < T; ++p)
                 if (matches(tok + p, last, T, p, g)) { next = p; break; }
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(Corpus corpus, State*
         // (the last step's `next` of a lane that is still walking is an occurrence that has to be taken)
         for (u64 todo = __ballot(walking); todo != 0; todo &= todo - 1) {
             u64 at = __shfl(cur, __ffsll(todo) - 1);         // taken; the next one lies n to 2 n - 2 positions on
-            if (lane == 0) sel[at] = g.merges;
+            if (lane == 0) sel[at] = step;
             for (bool on = true; on;) {
                 const u64 base = at + 1, here = starts(base);
                 u64 taken = 0;
@@ -606,7 +606,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_select(Corpus corpus, State*
                     taken |= 1ull << next;
                     c = next;
                 }
-                if ((taken >> lane) & 1) sel[base + lane] = g.merges;
+                if ((taken >> lane) & 1) sel[base + lane] = step;
                 at = base + c;
             }
         }
@@ -624,13 +624,13 @@ struct BlockTokens {
     __attribute__((aligned(16))) uint8_t start[kBlock + 16];
 };
 __device__ inline void block_keep(BlockTokens& s, const int32_t* __restrict__ tok, const uint8_t* __restrict__ last, const u32* __restrict__ sel,
-                                  u64 T, const Gram& g, u32& keep, u32& starts) {
+                                  u32 step, u64 T, const Gram& g, u32& keep, u32& starts) {
     const int64_t base = (int64_t)blockIdx.x * kBlock - 8;
     for (int q = threadIdx.x; q < kBlock + 16; q += kThreads) s.tok[q] = base + q >= 0 && base + q < (int64_t)T ? tok[base + q] : -1;
     __syncthreads();
     for (int q = threadIdx.x; q < kBlock + 8; q += kThreads) {
         const int64_t p = base + q;
-        s.start[q] = p >= 0 && p < (int64_t)T && (g.overlaps ? sel[p] == g.merges : matches(s.tok + q, last, T, (u64)p, g)) ? 1 : 0;
+        s.start[q] = p >= 0 && p < (int64_t)T && (g.overlaps ? sel[p] == step : matches(s.tok + q, last, T, (u64)p, g)) ? 1 : 0;
     }
     __syncthreads();
     u32 f = 0;                                               // bit 8 + e: an occurrence starts at the thread's position e
@@ -696,22 +696,22 @@ __global__ __launch_bounds__(kThreads) void k_scan(u32* bsum, u32 n) {      // i
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_sums(Corpus corpus, const u32* __restrict__ sel, const State* __restrict__ st, u32* bsum) {
+__global__ __launch_bounds__(kThreads) void k_sums(Corpus corpus, const u32* __restrict__ sel, u32 step, const State* __restrict__ st, u32* bsum) {
     __shared__ BlockTokens s;
     __shared__ u32 s_wave[kThreads / 64];
     if (no_merge(st)) return;
     const Gram g = running(st);
     const u32 from = (g.merges - 1) & 1;
     u32 keep, starts, sum;
-    block_keep(s, corpus.tok[from], corpus.last[from], sel, corpus.len[g.merges - 1], g, keep, starts);
+    block_keep(s, corpus.tok[from], corpus.last[from], sel, step, corpus.len[g.merges - 1], g, keep, starts);
     block_scan(__popc(keep), s_wave, &sum);
     if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
 }
-// bsum (nullable): k_sums' ; without, a block tells the others its own sum, as {launch, sum}, and waits for those before it: they were started
+// bsum (nullable): k_sums' ; without, a block tells the others its own sum, as {step, sum}, and waits for those before it: they were started
 // before it and wait for none after it.  A launch and another look at the corpus less, but every block reads every sum before its own: up to
 // kTellBlocks of them.
 constexpr u32 kTellBlocks = 1024, kTellLimit = 1u << 20;
-__global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __restrict__ sel, State* st, const u32* __restrict__ bsum, u64* told, u32 launch) {
+__global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __restrict__ sel, u32 step, State* st, const u32* __restrict__ bsum, u64* told) {
     __shared__ BlockTokens s;
     __shared__ u32 s_wave[kThreads / 64];
     if (no_merge(st)) return;
@@ -724,18 +724,18 @@ __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __
     static_assert(kItems == 4, "a word of ends");
     const u32 ends = *reinterpret_cast<const u32*>(last + (first < T ? first : 0));
     u32 keep, starts, sum, base;
-    block_keep(s, tok, last, sel, T, g, keep, starts);
+    block_keep(s, tok, last, sel, step, T, g, keep, starts);
     u32 to = block_scan(__popc(keep), s_wave, &sum);
     if (bsum) {
         base = blocks_before(bsum, s_wave);
     } else {
-        if (threadIdx.x == 0) __hip_atomic_store(&told[blockIdx.x], (u64)launch << 32 | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) __hip_atomic_store(&told[blockIdx.x], (u64)step << 32 | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         u32 n = 0;
         if (threadIdx.x < blockIdx.x) {
             u64 v = 0;
             u32 spins = 0;
             do v = __hip_atomic_load(&told[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while ((u32)(v >> 32) != launch && ++spins < kTellLimit);
+            while ((u32)(v >> 32) != step && ++spins < kTellLimit);
             if (spins == kTellLimit) st->late = 1;
             n = (u32)v;
         }
@@ -896,7 +896,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         return TASC_OK;
     };
     if (T0 && !run) TOK_TRY(look());
-    u32 launch = 0;
+    u32 step = 0;
     u32 full = 0, next_full = 4;                             // merges that are still counted in full; and how many the next time that the sieve gives up
     for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck || h.undo); batch = kBatch) {
         const int begin = done, end = std::min(budget, done + (full ? (int)std::min<u32>(full, kBatch) : batch));
@@ -923,11 +923,11 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
                 k_sift<<<grid_s, dim3(kSiftThreads), 0, st>>>(corpus, state, sums, since, i == begin, n_max, lists);
                 k_gather<<<dim3(gather_wgs), dim3(kGatherThreads), 0, st>>>(corpus, lists, since, i == begin, n_max, bits, state, d_merges, sifted);
             }
-            k_select<<<grid1, dim3(kSelectThreads), 0, st>>>(corpus, state, sel);
+            k_select<<<grid1, dim3(kSelectThreads), 0, st>>>(corpus, state, sel, ++step);
             const bool tell = grid2.x <= kTellBlocks;
-            if (!tell) k_sums<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, state, bsum);
+            if (!tell) k_sums<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, bsum);
             if (grid2.x > kScanFrom) k_scan<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, grid2.x);
-            k_apply<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, state, tell ? nullptr : bsum, told, ++launch);
+            k_apply<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, tell ? nullptr : bsum, told);
             TASC_LAUNCH_CHECK();
         }
         TOK_TRY(look());
