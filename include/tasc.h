@@ -360,12 +360,15 @@ tasc_status tasc_session_get_tokens(const tasc_session* s, int32_t b, int32_t* t
  *                        KiB of scratch that a table build or an enrichment may leave to the next one, per device (0 .. 2 GiB, the
  *                        default); setting it gives back what is kept beyond, so 0 and the value before free it for other users of the
  *                        device.  Results do not depend on it.
+ *   TASC_CFG_ENRICH_WAIT
+ *                        how often a workgroup of an enrichment looks for what the ones before it in the launch kept (default 2^20, a second
+ *                        or more) before the merge is made again without that wait, 0: at once.  Results do not depend on it.
  */
 enum {
     TASC_CFG_SMALL_PATH = 0, TASC_CFG_SMALL_GRID = 1, TASC_CFG_SMALL_LAYER_WGS = 2, TASC_CFG_SMALL_LAYER_STRIDE = 3,
     TASC_CFG_TILED_PATH = 4, TASC_CFG_SMALL_XCD_LOCAL = 5, TASC_CFG_SMALL_LAYER_WORKERS = 6, TASC_CFG_SMALL_KERNEL = 7,
     TASC_CFG_PIPE_SHARE = 8, TASC_CFG_CHAINS = 9, TASC_CFG_STEP_GRAPH = 10, TASC_CFG_BUILD_LIST_KIB = 11,
-    TASC_CFG_KEEP_SCRATCH_KIB = 12
+    TASC_CFG_KEEP_SCRATCH_KIB = 12, TASC_CFG_ENRICH_WAIT = 13
 };
 tasc_status tasc_config_set(int32_t key, int32_t value);
 

@@ -409,6 +409,7 @@ TASC_CFG_CHAINS = 9
 TASC_CFG_STEP_GRAPH = 10
 TASC_CFG_BUILD_LIST_KIB = 11
 TASC_CFG_KEEP_SCRATCH_KIB = 12
+TASC_CFG_ENRICH_WAIT = 13
 
 
 def tasc_config_set(key: int, value: int):

@@ -17,7 +17,8 @@
 #include <utility>
 
 TascConfig g_tasc_config = {/*small_path*/ 2, /*small_grid*/ 0, /*layer_wgs*/ 0, /*layer_stride*/ 0, /*tiled_path*/ 1, /*xcd_local*/ 1,
-                             /*layer_workers*/ 0, /*small_kernel*/ 1, /*pipe_share*/ 1, /*chains*/ 0, /*step_graph*/ 1, /*build_list_kib*/ 8 << 20};
+                             /*layer_workers*/ 0, /*small_kernel*/ 1, /*pipe_share*/ 1, /*chains*/ 0, /*step_graph*/ 1, /*build_list_kib*/ 8 << 20,
+                             /*enrich_wait*/ 1 << 20};
 // One-time set-up (kernel attributes, the compute-unit count) is kept per device and done under a lock, so that calls
 // from several host threads, or sessions on different devices of one process, each find their own device prepared.
 #include <mutex>
@@ -75,6 +76,9 @@ extern "C" tasc_status tasc_config_set(int32_t key, int32_t value) {
     } else if (key == TASC_CFG_KEEP_SCRATCH_KIB) {
         TASC_REQUIRE(value >= 0 && value <= 2 << 20, "config_set: kept scratch %d KiB outside [0, %d]", value, 2 << 20);
         tasc_scratch_limit((size_t)value << 10);
+    } else if (key == TASC_CFG_ENRICH_WAIT) {
+        TASC_REQUIRE(value >= 0, "config_set: enrichment wait %d", value);
+        g_tasc_config.enrich_wait = value;
     } else if (key == TASC_CFG_PIPE_SHARE) {
         TASC_REQUIRE(value >= 1 && value <= 3, "config_set: pipeline share %d outside [1, 3]", value);
         g_tasc_config.pipe_share = value;

@@ -381,6 +381,7 @@ struct TascConfig {
     int chains;               // ranges of sequences whose layers run side by side on streams of their own (0 = the library's rule)
     int step_graph;           // 1: verify steps outside the persistent kernels are recorded into a graph and replayed, 0: launched one by one
     int build_list_kib;       // KiB of kept-n-gram lists a table build fills before it builds their tables
+    int enrich_wait;          // looks of an enrichment's workgroup at another's sum before it gives up
 };
 extern TascConfig g_tasc_config;
 

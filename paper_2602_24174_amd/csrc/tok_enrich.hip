@@ -35,7 +35,7 @@ struct State {
     u32 stuck;           // 1: the sieve cannot tell the next merge (see below): every later step does nothing until the host has seen it
     u32 bad, foreign;    // a token outside the vocabulary, the new ids included: nothing is done; one of the new ids: the sieve is not used
     u32 gave_up;         // k_sift's: its lists or tables are full, or most buckets pass; k_gather makes `stuck` of it
-    u32 undo, late;      // k_apply's: the last merge was the wrong one; a workgroup did not hear from another.  As `stuck` for later steps
+    u32 undo, late;      // k_apply's: the last merge was the wrong one; it was left unfinished.  As `stuck` for later steps
     u32 arrived;         // workgroups of k_gather that are done with the running merge
     u32 top, taken;      // the fullest bucket of pairs; 1: there is a running merge
     u64 reward;          // of the last merge, or, where none was found for certain (retry), of the best n-gram that was
@@ -709,9 +709,10 @@ __global__ __launch_bounds__(kThreads) void k_sums(Corpus corpus, const u32* __r
 }
 // bsum (nullable): k_sums' ; without, a block tells the others its own sum, as {step, sum}, and waits for those before it: they were started
 // before it and wait for none after it.  A launch and another look at the corpus less, but every block reads every sum before its own: up to
-// kTellBlocks of them.
-constexpr u32 kTellBlocks = 1024, kTellLimit = 1u << 20;
-__global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __restrict__ sel, u32 step, State* st, const u32* __restrict__ bsum, u64* told) {
+// kTellBlocks of them.  A block that does not hear from another in `wait` looks gives up (the GPU may be shared): the call makes the merge again, with k_sums.
+constexpr u32 kTellBlocks = 1024;
+__global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __restrict__ sel, u32 step, State* st, const u32* __restrict__ bsum, u64* told,
+                                                    u32 wait) {
     __shared__ BlockTokens s;
     __shared__ u32 s_wave[kThreads / 64];
     if (no_merge(st)) return;
@@ -732,12 +733,13 @@ __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __
         if (threadIdx.x == 0) __hip_atomic_store(&told[blockIdx.x], (u64)step << 32 | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         u32 n = 0;
         if (threadIdx.x < blockIdx.x) {
-            u64 v = 0;
-            u32 spins = 0;
-            do v = __hip_atomic_load(&told[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while ((u32)(v >> 32) != step && ++spins < kTellLimit);
-            if (spins == kTellLimit) st->late = 1;
-            n = (u32)v;
+            bool heard = false;
+            for (u32 looks = 0; !heard && looks < wait; ++looks) {
+                const u64 v = __hip_atomic_load(&told[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                heard = (u32)(v >> 32) == step;
+                n = heard ? (u32)v : 0;
+            }
+            if (!heard) st->late = 1;                        // (what follows lands too far in front, and is not used)
         }
         block_scan(n, s_wave, &base);
     }
@@ -756,7 +758,8 @@ __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __
 }
 static_assert(kTellBlocks <= kThreads, "a thread per block before");
 
-// What the merges so far leave: where the outputs end, in order, and the tokens
+// What the merges so far leave: where the outputs end, in order, and the tokens; of a merge that is taken back, what it began with
+__device__ __forceinline__ u32 standing(const State* __restrict__ st) { return st->merges - ((st->undo | st->late) != 0 ? 1 : 0); }
 __device__ __forceinline__ u32 ends_here(const Corpus& c, u32 merges) {
     const u64 first = (u64)blockIdx.x * kBlock + kItems * threadIdx.x, T = c.len[merges];
     const uint8_t* __restrict__ const last = c.last[merges & 1];
@@ -768,13 +771,13 @@ __device__ __forceinline__ u32 ends_here(const Corpus& c, u32 merges) {
 __global__ __launch_bounds__(kThreads) void k_end_sums(Corpus c, const State* __restrict__ st, u32* bsum) {
     __shared__ u32 s_wave[kThreads / 64];
     u32 sum;
-    block_scan(__popc(ends_here(c, st->merges)), s_wave, &sum);
+    block_scan(__popc(ends_here(c, standing(st))), s_wave, &sum);
     if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
 }
 __global__ __launch_bounds__(kThreads) void k_ends(Corpus c, const State* __restrict__ st, const u32* __restrict__ bsum, u32* ends, int32_t* out) {
     __shared__ u32 s_wave[kThreads / 64];
     u32 sum;
-    const u32 merges = st->merges;
+    const u32 merges = standing(st);
     const u64 T = c.len[merges];
     if (out && !st->bad)
         for (u32 e = threadIdx.x; e < kBlock; e += kThreads) {
@@ -897,8 +900,9 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     };
     if (T0 && !run) TOK_TRY(look());
     u32 step = 0;
+    bool tell = true;
     u32 full = 0, next_full = 4;                             // merges that are still counted in full; and how many the next time that the sieve gives up
-    for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck || h.undo); batch = kBatch) {
+    for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck || h.undo || h.late); batch = kBatch) {
         const int begin = done, end = std::min(budget, done + (full ? (int)std::min<u32>(full, kBatch) : batch));
         if (full) TOK_TRY(full_counts());
         TascCountPlan p = plan;                              // (the records' strides are those of the whole corpus)
@@ -906,6 +910,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         const dim3 grid1((unsigned)std::min<u64>((T + kSelectThreads - 1) / kSelectThreads, kSelectBlocks)), grid2((unsigned)((T + kBlock - 1) / kBlock));
         const dim3 grid_p((unsigned)((T + span - 1) / span)), grid_s((unsigned)((T + kSiftSpan - 1) / kSiftSpan));
         const Ends since{(int32_t*)(ar.p + at_first), (int32_t*)(ar.p + at_last_of), vocab, vocab + begin, budget};
+        const bool told_all = tell && grid2.x <= kTellBlocks;
         if (!full) {
             k_pairs<<<grid_p, dim3(kPairThreads), 0, st>>>(corpus, state, span, pairs);
             k_pair_sums<<<dim3(kSumWgs), dim3(kSumThreads), 0, st>>>(pairs, grid_p.x, state, sums);
@@ -924,31 +929,30 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
                 k_gather<<<dim3(gather_wgs), dim3(kGatherThreads), 0, st>>>(corpus, lists, since, i == begin, n_max, bits, state, d_merges, sifted);
             }
             k_select<<<grid1, dim3(kSelectThreads), 0, st>>>(corpus, state, sel, ++step);
-            const bool tell = grid2.x <= kTellBlocks;
-            if (!tell) k_sums<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, bsum);
+            if (!told_all) k_sums<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, bsum);
             if (grid2.x > kScanFrom) k_scan<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, grid2.x);
-            k_apply<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, tell ? nullptr : bsum, told);
+            k_apply<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, told_all ? nullptr : bsum, told, (u32)g_tasc_config.enrich_wait);
             TASC_LAUNCH_CHECK();
         }
         TOK_TRY(look());
         TASC_REQUIRE(h.bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
-        if (h.late) {
-            tasc_set_error("tok_enrich: workgroups of one launch did not hear from each other");
-            return TASC_EHIP;
-        }
-        done = (int)(h.merges - h.undo);
+        done = (int)(h.merges - (h.undo || h.late ? 1 : 0));
         T = lens[done];
+        if (h.late) tell = false;
+        const bool uncertain = h.stuck || h.undo;
         if (full) {
-            full -= (u32)(end - begin);
-        } else if (h.stuck || h.undo) {
+            full -= std::min(full, (u32)(done - begin));
+        } else if (uncertain) {
             // (a look costs as much as the sieve gains on two or three merges; what it does not settle tends to come one after the other, and more
             // of it later)
             if (done - begin >= kFirst / 2) next_full = 4;
             full = h.foreign ? (u32)budget : next_full;
             next_full = std::min(2 * next_full, 1u << 16);
+        }
+        if (uncertain || h.late) {
             State again = h;
             again.merges = (u32)done;
-            again.stuck = again.gave_up = again.undo = again.retry = again.taken = again.done = 0;
+            again.stuck = again.gave_up = again.undo = again.late = again.retry = again.taken = again.done = 0;
             again.reward = 0;                                // (the pairs are counted again, or k_pick leaves one)
             TASC_HIP(hipMemcpyAsync(state, &again, sizeof again, hipMemcpyHostToDevice, st));
             TASC_HIP(hipStreamSynchronize(st));
