@@ -36,6 +36,7 @@ struct State {
     u32 bad, foreign;    // a token outside the vocabulary, the new ids included: nothing is done; one of the new ids: the sieve is not used
     u32 gave_up;         // k_sift's: its lists or tables are full, or most buckets pass; k_gather makes `stuck` of it
     u32 undo, late;      // k_apply's: the last merge was the wrong one; it was left unfinished.  As `stuck` for later steps
+    u64 length;          // of the corpus after the last merge, the wrong one included
     u32 arrived;         // workgroups of k_gather that are done with the running merge
     u32 top, taken;      // the fullest bucket of pairs; 1: there is a running merge
     u64 reward;          // of the last merge, or, where none was found for certain (retry), of the best n-gram that was
@@ -50,7 +51,7 @@ __device__ __forceinline__ bool no_merge(const State* st) { return !st->taken; }
 
 // st->bad = 1 if a token lies outside [0, vocab_all), st->foreign = 1 if outside [0, vocab); and the corpus' length where the steps look for it
 __global__ __launch_bounds__(kThreads) void k_check_tokens(const int32_t* __restrict__ tok, u64 T, int vocab, int vocab_all, State* st, u64* len) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) len[0] = T;
+    if (blockIdx.x == 0 && threadIdx.x == 0) len[0] = st->length = T;
     bool bad = false, foreign = false;
     for (u64 i = (u64)blockIdx.x * kThreads + threadIdx.x; i < T; i += (u64)gridDim.x * kThreads) {
         bad = bad || (u32)tok[i] >= (u32)vocab_all;
@@ -745,7 +746,7 @@ __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __
     }
     to += base;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        corpus.len[g.merges] = base + sum;
+        corpus.len[g.merges] = st->length = base + sum;
         // (of an n-gram that does not overlap itself every window is merged)
         if (g.overlaps ? st->seen != g.freq : T - (base + sum) != (u64)g.freq * (g.n - 1)) st->undo = 1;
     }
@@ -882,13 +883,20 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         if (!run) TASC_HIP(hipMemcpyAsync(len, &T0, sizeof T0, hipMemcpyHostToDevice, st));
         TASC_LAUNCH_CHECK();
     }
-    std::vector<char> report(at_ends + (size_t)n_docs * sizeof(u32));
-    const State& h = *reinterpret_cast<const State*>(report.data() + at_state);
+    std::vector<char> report(at_ends + (size_t)n_docs * sizeof(u32), 0);
+    State h;
+    memset(&h, 0, sizeof h);
     const u64* const lens = reinterpret_cast<const u64*>(report.data() + at_len);
-    memset(report.data(), 0, report.size());
     u64 T = T0;                                              // the corpus is no longer than this
-    // the corpus as it stands, and the host's look at it; nothing waits for the host in between
-    auto look = [&]() -> tasc_status {
+    // The host's look at the state, and, where the merges may have come to their end, at all that the caller gets; nothing waits for the host in between.
+    bool whole = false;
+    auto look = [&](bool all) -> tasc_status {
+        whole = all;
+        if (!all) {
+            TASC_HIP(hipMemcpyAsync(&h, state, sizeof h, hipMemcpyDeviceToHost, st));
+            TASC_HIP(hipStreamSynchronize(st));
+            return TASC_OK;
+        }
         const dim3 grid((unsigned)((T + kBlock - 1) / kBlock));
         k_end_sums<<<grid, dim3(kThreads), 0, st>>>(corpus, state, bsum);
         if (grid.x > kScanFrom) k_scan<<<dim3(1), dim3(kThreads), 0, st>>>(bsum, grid.x);
@@ -896,9 +904,9 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         TASC_LAUNCH_CHECK();
         TASC_HIP(hipMemcpyAsync(report.data(), ar.p, report.size(), hipMemcpyDeviceToHost, st));
         TASC_HIP(hipStreamSynchronize(st));
+        memcpy(&h, report.data() + at_state, sizeof h);
         return TASC_OK;
     };
-    if (T0 && !run) TOK_TRY(look());
     u32 step = 0;
     bool tell = true;
     u32 full = 0, next_full = 4;                             // merges that are still counted in full; and how many the next time that the sieve gives up
@@ -934,10 +942,10 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
             k_apply<<<grid2, dim3(kThreads), 0, st>>>(corpus, sel, step, state, told_all ? nullptr : bsum, told, (u32)g_tasc_config.enrich_wait);
             TASC_LAUNCH_CHECK();
         }
-        TOK_TRY(look());
+        TOK_TRY(look(end == budget));
         TASC_REQUIRE(h.bad == 0, "tok_enrich: corpus holds a token outside [0, %d)", vocab_all);
         done = (int)(h.merges - (h.undo || h.late ? 1 : 0));
-        T = lens[done];
+        if (!h.undo && !h.late) T = h.length;
         if (h.late) tell = false;
         const bool uncertain = h.stuck || h.undo;
         if (full) {
@@ -958,6 +966,7 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
             TASC_HIP(hipStreamSynchronize(st));
         }
     }
+    if (T0 && !whole) TOK_TRY(look(true));
     const int n_done = (int)h.merges;
     T = T0 ? lens[n_done] : 0;
     const Merge* const rows = reinterpret_cast<const Merge*>(report.data() + at_merges);
