@@ -72,6 +72,11 @@ tasc_status TascScratch::get(size_t need) {
     return rc;
 }
 
+bool tasc_scratch_kept(size_t bytes) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    return g_handles != 0 && bytes <= g_most;
+}
+
 void TascScratch::keep() {
     std::lock_guard<std::mutex> lock(g_mu);
     const int dev = device();

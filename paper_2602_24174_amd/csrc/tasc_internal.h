@@ -60,6 +60,8 @@ struct TascScratch {
 };
 // Every device allocation of the library: hipMalloc that gives kept scratch back where memory runs out
 tasc_status tasc_device_malloc(void** p, size_t bytes);
+// whether a block of so many bytes would be left to a later call
+bool tasc_scratch_kept(size_t bytes);
 // the most bytes a call may leave to later ones; what is kept beyond goes at once
 void tasc_scratch_limit(size_t bytes);
 // models and tables that exist: kept scratch is freed with the last of them

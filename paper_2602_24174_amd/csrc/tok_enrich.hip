@@ -7,10 +7,11 @@
 // What bounds a merge on a small corpus is its launches and whoever waits for them, so the steps of a merge follow each other
 // without the host: what one finds out (the n-gram, the new length, that nothing is left to merge) the next ones read from
 // device memory, and the host looks at it once per kBatch merges.  And most n-grams cannot win, which a count of pairs by hash shows (the sieve,
-// below): four launches a merge, some 40 us at 1.0 M tokens, of chains of round trips.  ms, every n-gram of every merge counted | so: 1.0 M tokens of
-// phrases, n_max 4, eight merges 1.00 | 0.57, 256 merges 23.0 | 19.8 (the later ones are counted in full); 20,000 tokens 0.69 | 0.43;
-// 16 M 9.0 | 4.0; 64 M, four merges 26.2 | 8.0.  Where every pair is as frequent as any other the sieve gives up each time that it is tried:
-// 1.0 M random tokens, eight merges 1.24 | 1.69.
+// below): four launches a merge (five above kTellBlocks blocks), some 42 us at 1.0 M tokens, of chains of round trips.  ms, every n-gram of every merge
+// counted | so, n_max 4, in turn: 1.0 M tokens of phrases, eight merges 0.92 | 0.48, 64 merges 6.25 | 4.1, 256 merges 22.3 | 19.1 (from some 50 on
+// nearly all are counted in full); 20,000 tokens, eight merges 0.66 | 0.39, 2000 merges 148.5 | 149; 16 M tokens, eight merges 8.5 | 3.6.  Where every pair is as
+// frequent as any other the sieve only costs, a tenth to a seventh of a call of eight merges, most of it the launches behind the one that gives up: 1.0 M
+// random tokens 1.39 | 1.53, of forty kinds 1.02 | 1.19, one token alone 0.60 | 0.70; 64 merges of random tokens 10.0 | 10.5.
 #include <algorithm>
 #include <string.h>
 #include <vector>
@@ -21,7 +22,7 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int kItems = 4;                            // positions of a thread
 constexpr int kBlock = kThreads * kItems;            // 4096
-constexpr int kFirst = 8, kBatch = 16;              // merges that the host launches before it looks: at first, and then
+constexpr int kFirst = 8, kBatch = 16;              // merges that the host launches before it looks: at first, and at most
 constexpr size_t kMostRecords = (size_t)2 << 30;
 
 struct Merge {           // one line of the result, as the caller's arrays have it
@@ -39,7 +40,7 @@ struct State {
     u64 length;          // of the corpus after the last merge, the wrong one included
     u32 arrived;         // workgroups of k_gather that are done with the running merge
     u32 top, taken;      // the fullest bucket of pairs; 1: there is a running merge
-    u64 reward;          // of the last merge, or, where none was found for certain (retry), of the best n-gram that was
+    u64 reward, want;    // of the last merge; what the next one is looked for from: a guess, or (retry) the best n-gram that the guess found
     u32 retry;
     u32 n, overlaps;     // the running merge: its n-gram, its windows, and whether two of them can overlap
     u32 freq, seen;      // (seen: counted again, where they can overlap)
@@ -101,7 +102,11 @@ __device__ void take_merge(const TascGram& best, int bits, const Ends& ends, Sta
         for (u32 j = 0; j + s < best.n; ++j) same = same && out.row[1 + j] == out.row[1 + j + s];
         overlaps = overlaps || same;
     }
-    st->reward = (u64)best.count * (best.n - 1);
+    // few merges are worth less than two fifths of the one before, but where they fall fast they tend to go on falling
+    const u64 before = st->reward, reward = (u64)best.count * (best.n - 1);
+    st->want = reward * 2 / 5;
+    if (before > reward) st->want = min(st->want, (u64)((double)reward / before * reward / 2));
+    st->reward = reward;
     st->retry = 0;
     st->taken = 1;
     st->n = best.n;
@@ -228,10 +233,10 @@ __global__ __launch_bounds__(kSumThreads) void k_pair_sums(const u32* __restrict
     if (lane == 0) atomicMax(&st->top, n);
 }
 // The least count of a bucket whose pairs are looked at.  (n_max - 1) times it has to stay below the best reward, which no pair's count exceeds
-// (fresh: the pairs are those of the corpus as it stands), and few merges are worth less than two fifths of the one before.  If that was
+// (fresh: the pairs are those of the corpus as it stands), nor, as a rule, what the merges before let expect (take_merge).  If that was
 // too much, the best of what was counted is a bound that holds.
 __device__ __forceinline__ u32 least_count(const State* __restrict__ st, bool fresh, int n_max) {
-    const u64 reward = st->reward, want = st->retry ? reward : max(fresh ? (u64)st->top * 3 / 5 : 0, reward * 2 / 5);
+    const u64 want = st->retry ? st->want : max(fresh ? (u64)st->top * 3 / 5 : 0, st->want);
     return max(1u, (u32)(want / (u64)(n_max - 1)));
 }
 
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
     __shared__ u64 s_ok[kSiftSpan / 64 + 1];                      // a bit per position: it and the next one are a pair that passes
     __shared__ u64 s_key[kSiftSlots];                             // 0 = free
     __shared__ u32 s_val[kSiftSlots];                             // {count : 13, one of its places : 12}, the place of whoever counted first
-    __shared__ u32 s_windows, s_total, s_open, s_listed[kGatherMost];              // of a range: how many, then where they go
+    __shared__ u32 s_full, s_windows, s_total, s_open, s_listed[kGatherMost];              // of a range: how many, then where they go
     __shared__ uint16_t s_window[kSiftWindows];                   // {place : 12, n - 1 : 4}
     if (blockIdx.x == 0 && threadIdx.x == 0) st->taken = 0;
     if (idle(st)) return;
@@ -300,7 +305,7 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
         s_val[u * kSiftThreads + tid] = 0;
     }
     if (tid < (int)kGatherMost) s_listed[tid] = 0;
-    if (tid == 0) s_windows = s_total = 0;
+    if (tid == 0) s_full = s_windows = s_total = 0;
     __syncthreads();
     if (s_open > kBuckets / 4) {                             // (nor is this)
         if (tid == 0) st->gave_up = 1;
@@ -347,7 +352,7 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
                 return;
             }
         }
-        st->gave_up = 1;
+        s_full = 1;
     };
     // Few positions have a window, and a window is a chain of LDS round trips: listed first, so that all lanes have one (a position a
     // lane, k_sift took 35 us); those of a quarter of the positions at a time where the list does not hold them all.
@@ -380,12 +385,16 @@ __global__ __launch_bounds__(kSiftThreads) void k_sift(Corpus corpus, State* st,
         if (at_once && w + 1 < W) continue;
         __syncthreads();
         const u32 windows = s_windows;
-        for (u32 e = tid; e < windows; e += kSiftThreads) count(s_window[e] >> 4, (s_window[e] & 15) + 1);
+        for (u32 e = tid; e < windows && !*(volatile u32*)&s_full; e += kSiftThreads) count(s_window[e] >> 4, (s_window[e] & 15) + 1);
         __syncthreads();
         if (tid == 0) s_windows = 0;
         __syncthreads();
     }
     static_assert(kSiftWindows >= kSiftThreads * (TASC_MAX_ORDER - 1), "windows of a quarter of the positions");
+    if (s_full) {
+        if (tid == 0) st->gave_up = 1;
+        return;
+    }
     u64 key[S];
     u32 at[S], range[S];
 #pragma unroll
@@ -510,9 +519,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(Corpus corpus, Lists 
         st->stuck = 1;
     } else if (best.count != 0 && reward > (u64)(n_max - 1) * (least - 1)) {
         take_merge(best, bits, ends, st, merges);
-    } else if (best.count != 0 && !st->retry) {
-        st->reward = reward;
+    } else if (!st->retry) {
+        st->want = reward;                                   // (nothing found: every pair is looked at)
         st->retry = 1;
+    } else if (best.count == 0 && least == 1) {
+        take_merge(best, bits, ends, st, merges);            // nothing left
     } else {
         st->stuck = 1;
     }
@@ -864,12 +875,18 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     TascGram* best = nullptr;
     TascCountBufs bufs{};
     auto full_counts = [&]() -> tasc_status {
-        if (counting.p) return TASC_OK;
+        if (best) return TASC_OK;
         const size_t at_best = counting.carve((size_t)orders * plan.parts * sizeof(TascGram)), at_rec = counting.carve(together * plan.rec_bytes);
         const size_t at_roff = counting.carve(together * plan.offs_bytes), at_deal = counting.carve(plan.deal_bytes);
-        TOK_TRY(counting.get(counting.used));
-        best = (TascGram*)(counting.p + at_best);
-        bufs = TascCountBufs{(u64*)(counting.p + at_rec), (uint16_t*)(counting.p + at_roff), (u64*)(counting.p + at_deal)};
+        // in what is left of the call's first block; or else in one that, if it is kept, holds all of the next call
+        char* p = ar.p + ar.used;
+        if (ar.bytes < ar.used + counting.used) {
+            const size_t all = ar.used + counting.used;
+            if (!tasc_scratch_kept(all) || counting.get(all) != TASC_OK) TOK_TRY(counting.get(counting.used));
+            p = counting.p;
+        }
+        best = (TascGram*)(p + at_best);
+        bufs = TascCountBufs{(u64*)(p + at_rec), (uint16_t*)(p + at_roff), (u64*)(p + at_deal)};
         return TASC_OK;
     };
 
@@ -909,8 +926,11 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
     };
     u32 step = 0;
     bool tell = true;
-    u32 full = 0, next_full = 4;                             // merges that are still counted in full; and how many the next time that the sieve gives up
-    for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck || h.undo || h.late); batch = kBatch) {
+    // Merges that are still counted in full, and how many the next time that the sieve gives up; merges that it has made since the last time.  A try
+    // that fails costs as much as it saves on some three merges, and what it does not settle tends to come one after the other: so the next one is
+    // short, and comes after twice as many merges unless there was something to gain.
+    u32 full = 0, next_full = kFirst, sieved = 0;
+    for (int done = 0, batch = kFirst; run && done < budget && (!h.done || h.stuck || h.undo || h.late);) {
         const int begin = done, end = std::min(budget, done + (full ? (int)std::min<u32>(full, kBatch) : batch));
         if (full) TOK_TRY(full_counts());
         TascCountPlan p = plan;                              // (the records' strides are those of the whole corpus)
@@ -951,17 +971,21 @@ extern "C" tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc
         if (full) {
             full -= std::min(full, (u32)(done - begin));
         } else if (uncertain) {
-            // (a look costs as much as the sieve gains on two or three merges; what it does not settle tends to come one after the other, and more
-            // of it later)
-            if (done - begin >= kFirst / 2) next_full = 4;
+            sieved += (u32)(done - begin);
+            if (sieved >= (u32)kFirst) next_full = kFirst;
             full = h.foreign ? (u32)budget : next_full;
             next_full = std::min(2 * next_full, 1u << 16);
+            sieved = 0;
+            batch = 1;
+        } else {
+            sieved += (u32)(done - begin);
+            batch = std::min(2 * batch, kBatch);
         }
         if (uncertain || h.late) {
             State again = h;
             again.merges = (u32)done;
             again.stuck = again.gave_up = again.undo = again.late = again.retry = again.taken = again.done = 0;
-            again.reward = 0;                                // (the pairs are counted again, or k_pick leaves one)
+            again.reward = again.want = 0;                           // (the pairs are counted again, or k_pick leaves one)
             TASC_HIP(hipMemcpyAsync(state, &again, sizeof again, hipMemcpyHostToDevice, st));
             TASC_HIP(hipStreamSynchronize(st));
         }
