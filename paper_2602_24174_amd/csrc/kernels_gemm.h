@@ -143,8 +143,9 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
     };
 
     // ---- loads: a wave instruction brings 64 chunks of 16 bytes, RPI tile rows, to 1 KB of LDS in lane order; chunk c of row
-    // r is parked at place c ^ swz(r) of its row, which spreads the rows a fragment read touches over all banks.  Rows past the
-    // matrix are read from its last row; what they produce is never stored.
+    // r is parked at place c ^ swz(r) of its row, which spreads the rows a fragment read touches over all banks.  A tile's buffer ends with
+    // the matrix' last row: rows past it arrive as zeros, and what they produce is never stored.  The k of a load is the scalar offset, which need not
+    // count for whether a load is inside: of a row inside it stays below the row's length, and past the last item it is 0.
     auto swz = [](int r) __attribute__((always_inline)) { return (r >> 1) & 7; };
     uint32_t loff[LPW];                                           // from the tile's first row: the same for every item
 #pragma unroll
@@ -160,7 +161,7 @@ void k_gemm(const BF16* __restrict__ A, const BF16* __restrict__ W, int M, int N
         int n0 = 0, m0 = 0;
         const bool any = l_it < x1;
         if (any) tile_of(l_it, n0, m0);
-        else l_left = 1 << 30;
+        else l_left = 1;                                          // (so this comes again after every stage)
         l_k = any ? (uint32_t)(l_it / total) * per * (TG_BK * 2) : 0;
         rs_w = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)n0 * K), 0, any ? min(BN, N - n0) * K * 2 : 0, 0x00027000);
         rs_a = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)m0 * K), 0, any ? min(BM, M - m0) * K * 2 : 0, 0x00027000);
