@@ -72,7 +72,6 @@ constexpr u32 kMarkOften = 4;      // it occurs more than once in the chunk alon
 // windows' slots [C], marks, a bit a position [3][C / 8 + 8].  A few rotations of the tokens make a hash that is good enough for the chunk's table; the key and its hash are
 // computed once per window that is left.
 //
-//
 // twice (nullable): a bit per range of the (N - 1)-grams' light hash, set for those that occur at least twice.  A window that begins or ends with
 // one that occurs once occurs once itself: it is counted and leaves no record.
 template <int N, int C, int TH>
