@@ -419,9 +419,10 @@ tasc_status tasc_ngram_from_bigram(const int32_t* next_tok, tasc_mem where, int3
  *   corpus_len          HOST int64[budget + 1]: corpus length before merge i; entry *n_merges = final.
  *   n_merges            HOST: merges performed (<= budget).
  * Limits: n_max in [2, TASC_MAX_ORDER], n_max * ceil(log2(vocab + budget)) <= 128, corpus < 2^32 - 1
- * tokens.  Synchronous (the host looks at the device once per 16 merges); 14 to 16 bytes of device scratch per corpus token, plus
- * 8 to 14 per token (16 to 22 for keys of more than 64 bits) for each order that is counted together with others: all of them up
- * to 2 GiB (or TASC_CFG_BUILD_LIST_KIB, if that is less), one at least.  Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
+ * tokens.  Synchronous (the host looks at the device once per 16 merges at most); 18 to 20 bytes of device scratch per corpus token and up
+ * to 16 MiB, plus, once merges have to be counted in full, 8 to 14 per token (16 to 22 for keys of more than 64 bits) for each order that is
+ * counted together with others: all of them up to 2 GiB (or TASC_CFG_BUILD_LIST_KIB, if that is less), one at least.
+ * Errors: TASC_EINVAL, TASC_ENOMEM, TASC_EHIP.
  * ---------------------------------------------------------------------------------------- */
 tasc_status tasc_tok_enrich(const int32_t* tokens, const int64_t* doc_offsets, int64_t n_docs, int32_t vocab,
                             int32_t n_max, int32_t budget, tasc_mem where, void* stream, int32_t* merges,

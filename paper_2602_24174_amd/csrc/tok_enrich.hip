@@ -719,8 +719,8 @@ __global__ __launch_bounds__(kThreads) void k_sums(Corpus corpus, const u32* __r
     block_scan(__popc(keep), s_wave, &sum);
     if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
 }
-// bsum (nullable): k_sums' ; without, a block tells the others its own sum, as {step, sum}, and waits for those before it: they were started
-// before it and wait for none after it.  A launch and another look at the corpus less, but every block reads every sum before its own: up to
+// bsum (nullable): k_sums' ; without, a block tells the others its own sum, as {step, sum}, and waits for those before it.  Every die starts its
+// blocks in order, so the first block that has not started waits only for room that started ones take up, and none of those waits for it.  A launch and another look at the corpus less, but every block reads every sum before its own: up to
 // kTellBlocks of them.  A block that does not hear from another in `wait` looks gives up (the GPU may be shared): the call makes the merge again, with k_sums.
 constexpr u32 kTellBlocks = 1024;
 __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __restrict__ sel, u32 step, State* st, const u32* __restrict__ bsum, u64* told,
