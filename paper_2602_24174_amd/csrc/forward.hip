@@ -227,8 +227,8 @@ namespace {
 // k_gemm (kernels_gemm.h) takes all launches but these, which fill their LDS through registers (kernels_tiled.h): one round of tiles over at
 // most kFewRows rows, whose weights come from memory for a few row tiles only and are fetched further ahead there (us, registers | straight to
 // LDS: gate/up 576 x 17920 x 1536 in 256 x 192 tiles 38.4 | 42.8, 224 x 9728 x 896 in 128 x 128 ones 12.3 | 12.7, 224 x 896 x 4864 in
-// six slices of 64 x 128 ones 8.5 | 8.8; with more row tiles gate/up 1000 x 9728 x 896 27.2 | 26.8, output 6336 x 1536 x 1536 46.4 | 42.2; straight to LDS over registers, warm operands, seven
-// products of one round of 256 x 192 tiles with N 1536 to 17920, at 384 to 768 rows 0.998 to 1.015 of the time, at 832 to 1152 rows 0.94 to 1.02), the
+// six slices of 64 x 128 ones 8.5 | 8.8; with more row tiles gate/up 1000 x 9728 x 896 27.2 | 26.8, output 6336 x 1536 x 1536 46.4 | 42.2; one round of
+// 256 x 192 tiles, N 2048 to 17920, warm operands: straight to LDS takes 0.998 to 1.015 of the time at 384 to 768 rows, 0.94 to 1.02 at 832 to 1152), the
 // narrow tile, and the 128 x 128 tile's SwiGLU, rotation and k-slices in one round.  The first two have spans of 64 or 128 features a wave, and so
 // four waves of 64 x 64; the other epilogues take eight of 32 x 64 (us, four waves through registers | eight straight to LDS: 1280 x 2048 x 2048
 // with residual 25.4 | 21.5, 3072 x 1536 x 8960 151 | 134; slices in one round: 1137 x 896 x 4864 in four 16.3 | 17.8 and the reduction behind them

@@ -550,8 +550,8 @@ __device__ __forceinline__ bool matches(const int32_t* tok, const uint8_t* __res
 }
 
 // Left-to-right choice among occurrences that can overlap (the others are all taken, and found where they are needed): sel[i] =
-// number of the step, which no other one has (a merge's number comes again if it is taken back, and its marks stay).  An occurrence with none in the n - 1 positions before it ("head") is always taken; from it, one lane
-// walks the run of occurrences that overlap each other, taking the first at or after the end of the last taken one, and stops when
+// number of the step, which no other one has (a merge's number comes again if it is taken back, and its marks stay).  An occurrence
+// with none in the n - 1 positions before it ("head") is always taken; from it, one lane walks the run of occurrences that overlap each other, taking the first at or after the end of the last taken one, and stops when
 // that one is a head itself (its own lane takes it) or lies beyond the reach of an overlap.  A walk is a chain of dependent loads, and
 // a long run of one token is one walk: after kLaneSteps steps the wave takes it over, 64 positions at a time, and the steps among them
 // are a few instructions (200,000 equal tokens, four merges of two: 176 ms with the lane alone; 61 with a byte per
@@ -720,8 +720,9 @@ __global__ __launch_bounds__(kThreads) void k_sums(Corpus corpus, const u32* __r
     if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
 }
 // bsum (nullable): k_sums' ; without, a block tells the others its own sum, as {step, sum}, and waits for those before it.  Every die starts its
-// blocks in order, so the first block that has not started waits only for room that started ones take up, and none of those waits for it.  A launch and another look at the corpus less, but every block reads every sum before its own: up to
-// kTellBlocks of them.  A block that does not hear from another in `wait` looks gives up (the GPU may be shared): the call makes the merge again, with k_sums.
+// blocks in order, so the first block that has not started waits only for room that started ones take up, and none of those waits for it.  A launch
+// and another look at the corpus less, but every block reads every sum before its own: up to kTellBlocks of them.  A block that does not hear from
+// another in `wait` looks gives up (the GPU may be shared): the call makes the merge again, with k_sums.
 constexpr u32 kTellBlocks = 1024;
 __global__ __launch_bounds__(kThreads) void k_apply(Corpus corpus, const u32* __restrict__ sel, u32 step, State* st, const u32* __restrict__ bsum, u64* told,
                                                     u32 wait) {
