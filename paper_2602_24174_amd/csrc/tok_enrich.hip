@@ -549,13 +549,14 @@ __device__ __forceinline__ bool matches(const int32_t* tok, const uint8_t* __res
     return ok;
 }
 
-// Left-to-right choice among occurrences that can overlap (the others are all taken, and found where they are needed): sel[i] =
-// number of the step, which no other one has (a merge's number comes again if it is taken back, and its marks stay).  An occurrence
-// with none in the n - 1 positions before it ("head") is always taken; from it, one lane walks the run of occurrences that overlap each other, taking the first at or after the end of the last taken one, and stops when
-// that one is a head itself (its own lane takes it) or lies beyond the reach of an overlap.  A walk is a chain of dependent loads, and
-// a long run of one token is one walk: after kLaneSteps steps the wave takes it over, 64 positions at a time, and the steps among them
-// are a few instructions (200,000 equal tokens, four merges of two: 176 ms with the lane alone; 61 with a byte per
-// position to read instead of the tokens; 16 so).  The walk ends at the latest at the end of the corpus.
+// Left-to-right choice among occurrences that can overlap (the others are all taken, and found where they are needed): sel[i] = number
+// of the step, which no other one has (a merge's number comes again if it is taken back, and its marks stay).  An occurrence with none
+// in the n - 1 positions before it ("head") is always taken; from it, one lane walks the run of occurrences that overlap each other,
+// taking the first at or after the end of the last taken one, and stops when that one is a head itself (its own lane takes it) or lies
+// beyond the reach of an overlap.  A walk is a chain of dependent loads, and a long run of one token is one walk: after kLaneSteps
+// steps the wave takes it over, 64 positions at a time, and the steps among them are a few instructions (200,000 equal tokens, four
+// merges of two: 176 ms with the lane alone; 61 with a byte per position to read instead of the tokens; 16 so).  The walk ends at the
+// latest at the end of the corpus.
 constexpr unsigned kSelectBlocks = 256, kSelectThreads = 256;
 constexpr int kLaneSteps = 8;
 __global__ __launch_bounds__(kSelectThreads) void k_select(Corpus corpus, State* st, u32* sel, u32 step) {
